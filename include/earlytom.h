@@ -265,9 +265,11 @@ int et_layernorm(const uint16_t *x_dev, const float *gamma_dev, const float *bet
  * epilogue: 0 bias only, 1 bias + GELU-tanh, 2 bias + residual (res_dev bf16 [M, N], may
  * alias c_dev).  bias_dev float32 [N].  Standalone form for tests: any M >= 1, N and K
  * multiples of 8; allocates and frees padded copies of the operands itself and synchronises.
- * tile_config: -1 = the library's choice (which may also split a thin last tile row or column
- * off into a launch of its own), else one workgroup tiling of the persistent kernel:
- * 0 = 256 x 256 x 64 with 8 wavefronts, 1 = 128 x 128 x 64 and 2 = 64 x 128 x 64 with 4. */
+ * tile_config: -1 = the library's choice (which may also split the last tile rows or a thin last
+ * column off into a launch of its own), else one workgroup tiling: 0 = 256 x 256 with 8 wavefronts
+ * and 1 = 128 x 128 with 4 (persistent kernel), 2 = 64 x 64 with 4, 3 = 128 x 64 and 4 = 128 x 128
+ * with 8 (kernels that split K over the wavefronts of a workgroup, for few rows), 5 = 256 x 128
+ * with 8. */
 int et_gemm_bf16(const uint16_t *a_dev, const uint16_t *w_dev, const float *bias_dev,
                  const uint16_t *res_dev, int32_t M, int32_t N, int32_t K, int32_t epilogue,
                  int32_t tile_config, uint16_t *c_dev, void *hip_stream);

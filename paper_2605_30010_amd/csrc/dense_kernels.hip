@@ -1,39 +1,12 @@
 // Dense encoder kernels for gfx950: LayerNorm, patch extraction, the bf16 MFMA GEMM with fused
 // epilogues (bias | bias + GELU-tanh | bias + residual) and per-frame multi-head attention.
 //
-// MFMA shape used throughout: v_mfma_f32_32x32x16_bf16.  Per 64-lane wavefront, with
-// g = lane / 32 and r = lane % 32:
-//   operand "A" (32 x 16): lane holds row r,    k = 8g .. 8g+7   (8 bf16 = one 16-byte vector)
-//   operand "B" (16 x 32): lane holds column r, k = 8g .. 8g+7
-//   accumulator (32 x 32): lane holds column r, rows (i / 4) * 8 + 4g + (i % 4), i = 0..15
-#include <type_traits>
-
-#include "et_common.h"
+// The MFMA operand layouts are described in mfma_common.h.
+#include "gemm_small.h"
 
 namespace et {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 namespace {
-
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-  bf16x2 v;
-  v.x = (__bf16)lo;
-  v.y = (__bf16)hi;
-  return __builtin_bit_cast(uint32_t, v);
-}
-
-__device__ __forceinline__ f32x16 mfma32(const uint4 &a, const uint4 &b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 
 // ---------------------------------------------------------------------------------------
 // LayerNorm: one wavefront per row, row held in registers, fp32 statistics (two passes over
@@ -199,16 +172,6 @@ __global__ __launch_bounds__(256) void im2col_stripe_kernel(const float *__restr
 // (columns = m): each lane then owns 4 consecutive n of one output row m per accumulator
 // quad, which packs to an 8-byte bf16 piece.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ float gelu_tanh_f(float u) {
-  // 0.5 u (1 + tanh(y)) = u / (1 + exp(-2y)),  y = sqrt(2/pi) (u + 0.044715 u^3)
-  // exp(-2y) = exp2(u (c1 + c3 u^2)) with the factor -2 log2(e) sqrt(2/pi) folded into c1, c3;
-  // hardware exp2 and reciprocal (1 ulp) are ample for a result that is rounded to bf16.
-  const float c1 = -2.0f * 1.4426950408889634f * 0.7978845608028654f;
-  const float c3 = c1 * 0.044715f;
-  const float t = u * fmaf(u * u, c3, c1);
-  return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-
 // acc[a][b] is the 32 x 32 tile at rows n_base + 32a (MFMA rows = output columns n) and columns
 // m_base + 32b: the lane owns output row m = .. + r32 and, per accumulator quad q, the four
 // consecutive columns n = .. + 8q + 4grp + (0..3).
@@ -314,21 +277,6 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
 // complete once this wavefront's loads have landed AND the workgroup barrier after that wait has
 // been passed.
 // ---------------------------------------------------------------------------------------
-#define ET_LDS_DMA16(gptr, lptr)                                                             \
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
-                                   (__attribute__((address_space(3))) void *)(lptr), 16, 0, 0)
-
-#define ET_LDS_DMA16_OFF(gptr, lptr, imm)                                                    \
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
-                                   (__attribute__((address_space(3))) void *)(lptr), 16, (imm), 0)
-
-// Waits until at most N of this wavefront's vector-memory operations are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // ---------------------------------------------------------------------------------------
 // The kernel is persistent: one workgroup per compute-unit slot walks over its output tiles
 // t = b, b + G, b + 2G, ... and treats their k-tiles as ONE stream through the LDS stages, so the
@@ -440,12 +388,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
       src = w_base + ko + w_off[j];
       dst = ws + (lwave * W_BLK + (j & ~3)) * 512;
     }
-    switch ((i < A_BLK ? i : i - A_BLK) & 3) {       // the immediate has to be a literal
-      case 0: ET_LDS_DMA16_OFF(src, dst, 0); break;
-      case 1: ET_LDS_DMA16_OFF(src, dst, 1024); break;
-      case 2: ET_LDS_DMA16_OFF(src, dst, 2048); break;
-      default: ET_LDS_DMA16_OFF(src, dst, 3072); break;
-    }
+    lds_dma16_of4(src, dst, i < A_BLK ? i : i - A_BLK);
   };
   auto issue_next = [&](int stage) {
     if (!is_loader) return;
@@ -970,19 +913,62 @@ int launch_im2col(const float *frames, int T, int C, int H, int W, int P, int Kp
   return ET_OK;
 }
 
-// Workgroup tilings of the GEMM kernel (tile_config of et_gemm_bf16):
-//   0  256 x 256 x 64, 8 wavefronts (2 x 4), one workgroup per compute unit
-//   1  128 x 128 x 64, 4 wavefronts (2 x 2), two workgroups per compute unit
-//   2   64 x 128 x 64, 4 wavefronts (2 x 2), two workgroups per compute unit
-enum { kCfgBig = 0, kCfg128 = 1, kCfg64 = 2, kCfgCount = 3 };
+// Workgroup tilings (tile_config of et_gemm_bf16):
+//   0  256 x 256, 8 wavefronts, persistent, one workgroup per compute unit
+//   1  128 x 128, 4 wavefronts, persistent, two workgroups per compute unit
+//   2   64 x  64, k split over 4 wavefronts, two workgroups per compute unit      (gemm_small.hip)
+//   3  128 x  64, k split over 4 groups of 2 wavefronts                           (gemm_small.hip)
+//   4  128 x 128, k split over 2 groups of 4 wavefronts                           (gemm_small.hip)
+//   5  256 x 128, 8 wavefronts in two alternating halves                          (gemm_small.hip)
+enum { kCfgBig = 0, kCfg128 = 1, kCfgWave = 2, kCfgPair64 = 3, kCfgPair128 = 4, kCfgHalf = 5, kCfgCount = 6 };
 int gemm_config_count() { return kCfgCount; }
 
 static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
   switch (cfg) {
     case kCfgBig: return launch_gemm_stream_cfg<256, 256, 64, 2, 4, 2>(g, s);
     case kCfg128: return launch_gemm_stream_cfg<128, 128, 64, 2, 2, 2, 2>(g, s);
-    case kCfg64: return launch_gemm_stream_cfg<64, 128, 64, 2, 2, 2, 2>(g, s);
+    case kCfgWave: return launch_gemm_wave(g, s);
+    case kCfgPair64: return launch_gemm_pair64(g, s);
+    case kCfgPair128: return launch_gemm_pair128(g, s);
+    case kCfgHalf: return launch_gemm_half(g, s);
     default: set_error("unknown gemm tile configuration %d", cfg); return ET_ERR_INVALID_ARG;
+  }
+}
+
+// Expected time of one launch in microseconds, launch overhead included: a fixed part (first loads,
+// epilogue) plus a part per k-tile of 64 in each round of tiles.  A compute unit is slower when its
+// neighbours work too (shared caches, and the clock falls with the power drawn), hence the terms in
+// t / slots.  Fitted to launches on 256 compute units at the encoder's shapes, 64 to 23328 rows; measured
+// at K = 1152 / 4352:
+//   wave     6.8 / 17 us for one round of 256 tiles, 10.3 / 28 for two, 15 / 42 for three
+//   pair64   9.3 / 25 for one round, 17.5 / 47 for two
+//   pair128  11-12 / 30 (up to 160 tiles), 14 / 36 (234 tiles), 25 / 67 for two rounds
+//   half     16.3 / 45 (up to 100 tiles), 22 / 59 (207), 42 / 120 for two rounds
+//   128      15 / 46 (up to 160 tiles), 20 (324), 23.5 / 64 (414), 36 / 107 (576)
+//   256      26 / 77 (70 tiles), 30 (182), 39 / 108 (230), 4 rounds 133 / 475
+static double gemm_cost(int cfg, long rows, long cols, int K) {
+  const double kt = K / 64;
+  auto tiles = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); };
+  auto rounds = [](long t, long slots) { return (double)((t + slots - 1) / slots); };
+  switch (cfg) {
+    case kCfgWave: return 3.2 + rounds(tiles(64, 64), 256) * 0.195 * kt;
+    case kCfgPair64: return 0.5 + rounds(tiles(128, 64), 256) * (2.9 + 0.32 * kt);
+    case kCfgPair128: {
+      const long t = tiles(128, 128);
+      return t <= 256 ? 3.6 + kt * (0.38 + 0.10 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.46 * kt);
+    }
+    case kCfgHalf: {
+      const long t = tiles(256, 128);
+      return t <= 256 ? 6.5 + kt * (0.53 + 0.25 * (double)t / 256.0) : rounds(t, 256) * (6.0 + 0.8 * kt);
+    }
+    case kCfg128: {
+      const long t = tiles(128, 128), last = t % 512;
+      return 2.2 + (double)(t / 512) * (3.5 + 1.05 * kt) + (last ? 2.4 + kt * (0.55 + 0.4 * (double)last / 512.0) : 0.0);
+    }
+    default: {
+      const long t = tiles(256, 256), last = t % 256;
+      return 0.5 + (double)(t / 256) * (4.5 + 1.6 * kt) + (last ? 4.5 + kt * (1.05 + 0.55 * (double)last / 256.0) : 0.0);
+    }
   }
 }
 
@@ -993,48 +979,41 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     return ET_ERR_INVALID_ARG;
   }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
-  // Tile choice among the persistent stream kernels, by a cost model in units of one round of
-  // 256 x 256 tiles (one per compute unit; all costs scale with K alike).  Measured on MI355X at
-  // the encoder's shapes: a round of 128 x 128 tiles (two workgroups per compute unit, 512 slots)
-  // costs 0.6 of it, 0.52 when at most 256 tiles leave every workgroup alone on its unit, 0.57 per
-  // round when there are several; 64 x 128 tiles 0.5 / 0.3 / 0.4.  The makespan is whole rounds:
-  // a workgroup with one tile more than the others finishes a tile time later.
-  //  - big tiles: a partly filled last tile row or column costs whole tiles, so it may be split
-  //    off into a launch of its own with small tiles (only if that saves at least half a round).
-  const long t256 = (long)((g.M + 255) / 256) * ((g.n_store + 255) / 256);
-  auto cost_small = [](long rows, long cols, int *cfg) {
-    const long s128 = ((rows + 127) / 128) * ((cols + 127) / 128), s64 = ((rows + 63) / 64) * ((cols + 127) / 128);
-    const long r128 = (s128 + 511) / 512, r64 = (s64 + 511) / 512;
-    const double c128 = r128 > 1 ? 0.57 * (double)r128 : (s128 <= 256 ? 0.52 : 0.6);
-    const double c64 = r64 > 1 ? 0.4 * (double)r64 : (s64 <= 256 ? 0.3 : 0.5);
-    if (cfg) *cfg = c128 <= c64 ? kCfg128 : kCfg64;
-    return c128 <= c64 ? c128 : c64;
+  auto cheapest = [&](long rows, long cols, double *cost) {
+    int best = kCfgBig;
+    double c = gemm_cost(kCfgBig, rows, cols, g.K);
+    for (int cfg = kCfg128; cfg < kCfgCount; ++cfg) {
+      const double x = gemm_cost(cfg, rows, cols, g.K);
+      if (x < c) { c = x; best = cfg; }
+    }
+    if (cost) *cost = c;
+    return best;
   };
-  const int tm = (g.M + 255) / 256, tn = (g.n_store + 255) / 256;
-  const double whole = (double)((t256 + 255) / 256);
+  double best = 0.0;
+  const int cfg = cheapest(g.M, g.n_store, &best);
+  // Big tiles over the whole matrix but the rows or columns that would make a last, nearly empty round
+  // (a partly filled last tile row or column, or the tile rows past a whole number of rounds): those
+  // go to launches of their own with smaller tiles, if that saves at least 3 % and 4 us over the best
+  // single launch.
   int best_dr = 0, best_dc = 0;
-  double best = whole;
-  if (t256 > 256) {
-    const bool rows_splittable = (g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M) && g.M % 256 != 0 && tm > 1;
+  const int tm = (g.M + 255) / 256, tn = (g.n_store + 255) / 256;
+  if ((long)tm * tn > 256) {
+    const bool rows_splittable = (g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M) && tm > 1;
     const bool cols_splittable = g.n_store % 256 != 0 && tn > 1;
-    double split_best = whole - 0.5;
-    for (int dr = 0; dr <= (rows_splittable ? 1 : 0); ++dr)
+    double split_best = best - (best * 0.03 > 4.0 ? best * 0.03 : 4.0);
+    for (int dr = 0; dr <= (rows_splittable ? (tm < 8 ? tm - 1 : 8) : 0); ++dr)
       for (int dc = 0; dc <= (cols_splittable ? 1 : 0); ++dc) {
         if (!dr && !dc) continue;
-        const long rm = (long)(tm - dr) * 256 < g.M ? (long)(tm - dr) * 256 : g.M;
-        const long cm = (long)(tn - dc) * 256 < g.n_store ? (long)(tn - dc) * 256 : g.n_store;
-        double c = (double)(((long)(tm - dr) * (tn - dc) + 255) / 256);
-        if (dc) c += 0.08 + cost_small(rm, g.n_store - cm, nullptr);     // right strip next to the main block
-        if (dr) c += 0.08 + cost_small(g.M - rm, g.n_store, nullptr);    // bottom strip over the full width
+        const long rm = dr ? (long)(tm - dr) * 256 : g.M, cm = dc ? (long)(tn - dc) * 256 : g.n_store;
+        double right = 0.0, bottom = 0.0;
+        if (dc) cheapest(rm, g.n_store - cm, &right);      // right strip next to the main block
+        if (dr) cheapest(g.M - rm, g.n_store, &bottom);    // bottom strip over the full width
+        const double c = gemm_cost(kCfgBig, rm, cm, g.K) + right + bottom;
         if (c < split_best - 1e-9) { split_best = c; best_dr = dr; best_dc = dc; }
       }
-    if (best_dr || best_dc) best = split_best;
   }
-  int small_cfg = kCfg64;
-  const double small = cost_small(g.M, g.n_store, &small_cfg);
-  if (small < best) return launch_gemm_id(g, s, small_cfg);
-  if (!best_dr && !best_dc) return launch_gemm_id(g, s, kCfgBig);
-  const int rm = best_dr ? (tm - 1) * 256 : g.M, cm = best_dc ? (tn - 1) * 256 : g.n_store;
+  if (!best_dr && !best_dc) return launch_gemm_id(g, s, cfg);
+  const int rm = best_dr ? (tm - best_dr) * 256 : g.M, cm = best_dc ? (tn - best_dc) * 256 : g.n_store;
   GemmArgs part = g;
   part.M = rm;
   part.n_store = cm;

@@ -1,0 +1,488 @@
+// GEMM kernels for few rows (a short clip, or the blocks on the kept tokens), where the output has
+// too few tiles to fill the chip: the contraction is split over the wavefronts of a workgroup and
+// the partial sums meet in LDS, so nothing but the result goes through memory.
+//
+// What bounds these launches (measured): a launch costs 2.2 us before it does anything; after that
+// a compute unit takes its operands through one 64-byte-per-clock path (59 B/clk reached, and only
+// with rows of 128 bytes: 64-byte row segments halve it), i.e. 256 cycles per 64 x 64 x 64 step and
+// 512 per 128 x 128 x 64, against 128 and 512 cycles of the matrix unit.  What cost the time before
+// was neither: a 64 x 128 workgroup tile walked its k-tiles one after the other, each a chain of
+// barrier, LDS reads waited for one by one, two MFMAs per wait (0.6-1.2 us per k-tile).
+#include <atomic>
+
+#include "gemm_small.h"
+
+namespace et {
+
+namespace {
+
+// Workgroups go to the 8 XCDs round-robin by index; XCD x takes the x-th contiguous run of tiles
+// (bands of 8 tile rows, column by column inside a band), so that the tiles an XCD works on at
+// once share operand slices through its L2.
+__device__ __forceinline__ void small_tile_of(int tiles_m, int tiles_n, int &tm, int &tn) {
+  const int total = gridDim.x, per = total / 8, rem = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  const int v = xcd * per + (xcd < rem ? xcd : rem) + slot;
+  const int band = v / (8 * tiles_n), r = v - band * 8 * tiles_n;
+  const int hb = (tiles_m - band * 8 < 8) ? (tiles_m - band * 8) : 8;
+  tm = band * 8 + r % hb;
+  tn = r / hb;
+}
+
+// The lane offsets of the direct loads are lowered by the immediate of their group of four (see
+// lds_dma16_of4); the bias keeps them non-negative and is taken off the scalar base.
+constexpr uint32_t kOffBias = 4096;
+
+// Byte offset of this lane's piece of row `row` (stride `ld` elements) in the i-th 1 KiB load of an
+// operand: lane L lands at row L / 8, slot L % 8 of the 8-row piece and fetches 16-byte chunk
+// slot ^ (row >> 1) % 8, an XOR swizzle that spreads the fragment reads over the banks.
+__device__ __forceinline__ uint32_t piece_offset(int row, int src_row, int ld, int slot, int i) {
+  return (uint32_t)src_row * (uint32_t)ld * 2u + (uint32_t)((slot ^ ((row >> 1) & 7)) * 16) + kOffBias - (uint32_t)(i % 4) * 1024u;
+}
+
+// Sum of the PARTS partial 64 x 64 tiles of one output tile and the epilogue.  Every wavefront has
+// written its accumulators to its own 16 KiB of LDS (fragment order, 16-byte cells); wavefront
+// `rank` of the PARTS finishes 64 / PARTS rows, reading the cells row by row so that residual loads
+// and stores are 128-byte row segments.  Partial sums are added in ascending order of the wavefronts:
+// the result does not depend on timing.  The cell of (column octet c, lane l) sits at l ^ (c << 1):
+// both the writes (fixed c) and the row-wise reads (8 octets x 8 rows) are then conflict-free.
+template <int PARTS, int STRIDE, int EPI>
+__device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const GemmArgs &g, f32x4 *xch, int wave, int first,
+                                              int rank, int m_tile, int n_tile, int lane) {
+  constexpr int ROWS = 64 / PARTS, PASS = ROWS / 8;
+  const int pr = lane >> 3, oct = lane & 7;
+  const int n = n_tile + oct * 8, row0 = rank * ROWS + pr;
+  const bool n_ok = n < g.n_store;                       // n_store is a multiple of 8
+  u32x4 res[PASS];
+  float rs[PASS];
+#pragma unroll
+  for (int p = 0; p < PASS; ++p) {                       // fetched before the exchange: the latency is hidden by it
+    const int m = m_tile + row0 + p * 8;
+    res[p] = u32x4{0u, 0u, 0u, 0u};
+    if (EPI == EPI_BIAS_RES && m < g.M && n_ok)
+      res[p] = *reinterpret_cast<const u32x4 *>(g.res + (size_t)(m % g.res_mod) * g.ldr + n);
+    rs[p] = (g.row_scale && m < g.M) ? g.row_scale[m] : 1.0f;   // (fma(1, acc, bias) == acc + bias exactly)
+  }
+  f32x4 b0 = {0.f, 0.f, 0.f, 0.f}, b1 = b0;
+  if (n_ok) {
+    b0 = *reinterpret_cast<const f32x4 *>(g.bias + n);
+    b1 = *reinterpret_cast<const f32x4 *>(g.bias + n + 4);
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = a * 4 + q;
+        xch[wave * 1024 + (b * 8 + c) * 64 + (lane ^ (c << 1))] =
+            f32x4{acc[a][b][q * 4], acc[a][b][q * 4 + 1], acc[a][b][q * 4 + 2], acc[a][b][q * 4 + 3]};
+      }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < PASS; ++p) {
+    const int ml = row0 + p * 8, m = m_tile + ml, r = ml & 31;
+    const f32x4 *cell = xch + first * 1024 + ((ml >> 5) * 8 + oct) * 64;
+    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+    for (int j = 0; j < PARTS; ++j) {
+      lo += cell[j * STRIDE * 1024 + (r ^ (oct << 1))];
+      hi += cell[j * STRIDE * 1024 + ((32 + r) ^ (oct << 1))];
+    }
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const f32x4 &s = e < 2 ? lo : hi, &bi = e < 2 ? b0 : b1;
+      float x0 = fmaf(rs[p], s[(e & 1) * 2], bi[(e & 1) * 2]), x1 = fmaf(rs[p], s[(e & 1) * 2 + 1], bi[(e & 1) * 2 + 1]);
+      if (EPI == EPI_BIAS_GELU) {
+        x0 = gelu_tanh_f(x0);
+        x1 = gelu_tanh_f(x1);
+      }
+      if (EPI == EPI_BIAS_RES) {
+        x0 += bf16lo_to_f32(res[p][e]);
+        x1 += bf16hi_to_f32(res[p][e]);
+      }
+      o[e] = cvt_pk_bf16(x0, x1);
+    }
+    if (m < g.M && n_ok) *reinterpret_cast<u32x4 *>(g.C + (size_t)m * g.ldc + n) = o;
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// 64 x 64 tile, 4 wavefronts, two workgroups per compute unit.  Every wavefront computes the WHOLE
+// tile over its own k-tiles (t = wave, wave + 4, ...) from its own 16 KiB LDS slot, so the k-loop
+// has no barrier: wait for the slot's loads, read all 16 fragments at once, refill the slot, 16
+// MFMAs under which the refill is in flight.  The wavefronts drift apart and fill each other's gaps.
+// Measured per launch (back to back, weights cold; before: the 64 x 128 workgroup tile):
+//   729 rows, 1152 x 1152: 12.8 -> 7.1 us; 1152 x 4352: 50 -> 18 us; 64 rows, 3456 x 1152: 12.0 -> 6.9.
+// Eight wavefronts per workgroup (128 KiB of slots) are level for one tile per compute unit and
+// 20-40 % slower from two on.
+// ---------------------------------------------------------------------------------------
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_wave_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int NW = 4;
+  extern __shared__ __align__(16) uint16_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, grp = lane >> 5, lrow = lane >> 3, lslot = lane & 7;
+  int m0, n0;
+  small_tile_of(tiles_m, tiles_n, m0, n0);
+  m0 *= 64;
+  n0 *= 64;
+  const int kt_n = g.K / 64;
+  const char *a_base = reinterpret_cast<const char *>(g.A + (size_t)m0 * g.lda) - kOffBias;
+  const char *w_base = reinterpret_cast<const char *>(g.W + (size_t)n0 * g.K) - kOffBias;
+  uint32_t a_off[8], w_off[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = i * 8 + lrow;
+    a_off[i] = piece_offset(row, (m0 + row < g.M) ? row : g.M - 1 - m0, g.lda, lslot, i);   // rows past M: the last row again
+    w_off[i] = piece_offset(row, row, g.K, lslot, i);
+  }
+  uint16_t *slot = lds + wave * 8192;                    // 64 rows of A, 64 rows of W, 128 bytes each
+  auto issue = [&](int t) {
+    const char *ab = a_base + (size_t)t * 128, *wb = w_base + (size_t)t * 128;
+    asm volatile("" : "+s"(ab), "+s"(wb));               // scalar base + 32-bit lane offset form of the load
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      asm volatile("" : "+v"(a_off[i]));
+      lds_dma16_of4(ab + a_off[i], slot + (i & ~3) * 512, i);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      asm volatile("" : "+v"(w_off[i]));
+      lds_dma16_of4(wb + w_off[i], slot + 4096 + (i & ~3) * 512, i);
+    }
+  };
+  if (wave < kt_n) issue(wave);
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  const int fx = (r32 >> 1) & 7;
+  u32x4 fa[4][2], fw[4][2];
+  for (int t = wave; t < kt_n; t += NW) {
+    wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const uint16_t *p = slot + r32 * 64 + ((2 * ks + grp) ^ fx) * 8;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) fa[ks][b] = *reinterpret_cast<const u32x4 *>(p + b * 2048);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(p + 4096 + a * 2048);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read: it may be refilled
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + NW < kt_n) issue(t + NW);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = mfma32(fw[ks][a], fa[ks][b], acc[a][b]);
+  }
+  // (a wavefront's 16 KiB of the exchange are its own slot: no barrier before they are written)
+  finish_tile64<NW, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, 0, wave, m0, n0, lane);
+}
+
+// ---------------------------------------------------------------------------------------
+// BM x BN tile (128 x 128 or 128 x 64), 8 wavefronts with 64 x 64 wavefront tiles: KG = 2 or 4 groups
+// of wavefronts split the contraction, half of the groups (one wavefront per SIMD) reads fragments
+// while the other half runs its 16 MFMAs, a barrier after each phase.  Operands are shared inside
+// a group, so the load path carries half (128 x 128) or three quarters (128 x 64) of what four
+// 64 x 64 tiles would.  A set of k-tiles (one per group of a half) is loaded four phases ahead (three
+// stages: two phases).  Measured, one workgroup per compute unit (before: 64 x 128 workgroup tile):
+//   729 rows, 3456 x 1152 (162 workgroups of 128 x 128): 14.0 -> 12.0 us; 1092 rows, 1152 x 4352 (162 of
+//   128 x 64): 51 -> 26 us; 3276 rows, 1152 x 4352 (234 of 128 x 128): 54 -> 38 us.
+// ---------------------------------------------------------------------------------------
+template <int BM, int BN>
+struct PairShape {
+  static constexpr int WPG = (BM / 64) * (BN / 64), KG = 8 / WPG, KH = KG / 2;   // wavefronts per group, groups, groups per half
+  static constexpr int TILE = (BM + BN) * 64, SET = KH * TILE;                  // elements of one k-tile, of one stage
+  static constexpr int ST = KH == 1 ? 5 : 3;
+  static constexpr size_t kLdsBytes = (size_t)ST * SET * 2;
+  static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= 8 * 16384, "stages fit, and the exchange fits over them");
+};
+
+template <int BM, int BN, int EPI>
+__global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  using S = PairShape<BM, BN>;
+  constexpr int WN = BN / 64, WPG = S::WPG, KH = S::KH, ST = S::ST;
+  constexpr int A_BLK = BM / 8 / WPG, W_BLK = BN / 8 / WPG, LOADS = A_BLK + W_BLK;     // 1 KiB loads per wavefront and k-tile
+  static_assert(ST % 2 == 1, "the k-tiles of a half are loaded by that half");
+  extern __shared__ __align__(16) uint16_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = wave >> 2, gi = (wave & 3) / WPG, wi = (wave & 3) % WPG, wm = wi / WN, wn = wi % WN;
+  const int r32 = lane & 31, grp = lane >> 5, lrow = lane >> 3, lslot = lane & 7;
+  int m0, n0;
+  small_tile_of(tiles_m, tiles_n, m0, n0);
+  m0 *= BM;
+  n0 *= BN;
+  const int kt_n = g.K / 64, n_sets = (kt_n + KH - 1) / KH;
+  const char *a_base = reinterpret_cast<const char *>(g.A + (size_t)m0 * g.lda) - kOffBias;
+  const char *w_base = reinterpret_cast<const char *>(g.W + (size_t)n0 * g.K) - kOffBias;
+  uint32_t a_off[A_BLK], w_off[W_BLK];
+#pragma unroll
+  for (int i = 0; i < A_BLK; ++i) {
+    const int row = (wi * A_BLK + i) * 8 + lrow;
+    a_off[i] = piece_offset(row, (m0 + row < g.M) ? row : g.M - 1 - m0, g.lda, lslot, i);
+  }
+#pragma unroll
+  for (int i = 0; i < W_BLK; ++i) {
+    const int row = (wi * W_BLK + i) * 8 + lrow;
+    w_off[i] = piece_offset(row, row, g.K, lslot, i);
+  }
+  // Set s = k-tiles s * KH .. of the contraction; sets of even / odd index belong to half 0 / 1.
+  auto has = [&](int s) { return s * KH + gi < kt_n; };
+  auto issue = [&](int stage, int s) {
+    uint16_t *as = lds + stage * S::SET + gi * S::TILE, *ws = as + BM * 64;
+    const size_t ko = (size_t)(s * KH + gi) * 128;
+    const char *ab = a_base + ko, *wb = w_base + ko;
+    asm volatile("" : "+s"(ab), "+s"(wb));
+#pragma unroll
+    for (int i = 0; i < A_BLK; ++i) {
+      asm volatile("" : "+v"(a_off[i]));
+      lds_dma16_of4(ab + a_off[i], as + (wi * A_BLK + (i & ~3)) * 512, i);
+    }
+#pragma unroll
+    for (int i = 0; i < W_BLK; ++i) {
+      asm volatile("" : "+v"(w_off[i]));
+      lds_dma16_of4(wb + w_off[i], ws + (wi * W_BLK + (i & ~3)) * 512, i);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < ST - 1; ++s)
+    if ((s & 1) == half && has(s)) issue(s, s);
+
+  const int fx = (r32 >> 1) & 7;
+  const int a_row = gi * S::TILE + (wm * 64 + r32) * 64, w_row = gi * S::TILE + BM * 64 + (wn * 64 + r32) * 64;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  u32x4 fa[4][2], fw[4][2];
+  // Set s has landed (this wavefront's share): younger loads in flight are those of set s + 2, which
+  // with three stages has not been issued yet when this is asked.
+  auto wait_set = [&](int s) {
+    if (ST > 3 && has(s + 2)) wait_vmcnt<LOADS>();
+    else wait_vmcnt<0>();
+  };
+  auto phase_end = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Phase p: half p % 2 reads set p, the other half runs the MFMAs of set p - 1.
+  wait_set(half);
+  phase_end();
+  if (half) phase_end();
+  int stage = half, fill = half ? 0 : ST - 1;            // fill: stage of the previous set, read by everyone
+  for (int s = half; s < n_sets; s += 2) {
+    if (has(s)) {
+      const uint16_t *sp = lds + stage * S::SET;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const int ko = ((2 * ks + grp) ^ fx) * 8;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) fa[ks][b] = *reinterpret_cast<const u32x4 *>(sp + a_row + b * 2048 + ko);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(sp + w_row + a * 2048 + ko);
+      }
+    }
+    if (has(s + ST - 1)) issue(fill, s + ST - 1);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    phase_end();
+    if (has(s)) {
+      __builtin_amdgcn_s_setprio(1);                     // (wave priority: the other half is reading and loading)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) acc[a][b] = mfma32(fw[ks][a], fa[ks][b], acc[a][b]);
+      __builtin_amdgcn_s_setprio(0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + 2 < n_sets) wait_set(s + 2);
+    phase_end();
+    stage += 2;
+    if (stage >= ST) stage -= ST;
+    fill += 2;
+    if (fill >= ST) fill -= ST;
+  }
+  // Half 0 has passed 1 + 2 ceil(n_sets / 2) barriers, half 1 two plus 2 floor(n_sets / 2): level them.
+  if (half == (n_sets & 1)) phase_end();
+  finish_tile64<S::KG, WPG, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, wi, half * KH + gi, m0 + wm * 64, n0 + wn * 64,
+                                 lane);
+}
+
+// ---------------------------------------------------------------------------------------
+// 256 x 128 tile, 8 wavefronts with 64 x 64 wavefront tiles, one k-tile stream for all: half 0 owns the
+// upper 128 rows, half 1 the lower ones.  The halves alternate as above (phase 2 u: half 0 reads
+// k-tile u while half 1 runs the MFMAs of u - 1; phase 2 u + 1: the other way round), so the load path
+// carries 48 KiB per 1024 cycles of the matrix unit instead of 32 per 512.  Three stages of 48 KiB; a
+// stage is refilled when both halves have read it, three phases before it is needed again.  Pays where
+// this tiling makes one full round (or two) and 128 x 128 a started second one: 5832 rows, 1152 x 4352
+// (207 workgroups): 64 -> 59 us; 13122 rows: 131 -> 124 us; 1456 rows, 3456 x 1152: 20 -> 18.8 us.
+// ---------------------------------------------------------------------------------------
+template <int EPI>
+__global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int BM = 256, BN = 128, ST = 3, STAGE = (BM + BN) * 64;
+  constexpr int A_BLK = BM / 64, W_BLK = BN / 64, LOADS = A_BLK + W_BLK;      // 1 KiB loads per wavefront and k-tile
+  extern __shared__ __align__(16) uint16_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = wave >> 2, wm = wave >> 1, wn = wave & 1;
+  const int r32 = lane & 31, grp = lane >> 5, lrow = lane >> 3, lslot = lane & 7;
+  int m0, n0;
+  small_tile_of(tiles_m, tiles_n, m0, n0);
+  m0 *= BM;
+  n0 *= BN;
+  const int kt_n = g.K / 64;
+  const char *a_base = reinterpret_cast<const char *>(g.A + (size_t)m0 * g.lda) - kOffBias;
+  const char *w_base = reinterpret_cast<const char *>(g.W + (size_t)n0 * g.K) - kOffBias;
+  uint32_t a_off[A_BLK], w_off[W_BLK];
+#pragma unroll
+  for (int i = 0; i < A_BLK; ++i) {
+    const int row = (wave * A_BLK + i) * 8 + lrow;
+    a_off[i] = piece_offset(row, (m0 + row < g.M) ? row : g.M - 1 - m0, g.lda, lslot, i);
+  }
+#pragma unroll
+  for (int i = 0; i < W_BLK; ++i) {
+    const int row = (wave * W_BLK + i) * 8 + lrow;
+    w_off[i] = piece_offset(row, row, g.K, lslot, i);
+  }
+  auto issue = [&](int stage, int t) {
+    uint16_t *as = lds + stage * STAGE + wave * A_BLK * 512, *ws = lds + stage * STAGE + BM * 64 + wave * W_BLK * 512;
+    const char *ab = a_base + (size_t)t * 128, *wb = w_base + (size_t)t * 128;
+    asm volatile("" : "+s"(ab), "+s"(wb));
+#pragma unroll
+    for (int i = 0; i < A_BLK; ++i) {
+      asm volatile("" : "+v"(a_off[i]));
+      lds_dma16_of4(ab + a_off[i], as, i);
+    }
+#pragma unroll
+    for (int i = 0; i < W_BLK; ++i) {
+      asm volatile("" : "+v"(w_off[i]));
+      lds_dma16_of4(wb + w_off[i], ws, i);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t)
+    if (t < kt_n) issue(t, t);
+  const int fx = (r32 >> 1) & 7;
+  const int a_row = (wm * 64 + r32) * 64, w_row = BM * 64 + (wn * 64 + r32) * 64;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  u32x4 fa[4][2], fw[4][2];
+  // k-tile t has landed (this wavefront's share); the loads of t + 1 may still be in flight
+  auto wait_tile = [&](int t) {
+    if (t + 1 < kt_n) wait_vmcnt<LOADS>();
+    else wait_vmcnt<0>();
+  };
+  auto phase_end = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  wait_tile(0);
+  phase_end();
+  if (half) phase_end();
+  int stage = 0;
+  for (int t = 0; t < kt_n; ++t) {
+    const uint16_t *sp = lds + stage * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int ko = ((2 * ks + grp) ^ fx) * 8;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) fa[ks][b] = *reinterpret_cast<const u32x4 *>(sp + a_row + b * 2048 + ko);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(sp + w_row + a * 2048 + ko);
+    }
+    // (both halves have read k-tile t - 1 by now: its stage takes t + 2)
+    if (t + ST - 1 < kt_n) issue(stage == 0 ? ST - 1 : stage - 1, t + ST - 1);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (half && t + 1 < kt_n) wait_tile(t + 1);
+    phase_end();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = mfma32(fw[ks][a], fa[ks][b], acc[a][b]);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!half && t + 1 < kt_n) wait_tile(t + 1);
+    phase_end();
+    stage = (stage + 1 == ST) ? 0 : stage + 1;
+  }
+  if (!half) phase_end();
+  finish_tile64<1, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, wave, 0, m0 + wm * 64, n0 + wn * 64, lane);
+}
+
+}  // namespace
+
+// Launches KERN with its dynamic LDS size allowed once per device.
+template <void (*KERN)(GemmArgs, int, int)>
+static int launch_small(const GemmArgs &g, hipStream_t s, int bm, int bn, int threads, size_t lds_bytes) {
+  static std::atomic<uint64_t> allowed{0};
+  int dev = 0;
+  ET_HIP(hipGetDevice(&dev));
+  const uint64_t bit = 1ull << (dev & 63);
+  if (!(allowed.load(std::memory_order_relaxed) & bit)) {
+    ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+    allowed.fetch_or(bit, std::memory_order_relaxed);
+  }
+  const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.n_store + bn - 1) / bn;
+  hipLaunchKernelGGL(KERN, dim3(tiles_m * tiles_n), dim3(threads), lds_bytes, s, g, tiles_m, tiles_n);
+  ET_LAUNCH_CHECK();
+  return ET_OK;
+}
+
+int launch_gemm_wave(const GemmArgs &g, hipStream_t s) {
+  switch (g.epilogue) {
+    case EPI_BIAS: return launch_small<gemm_wave_kernel<EPI_BIAS>>(g, s, 64, 64, 256, 65536);
+    case EPI_BIAS_GELU: return launch_small<gemm_wave_kernel<EPI_BIAS_GELU>>(g, s, 64, 64, 256, 65536);
+    case EPI_BIAS_RES: return launch_small<gemm_wave_kernel<EPI_BIAS_RES>>(g, s, 64, 64, 256, 65536);
+    default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
+  }
+}
+
+template <int BM, int BN>
+static int launch_pair_shape(const GemmArgs &g, hipStream_t s) {
+  constexpr size_t bytes = PairShape<BM, BN>::kLdsBytes;
+  switch (g.epilogue) {
+    case EPI_BIAS: return launch_small<gemm_pair_kernel<BM, BN, EPI_BIAS>>(g, s, BM, BN, 512, bytes);
+    case EPI_BIAS_GELU: return launch_small<gemm_pair_kernel<BM, BN, EPI_BIAS_GELU>>(g, s, BM, BN, 512, bytes);
+    case EPI_BIAS_RES: return launch_small<gemm_pair_kernel<BM, BN, EPI_BIAS_RES>>(g, s, BM, BN, 512, bytes);
+    default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
+  }
+}
+int launch_gemm_half(const GemmArgs &g, hipStream_t s) {
+  constexpr size_t bytes = 3 * (256 + 128) * 64 * 2;
+  switch (g.epilogue) {
+    case EPI_BIAS: return launch_small<gemm_half_kernel<EPI_BIAS>>(g, s, 256, 128, 512, bytes);
+    case EPI_BIAS_GELU: return launch_small<gemm_half_kernel<EPI_BIAS_GELU>>(g, s, 256, 128, 512, bytes);
+    case EPI_BIAS_RES: return launch_small<gemm_half_kernel<EPI_BIAS_RES>>(g, s, 256, 128, 512, bytes);
+    default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
+  }
+}
+int launch_gemm_pair128(const GemmArgs &g, hipStream_t s) { return launch_pair_shape<128, 128>(g, s); }
+int launch_gemm_pair64(const GemmArgs &g, hipStream_t s) { return launch_pair_shape<128, 64>(g, s); }
+
+}  // namespace et

@@ -1,0 +1,70 @@
+// Device helpers shared by the matrix kernels: MFMA and conversion wrappers, direct global -> LDS
+// loads, explicit waits, the GELU of the fused epilogues.  Device code only.
+//
+// MFMA shape used throughout: v_mfma_f32_32x32x16_bf16.  Per 64-lane wavefront, with
+// g = lane / 32 and r = lane % 32:
+//   operand "A" (32 x 16): lane holds row r,    k = 8g .. 8g+7   (8 bf16 = one 16-byte vector)
+//   operand "B" (16 x 32): lane holds column r, k = 8g .. 8g+7
+//   accumulator (32 x 32): lane holds column r, rows (i / 4) * 8 + 4g + (i % 4), i = 0..15
+#pragma once
+#include "et_common.h"
+
+namespace et {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
+  bf16x2 v;
+  v.x = (__bf16)lo;
+  v.y = (__bf16)hi;
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+__device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ float gelu_tanh_f(float u) {
+  // 0.5 u (1 + tanh(y)) = u / (1 + exp(-2y)),  y = sqrt(2/pi) (u + 0.044715 u^3)
+  // exp(-2y) = exp2(u (c1 + c3 u^2)) with the factor -2 log2(e) sqrt(2/pi) folded into c1, c3;
+  // hardware exp2 and reciprocal (1 ulp) are ample for a result that is rounded to bf16.
+  const float c1 = -2.0f * 1.4426950408889634f * 0.7978845608028654f;
+  const float c3 = c1 * 0.044715f;
+  const float t = u * fmaf(u * u, c3, c1);
+  return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
+}
+
+// One wavefront moves 64 x 16 bytes to 1 KiB of consecutive LDS (no staging registers).  The
+// immediate offset moves the global AND the LDS address and has to be a literal.
+#define ET_LDS_DMA16(gptr, lptr)                                                             \
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
+                                   (__attribute__((address_space(3))) void *)(lptr), 16, 0, 0)
+
+#define ET_LDS_DMA16_OFF(gptr, lptr, imm)                                                    \
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
+                                   (__attribute__((address_space(3))) void *)(lptr), 16, (imm), 0)
+
+// The i-th of a group of four loads that share one LDS base (M0 cannot be rewritten before the
+// previous load has read it): `src` has to be lowered by (i % 4) KiB by the caller.
+__device__ __forceinline__ void lds_dma16_of4(const char *src, uint16_t *dst, int i) {
+  switch (i & 3) {
+    case 0: ET_LDS_DMA16_OFF(src, dst, 0); break;
+    case 1: ET_LDS_DMA16_OFF(src, dst, 1024); break;
+    case 2: ET_LDS_DMA16_OFF(src, dst, 2048); break;
+    default: ET_LDS_DMA16_OFF(src, dst, 3072); break;
+  }
+}
+
+// Waits until at most N of this wavefront's vector-memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+}  // namespace et

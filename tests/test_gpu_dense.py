@@ -268,3 +268,21 @@ def test_projector_matches_oracle(rows, d_in, d_hidden, d_out):
     assert got.shape == ref.shape
     assert rel_l2(got, ref) < 1e-2
     assert np.max(np.abs(got - ref)) < 0.05 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("cfg", [2, 3, 4, 5])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (63, 72, 128), (64, 64, 192), (65, 136, 320), (257, 200, 448), (130, 1152, 4352)])
+def test_gemm_split_over_wavefronts(cfg, M, N, K):
+    """The kernels for few rows: fewer k-tiles than wavefront groups, k-tiles that do not divide among them, ragged
+    rows and columns; in fp64 against bf16 inputs (one rounding of an fp32 sum: 2^-8 relative + accumulation noise)."""
+    rng = np.random.default_rng(M + N + K)
+    a_bits, a = _bf(rng, (M, K))
+    w_bits, w = _bf(rng, (N, K), scale=0.05)
+    bias = (0.1 * rng.standard_normal(N)).astype(np.float32)
+    r_bits, r = _bf(rng, (M, N))
+    plain = a @ w.T + bias.astype(np.float64)
+    a_d, w_d, b_d, r_d = bits_to_dev(a_bits), bits_to_dev(w_bits), torch.from_numpy(bias).cuda(), bits_to_dev(r_bits)
+    for epi, ref in ((0, plain), (1, O.gelu_tanh(plain)), (2, plain + r)):
+        got = dev_to_f64(et.et_gemm_bf16(a_d, w_d, b_d, epi, residual=r_d if epi == 2 else None, tile_config=cfg))
+        assert np.max(np.abs(got - ref) - 2 ** -8 * np.abs(ref)) < 2e-4 * (np.sqrt(K) * 0.05 + 1.0)
+        assert rel_l2(got, ref) < 4e-3
