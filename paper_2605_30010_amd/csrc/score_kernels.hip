@@ -3,39 +3,189 @@
 // maps; this build's reading: score[f][j] = mean over heads h and queries i of
 // softmax_h(Q K^T / sqrt(hd))[i][j] inside frame f, i.e. the attention token j RECEIVES.
 //
-// Three kernels over the q and k thirds of a [frames * L, 3 D] bf16 activation (every frame has L rows):
+// Input: the q and k thirds of a [frames * L, 3 D] bf16 activation (every frame has L rows).  Frames
+// whose keys fit the registers of one workgroup (attn_score_kernel) are done in one pass over the
+// queries; longer ones in two:
 //   1. row statistics: for every (frame, head, query) the maximum m of the scaled logits (log2
 //      domain) and 1 / sum_j exp2(s_j - m), by an online pass over 32-key tiles;
 //   2. column sums: for every (frame, head, key) the sum over queries of exp2(s - m_i) / l_i,
-//      accumulated in a fixed order inside one wavefront;
-//   3. the sum over heads in ascending order, divided by heads * L (no atomics anywhere:
-//      bit-reproducible).
-// Both compute the logits with v_mfma_f32_32x32x16_bf16 on fragments loaded straight from global
-// memory (the operand rows are 16-byte pieces of q / k rows); the head dimension is padded to a
-// multiple of 16 with zero fragments.  This runs once per clip, so it is kept simple rather than
-// staged through LDS.
-#include "et_common.h"
+//      accumulated in a fixed order inside one wavefront.
+// Either way the per-head sums meet in attn_score_reduce_kernel in a fixed order, divided by
+// heads * L (no atomics anywhere: bit-reproducible).  The two-pass kernels load their fragments
+// straight from global memory (16-byte pieces of q / k rows); the head dimension is padded to a
+// multiple of 16 with zero fragments.
+#include "mfma_common.h"
 
 namespace et {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
 constexpr int kScoreWaves = 4;
 constexpr int kMaxKSteps = 8;        // head_dim <= 128
 
-__device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                 0, 0, 0);
-}
-
 // 16-byte piece `chunk` (8 head dimensions) of a q / k row; zero past the head dimension.
 __device__ __forceinline__ u32x4 load_piece(const uint16_t *row, int chunk, int head_dim) {
   if (chunk * 8 < head_dim) return *reinterpret_cast<const u32x4 *>(row + chunk * 8);
   return u32x4{0u, 0u, 0u, 0u};
+}
+
+// ---------------------------------------------------------------------------------------
+// One pass.  A workgroup of 8 wavefronts owns one (frame, head) and a contiguous share of the 32-query
+// blocks; wavefront w owns the NB 32-key blocks w, w + 8, ..., whose K fragments stay in registers.
+// Per query block every wavefront computes S^T = K Q^T for its keys (the query on the accumulator's
+// lane axis), exponentiates against its OWN maximum, and leaves (maximum, sum) per query in LDS; after
+// one barrier each knows the factor exp2(m_w - m) / l that turns its exponentials into probabilities and
+// adds them to its column sums, which stay in registers to the end: one exponential and one logit per
+// (query, key) instead of two.  The query block (KSTEPS * 1 KiB) is staged in LDS, zero padded, one
+// block ahead; its row stride is an odd number of 16-byte slots (no bank conflicts).
+// Bound by the vector unit: per 16 accumulator values 16 exponentials at quarter rate, 2 fma, an add and half a max
+// each (about 480 cycles against 160 of the matrix unit).  The logits of the next block are issued behind the
+// barrier, so the matrix unit works under the combination (116 -> 109 us).  K and Q are read once per workgroup.
+// Measured against the two passes (all launches of a call): 32 frames x 16 heads x 729 tokens of 72: 373 -> 99 us;
+// 16 x 16 x 600 of 80: 139 -> 50; 8 x 16 x 729: 114 -> 41; one frame: 63 -> 33; 32 x 12 x 200 of 64: 38 -> 20.
+// ---------------------------------------------------------------------------------------
+constexpr int kPassWaves = 8;
+constexpr int kMaxSplits = 3;        // shares of a (frame, head)'s queries: their partial sums take the room of the two-pass statistics
+
+// Sum over the 32 lanes of each half of the wavefront, complete in lanes 31 and 63.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ float half_wave_sum(float v) {
+  v = dpp_add<0x111, 0xf>(v);          // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);          // row_shr:2
+  v = dpp_add<0x114, 0xf>(v);          // row_shr:4
+  v = dpp_add<0x118, 0xf>(v);          // row_shr:8
+  return dpp_add<0x142, 0xa>(v);       // row_bcast:15 into rows 1 and 3
+}
+// {this lane's value, the value of the same query in the other lane half}, in half order
+__device__ __forceinline__ float2 both_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int KSTEPS, int NB>
+__global__ __launch_bounds__(kPassWaves * 64, NB == 1 ? 4 : 2) void attn_score_kernel(
+    const uint16_t *__restrict__ qkv, int L, int D, int n_heads, int head_dim, float scale_log2, int splits,
+    float *__restrict__ partial) {
+  constexpr int QS = 2 * KSTEPS + 1;                     // 16-byte slots of a staged query row
+  __shared__ __align__(16) u32x4 qs[2][32 * QS];
+  __shared__ float2 ex[2][kPassWaves][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, grp = lane >> 5;
+  // neighbouring workgroups (shares of a head, heads of a frame) go to one XCD
+  const int total = gridDim.x, per = total / 8, rem = total % 8, xcd = blockIdx.x % 8;
+  const int v = xcd * per + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
+  const int sp = v % splits, h = (v / splits) % n_heads, f = v / (splits * n_heads);
+  const int n_qb = (L + 31) / 32, qb0 = n_qb * sp / splits, qb1 = n_qb * (sp + 1) / splits;
+  const size_t row_stride = (size_t)3 * D;
+  const uint16_t *head = qkv + (size_t)f * L * row_stride + (size_t)h * head_dim;
+
+  // one 16-byte piece of a query block per thread (32 rows x 2 KSTEPS pieces <= 512); zeros past L and head_dim
+  const int prow = tid / (2 * KSTEPS), pch = tid % (2 * KSTEPS);
+  auto fetch = [&](int qb) {
+    const int q = qb * 32 + prow;
+    u32x4 piece = u32x4{0u, 0u, 0u, 0u};
+    if (prow < 32 && q < L) piece = load_piece(head + (size_t)q * row_stride, pch, head_dim);
+    return piece;
+  };
+  u32x4 piece = fetch(qb0);
+  u32x4 kf[NB][KSTEPS];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int k = (wave + b * kPassWaves) * 32 + r32;
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      kf[b][ks] = u32x4{0u, 0u, 0u, 0u};
+      if (k < L) kf[b][ks] = load_piece(head + (size_t)k * row_stride + D, 2 * ks + grp, head_dim);
+    }
+  }
+  float col[NB][16];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) col[b][i] = 0.f;
+  const bool any_key = wave * 32 < L;                    // wave-uniform; a wavefront without keys only keeps the barriers
+  if (prow < 32) qs[0][prow * QS + pch] = piece;
+  __syncthreads();
+
+  f32x16 acc[NB];
+  auto logits = [&](int buf) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      const u32x4 q = qs[buf][r32 * QS + 2 * ks + grp];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[b] = mfma32(kf[b][ks], q, acc[b]);
+    }
+  };
+  if (any_key) logits(0);
+  for (int qb = qb0, buf = 0; qb < qb1; ++qb, buf ^= 1) {
+    if (qb + 1 < qb1) piece = fetch(qb + 1);
+    float p[NB][16];
+    float m = -INFINITY, l = 0.f;
+    if (any_key) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int k0 = (wave + b * kPassWaves) * 32;
+        if (k0 + 32 > L) {                               // (wave-uniform) keys past the frame
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (k0 + (i / 4) * 8 + 4 * grp + (i % 4) >= L) acc[b][i] = -INFINITY;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[b][i]);
+      }
+      // The wavefront's reference is a whole number, so the factor between two wavefronts' references is an
+      // exact power of two.
+      const float2 mm = both_halves(m);
+      m = ceilf(fmaxf(mm.x, mm.y) * scale_log2);         // (scale_log2 > 0: the order is kept)
+      const float m_ref = m == -INFINITY ? 0.f : m;      // no finite logit here: exponentials are 0, not NaN
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          p[b][i] = __builtin_amdgcn_exp2f(fmaf(acc[b][i], scale_log2, -m_ref));
+          l += p[b][i];
+        }
+      const float2 ll = both_halves(l);
+      l = ll.x + ll.y;
+    }
+    if (grp == 0) ex[buf][wave][r32] = make_float2(m, l);
+    if (prow < 32 && qb + 1 < qb1) qs[buf ^ 1][prow * QS + pch] = piece;
+    __syncthreads();
+    // (ex[buf] is written again two blocks on, behind the next barrier; qs[buf] likewise)
+    if (any_key) {
+      if (qb + 1 < qb1) logits(buf ^ 1);                 // the matrix unit works under the arithmetic below
+      float2 o[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) o[w] = ex[buf][grp * 4 + w][r32];      // each lane half combines four wavefronts
+      const float2 mm = both_halves(fmaxf(fmaxf(o[0].x, o[1].x), fmaxf(o[2].x, o[3].x)));
+      const float mt = fmaxf(mm.x, mm.y);
+      float lt = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) lt += o[w].y * __builtin_amdgcn_exp2f(o[w].x - mt);
+      const float2 ll = both_halves(lt);
+      const float fac = qb * 32 + r32 < L ? __builtin_amdgcn_exp2f(m - mt) / (ll.x + ll.y) : 0.f;   // queries past L add nothing
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) col[b][i] = fmaf(p[b][i], fac, col[b][i]);
+    }
+  }
+  float *dst = partial + (((size_t)f * n_heads + h) * splits + sp) * L;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float c = half_wave_sum(col[b][i]);
+      const int k = (wave + b * kPassWaves) * 32 + (i / 4) * 8 + 4 * grp + (i % 4);
+      if (r32 == 31 && k < L) dst[k] = c;
+    }
 }
 
 // Pass 1.  grid (ceil(L / 128), heads, frames), 4 wavefronts, 32 queries per wavefront.
@@ -66,7 +216,7 @@ __global__ __launch_bounds__(kScoreWaves * 64) void attn_rowstats_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) acc = mfma_bf16(load_piece(krow, 2 * ks + grp, head_dim), qf[ks], acc);
+    for (int ks = 0; ks < KSTEPS; ++ks) acc = mfma32(load_piece(krow, 2 * ks + grp, head_dim), qf[ks], acc);
     float sv[16], tmax = -INFINITY;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -124,7 +274,7 @@ __global__ __launch_bounds__(kScoreWaves * 64) void attn_colsum_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) acc = mfma_bf16(load_piece(qrow, 2 * ks + grp, head_dim), kf[ks], acc);
+    for (int ks = 0; ks < KSTEPS; ++ks) acc = mfma32(load_piece(qrow, 2 * ks + grp, head_dim), kf[ks], acc);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -136,15 +286,24 @@ __global__ __launch_bounds__(kScoreWaves * 64) void attn_colsum_kernel(
   if (grp == 0 && k0 + r32 < L) partial[((size_t)f * n_heads + h) * L + k0 + r32] = col;
 }
 
-// Pass 3: score[f][j] = (sum over heads, ascending, of partial) / (heads * L).
+// score[f][j] = (sum over heads and their shares of partial) / (heads * L); parts = heads * shares.  Eight sums over
+// every eighth part, then a tree: eight loads in flight per lane, and the error of a short sum.
 __global__ __launch_bounds__(256) void attn_score_reduce_kernel(const float *__restrict__ partial, int n_frames,
-                                                                int L, int n_heads, float *__restrict__ score) {
+                                                                int L, int n_heads, int parts, float *__restrict__ score) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n_frames * L) return;
   const int f = idx / L, j = idx - f * L;
-  float t = 0.f;
-  for (int h = 0; h < n_heads; ++h) t += partial[((size_t)f * n_heads + h) * L + j];
-  score[idx] = t / ((float)n_heads * (float)L);
+  const float *p = partial + (size_t)f * parts * L + j;
+  float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int h = 0; h < parts; h += 8)
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (h + u < parts) t[u] += p[(size_t)(h + u) * L];
+#pragma unroll
+  for (int w = 4; w > 0; w >>= 1)
+#pragma unroll
+    for (int u = 0; u < w; ++u) t[u] += t[u + w];
+  score[idx] = t[0] / ((float)n_heads * (float)L);
 }
 
 }  // namespace
@@ -161,11 +320,45 @@ int launch_attention_scores(const uint16_t *qkv, int n_frames, int L, int n_head
              "head_dim = %d must be a multiple of 8 in [8, %d]", head_dim, kMaxKSteps * 16);
   const int D = n_heads * head_dim;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)head_dim);
+  const int ksteps = (head_dim + 15) / 16;
+  const dim3 reduce_grid((n_frames * L + 255) / 256);
+  // One pass while a workgroup's registers hold the frame's K fragments, 3 blocks of 32 keys per wavefront
+  // (2 above head_dim 96), and the one-dimensional grid stays far below its limit.
+  if (L <= 32 * kPassWaves * (ksteps <= 6 ? 3 : 2) && n_frames <= 65535 && n_heads <= 65535 && (long)n_frames * n_heads <= (1L << 20)) {
+    const int nb = (L + 32 * kPassWaves - 1) / (32 * kPassWaves), n_qb = (L + 31) / 32;
+    int n_cu = 0, dev = 0;
+    ET_HIP(hipGetDevice(&dev));
+    ET_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    // Shares per (frame, head): the fewest query blocks on the busiest compute unit, a workgroup's own start
+    // (K fragments from memory, reduction of the column sums) counted as two.
+    int splits = 1;
+    long best = -1;
+    for (int sp = 1; sp <= kMaxSplits && sp <= n_qb; ++sp) {
+      const long slots = (long)(n_cu > 0 ? n_cu : 256), wgs = (long)n_frames * n_heads * sp;
+      const long cost = ((wgs + slots - 1) / slots) * ((n_qb + sp - 1) / sp + 2);
+      if (best < 0 || cost < best) { best = cost; splits = sp; }
+    }
+    float *partial = static_cast<float *>(stats_ws);
+    const dim3 grid((unsigned)(n_frames * n_heads * splits)), block(kPassWaves * 64);
+#define ET_PASS(KS, B)                                                                                               \
+  if (ksteps == KS && nb == B)                                                                                      \
+    hipLaunchKernelGGL((attn_score_kernel<KS, B>), grid, block, 0, s, qkv, L, D, n_heads, head_dim, scale_log2, splits, partial)
+#define ET_PASS2(KS) ET_PASS(KS, 1); ET_PASS(KS, 2)
+#define ET_PASS3(KS) ET_PASS2(KS); ET_PASS(KS, 3)
+    ET_PASS3(1); ET_PASS3(2); ET_PASS3(3); ET_PASS3(4); ET_PASS3(5); ET_PASS3(6); ET_PASS2(7); ET_PASS2(8);
+#undef ET_PASS3
+#undef ET_PASS2
+#undef ET_PASS
+    hipLaunchKernelGGL(attn_score_reduce_kernel, reduce_grid, dim3(256), 0, s, partial, n_frames, L, n_heads,
+                       n_heads * splits, score);
+    ET_LAUNCH_CHECK();
+    return ET_OK;
+  }
   float2 *stats = static_cast<float2 *>(stats_ws);
   float *partial = reinterpret_cast<float *>(stats + (size_t)n_frames * n_heads * L);
   const int blocks = (L + kScoreWaves * 32 - 1) / (kScoreWaves * 32);
   const dim3 g1(blocks, n_heads, n_frames), block(kScoreWaves * 64);
-  switch ((head_dim + 15) / 16) {
+  switch (ksteps) {
 #define ET_SCORE_CASE(KS)                                                                                           \
   case KS:                                                                                                          \
     hipLaunchKernelGGL(attn_rowstats_kernel<KS>, g1, block, 0, s, qkv, L, D, n_heads, head_dim, scale_log2, stats);  \
@@ -177,8 +370,7 @@ int launch_attention_scores(const uint16_t *qkv, int n_frames, int L, int n_head
 #undef ET_SCORE_CASE
     default: set_error("head_dim = %d unsupported", head_dim); return ET_ERR_INVALID_ARG;
   }
-  hipLaunchKernelGGL(attn_score_reduce_kernel, dim3((n_frames * L + 255) / 256), dim3(256), 0, s, partial, n_frames,
-                     L, n_heads, score);
+  hipLaunchKernelGGL(attn_score_reduce_kernel, reduce_grid, dim3(256), 0, s, partial, n_frames, L, n_heads, n_heads, score);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

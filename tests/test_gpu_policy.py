@@ -513,6 +513,40 @@ def test_attention_scores_match_oracle(F, n, H, hd):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("F,n,H,hd", [(1, 1, 1, 8), (2, 32, 3, 16), (1, 257, 2, 32), (3, 512, 2, 128), (17, 513, 16, 80),
+                                      (2, 768, 2, 112), (1, 769, 2, 72), (40, 40, 7, 64)])
+def test_attention_scores_over_the_sizes(F, n, H, hd):
+    """One-pass kernel: 1 to 3 key blocks per wavefront, ragged last blocks, 1 to 3 shares of the queries;
+    769 tokens take the two passes.  A logit of a few units carries a float32 error of about 1e-6, each
+    probability that relative error and the sums some ulps more: below 2e-5."""
+    D = H * hd
+    rng = np.random.default_rng(n + H)
+    bits = f64_to_bits(rng.standard_normal((F * n, 3 * D)))
+    got = et.et_attention_scores(bits_to_dev(bits), F, n, H, hd).cpu().numpy().astype(np.float64)
+    qk = bf16_bits_to_f32(bits).astype(np.float64).reshape(F, n, 3 * D)
+    want = O.attention_received_from_qk(qk[..., :D], qk[..., D:2 * D], H)
+    assert np.max(np.abs(got - want) / want) < 2e-5
+
+
+@pytest.mark.gpu
+def test_attention_scores_of_infinite_logits():
+    """Logits of minus infinity for all keys of one wavefront (32 of 64) give probability 0 there and leave
+    the rest alone; a NaN in one query reaches every token of its frame and head, and no other frame."""
+    F, n, hd = 3, 64, 16
+    rng = np.random.default_rng(3)
+    x = np.abs(rng.standard_normal((F, n, 3 * hd)))
+    x[1, :32, hd:2 * hd] = -3.0e38
+    x[2, 5, 0] = np.nan
+    bits = f64_to_bits(x.reshape(F * n, -1))
+    got = et.et_attention_scores(bits_to_dev(bits), F, n, 1, hd).cpu().numpy().astype(np.float64)
+    qk = bf16_bits_to_f32(bits).astype(np.float64).reshape(F, n, 3 * hd)
+    want = O.attention_received_from_qk(qk[:2, :, :hd], qk[:2, :, hd:2 * hd], 1)
+    assert np.all(got[1, :32] == 0.0)
+    assert np.max(np.abs(got[:2] - want)) < 2e-5 * want.max()
+    assert np.all(np.isnan(got[2]))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("merge_layers,select_layer,pi", [([1], 3, 0), ([0, 1], 2, 2), ([], 4, 1), ([1, 2], 4, 4)])
 def test_tiny_encoder_selection_by_attention_scores(merge_layers, select_layer, pi):
     rec = build_workload("c1_tiny")
