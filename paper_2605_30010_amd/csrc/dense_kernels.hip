@@ -92,6 +92,24 @@ __global__ __launch_bounds__(kLnRows * kWave) void rowstats_kernel(const uint16_
   if (lane == 0) rstd_out[row] = rstd;
 }
 
+// The statistics of rows that no GEMM has written (after a merge or selection), by pieces of 64 columns as the
+// residual epilogues leave them and with the same arithmetic: stats[p * ld + row] = (mean, sum of squares about it).
+template <int NV>
+__global__ __launch_bounds__(kLnRows * kWave) void piece_stats_kernel(const uint16_t *__restrict__ x, int rows, int D, int ld,
+                                                                      float2 *__restrict__ stats) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * kLnRows + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  uint4 raw[NV];
+  load_row<NV>(x + (size_t)row * D, D, lane, raw);
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const float2 st = piece_moments(u32x4{raw[j].x, raw[j].y, raw[j].z, raw[j].w});
+    const int piece = j * 8 + (lane >> 3);
+    if ((lane & 7) == 0 && piece < D / 64) stats[(size_t)piece * ld + row] = st;
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // Patch extraction: frames fp32 [T, C, H, W] -> bf16 [T * L, Kpad]; row (t, gy, gx), column
 // (c, py, px) flattened; columns >= C*P*P are zero.  One thread writes 8 columns (16 bytes).
@@ -183,7 +201,9 @@ __global__ __launch_bounds__(256) void im2col_stripe_kernel(const float *__restr
 // pieces to the slice; finally the slice is read row-wise and stored.  16-byte slots of a row are
 // XOR-swizzled by (row >> 1) & 7.  LDS operations of one wavefront execute in order, so the phases
 // need no barrier.
-template <int EPI, int FM, int FN>
+// STATS: the residual epilogue leaves the rows' statistics; for the others the row scales of the wavefront's FM * 32
+// rows lie at the start of the slice as floats.
+template <int EPI, bool STATS, int FM, int FN>
 __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const GemmArgs &g, int m_base,
                                                   int n_base, int lane, uint16_t *slice) {
   static_assert(FN % 2 == 0, "the staged epilogue handles 64-column pieces of the wavefront tile");
@@ -194,8 +214,11 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
 #pragma unroll
   for (int b = 0; b < FM; ++b) {
     const int m = m_base + b * 32 + r32;
-    rsv[b] = (g.row_scale && m < g.M) ? g.row_scale[m] : 1.0f;   // (fma(1, acc, bias) == acc + bias exactly)
+    if (EPI == EPI_BIAS_RES) rsv[b] = 1.0f;                   // (no LayerNorm in front of these)
+    else if (STATS) rsv[b] = reinterpret_cast<const float *>(slice)[b * 32 + r32];
+    else rsv[b] = (g.row_scale && m < g.M) ? g.row_scale[m] : 1.0f;   // (fma(1, acc, bias) == acc + bias exactly)
   }
+  if (STATS) asm volatile("" ::: "memory");                   // read before the slice takes the results
 #pragma unroll
   for (int half = 0; half < FN / 2; ++half) {
   const int nb = n_base + half * 64;
@@ -262,6 +285,11 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
       const int row = j * 8 + prow, m = mb + row;
       const u32x4 v = *reinterpret_cast<const u32x4 *>(slice + row * 64 + ((pch ^ ((row >> 1) & 7)) * 8));
       if (m < g.M && n_ok) *reinterpret_cast<u32x4 *>(g.C + (size_t)m * g.ldc + n_lane) = v;
+      if (EPI == EPI_BIAS_RES && STATS) {                     // (n_store is a multiple of 64 then)
+        const float2 st = piece_moments(v);
+        if (pch == 0 && m < g.M && n_ok) g.stats_out[(size_t)(nb >> 6) * g.stats_ld + m] = st;
+        asm volatile("" ::: "memory");                          // (one piece at a time: the accumulators leave no registers)
+      }
     }
   }
   }
@@ -284,7 +312,11 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
 // registers) while the finished tile's epilogue runs.  That removes the per-tile prologue latency
 // and the workgroup relaunch between tiles.
 // ---------------------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI>
+// STATS, residual epilogue: leaves g.stats_out.  STATS, others: the row scales come from g.stats_in: one wavefront per 64 rows combines them (a row per lane) before the
+// k-loop and leaves them, with the last k-tile, in the epilogue slices of the wavefronts that need them.  Only for
+// launches of one tile per workgroup: further tiles' scales cost more than a launch that computes them
+// (fetched beside the k-loop, 46656 rows: QKV 292 -> 324 us, fc1 445 -> 475).
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool STATS>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
@@ -419,11 +451,23 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
   };
-  clear_acc();
-
+  constexpr bool LNF = STATS && EPI != EPI_BIAS_RES;
+  static_assert(!LNF || (WTM % 64 == 0 && BM / 64 <= NW), "one wavefront per 64 rows");
+  float my_scale = 1.0f;
+  RowScale<6> scale;
+  if (LNF && wave < BM / 64) {
+    int m0, n0;
+    tile_of(0, m0, n0);
+    scale.fetch(g, m0 + wave * 64 + lane);
+  }
   if (is_loader) set_load_tile(0);
 #pragma unroll
   for (int st = 0; st < STAGES; ++st) issue_next(st);
+  if (LNF && wave < BM / 64) {
+    my_scale = scale.value(g);
+    asm volatile("" : "+v"(my_scale));
+  }
+  clear_acc();
 
   // Fragments are double-buffered in registers: the LDS reads of k-step s+1 are issued under the
   // MFMAs of step s, also across k-tiles (the one barrier per tile sits before the tile's last step).
@@ -460,6 +504,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
   int stage = 0, kt = 0, my_tile = 0, relax = 0;
   constexpr int N_ST = FM * (FN / 2) * 4;            // global stores per wavefront in the staged epilogue
   const int units = n_my * kt_n;
+  uint16_t *const slices = lds + STAGES * STAGE_ELEMS;
   for (int u = 0; u < units; ++u) {
 #pragma unroll
     for (int ks = 0; ks < KS - 1; ++ks) {
@@ -479,6 +524,11 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
     } else {
       wait_vmcnt<(STAGES - 2) * LOADS>();
     }
+    if (LNF && wave < BM / 64 && kt + 1 == kt_n) {
+      uint16_t *dst = slices + (wave * 64 / WTM) * WAVES_N * (32 * 64);
+#pragma unroll
+      for (int w = 0; w < WAVES_N; ++w) reinterpret_cast<float *>(dst + w * (32 * 64))[(wave * 64) % WTM + lane] = my_scale;
+    }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -491,12 +541,11 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
     if (++kt == kt_n) {                             // an output tile is complete
       int m0, n0;
       tile_of(my_tile, m0, n0);
-      gemm_epilogue_lds<EPI, FM, FN>(acc, g, m0 + wm * WTM, n0 + wn * WTN, lane,
-                                     lds + STAGES * STAGE_ELEMS + wave * (32 * 64));
+      gemm_epilogue_lds<EPI, STATS, FM, FN>(acc, g, m0 + wm * WTM, n0 + wn * WTN, lane, slices + wave * (32 * 64));
       if (m0 + BM <= g.M && n0 + BN <= g.n_store) relax = STAGES - 1;
-      clear_acc();
       kt = 0;
       ++my_tile;
+      clear_acc();
     }
   }
   wait_vmcnt<0>();                     // drain the padding loads before the workgroup's LDS is released
@@ -520,9 +569,13 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
   const int n_tiles = tiles_m * tiles_n;
   const int slots = n_cu * MINB;
   const dim3 grid(n_tiles < slots ? n_tiles : slots), block(NT);
-#define ET_GEMM_LAUNCH(E)                                                                        \
+  if (g.stats_in && n_tiles > slots) {
+    set_error("gemm: row statistics by pieces need one tile per workgroup (%d tiles, %d slots)", n_tiles, slots);
+    return ET_ERR_INVALID_ARG;
+  }
+#define ET_GEMM_LAUNCH(E, STATS)                                                                  \
   {                                                                                              \
-    auto kern = gemm_stream_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, MINB, E>;               \
+    auto kern = gemm_stream_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, MINB, E, STATS>;        \
     static bool attr_set = false;                                                                \
     if (!attr_set) {                                                                             \
       ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                           \
@@ -532,9 +585,15 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
     hipLaunchKernelGGL(kern, grid, block, lds_bytes, s, g, tiles_m, tiles_n);                    \
   }
   switch (g.epilogue) {
-    case EPI_BIAS: ET_GEMM_LAUNCH(EPI_BIAS); break;
-    case EPI_BIAS_GELU: ET_GEMM_LAUNCH(EPI_BIAS_GELU); break;
-    case EPI_BIAS_RES: ET_GEMM_LAUNCH(EPI_BIAS_RES); break;
+    case EPI_BIAS:
+      if (g.stats_in) ET_GEMM_LAUNCH(EPI_BIAS, true) else ET_GEMM_LAUNCH(EPI_BIAS, false)
+      break;
+    case EPI_BIAS_GELU:
+      if (g.stats_in) ET_GEMM_LAUNCH(EPI_BIAS_GELU, true) else ET_GEMM_LAUNCH(EPI_BIAS_GELU, false)
+      break;
+    case EPI_BIAS_RES:
+      if (g.stats_out) ET_GEMM_LAUNCH(EPI_BIAS_RES, true) else ET_GEMM_LAUNCH(EPI_BIAS_RES, false)
+      break;
     default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
   }
 #undef ET_GEMM_LAUNCH
@@ -896,6 +955,14 @@ int launch_rowstats(const uint16_t *x, float eps, int rows, int D, float *rstd, 
   return ET_OK;
 }
 
+int launch_piece_stats(const uint16_t *x, int rows, int D, int ld, float2 *stats, hipStream_t s) {
+  if (rows <= 0) return ET_OK;
+  dim3 grid((rows + kLnRows - 1) / kLnRows), block(kLnRows * kWave);
+  ET_DISPATCH_NV(D, hipLaunchKernelGGL(piece_stats_kernel<NV>, grid, block, 0, s, x, rows, D, ld, stats));
+  ET_LAUNCH_CHECK();
+  return ET_OK;
+}
+
 int launch_im2col(const float *frames, int T, int C, int H, int W, int P, int Kpad, uint16_t *out,
                   hipStream_t s) {
   const int GX = W / P, GY = H / P, L = GX * GY;
@@ -972,17 +1039,33 @@ static double gemm_cost(int cfg, long rows, long cols, int K) {
   }
 }
 
+// Whether gemm_stream_kernel walks one tile per workgroup (the others always do).
+static bool one_round(int cfg, long rows, long cols) {
+  if (cfg == kCfgBig) return ((rows + 255) / 256) * ((cols + 255) / 256) <= 256;
+  if (cfg == kCfg128) return ((rows + 127) / 128) * ((cols + 127) / 128) <= 512;
+  return true;
+}
+
+// Whether a GEMM over `rows` rows is best done in one round of tiles, i.e. takes the statistics of its rows by
+// pieces (launch_gemm accepts them for any size; beyond one round the row scales' own launch is cheaper).
+bool gemm_takes_pieces(int rows, int cols) { return one_round(kCfgBig, rows, cols); }
+
 int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
   if (g.M <= 0) return ET_OK;
   if (g.K % 64 != 0 || g.n_store % 8 != 0) {
     set_error("gemm: K = %d must be a multiple of 64 and n_store = %d of 8", g.K, g.n_store);
     return ET_ERR_INVALID_ARG;
   }
+  if ((g.stats_in && (g.row_scale || g.epilogue == EPI_BIAS_RES)) || (g.stats_out && (g.epilogue != EPI_BIAS_RES || g.n_store % 64 != 0))) {
+    set_error("gemm: row statistics asked of an epilogue that has none");
+    return ET_ERR_INVALID_ARG;
+  }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
   auto cheapest = [&](long rows, long cols, double *cost) {
-    int best = kCfgBig;
-    double c = gemm_cost(kCfgBig, rows, cols, g.K);
-    for (int cfg = kCfg128; cfg < kCfgCount; ++cfg) {
+    int best = kCfgWave;
+    double c = gemm_cost(best, rows, cols, g.K);
+    for (int cfg = 0; cfg < kCfgCount; ++cfg) {
+      if (g.stats_in && !one_round(cfg, rows, cols)) continue;
       const double x = gemm_cost(cfg, rows, cols, g.K);
       if (x < c) { c = x; best = cfg; }
     }
@@ -997,7 +1080,7 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
   // single launch.
   int best_dr = 0, best_dc = 0;
   const int tm = (g.M + 255) / 256, tn = (g.n_store + 255) / 256;
-  if ((long)tm * tn > 256) {
+  if (!g.stats_in && (long)tm * tn > 256) {
     const bool rows_splittable = (g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M) && tm > 1;
     const bool cols_splittable = g.n_store % 256 != 0 && tn > 1;
     double split_best = best - (best * 0.03 > 4.0 ? best * 0.03 : 4.0);
@@ -1025,6 +1108,7 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     part.bias = g.bias + cm;
     part.C = g.C + cm;
     if (g.res) part.res = g.res + cm;
+    if (g.stats_out) part.stats_out = g.stats_out + (size_t)(cm / 64) * g.stats_ld;
     part.n_store = g.n_store - cm;
     rc = launch_gemm(part, s);
   }
@@ -1034,6 +1118,8 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     part.C = g.C + (size_t)rm * g.ldc;
     if (g.res) part.res = g.res + (size_t)rm * g.ldr;
     if (g.row_scale) part.row_scale = g.row_scale + rm;
+    if (g.stats_in) part.stats_in = g.stats_in + rm;
+    if (g.stats_out) part.stats_out = g.stats_out + rm;
     part.M = g.M - rm;
     rc = launch_gemm(part, s);
   }

@@ -114,10 +114,14 @@ static int upload_f32(et_encoder *e, const float *src, int n, int n_pad, float *
 
 struct EncWs {
   uint16_t *x, *qkv, *att, *hid;
-  float *rstd;         // [R]: 1 / sqrt(var + eps) of the rows of x (LayerNorm folded into the next GEMM)
   int32_t *cu_full;
   void *merge;
-  void *score_ws;      // row statistics and per-head column sums of the attention-received scores
+  // row statistics and per-head column sums of the attention-received scores.  The statistics of the residual
+  // stream live there too, from a residual GEMM to the GEMM that follows it (no scores are computed between):
+  void *score_ws;
+  float *rstd;         // [R]: 1 / sqrt(var + eps) of the rows of x, or
+  float2 *pieces;      // [D / 64][piece_ld]: see GemmArgs::stats_out
+  int piece_ld;
   float *att_score;    // [T, L]
   size_t bytes;
 };
@@ -133,14 +137,17 @@ static EncWs carve_encoder(const et_encoder *e, void *ws, int T) {
   const size_t R = (size_t)T * e->L;
   EncWs w;
   w.x = static_cast<uint16_t *>(take(R * e->D * 2));
-  w.rstd = static_cast<float *>(take(R * sizeof(float)));
   w.qkv = static_cast<uint16_t *>(take(R * 3 * e->D * 2));
   w.att = static_cast<uint16_t *>(take(R * e->D * 2));
   const size_t hid_cols = (size_t)(e->Mhp > e->Kp_pad ? e->Mhp : e->Kp_pad);
   w.hid = static_cast<uint16_t *>(take(R * hid_cols * 2));
   w.cu_full = static_cast<int32_t *>(take((size_t)(T + 1) * 4));
   w.merge = take(carve_merge(nullptr, T, e->L, e->D).bytes);
-  w.score_ws = take(attention_scores_workspace_bytes(T, e->L, e->cfg.n_heads));
+  const size_t score_bytes = attention_scores_workspace_bytes(T, e->L, e->cfg.n_heads), piece_bytes = R * (e->D / 64) * sizeof(float2);
+  w.score_ws = take(score_bytes > piece_bytes ? score_bytes : piece_bytes);
+  w.rstd = static_cast<float *>(w.score_ws);
+  w.pieces = static_cast<float2 *>(w.score_ws);
+  w.piece_ld = (int)R;
   w.att_score = static_cast<float *>(take(R * sizeof(float)));
   w.bytes = off;
   return w;
@@ -148,16 +155,42 @@ static EncWs carve_encoder(const et_encoder *e, void *ws, int T) {
 
 #define ET_TIMED(kind, call) ET_TIMED_P(&e->prof, kind, call)
 
+static bool takes_pieces(const et_encoder *e, int rows) {
+  return gemm_takes_pieces(rows, 3 * e->D) && gemm_takes_pieces(rows, e->Mhp);
+}
+
+// have_pieces: w.pieces holds the statistics of w.x (only looked at where takes_pieces(rows)).
 // with_scores: also leave the attention each token receives in this block in w.att_score (frames of
 // equal length only).
 static int run_block(et_encoder *e, const LayerDev &lw, const EncWs &w, int rows, const int32_t *cu,
-                     int n_frames, int max_len, bool ragged, hipStream_t s, bool with_scores = false) {
+                     int n_frames, int max_len, bool ragged, bool have_pieces, hipStream_t s, bool with_scores = false) {
   const et_config &c = e->cfg;
   const int D = e->D;
-  // LayerNorm 1 and 2 are folded into the QKV and fc1 weights (fold_layernorm): only the row scales are computed here
-  ET_TIMED(ET_K_LAYERNORM, launch_rowstats(w.x, c.ln_eps, rows, D, w.rstd, s));
-  GemmArgs g;
-  g = GemmArgs{w.x, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, w.qkv, 3 * D, rows, 3 * D, D, EPI_BIAS, w.rstd};
+  // LayerNorm 1 and 2 are folded into the QKV and fc1 weights (fold_layernorm): only the row scales are needed.  On
+  // few rows (`by_pieces`) the GEMMs that write the residual stream leave its statistics by pieces of 64 columns
+  // and the next GEMM combines them; after a merge or selection the pieces are computed here.  On many rows the scales
+  // have a launch of their own, small beside the GEMMs.
+  const bool by_pieces = takes_pieces(e, rows);
+  auto normed = [&](GemmArgs g) {
+    if (by_pieces) {
+      g.stats_in = w.pieces;
+      g.stats_ld = w.piece_ld;
+      g.ln_eps = c.ln_eps;
+    } else {
+      g.row_scale = w.rstd;
+    }
+    return g;
+  };
+  auto leaving_pieces = [&](GemmArgs g) {
+    if (by_pieces) {
+      g.stats_out = w.pieces;
+      g.stats_ld = w.piece_ld;
+    }
+    return g;
+  };
+  if (!by_pieces) ET_TIMED(ET_K_LAYERNORM, launch_rowstats(w.x, c.ln_eps, rows, D, w.rstd, s));
+  else if (!have_pieces) ET_TIMED(ET_K_LAYERNORM, launch_piece_stats(w.x, rows, D, w.piece_ld, w.pieces, s));
+  GemmArgs g = normed(GemmArgs{w.x, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, w.qkv, 3 * D, rows, 3 * D, D, EPI_BIAS});
   ET_TIMED(ET_K_GEMM_QKV, launch_gemm(g, s));
   if (with_scores)
     ET_TIMED(ET_K_SCORE, launch_attention_scores(w.qkv, n_frames, max_len, c.n_heads, e->hd, w.score_ws, w.att_score, s));
@@ -166,12 +199,12 @@ static int run_block(et_encoder *e, const LayerDev &lw, const EncWs &w, int rows
   } else {        // every frame has max_len tokens
     ET_TIMED(ET_K_ATTENTION, launch_attention_uniform(w.qkv, n_frames, max_len, c.n_heads, e->hd, w.att, s));
   }
-  g = GemmArgs{w.att, D, lw.wo, lw.bo, w.x, D, rows, w.x, D, rows, D, D, EPI_BIAS_RES};
+  g = leaving_pieces(GemmArgs{w.att, D, lw.wo, lw.bo, w.x, D, rows, w.x, D, rows, D, D, EPI_BIAS_RES});
   ET_TIMED(ET_K_GEMM_OUT, launch_gemm(g, s));
-  ET_TIMED(ET_K_LAYERNORM, launch_rowstats(w.x, c.ln_eps, rows, D, w.rstd, s));
-  g = GemmArgs{w.x, D, lw.w1, lw.b1, nullptr, 0, 1, w.hid, e->Mhp, rows, e->Mhp, D, EPI_BIAS_GELU, w.rstd};
+  if (!by_pieces) ET_TIMED(ET_K_LAYERNORM, launch_rowstats(w.x, c.ln_eps, rows, D, w.rstd, s));
+  g = normed(GemmArgs{w.x, D, lw.w1, lw.b1, nullptr, 0, 1, w.hid, e->Mhp, rows, e->Mhp, D, EPI_BIAS_GELU});
   ET_TIMED(ET_K_GEMM_FC1, launch_gemm(g, s));
-  g = GemmArgs{w.hid, e->Mhp, lw.w2, lw.b2, w.x, D, rows, w.x, D, rows, D, e->Mhp, EPI_BIAS_RES};
+  g = leaving_pieces(GemmArgs{w.hid, e->Mhp, lw.w2, lw.b2, w.x, D, rows, w.x, D, rows, D, e->Mhp, EPI_BIAS_RES});
   ET_TIMED(ET_K_GEMM_FC2, launch_gemm(g, s));
   return ET_OK;
 }
@@ -377,14 +410,20 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
   ET_TIMED(ET_K_IM2COL, launch_im2col(frames_dev, T, c.channels, c.image_h, c.image_w, c.patch, e->Kp_pad, w.hid, s));
   {
     GemmArgs g{w.hid, e->Kp_pad, e->patch_w, e->patch_b, e->pos_emb, D, L, w.x, D, T * L, D, e->Kp_pad, EPI_BIAS_RES};
+    if (takes_pieces(e, T * L)) {
+      g.stats_out = w.pieces;
+      g.stats_ld = w.piece_ld;
+    }
     ET_TIMED(ET_K_GEMM_PATCH, launch_gemm(g, s));
   }
 
   bool ragged = false, selected = false, first_stage = true, warmed = false;
+  bool have_pieces = true;         // w.pieces belongs to w.x: not after a stage has replaced it
   int n_segments = T, next_merge = 0;
   for (int i = 0; i <= c.n_layers; ++i) {
     const bool merge_here = compress && policy && !selected && next_merge < n_merge && merge_layers[next_merge] == i;
     const bool select_here = compress && !selected && i == merge_layer;
+    if (merge_here || select_here) have_pieces = false;
     if (policy && (merge_here || select_here)) {
       const MergeWs mw = carve_merge(w.merge, T, L, D);
       int32_t *info = mw.n_seg + 8;
@@ -451,7 +490,8 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
         if ((rc = warm_weights(e, i, s))) return rc;
         warmed = true;
       }
-      if ((rc = run_block(e, e->layers[i], w, rows, cu, n_frames, max_len, ragged, s, with_scores))) return rc;
+      if ((rc = run_block(e, e->layers[i], w, rows, cu, n_frames, max_len, ragged, have_pieces, s, with_scores))) return rc;
+      have_pieces = true;
     }
   }
   if (warmed) {      // the caller's stream ends after the warm-up stream

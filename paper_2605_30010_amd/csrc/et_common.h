@@ -223,10 +223,20 @@ struct GemmArgs {
   uint16_t *C; int ldc;
   int M, n_store, K, epilogue;
   const float *row_scale = nullptr;
+  // LayerNorm statistics without a launch of their own: the residual epilogue that writes a row leaves (mean,
+  // sum of squares about that mean) of each 64-column piece p in stats_out[p * stats_ld + m]; a GEMM that reads
+  // the rows (K = row length) derives its row scales 1 / sqrt(var + ln_eps) from stats_in, in place of row_scale.
+  float2 *stats_out = nullptr;
+  const float2 *stats_in = nullptr;
+  int stats_ld = 0;
+  float ln_eps = 0.f;
 };
 // 1 / sqrt(var + eps) of every row of x [rows, D] bf16 (biased variance, fp32 two-pass like layernorm_kernel).
 int launch_rowstats(const uint16_t *x, float eps, int rows, int D, float *rstd, hipStream_t s);
+// The rows' statistics as GemmArgs::stats_out leaves them (D a multiple of 64).
+int launch_piece_stats(const uint16_t *x, int rows, int D, int ld, float2 *stats, hipStream_t s);
 int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg = -1);
+bool gemm_takes_pieces(int rows, int cols);
 int gemm_config_count();
 int launch_attention(const uint16_t *qkv, const int32_t *cu, int n_frames, int max_len, int n_heads,
                      int head_dim, uint16_t *out, hipStream_t s);

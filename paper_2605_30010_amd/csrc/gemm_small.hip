@@ -43,24 +43,23 @@ __device__ __forceinline__ uint32_t piece_offset(int row, int src_row, int ld, i
 // written its accumulators to its own 16 KiB of LDS (fragment order, 16-byte cells); wavefront
 // `rank` of the PARTS finishes 64 / PARTS rows, reading the cells row by row so that residual loads
 // and stores are 128-byte row segments.  Partial sums are added in ascending order of the wavefronts:
-// the result does not depend on timing.  The cell of (column octet c, lane l) sits at l ^ (c << 1):
+// the result does not depend on timing.  rs_tile (LDS): the row scales of the 64 rows, written before the barrier.
+// The cell of (column octet c, lane l) sits at l ^ (c << 1):
 // both the writes (fixed c) and the row-wise reads (8 octets x 8 rows) are then conflict-free.
 template <int PARTS, int STRIDE, int EPI>
 __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const GemmArgs &g, f32x4 *xch, int wave, int first,
-                                              int rank, int m_tile, int n_tile, int lane) {
+                                              int rank, int m_tile, int n_tile, int lane, const float *rs_tile) {
   constexpr int ROWS = 64 / PARTS, PASS = ROWS / 8;
   const int pr = lane >> 3, oct = lane & 7;
   const int n = n_tile + oct * 8, row0 = rank * ROWS + pr;
   const bool n_ok = n < g.n_store;                       // n_store is a multiple of 8
   u32x4 res[PASS];
-  float rs[PASS];
 #pragma unroll
   for (int p = 0; p < PASS; ++p) {                       // fetched before the exchange: the latency is hidden by it
     const int m = m_tile + row0 + p * 8;
     res[p] = u32x4{0u, 0u, 0u, 0u};
     if (EPI == EPI_BIAS_RES && m < g.M && n_ok)
       res[p] = *reinterpret_cast<const u32x4 *>(g.res + (size_t)(m % g.res_mod) * g.ldr + n);
-    rs[p] = (g.row_scale && m < g.M) ? g.row_scale[m] : 1.0f;   // (fma(1, acc, bias) == acc + bias exactly)
   }
   f32x4 b0 = {0.f, 0.f, 0.f, 0.f}, b1 = b0;
   if (n_ok) {
@@ -81,6 +80,7 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
 #pragma unroll
   for (int p = 0; p < PASS; ++p) {
     const int ml = row0 + p * 8, m = m_tile + ml, r = ml & 31;
+    const float rs = EPI == EPI_BIAS_RES ? 1.0f : rs_tile[ml];       // (no LayerNorm in front of a residual GEMM)
     const f32x4 *cell = xch + first * 1024 + ((ml >> 5) * 8 + oct) * 64;
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll
@@ -92,7 +92,7 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const f32x4 &s = e < 2 ? lo : hi, &bi = e < 2 ? b0 : b1;
-      float x0 = fmaf(rs[p], s[(e & 1) * 2], bi[(e & 1) * 2]), x1 = fmaf(rs[p], s[(e & 1) * 2 + 1], bi[(e & 1) * 2 + 1]);
+      float x0 = fmaf(rs, s[(e & 1) * 2], bi[(e & 1) * 2]), x1 = fmaf(rs, s[(e & 1) * 2 + 1], bi[(e & 1) * 2 + 1]);
       if (EPI == EPI_BIAS_GELU) {
         x0 = gelu_tanh_f(x0);
         x1 = gelu_tanh_f(x1);
@@ -104,6 +104,10 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
       o[e] = cvt_pk_bf16(x0, x1);
     }
     if (m < g.M && n_ok) *reinterpret_cast<u32x4 *>(g.C + (size_t)m * g.ldc + n) = o;
+    if (EPI == EPI_BIAS_RES && g.stats_out) {              // (n_store is a multiple of 64 then)
+      const float2 st = piece_moments(o);
+      if (oct == 0 && m < g.M && n_ok) g.stats_out[(size_t)(n_tile >> 6) * g.stats_ld + m] = st;
+    }
   }
 }
 
@@ -152,7 +156,13 @@ __global__ __launch_bounds__(256, 2) void gemm_wave_kernel(GemmArgs g, int tiles
       lds_dma16_of4(wb + w_off[i], slot + 4096 + (i & ~3) * 512, i);
     }
   };
+  float *rs_tile = reinterpret_cast<float *>(lds + NW * 8192);
+  RowScale<18> scale;
+  const bool scales = EPI != EPI_BIAS_RES && wave == 0;
+  if (scales) scale.fetch(g, m0 + lane);
+  __builtin_amdgcn_sched_barrier(0);
   if (wave < kt_n) issue(wave);
+  if (scales) rs_tile[lane] = scale.value(g);
   f32x16 acc[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -185,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wave_kernel(GemmArgs g, int tiles
         for (int b = 0; b < 2; ++b) acc[a][b] = mfma32(fw[ks][a], fa[ks][b], acc[a][b]);
   }
   // (a wavefront's 16 KiB of the exchange are its own slot: no barrier before they are written)
-  finish_tile64<NW, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, 0, wave, m0, n0, lane);
+  finish_tile64<NW, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, 0, wave, m0, n0, lane, rs_tile);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -204,7 +214,7 @@ struct PairShape {
   static constexpr int TILE = (BM + BN) * 64, SET = KH * TILE;                  // elements of one k-tile, of one stage
   static constexpr int ST = KH == 1 ? 5 : 3;
   static constexpr size_t kLdsBytes = (size_t)ST * SET * 2;
-  static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= 8 * 16384, "stages fit, and the exchange fits over them");
+  static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= 8 * 16384 + BM * 4, "stages fit, and the exchange and the row scales fit over them");
 };
 
 template <int BM, int BN, int EPI>
@@ -253,9 +263,18 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g, int tiles
       lds_dma16_of4(wb + w_off[i], ws + (wi * W_BLK + (i & ~3)) * 512, i);
     }
   };
+  // (the row scales stay in a register: with five stages LDS has room for them only once the k-loop is over)
+  float *rs_tile = reinterpret_cast<float *>(lds + 8 * 8192);
+  RowScale<18> scale;
+  float my_scale = 1.0f;
+  const bool scales = EPI != EPI_BIAS_RES && wave < BM / 64;
+  if (scales) scale.fetch(g, m0 + wave * 64 + lane);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int s = 0; s < ST - 1; ++s)
     if ((s & 1) == half && has(s)) issue(s, s);
+  if (scales) my_scale = scale.value(g);
+  asm volatile("" : "+v"(my_scale));
 
   const int fx = (r32 >> 1) & 7;
   const int a_row = gi * S::TILE + (wm * 64 + r32) * 64, w_row = gi * S::TILE + BM * 64 + (wn * 64 + r32) * 64;
@@ -320,8 +339,9 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g, int tiles
   }
   // Half 0 has passed 1 + 2 ceil(n_sets / 2) barriers, half 1 two plus 2 floor(n_sets / 2): level them.
   if (half == (n_sets & 1)) phase_end();
+  if (scales) rs_tile[wave * 64 + lane] = my_scale;
   finish_tile64<S::KG, WPG, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, wi, half * KH + gi, m0 + wm * 64, n0 + wn * 64,
-                                 lane);
+                                 lane, rs_tile + wm * 64);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -374,9 +394,15 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
       lds_dma16_of4(wb + w_off[i], ws, i);
     }
   };
+  float *rs_tile = reinterpret_cast<float *>(lds + 3 * STAGE);
+  RowScale<18> scale;
+  const bool scales = EPI != EPI_BIAS_RES && wave < BM / 64;
+  if (scales) scale.fetch(g, m0 + wave * 64 + lane);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int t = 0; t < ST - 1; ++t)
     if (t < kt_n) issue(t, t);
+  if (scales) rs_tile[wave * 64 + lane] = scale.value(g);
   const int fx = (r32 >> 1) & 7;
   const int a_row = (wm * 64 + r32) * 64, w_row = BM * 64 + (wn * 64 + r32) * 64;
   f32x16 acc[2][2];
@@ -432,7 +458,7 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
     stage = (stage + 1 == ST) ? 0 : stage + 1;
   }
   if (!half) phase_end();
-  finish_tile64<1, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, wave, 0, m0 + wm * 64, n0 + wn * 64, lane);
+  finish_tile64<1, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, wave, 0, m0 + wm * 64, n0 + wn * 64, lane, rs_tile + wm * 64);
 }
 
 }  // namespace
@@ -455,10 +481,11 @@ static int launch_small(const GemmArgs &g, hipStream_t s, int bm, int bn, int th
 }
 
 int launch_gemm_wave(const GemmArgs &g, hipStream_t s) {
+  constexpr size_t kWaveLds = 4 * 16384 + 64 * 4;        // slots and row scales
   switch (g.epilogue) {
-    case EPI_BIAS: return launch_small<gemm_wave_kernel<EPI_BIAS>>(g, s, 64, 64, 256, 65536);
-    case EPI_BIAS_GELU: return launch_small<gemm_wave_kernel<EPI_BIAS_GELU>>(g, s, 64, 64, 256, 65536);
-    case EPI_BIAS_RES: return launch_small<gemm_wave_kernel<EPI_BIAS_RES>>(g, s, 64, 64, 256, 65536);
+    case EPI_BIAS: return launch_small<gemm_wave_kernel<EPI_BIAS>>(g, s, 64, 64, 256, kWaveLds);
+    case EPI_BIAS_GELU: return launch_small<gemm_wave_kernel<EPI_BIAS_GELU>>(g, s, 64, 64, 256, kWaveLds);
+    case EPI_BIAS_RES: return launch_small<gemm_wave_kernel<EPI_BIAS_RES>>(g, s, 64, 64, 256, kWaveLds);
     default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
   }
 }
@@ -474,7 +501,7 @@ static int launch_pair_shape(const GemmArgs &g, hipStream_t s) {
   }
 }
 int launch_gemm_half(const GemmArgs &g, hipStream_t s) {
-  constexpr size_t bytes = 3 * (256 + 128) * 64 * 2;
+  constexpr size_t bytes = 3 * (256 + 128) * 64 * 2 + 256 * 4;      // stages and row scales
   switch (g.epilogue) {
     case EPI_BIAS: return launch_small<gemm_half_kernel<EPI_BIAS>>(g, s, 256, 128, 512, bytes);
     case EPI_BIAS_GELU: return launch_small<gemm_half_kernel<EPI_BIAS_GELU>>(g, s, 256, 128, 512, bytes);

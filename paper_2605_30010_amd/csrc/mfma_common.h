@@ -60,6 +60,79 @@ __device__ __forceinline__ void lds_dma16_of4(const char *src, uint16_t *dst, in
   }
 }
 
+// Sum over the eight lanes of an aligned group, in every one of them (lane ^ 1, lane ^ 2, mirror of the eight).
+template <int CTRL>
+__device__ __forceinline__ float dpp_plus(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_of_8_lanes(float v) { return dpp_plus<0x141>(dpp_plus<0x4E>(dpp_plus<0xB1>(v))); }
+
+// (mean, sum of squares about it) of the 64 bf16 values that eight lanes hold, eight each.
+__device__ __forceinline__ float2 piece_moments(u32x4 v) {
+  float x[8], s = 0.f, q = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    x[2 * e] = bf16lo_to_f32(v[e]);
+    x[2 * e + 1] = bf16hi_to_f32(v[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s += x[e];
+  const float mean = sum_of_8_lanes(s) * (1.0f / 64.0f);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float d = x[e] - mean;
+    q = fmaf(d, d, q);
+  }
+  return make_float2(mean, sum_of_8_lanes(q));
+}
+
+// Row scale of one row per lane: 1 / sqrt(var + eps) from the statistics of the row's pieces, or g.row_scale, or 1
+// (fma(1, acc, bias) == acc + bias exactly).  fetch() issues the loads, value() combines them, so that a kernel
+// can put its first operand loads between.  The pieces' means are taken relative to the first one's: nothing
+// cancels when the row's mean is many standard deviations.
+template <int BATCH>                                    // pieces in flight
+struct RowScale {
+  float2 v[BATCH];
+  uint32_t off;                                         // byte offset of the row in a piece
+  __device__ __forceinline__ float2 piece(const GemmArgs &g, int c) const {
+    return *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(g.stats_in + (size_t)c * g.stats_ld) + off);
+  }
+  __device__ __forceinline__ void fetch(const GemmArgs &g, int m) {
+    const int mc = m < g.M ? m : g.M - 1;
+    off = (uint32_t)mc * (uint32_t)sizeof(float2);
+    if (g.stats_in) {
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u)
+        if (u < g.K / 64) v[u] = piece(g, u);
+    } else {
+      v[0].x = g.row_scale ? g.row_scale[mc] : 1.0f;
+    }
+  }
+  __device__ __forceinline__ float value(const GemmArgs &g) {
+    if (!g.stats_in) return v[0].x;
+    const int pieces = g.K / 64;
+    const float ref = v[0].x, n = (float)pieces;
+    float s1 = 0.f, s2 = 0.f;
+    auto add = [&](float2 p) {
+      const float d = p.x - ref;
+      s1 += d;
+      s2 = fmaf(64.f * d, d, s2 + p.y);
+    };
+    for (int c = 0;;) {
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u)
+        if (c + u < pieces) add(v[u]);
+      c += BATCH;
+      if (c >= pieces) break;
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u)
+        if (c + u < pieces) v[u] = piece(g, c + u);
+    }
+    const float m2 = s2 - 64.f * s1 * (s1 / n);
+    return 1.0f / sqrtf((m2 < 0.f ? 0.f : m2) / (64.f * n) + g.ln_eps);   // (NaN stays NaN)
+  }
+};
+
 // Waits until at most N of this wavefront's vector-memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

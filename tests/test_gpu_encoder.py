@@ -14,7 +14,7 @@ import pytest
 import torch
 
 import paper_2605_30010_amd as et
-from et_inputs import TINY, SIGLIP, build_workload, make_clip, make_weights, bf16_bits_to_f32
+from et_inputs import TINY, SIGLIP, build_workload, make_clip, make_weights, bf16_bits_to_f32, f32_to_bf16_bits
 from oracle import earlytom_oracle as O
 from tests._util import dev_to_bits, dev_to_f64, rel_l2
 
@@ -315,3 +315,28 @@ def test_full_size_32_frame_clip(siglip_weights, m, keep):
 def test_full_size_64_frame_clip(siglip_weights):
     """Config 4: 64 frames, noisier scenes with abrupt cuts, merge after 4 blocks, keep 0.25."""
     _full_size_check("c4_siglip_t64", siglip_weights, range(0, 6))
+
+
+@pytest.mark.parametrize("d,heads,mlp,side,T", [(64, 4, 72, 28, 3), (128, 4, 200, 56, 1), (192, 2, 128, 56, 5), (192, 2, 256, 224, 24),
+                                                (576, 8, 320, 112, 8), (2176, 17, 64, 56, 2)])
+def test_row_statistics_taken_along_by_the_gemms(d, heads, mlp, side, T):
+    """The LayerNorm statistics travel from the GEMM that writes a row to the one that reads it, by pieces of 64
+    columns: 1, 2, 3, 9 and 34 pieces, ragged row counts, few rows and enough for the large tiles.  A wrong scale
+    shows in its row: every row within 3e-2 (the residual stream is rounded to bf16 five times; a row of mean 4 standard
+    deviations, the largest here, has steps of 2^-7 of one, so below 1e-2 each).  With a selection that keeps everything
+    in between, the statistics come from their own kernel: identical bits."""
+    from et_inputs import EncoderShape
+    shape = EncoderShape(n_layers=2, d_model=d, n_heads=heads, d_mlp=mlp, patch=14, image_h=side, image_w=side)
+    w = make_weights(shape, seed=d + T, bf16=True)
+    rng = np.random.default_rng(T)
+    w["pos_emb"] = bf16_bits_to_f32(f32_to_bf16_bits(rng.standard_normal(w["pos_emb"].shape).astype(np.float32)
+                                                     + rng.standard_normal((w["pos_emb"].shape[0], 1)).astype(np.float32)))
+    frames = rng.standard_normal((T, 3, side, side)).astype(np.float32)
+    enc = et.Encoder(shape, w, T)
+    got = _encode(enc, frames, -1, 0.9, 1.0)["tokens"]
+    off = _encode(enc, frames, 1, math.inf, 1.0)["tokens"]
+    enc.close()
+    assert torch.equal(off, got)
+    ref = O.encode_clip(shape, w, frames, -1, 0.9, 1.0)["tokens"]
+    err = np.linalg.norm(dev_to_f64(got) - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 3e-2, err.max()
