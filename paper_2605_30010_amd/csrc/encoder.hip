@@ -35,9 +35,6 @@ struct et_encoder {
   float *patch_b = nullptr, *final_g = nullptr, *final_b = nullptr;
   std::vector<et::LayerDev> layers;
   et::Profiler prof;
-  // weight warm-up (see warm_weights): a stream and two events of its own
-  hipStream_t warm_stream = nullptr;
-  hipEvent_t warm_go = nullptr, warm_done = nullptr;
   int32_t *count_host = nullptr;        // pinned: segment count read back in the middle of the compression stage
   hipEvent_t count_ready = nullptr;
 };
@@ -209,29 +206,6 @@ static int run_block(et_encoder *e, const LayerDev &lw, const EncWs &w, int rows
   return ET_OK;
 }
 
-// A block that runs on few rows (after the selection) is short against the time HBM needs to
-// deliver its weights: every GEMM there starts on cold weights (the 27 layers' 0.8 GB stay in no
-// cache) with two stages of look-ahead per workgroup, and the compute units are not full.  When
-// such a block starts, its four weight matrices are therefore pulled through the cache hierarchy by
-// small kernels on a stream of the encoder's own, released by an event on the caller's stream;
-// nothing waits for them but the end of the encode call.  Measured on the 32-frame clip (19 blocks
-// on 2912 rows): fc2 59 -> 48 us per launch, -1.5 % per clip; on blocks with many rows, or one
-// matrix at a time just before its GEMM, it costs more than it gains.
-constexpr int kWarmRows = 8192;
-static int warm_weights(et_encoder *e, int li, hipStream_t s) {
-  if (!e->warm_stream || li < 0 || li >= (int)e->layers.size()) return ET_OK;
-  const LayerDev &lw = e->layers[li];
-  const size_t D = e->D, Dn = round_up(e->D, 256);
-  ET_HIP(hipEventRecord(e->warm_go, s));
-  ET_HIP(hipStreamWaitEvent(e->warm_stream, e->warm_go, 0));
-  const void *const mats[4] = {lw.wqkv, lw.wo, lw.w1, lw.w2};
-  const size_t bytes[4] = {(size_t)round_up(3 * e->D, 256) * D * 2, Dn * D * 2, (size_t)round_up(e->Mhp, 256) * D * 2,
-                           Dn * e->Mhp * 2};
-  int rc;
-  if ((rc = launch_touch(mats, bytes, 4, e->warm_stream))) return rc;
-  return ET_OK;
-}
-
 }  // namespace et
 
 using namespace et;
@@ -316,14 +290,11 @@ int et_encoder_create(const et_config *config, const et_weights *weights, int32_
     ET_TRY(upload_f32(e, weights->b2[i], D, Dn, &l.b2));
   }
 #undef ET_TRY
-  if (hipStreamCreateWithFlags(&e->warm_stream, hipStreamNonBlocking) != hipSuccess ||      // (default priority)
-      hipEventCreateWithFlags(&e->warm_go, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&e->warm_done, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&e->count_ready, hipEventDisableTiming) != hipSuccess ||
+  if (hipEventCreateWithFlags(&e->count_ready, hipEventDisableTiming) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void **>(&e->count_host), 64, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     et_encoder_destroy(e);
-    set_error("creating the warm-up stream, the read-back event or its pinned word failed");
+    set_error("creating the read-back event or its pinned word failed");
     return ET_ERR_HIP;
   }
   *out = e;
@@ -332,9 +303,6 @@ int et_encoder_create(const et_config *config, const et_weights *weights, int32_
 
 void et_encoder_destroy(et_encoder *e) {
   if (!e) return;
-  if (e->warm_stream) (void)hipStreamDestroy(e->warm_stream);
-  if (e->warm_go) (void)hipEventDestroy(e->warm_go);
-  if (e->warm_done) (void)hipEventDestroy(e->warm_done);
   if (e->count_ready) (void)hipEventDestroy(e->count_ready);
   if (e->count_host) (void)hipHostFree(e->count_host);
   for (void *p : e->allocs) (void)hipFree(p);
@@ -417,7 +385,7 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
     ET_TIMED(ET_K_GEMM_PATCH, launch_gemm(g, s));
   }
 
-  bool ragged = false, selected = false, first_stage = true, warmed = false;
+  bool ragged = false, selected = false, first_stage = true;
   bool have_pieces = true;         // w.pieces belongs to w.x: not after a stage has replaced it
   int n_segments = T, next_merge = 0;
   for (int i = 0; i <= c.n_layers; ++i) {
@@ -486,17 +454,9 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
     if (i < c.n_layers) {
       const bool with_scores = by_attention && !selected && i == merge_layer - 1;
       int rc;
-      if (rows < kWarmRows) {
-        if ((rc = warm_weights(e, i, s))) return rc;
-        warmed = true;
-      }
       if ((rc = run_block(e, e->layers[i], w, rows, cu, n_frames, max_len, ragged, have_pieces, s, with_scores))) return rc;
       have_pieces = true;
     }
-  }
-  if (warmed) {      // the caller's stream ends after the warm-up stream
-    ET_HIP(hipEventRecord(e->warm_done, e->warm_stream));
-    ET_HIP(hipStreamWaitEvent(s, e->warm_done, 0));
   }
   if (plan) plan->n_segments = n_segments;
   if (c.has_final_ln) {
