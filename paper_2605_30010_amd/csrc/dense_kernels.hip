@@ -2,6 +2,8 @@
 // epilogues (bias | bias + GELU-tanh | bias + residual) and per-frame multi-head attention.
 //
 // The MFMA operand layouts are described in mfma_common.h.
+#include <atomic>
+
 #include "gemm_small.h"
 
 namespace et {
@@ -651,23 +653,283 @@ __device__ __forceinline__ uint2 lds_read_tr16(const uint16_t *p) {
 #endif
 }
 
+// What one wavefront keeps and does for its QB blocks of 32 queries, shared by the kernels below.
+template <int HD, int QB>
+struct AttentionRows {
+  static constexpr int NC = (HD + 15) / 16;
+  static constexpr int NDB = (HD + 31) / 32;
+  // When head_dim is not a multiple of 32 the last O^T row block has spare rows: the V^T fragment
+  // of row head_dim is overridden with ones, and accumulator row head_dim of O^T is the softmax
+  // denominator (the sum of the bf16-rounded probabilities, exactly what the numerator used), for free.
+  static constexpr bool SUM_BY_MFMA = (HD % 32) != 0;
+  // When head_dim is not a multiple of 16 the Q K^T contraction has spare slots: slot head_dim of
+  // every K row is read as 1 and slot head_dim of a query holds minus its reference maximum, so
+  // the MFMA delivers s - m_ref.  Otherwise the subtraction is a vector instruction per logit.
+  static constexpr bool REF_IN_PAD = (HD % 16) != 0;
+  // Reference maximum of the online softmax, per query, in exponent units.  It is moved only when
+  // the maximum of a 32-key block exceeds it by more than kLazy (probabilities then stay below
+  // 2^kLazy, harmless in fp32 / bf16), so the rescaling of O^T is rare after the first block.  With
+  // REF_IN_PAD it is kept bf16-representable (any reference serves as long as numerator and
+  // denominator use the same one).
+  static constexpr float kLazy = 8.0f;
+  u32x4 qf[QB][NC];
+  f32x16 o_acc[QB][NDB];
+  float m_ref[QB], l_run[QB];
+
+  // Q is scaled by log2(e) / sqrt(head_dim) once, here, and rounded back to bf16: the logits leave
+  // the MFMA already in the exponent's units.  A wavefront owns QB blocks of 32 queries: every K and
+  // V^T fragment it reads from LDS feeds QB MFMAs.
+  __device__ __forceinline__ void start(const uint16_t *qbase, int q_first, int n, int ld, float scale_log2, int r32, int grp) {
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+      const int q = q_first + j * 32 + r32;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int d = c * 16 + grp * 8;
+        u32x4 raw = u32x4{0u, 0u, 0u, 0u};
+        if (q < n && d < HD) raw = *reinterpret_cast<const u32x4 *>(qbase + (size_t)q * ld + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          qf[j][c][e] = cvt_pk_bf16(bf16lo_to_f32(raw[e]) * scale_log2, bf16hi_to_f32(raw[e]) * scale_log2);
+      }
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o_acc[j][b][i] = 0.f;
+      m_ref[j] = l_run[j] = 0.f;
+    }
+  }
+
+  // V^T fragment of 16-key chunk c, row block b = two transpose reads.  P's k-slots 0-3 of lane group
+  // grp are keys 16 c + 4 grp + (0..3), slots 4-7 keys 16 c + 8 + 4 grp + (0..3); lane s of a 16-lane
+  // group points at key + s / 4, features 32 b + 16 (group % 2) + 4 (s % 4) .. + 3.
+  static __device__ __forceinline__ u32x4 read_vfrag(const uint16_t *vs, int c, int b, int lane) {
+    const int vr_off = (4 * (lane >> 5) + ((lane & 15) >> 2)) * HD + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    const uint16_t *p = vs + vr_off + c * 16 * HD + b * 32;
+    const uint2 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 8 * HD);
+    u32x4 v = u32x4{lo.x, lo.y, hi.x, hi.y};
+    if (SUM_BY_MFMA && b == NDB - 1 && (lane & 31) == HD % 32) v = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    return v;
+  }
+
+  // The 32 keys kv0 + 32 kb .. of the 64-key tile at kv0, whose K and V rows lie at ks and vs.  `first`: nothing
+  // has been accumulated yet (the block then holds a valid key).
+  __device__ __forceinline__ void block(const uint16_t *ks, const uint16_t *vs, int kb, int kv0, int n, bool first, int lane) {
+    const int r32 = lane & 31, grp = lane >> 5;
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // S^T = K Q^T.  K fragments are double-buffered: the LDS read of contraction chunk c+1 is
+    // issued before the MFMAs of chunk c (scheduling barriers keep that order); the query blocks
+    // are independent MFMA chains.
+    f32x16 s_acc[QB];
+    u32x4 kf[2];
+    kf[0] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + grp * 8);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (c + 1 < NC)
+        kf[(c + 1) & 1] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + (c + 1) * 16 + grp * 8);
+      u32x4 kk = kf[c & 1];
+      if (REF_IN_PAD && c == NC - 1 && grp) kk = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < QB; ++j) s_acc[j] = mfma32(kk, qf[j][c], c == 0 ? zero16 : s_acc[j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // V^T fragments of the block's first 16 keys: fetched now, consumed after the softmax arithmetic
+    u32x4 vf[2][NDB];
+#pragma unroll
+    for (int b = 0; b < NDB; ++b)
+      vf[0][b] = read_vfrag(vs, 2 * kb, b, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    float mx[QB];
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+      if (!REF_IN_PAD) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s_acc[j][i] -= m_ref[j];
+      }
+      if (kv0 + kAttBKV > n) {               // only the last tile can hold keys past the frame
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int key = kv0 + kb * 32 + (i >> 2) * 8 + grp * 4 + (i & 3);
+          if (key >= n) s_acc[j][i] = -INFINITY;
+        }
+      }
+      float m = s_acc[j][0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) m = fmaxf(m, s_acc[j][i]);
+      // maximum over the two lane halves (the other 16 keys of the same query), without an LDS round trip
+      const uint32_t mb = __float_as_uint(m);
+      const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
+      mx[j] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));   // relative to m_ref
+    }
+    bool over = false;
+#pragma unroll
+    for (int j = 0; j < QB; ++j) over = over || mx[j] > kLazy;
+    if (first || __any(over)) {              // wave-uniform: move the references
+#pragma unroll
+      for (int j = 0; j < QB; ++j) {
+        // a block of the last tile may hold no valid key at all (mx = -inf): it moves nothing
+        float target = m_ref[j] + (first ? mx[j] : fmaxf(mx[j], 0.f));
+        if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
+        const float delta = target - m_ref[j];
+        if (!first) {                        // (nothing accumulated yet in the first block; later delta >= 0)
+          const float alpha = __builtin_amdgcn_exp2f(-delta);
+          l_run[j] *= alpha;
+#pragma unroll
+          for (int b = 0; b < NDB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o_acc[j][b][i] *= alpha;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s_acc[j][i] -= delta;
+        m_ref[j] = target;
+        if (REF_IN_PAD && grp) qf[j][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
+      }
+    }
+    u32x4 pf[QB][2];
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+      float p[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        p[i] = __builtin_amdgcn_exp2f(s_acc[j][i]);
+        if (!SUM_BY_MFMA) l_run[j] += p[i];
+      }
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        u32x4 v;
+        v.x = cvt_pk_bf16(p[hh * 8 + 0], p[hh * 8 + 1]); v.y = cvt_pk_bf16(p[hh * 8 + 2], p[hh * 8 + 3]);
+        v.z = cvt_pk_bf16(p[hh * 8 + 4], p[hh * 8 + 5]); v.w = cvt_pk_bf16(p[hh * 8 + 6], p[hh * 8 + 7]);
+        pf[j][hh] = v;
+      }
+    }
+    // O^T += V^T P^T; row blocks and query blocks are independent MFMA chains.
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      if (hh == 0) {
+#pragma unroll
+        for (int b = 0; b < NDB; ++b)
+          vf[1][b] = read_vfrag(vs, 2 * kb + 1, b, lane);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int j = 0; j < QB; ++j) o_acc[j][b] = mfma32(vf[hh][b], pf[j][hh], o_acc[j][b]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // A whole 64-key tile.  One query block alone (QB = 1) is bound by latency, not by issue: LDS reads, dependent MFMAs and
+  // the softmax chain follow one another.  Both 32-key blocks are then taken together: all K fragments are read up
+  // front, the two MFMA chains fill each other's gaps, one maximum and one reference check serve 64 keys (heads of 72,
+  // 8 x 729: 35.8 -> 34.0 us per launch, 5 x 729: 26.4 -> 25.0).
+  __device__ __forceinline__ void tile(const uint16_t *ks, const uint16_t *vs, int kv0, int n, bool first, int lane) {
+    if constexpr (QB > 1) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) block(ks, vs, kb, kv0, n, first && kb == 0, lane);
+    } else {
+      const int r32 = lane & 31, grp = lane >> 5;
+      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      u32x4 kf[NC][2];
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          kf[c][kb] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + c * 16 + grp * 8);
+          if (REF_IN_PAD && c == NC - 1 && grp) kf[c][kb] = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
+        }
+      u32x4 vf[2][NDB];
+#pragma unroll
+      for (int b = 0; b < NDB; ++b) vf[0][b] = read_vfrag(vs, 0, b, lane);
+      f32x16 s[2];
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32(kf[c][kb], qf[0][c], c == 0 ? zero16 : s[kb]);
+      if (!REF_IN_PAD) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[kb][i] -= m_ref[0];
+      }
+      if (kv0 + kAttBKV > n) {               // only the last tile can hold keys past the frame
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (kv0 + kb * 32 + (i >> 2) * 8 + grp * 4 + (i & 3) >= n) s[kb][i] = -INFINITY;
+      }
+      float m4[4];                           // four chains of maxima
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m4[u] = s[u >> 1][(u & 1) * 8];
+#pragma unroll
+      for (int i = 1; i < 8; ++i)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m4[u] = fmaxf(m4[u], s[u >> 1][(u & 1) * 8 + i]);
+      const uint32_t mb = __float_as_uint(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
+      const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
+      const float mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));      // relative to m_ref
+      if (first || __any(mx > kLazy)) {      // wave-uniform: move the reference
+        float target = m_ref[0] + (first ? mx : fmaxf(mx, 0.f));
+        if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
+        const float delta = target - m_ref[0];
+        if (!first) {                        // (nothing accumulated yet in the first tile; later delta >= 0)
+          const float alpha = __builtin_amdgcn_exp2f(-delta);
+          l_run[0] *= alpha;
+#pragma unroll
+          for (int b = 0; b < NDB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o_acc[0][b][i] *= alpha;
+        }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
+        m_ref[0] = target;
+        if (REF_IN_PAD && grp) qf[0][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
+      }
+      // P V by 16-key chunks: the exponentials of chunk c + 1 run beside the MFMAs of chunk c
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (c + 1 < 4) {
+#pragma unroll
+          for (int b = 0; b < NDB; ++b) vf[(c + 1) & 1][b] = read_vfrag(vs, c + 1, b, lane);
+        }
+        float p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          p[i] = __builtin_amdgcn_exp2f(s[c >> 1][(c & 1) * 8 + i]);
+          if (!SUM_BY_MFMA) l_run[0] += p[i];
+        }
+        u32x4 pf;
+        pf.x = cvt_pk_bf16(p[0], p[1]); pf.y = cvt_pk_bf16(p[2], p[3]);
+        pf.z = cvt_pk_bf16(p[4], p[5]); pf.w = cvt_pk_bf16(p[6], p[7]);
+#pragma unroll
+        for (int b = 0; b < NDB; ++b) o_acc[0][b] = mfma32(vf[c & 1][b], pf, o_acc[0][b]);
+      }
+    }
+  }
+
+  // Softmax denominator of this lane's query of block j.
+  __device__ __forceinline__ float denominator(int j, int r32) const {
+    if (SUM_BY_MFMA) {                        // accumulator row head_dim of O^T: lane group (row % 8) / 4, register (row / 8) * 4 + row % 4
+      constexpr int ROW = HD % 32;
+      return __shfl(o_acc[j][NDB - 1][(ROW / 8) * 4 + (ROW % 4)], r32 + 32 * ((ROW % 8) / 4), 64);
+    }
+    return l_run[j] + __shfl_xor(l_run[j], 32, 64);
+  }
+};
+
 template <int HD, int QB, int MINB>
 __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     const uint16_t *__restrict__ qkv, const int32_t *__restrict__ cu, int n, int n_heads, int n_qblk, float scale_log2,
     uint16_t *__restrict__ out) {
-  constexpr int NC = (HD + 15) / 16;
-  constexpr int NDB = (HD + 31) / 32;
+  using Rows = AttentionRows<HD, QB>;
+  constexpr int NDB = Rows::NDB;
   constexpr int STAGES = 2;
   constexpr int T_LOADS = HD / 8;            // 1 KiB pieces of a K (or V) tile: 64 keys * HD * 2 bytes
   constexpr int PW = (T_LOADS + kAttWaves - 1) / kAttWaves;   // pieces per wavefront
-  // When head_dim is not a multiple of 32 the last O^T row block has spare rows: the V^T fragment
-  // of row head_dim is overridden with ones, and accumulator row head_dim of O^T is the softmax
-  // denominator (the sum of the bf16-rounded probabilities, exactly what the numerator used), for free.
-  constexpr bool SUM_BY_MFMA = (HD % 32) != 0;
-  // When head_dim is not a multiple of 16 the Q K^T contraction has spare slots: slot head_dim of
-  // every K row is read as 1 and slot head_dim of a query holds minus its reference maximum, so
-  // the MFMA delivers s - m_ref.  Otherwise the subtraction is a vector instruction per logit.
-  constexpr bool REF_IN_PAD = (HD % 16) != 0;
   constexpr int K_ELEMS = kAttBKV * HD, V_ELEMS = kAttBKV * HD;
   constexpr int STAGE = K_ELEMS + V_ELEMS;
   // tail pad: the last V row's fragments of row blocks past head_dim read up to NDB * 32 - HD elements
@@ -743,51 +1005,8 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
 
   issue(0);
 
-  // Q is scaled by log2(e) / sqrt(head_dim) once, here, and rounded back to bf16: the logits leave
-  // the MFMA already in the exponent's units.  A wavefront owns QB blocks of 32 queries: every K and
-  // V^T fragment it reads from LDS feeds QB MFMAs.
-  u32x4 qf[QB][NC];
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-    const int q = q0 + (wave * QB + j) * 32 + r32;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int d = c * 16 + grp * 8;
-      u32x4 raw = u32x4{0u, 0u, 0u, 0u};
-      if (q < n && d < HD) raw = *reinterpret_cast<const u32x4 *>(qbase + (size_t)q * ld + d);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        qf[j][c][e] = cvt_pk_bf16(bf16lo_to_f32(raw[e]) * scale_log2, bf16hi_to_f32(raw[e]) * scale_log2);
-    }
-  }
-  f32x16 o_acc[QB][NDB];
-#pragma unroll
-  for (int j = 0; j < QB; ++j)
-#pragma unroll
-    for (int b = 0; b < NDB; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o_acc[j][b][i] = 0.f;
-  // Reference maximum of the online softmax, per query, in exponent units.  It is moved only when
-  // the maximum of a 32-key block exceeds it by more than kLazy (probabilities then stay below
-  // 2^kLazy, harmless in fp32 / bf16), so the rescaling of O^T is rare after the first block.  With
-  // REF_IN_PAD it is kept bf16-representable (any reference serves as long as numerator and
-  // denominator use the same one).
-  constexpr float kLazy = 8.0f;
-  float m_ref[QB], l_run[QB];
-#pragma unroll
-  for (int j = 0; j < QB; ++j) m_ref[j] = l_run[j] = 0.f;
-  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // V^T fragment of 16-key chunk c, row block b = two transpose reads.  P's k-slots 0-3 of lane group
-  // grp are keys 16 c + 4 grp + (0..3), slots 4-7 keys 16 c + 8 + 4 grp + (0..3); lane s of a 16-lane
-  // group points at key + s / 4, features 32 b + 16 (group % 2) + 4 (s % 4) .. + 3.
-  const int vr_off = (4 * grp + ((lane & 15) >> 2)) * HD + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-  auto read_vfrag = [&](const uint16_t *vs, int c, int b) -> u32x4 {
-    const uint16_t *p = vs + vr_off + c * 16 * HD + b * 32;
-    const uint2 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 8 * HD);
-    u32x4 v = u32x4{lo.x, lo.y, hi.x, hi.y};
-    if (SUM_BY_MFMA && b == NDB - 1 && r32 == HD % 32) v = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-    return v;
-  };
+  Rows rows;
+  rows.start(qbase, q0 + wave * QB * 32, n, ld, scale_log2, r32, grp);
 
   for (int t = 0; t < n_tiles; ++t) {
     const int kv0 = t * kAttBKV, stage = t & 1;
@@ -798,125 +1017,12 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     asm volatile("" ::: "memory");
     if (t + 1 < n_tiles) issue(stage ^ 1);
     const uint16_t *ks = lds + stage * STAGE;
-    const uint16_t *vs = ks + K_ELEMS;
-
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {           // the tile's two 32-key blocks
-      // S^T = K Q^T.  K fragments are double-buffered: the LDS read of contraction chunk c+1 is
-      // issued before the MFMAs of chunk c (scheduling barriers keep that order); the query blocks
-      // are independent MFMA chains.
-      f32x16 s_acc[QB];
-      u32x4 kf[2];
-      kf[0] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + grp * 8);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (c + 1 < NC)
-          kf[(c + 1) & 1] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + (c + 1) * 16 + grp * 8);
-        u32x4 kk = kf[c & 1];
-        if (REF_IN_PAD && c == NC - 1 && grp) kk = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < QB; ++j) s_acc[j] = mfma32(kk, qf[j][c], c == 0 ? zero16 : s_acc[j]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // V^T fragments of the block's first 16 keys: fetched now, consumed after the softmax arithmetic
-      u32x4 vf[2][NDB];
-#pragma unroll
-      for (int b = 0; b < NDB; ++b)
-        vf[0][b] = read_vfrag(vs, 2 * kb, b);
-      __builtin_amdgcn_sched_barrier(0);
-      float mx[QB];
-#pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        if (!REF_IN_PAD) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s_acc[j][i] -= m_ref[j];
-        }
-        if (kv0 + kAttBKV > n) {               // only the last tile can hold keys past the frame
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = kv0 + kb * 32 + (i >> 2) * 8 + grp * 4 + (i & 3);
-            if (key >= n) s_acc[j][i] = -INFINITY;
-          }
-        }
-        float m = s_acc[j][0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) m = fmaxf(m, s_acc[j][i]);
-        // maximum over the two lane halves (the other 16 keys of the same query), without an LDS round trip
-        const uint32_t mb = __float_as_uint(m);
-        const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
-        mx[j] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));   // relative to m_ref
-      }
-      const bool first = t == 0 && kb == 0;    // (its block always holds a valid key: mx is finite)
-      bool over = false;
-#pragma unroll
-      for (int j = 0; j < QB; ++j) over = over || mx[j] > kLazy;
-      if (first || __any(over)) {              // wave-uniform: move the references
-#pragma unroll
-        for (int j = 0; j < QB; ++j) {
-          // a block of the last tile may hold no valid key at all (mx = -inf): it moves nothing
-          float target = m_ref[j] + (first ? mx[j] : fmaxf(mx[j], 0.f));
-          if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
-          const float delta = target - m_ref[j];
-          if (!first) {                        // (nothing accumulated yet in the first block; later delta >= 0)
-            const float alpha = __builtin_amdgcn_exp2f(-delta);
-            l_run[j] *= alpha;
-#pragma unroll
-            for (int b = 0; b < NDB; ++b)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) o_acc[j][b][i] *= alpha;
-          }
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s_acc[j][i] -= delta;
-          m_ref[j] = target;
-          if (REF_IN_PAD && grp) qf[j][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
-        }
-      }
-      u32x4 pf[QB][2];
-#pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        float p[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          p[i] = __builtin_amdgcn_exp2f(s_acc[j][i]);
-          if (!SUM_BY_MFMA) l_run[j] += p[i];
-        }
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          u32x4 v;
-          v.x = cvt_pk_bf16(p[hh * 8 + 0], p[hh * 8 + 1]); v.y = cvt_pk_bf16(p[hh * 8 + 2], p[hh * 8 + 3]);
-          v.z = cvt_pk_bf16(p[hh * 8 + 4], p[hh * 8 + 5]); v.w = cvt_pk_bf16(p[hh * 8 + 6], p[hh * 8 + 7]);
-          pf[j][hh] = v;
-        }
-      }
-      // O^T += V^T P^T; row blocks and query blocks are independent MFMA chains.
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        if (hh == 0) {
-#pragma unroll
-          for (int b = 0; b < NDB; ++b)
-            vf[1][b] = read_vfrag(vs, 2 * kb + 1, b);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < NDB; ++b)
-#pragma unroll
-          for (int j = 0; j < QB; ++j) o_acc[j][b] = mfma32(vf[hh][b], pf[j][hh], o_acc[j][b]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    rows.tile(ks, ks + K_ELEMS, kv0, n, t == 0, lane);
   }
 
 #pragma unroll
   for (int j = 0; j < QB; ++j) {
-    float l_tot;
-    if (SUM_BY_MFMA) {                        // accumulator row head_dim of O^T: lane group (row % 8) / 4, register (row / 8) * 4 + row % 4
-      constexpr int ROW = HD % 32;
-      l_tot = __shfl(o_acc[j][NDB - 1][(ROW / 8) * 4 + (ROW % 4)], r32 + 32 * ((ROW % 8) / 4), 64);
-    } else {
-      l_tot = l_run[j] + __shfl_xor(l_run[j], 32, 64);
-    }
-    const float inv = 1.0f / l_tot;
+    const float inv = 1.0f / rows.denominator(j, r32);
     const int q = q0 + (wave * QB + j) * 32 + r32;
     if (q < n) {
       uint16_t *orow = out + ((size_t)start + q) * D + h * HD;
@@ -926,13 +1032,140 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
         for (int qd = 0; qd < 4; ++qd) {
           const int d = b * 32 + qd * 8 + grp * 4;
           if (d < HD) {
-            uint2 o;
-            o.x = cvt_pk_bf16(o_acc[j][b][qd * 4 + 0] * inv, o_acc[j][b][qd * 4 + 1] * inv);
-            o.y = cvt_pk_bf16(o_acc[j][b][qd * 4 + 2] * inv, o_acc[j][b][qd * 4 + 3] * inv);
-            *reinterpret_cast<uint2 *>(orow + d) = o;
+            const f32x16 &o = rows.o_acc[j][b];
+            uint2 w;
+            w.x = cvt_pk_bf16(o[qd * 4 + 0] * inv, o[qd * 4 + 1] * inv);
+            w.y = cvt_pk_bf16(o[qd * 4 + 2] * inv, o[qd * 4 + 3] * inv);
+            *reinterpret_cast<uint2 *>(orow + d) = w;
           }
         }
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The same for few queries, where a workgroup per 128 queries leaves most of the chip idle and walks all key tiles
+// one after the other (1.4 us per tile): the 8 wavefronts of a workgroup form KG groups; a group takes 256 / KG
+// queries, one block of 32 per wavefront, and every KG-th key tile, with LDS stages of its own.  The groups'
+// partial results (reference maximum, denominator, O^T) meet in LDS; a thread finishes 8 features of a query
+// and stores 16 bytes.  (One query block per workgroup, its tiles split over 4 wavefronts with private slots, loads every
+// tile once per 32 queries: 729 tokens x 16 heads 18.0 -> 13.6 us, and slower than the kernel above from two frames on.)
+// ---------------------------------------------------------------------------------------
+template <int HD, int KG>
+struct GroupShape {
+  static constexpr int WPG = 8 / KG, NDB = (HD + 31) / 32, TILE = kAttBKV * HD;
+  static constexpr int GROUP = 4 * TILE + 64;               // elements: two stages of K and V, and what the last fragments read past them
+  static constexpr int O_LD = NDB * 32 + 4;                 // floats of a query's partial row: no bank conflicts on 16-byte cells
+  static constexpr size_t kStages = (size_t)KG * GROUP * 2, kPartials = (size_t)8 * 32 * O_LD * 4;
+  static constexpr size_t kLdsBytes = kStages > kPartials ? kStages : kPartials;
+  static constexpr bool kFits = kLdsBytes + 8 * 32 * sizeof(float2) <= 160 * 1024;
+};
+
+template <int HD, int KG>
+__global__ __launch_bounds__(512, 1) void attention_group_kernel(
+    const uint16_t *__restrict__ qkv, const int32_t *__restrict__ cu, int n, int n_heads, int n_qblk, float scale_log2,
+    uint16_t *__restrict__ out) {
+  using S = GroupShape<HD, KG>;
+  using Rows = AttentionRows<HD, 1>;
+  constexpr int WPG = S::WPG, T_LOADS = HD / 8, PW = (T_LOADS + WPG - 1) / WPG;
+  extern __shared__ __align__(16) uint16_t lds[];
+  __shared__ float2 ml[8][32];
+  const int v = xcd_contiguous_index();
+  const int q0 = (v % n_qblk) * (32 * WPG), h = (v / n_qblk) % n_heads, f = v / (n_qblk * n_heads);
+  int start = f * n;
+  if (cu) {                                            // ragged frames (workgroup-uniform)
+    start = cu[f];
+    n = cu[f + 1] - start;
+    if (q0 >= n) return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp_k = wave / WPG, wi = wave % WPG;       // group (its key tiles) and query block inside the workgroup
+  const int r32 = lane & 31, grp = lane >> 5;
+  const int D = n_heads * HD, ld = 3 * D;
+  const uint16_t *qbase = qkv + (size_t)start * ld + h * HD;
+  const uint16_t *kbase = qbase + D;                    // (V: + D again)
+  const int n_tiles = (n + kAttBKV - 1) / kAttBKV;
+  uint16_t *mem = lds + grp_k * S::GROUP;
+
+  // Pieces wi, wi + WPG, ... of the group's tiles: K by direct loads, V through registers (see above).  Key rows past
+  // the frame are clamped to its last one (masked later).
+  u32x4 vreg[PW];
+  auto issue = [&](int t, int stage) {
+    const uint16_t *src[PW];
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      const int id = j * WPG + wi, q = (id < T_LOADS ? id : 0) * 64 + lane, key = q / (HD / 8), ch = q % (HD / 8);
+      const int row = t * kAttBKV + key;
+      src[j] = kbase + (size_t)(row < n ? row : n - 1) * ld + ch * 8;
+    }
+#pragma unroll
+    for (int j = 0; j < PW; ++j)
+      if (j * WPG + wi < T_LOADS) ET_LDS_DMA16(src[j], mem + stage * 2 * S::TILE + (j * WPG + wi) * 512);
+#pragma unroll
+    for (int j = 0; j < PW; ++j)
+      if (j * WPG + wi < T_LOADS) vreg[j] = *reinterpret_cast<const u32x4 *>(src[j] + D);
+  };
+  if (grp_k < n_tiles) issue(grp_k, 0);
+  Rows rows;
+  rows.start(qbase, q0 + wi * 32, n, ld, scale_log2, r32, grp);
+  int stage = 0;
+  for (int t0 = 0; t0 < n_tiles; t0 += KG, stage ^= 1) {
+    const int t = t0 + grp_k;
+    wait_vmcnt<0>();                                   // tile t: K has landed in LDS, V in registers
+    if (t < n_tiles) {
+#pragma unroll
+      for (int j = 0; j < PW; ++j)
+        if (j * WPG + wi < T_LOADS)
+          *reinterpret_cast<u32x4 *>(mem + (stage * 2 + 1) * S::TILE + (j * WPG + wi) * 512 + lane * 8) = vreg[j];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();                      // ... for every wavefront; everyone is done with the other stage
+    asm volatile("" ::: "memory");
+    if (t + KG < n_tiles) issue(t + KG, stage ^ 1);
+    if (t < n_tiles) {
+      const uint16_t *ks = mem + stage * 2 * S::TILE;
+      rows.tile(ks, ks + S::TILE, t * kAttBKV, n, t0 == 0, lane);
+    }
+  }
+  const bool any = grp_k < n_tiles;
+  const float l = rows.denominator(0, r32);
+  if (grp == 0) ml[wave][r32] = any ? make_float2(rows.m_ref[0], l) : make_float2(-INFINITY, 0.f);
+  __syncthreads();                                     // the stages have been read
+  float *part = reinterpret_cast<float *>(lds);
+#pragma unroll
+  for (int b = 0; b < S::NDB; ++b)
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) {
+      const f32x16 &a = rows.o_acc[0][b];
+      *reinterpret_cast<f32x4 *>(part + (wave * 32 + r32) * S::O_LD + b * 32 + qd * 8 + grp * 4) =
+          f32x4{a[qd * 4], a[qd * 4 + 1], a[qd * 4 + 2], a[qd * 4 + 3]};
+    }
+  __syncthreads();
+  for (int i = tid; i < 32 * WPG * (HD / 8); i += 512) {
+    const int q = i / (HD / 8), ch = i % (HD / 8);     // (q = 32 * wavefront of the group + query)
+    if (q0 + q >= n) continue;
+    float m = -INFINITY, den = 0.f, fac[KG];
+#pragma unroll
+    for (int k = 0; k < KG; ++k) m = fmaxf(m, ml[k * WPG + (q >> 5)][q & 31].x);
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      const float2 w = ml[k * WPG + (q >> 5)][q & 31];
+      fac[k] = __builtin_amdgcn_exp2f(w.x - m);
+      den = fmaf(fac[k], w.y, den);
+    }
+    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      const float *p = part + (k * WPG * 32 + q) * S::O_LD + ch * 8;
+      lo += *reinterpret_cast<const f32x4 *>(p) * fac[k];
+      hi += *reinterpret_cast<const f32x4 *>(p + 4) * fac[k];
+    }
+    const float inv = 1.0f / den;
+    u32x4 r;
+    r.x = cvt_pk_bf16(lo[0] * inv, lo[1] * inv); r.y = cvt_pk_bf16(lo[2] * inv, lo[3] * inv);
+    r.z = cvt_pk_bf16(hi[0] * inv, hi[1] * inv); r.w = cvt_pk_bf16(hi[2] * inv, hi[3] * inv);
+    *reinterpret_cast<u32x4 *>(out + ((size_t)start + q0 + q) * D + h * HD + ch * 8) = r;
   }
 }
 
@@ -1130,60 +1363,85 @@ bool head_dim_supported(int hd) {
   return hd == 16 || hd == 32 || hd == 64 || hd == 72 || hd == 80 || hd == 96 || hd == 128;
 }
 
-int launch_attention(const uint16_t *qkv, const int32_t *cu, int n_frames, int max_len, int n_heads,
-                     int head_dim, uint16_t *out, hipStream_t s) {
-  if (n_frames <= 0 || max_len <= 0) return ET_OK;
-  const int n_qblk = (max_len + kAttBQ - 1) / kAttBQ;
-  const dim3 grid((unsigned)n_qblk * n_heads * n_frames), block(kAttWaves * 64);
-  const float scale_log2 = 1.4426950408889634f / sqrtf((float)head_dim);
-#define ET_ATT(HD)                                                                                           \
-  case HD:                                                                                                   \
-    hipLaunchKernelGGL((attention_dma_kernel<HD, 1, (HD <= 96 ? 2 : 1)>), grid, block, 0, s, qkv, cu, 0, n_heads, \
-                       n_qblk, scale_log2, out);                                                             \
-    break;
-  switch (head_dim) {
-    ET_ATT(16) ET_ATT(32) ET_ATT(64) ET_ATT(72) ET_ATT(80) ET_ATT(96) ET_ATT(128)
-    default: set_error("head_dim %d is not instantiated", head_dim); return ET_ERR_UNSUPPORTED;
+static int attention_cus() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
+    (void)hipGetLastError();
+    return 256;
   }
-#undef ET_ATT
+  return n;
+}
+
+template <int HD, int KG>
+static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n, int n_heads, int n_qblk, long long pairs,
+                                  float scale_log2, uint16_t *out, hipStream_t s) {
+  constexpr size_t bytes = GroupShape<HD, KG>::kLdsBytes;
+  static std::atomic<uint64_t> allowed{0};
+  int dev = 0;
+  ET_HIP(hipGetDevice(&dev));
+  const uint64_t bit = 1ull << (dev & 63);
+  auto kern = attention_group_kernel<HD, KG>;
+  if (!(allowed.load(std::memory_order_relaxed) & bit)) {
+    ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    allowed.fetch_or(bit, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(n_qblk * pairs)), dim3(512), bytes, s, qkv, cu, n, n_heads, n_qblk, scale_log2, out);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }
 
-int launch_attention_uniform(const uint16_t *qkv, int n_frames, int len, int n_heads, int head_dim,
-                             uint16_t *out, hipStream_t s) {
-  if (n_frames <= 0 || len <= 0) return ET_OK;
-  const dim3 agrid((len + kAttBQ - 1) / kAttBQ, n_heads, n_frames);
-  const dim3 agrid2((len + 2 * kAttBQ - 1) / (2 * kAttBQ), n_heads, n_frames);
-  // two query blocks per wavefront (half the LDS reads and loads per query) when that still leaves
-  // every workgroup slot of the chip (2 per compute unit) with work
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0;
-    ET_HIP(hipGetDevice(&dev));
-    ET_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    if (n_cu <= 0) n_cu = 256;
+// cu == nullptr: frames of `len` rows each; else row ranges cu[f] .. cu[f + 1] of at most `len` rows.
+template <int HD>
+static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_frames, int len, int n_heads, uint16_t *out,
+                               hipStream_t s) {
+  const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
+  const long long pairs = (long long)n_heads * n_frames, cus = attention_cus(), slots = 2 * cus;
+  const int n = cu ? 0 : len;
+  auto blocks = [&](int rows) { return (len + rows - 1) / rows; };
+  // Key tiles split over groups of wavefronts while that still makes one workgroup per compute unit at most, and
+  // while a group keeps enough tiles for the exchange to pay.  Measured, microseconds per launch against the
+  // kernel of 128 queries (heads of 72): 1 x 729 (192 workgroups of four groups) 17.3 -> 12.8, 2 x 729 (192 of two groups)
+  // 17.0 -> 15.3, 3 x 364 (144) 12.1 -> 10.6; heads of 64: 1 x 196 8.7 -> 6.8, 4 x 98 6.3 -> 6.0.  Past the line: 4 x 729
+  // 23.9 -> 30.0, 8 x 182 (3 tiles, two groups) 8.1 -> 8.6.
+  const int n_tiles = blocks(kAttBKV);
+  if constexpr (GroupShape<HD, 4>::kFits) {
+    if (n_tiles >= 2 && blocks(64) * pairs <= cus)
+      return launch_attention_group<HD, 4>(qkv, cu, n, n_heads, blocks(64), pairs, scale_log2, out, s);
   }
-  const bool wide = (long long)agrid2.x * agrid2.y * agrid2.z >= 2LL * n_cu;
-  const float scale_log2 = 1.4426950408889634f / sqrtf((float)head_dim);
-#define ET_ATT(HD)                                                                                        \
-  case HD:                                                                                                \
-    if (HD <= 80 && wide)                                                                                 \
-      hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 80 ? 2 : 1), (HD <= 96 ? 2 : 1)>),            \
-                         dim3(agrid2.x * agrid2.y * agrid2.z), dim3(kAttWaves * 64), 0, s, qkv,                 \
-                         (const int32_t *)nullptr, len, n_heads, (int)agrid2.x, scale_log2, out);                                                 \
-    else                                                                                                  \
-      hipLaunchKernelGGL((attention_dma_kernel<HD, 1, (HD <= 96 ? 2 : 1)>), dim3(agrid.x * agrid.y * agrid.z),   \
-                         dim3(kAttWaves * 64), 0, s, qkv, (const int32_t *)nullptr, len, n_heads, (int)agrid.x,   \
-                         scale_log2, out);                                                                \
-    break;
-  switch (head_dim) {
-    ET_ATT(16) ET_ATT(32) ET_ATT(64) ET_ATT(72) ET_ATT(80) ET_ATT(96) ET_ATT(128)
-    default: set_error("head_dim %d is not instantiated", head_dim); return ET_ERR_UNSUPPORTED;
+  if constexpr (GroupShape<HD, 2>::kFits) {
+    if (n_tiles >= 5 && blocks(128) * pairs <= cus)
+      return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s);
   }
-#undef ET_ATT
+  if (HD <= 80 && blocks(2 * kAttBQ) * pairs >= slots) {
+    // two query blocks per wavefront (half the LDS reads and loads per query) when that still leaves
+    // every workgroup slot of the chip (2 per compute unit) with work
+    hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 80 ? 2 : 1), 2>), dim3((unsigned)(blocks(2 * kAttBQ) * pairs)),
+                       dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(2 * kAttBQ), scale_log2, out);
+  } else {
+    hipLaunchKernelGGL((attention_dma_kernel<HD, 1, (HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
+                       dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(kAttBQ), scale_log2, out);
+  }
   ET_LAUNCH_CHECK();
   return ET_OK;
+}
+
+int launch_attention(const uint16_t *qkv, const int32_t *cu, int n_frames, int len, int n_heads, int head_dim, uint16_t *out,
+                     hipStream_t s) {
+  if (n_frames <= 0 || len <= 0) return ET_OK;
+  switch (head_dim) {
+    case 16: return launch_attention_hd<16>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 32: return launch_attention_hd<32>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 64: return launch_attention_hd<64>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 72: return launch_attention_hd<72>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 80: return launch_attention_hd<80>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 96: return launch_attention_hd<96>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 128: return launch_attention_hd<128>(qkv, cu, n_frames, len, n_heads, out, s);
+    default: set_error("head_dim %d is not instantiated", head_dim); return ET_ERR_UNSUPPORTED;
+  }
+}
+
+int launch_attention_uniform(const uint16_t *qkv, int n_frames, int len, int n_heads, int head_dim, uint16_t *out, hipStream_t s) {
+  return launch_attention(qkv, nullptr, n_frames, len, n_heads, head_dim, out, s);
 }
 
 }  // namespace et

@@ -286,3 +286,30 @@ def test_gemm_split_over_wavefronts(cfg, M, N, K):
         got = dev_to_f64(et.et_gemm_bf16(a_d, w_d, b_d, epi, residual=r_d if epi == 2 else None, tile_config=cfg))
         assert np.max(np.abs(got - ref) - 2 ** -8 * np.abs(ref)) < 2e-4 * (np.sqrt(K) * 0.05 + 1.0)
         assert rel_l2(got, ref) < 4e-3
+
+
+@pytest.mark.parametrize("n_heads,hd,lens", [
+    (16, 72, [729]),                      # key tiles over four groups of wavefronts, uneven shares, ragged last tile
+    (4, 64, [65, 0, 1, 128, 129]),        # the same: fewer tiles than groups, an empty and a one-token frame
+    (2, 16, [300] * 3), (3, 32, [511, 64]), (1, 72, [70]),
+    (16, 72, [729, 700]),                 # two groups
+    (2, 80, [400, 321]), (2, 96, [330]), (1, 128, [577]),
+    (16, 72, [729, 33, 515, 256, 1, 700, 257, 640, 90, 729, 600]),   # ragged, two query blocks per wavefront
+])
+def test_attention_split_and_ragged_forms(n_heads, hd, lens):
+    """Same bounds as the oracle test above: probabilities pass through bf16 once, the output is rounded once; partial
+    results of the groups are combined in float32."""
+    rng = np.random.default_rng(n_heads * hd + len(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, D = int(cu[-1]), n_heads * hd
+    _, qkv = _bf(rng, (rows, 3 * D))
+    qkv[:, :D] *= 2.0
+    bits = f32_to_bf16_bits(qkv.astype(np.float32))
+    qkv = bf16_bits_to_f32(bits).astype(np.float64)
+    ref = _attention_ref(qkv, cu, n_heads, hd)
+    got = [et.et_attention(bits_to_dev(bits), torch.from_numpy(cu).cuda(), max(lens), n_heads, hd)]
+    if len(set(lens)) == 1:
+        got.append(et.et_attention_uniform(bits_to_dev(bits), len(lens), lens[0], n_heads, hd))
+    for out in got:
+        assert rel_l2(dev_to_f64(out), ref) < 6e-3
+        assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05
