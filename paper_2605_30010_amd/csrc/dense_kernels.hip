@@ -1395,7 +1395,7 @@ template <int HD>
 static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_frames, int len, int n_heads, uint16_t *out,
                                hipStream_t s) {
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
-  const long long pairs = (long long)n_heads * n_frames, cus = attention_cus(), slots = 2 * cus;
+  const long long pairs = (long long)n_heads * n_frames, cus = attention_cus();
   const int n = cu ? 0 : len;
   auto blocks = [&](int rows) { return (len + rows - 1) / rows; };
   // Key tiles split over groups of wavefronts while that still makes one workgroup per compute unit at most, and
@@ -1412,9 +1412,11 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
     if (n_tiles >= 5 && blocks(128) * pairs <= cus)
       return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s);
   }
-  if (HD <= 80 && blocks(2 * kAttBQ) * pairs >= slots) {
-    // two query blocks per wavefront (half the LDS reads and loads per query) when that still leaves
-    // every workgroup slot of the chip (2 per compute unit) with work
+  if (HD <= 80 && blocks(2 * kAttBQ) * pairs >= 6 * cus) {
+    // Two query blocks per wavefront (half the LDS reads and loads per query) from three rounds of workgroups on; below,
+    // three smaller workgroups per compute unit win (heads of 72, one / two blocks, us per launch: 64 x 729
+    // 285 / 274, 32 x 729 152 / 150, 23 x 729 94 / 104, 12 x 729 54 / 66, 32 x 364 39 / 48, 16 x 364 23 / 28; ragged 13 frames of
+    // 700-729 55 / 65).
     hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 80 ? 2 : 1), 2>), dim3((unsigned)(blocks(2 * kAttBQ) * pairs)),
                        dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(2 * kAttBQ), scale_log2, out);
   } else {
