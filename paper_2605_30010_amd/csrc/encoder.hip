@@ -398,7 +398,7 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
       const PlanStep step{merge_here ? 1 : 0, select_here ? 1 : 0, first_stage ? 1 : 0, T};
       int rc = enqueue_policy_stage(w.x, n_frames, L, D, *policy, step, mw, first_stage ? out->frame_sim_dev : nullptr,
                                     out->seg_start_dev, out->kept_idx_dev, out->cu_tokens_dev, w.x, info, s,
-                                    &e->prof, (select_here && by_attention) ? w.att_score : nullptr);
+                                    &e->prof, select_here ? plan : nullptr, (select_here && by_attention) ? w.att_score : nullptr);
       if (rc) return rc;
       if (!select_here)      // frames keep all L tokens: the merged frames become the residual stream
         ET_HIP(hipMemcpyAsync(w.x, mw.merged, (size_t)n_frames * L * D * 2, hipMemcpyDeviceToDevice, s));
@@ -418,7 +418,6 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
           set_error("token counts read back from the device are inconsistent (tokens = %d)", hi[2]);
           return ET_ERR_HIP;
         }
-        if ((rc = copy_plan_out(mw, hi[0], plan, s))) return rc;
         rows = hi[2];
         max_len = hi[3] > hi[4] ? hi[3] : hi[4];
         ragged = policy->select_mode == ET_SELECT_DECOUPLED && hi[3] != hi[4];

@@ -144,17 +144,23 @@ int check_policy(const et_policy *p) {
 int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy &pol, const PlanStep &step,
                          const MergeWs &w, float *sim_out, int32_t *seg_start, int32_t *kept,
                          int32_t *cu_tokens, uint16_t *packed, int32_t *info, hipStream_t s, Profiler *prof,
-                         const float *score_override) {
+                         const et_plan_out *plan, const float *score_override) {
   float *sim = sim_out ? sim_out : w.sim;
   const PolicyArgs pa{pol.merge_mode, pol.select_mode, pol.alpha, pol.tau_seg, pol.tau_merge, pol.ratio};
   const int k_uniform = et_keep_count(L, pol.ratio);
+  PlanOut po;
+  if (plan) {
+    po.first = plan->frame_first_dev;
+    po.count = plan->frame_count_dev;
+    po.dyn = plan->frame_dynamic_dev;
+  }
   if (step.do_plan) {
     ET_TIMED_P(prof, ET_K_SIMILARITY, launch_similarity(x, T, L, D, w.cos, w.part, s));
     ET_TIMED_P(prof, ET_K_SCAN, launch_sim_mean_scan(w.part, similarity_blocks(L), T, L, 0.f, sim, nullptr, nullptr,
                                                      true, false, s));
   }
   ET_TIMED_P(prof, ET_K_SCAN, launch_plan(sim, T, L, pa, k_uniform, step, seg_start, w.frame_first, w.frame_count,
-                                          w.frame_dyn, w.frame_w, w.orig_first, w.orig_count, cu_tokens, info, s));
+                                          w.frame_dyn, w.frame_w, w.orig_first, w.orig_count, cu_tokens, info, po, s));
   ET_TIMED_P(prof, ET_K_MERGE, launch_plan_merge(x, T, L, D, info, w.frame_first, w.frame_count, w.frame_w,
                                                  step.do_plan && pol.merge_mode == ET_MERGE_MEAN, w.merged,
                                                  w.score, s));
@@ -164,15 +170,6 @@ int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy
                                                        pol.select_mode == ET_SELECT_UNIFORM, kept, s));
     ET_TIMED_P(prof, ET_K_COMPACT, launch_compact_ragged(w.merged, kept, T, info, cu_tokens, L, D, packed, s));
   }
-  return ET_OK;
-}
-
-int copy_plan_out(const MergeWs &w, int N, et_plan_out *plan, hipStream_t s) {
-  if (!plan || N <= 0) return ET_OK;
-  const size_t bytes = (size_t)N * sizeof(int32_t);
-  if (plan->frame_first_dev) ET_HIP(hipMemcpyAsync(plan->frame_first_dev, w.orig_first, bytes, hipMemcpyDeviceToDevice, s));
-  if (plan->frame_count_dev) ET_HIP(hipMemcpyAsync(plan->frame_count_dev, w.orig_count, bytes, hipMemcpyDeviceToDevice, s));
-  if (plan->frame_dynamic_dev) ET_HIP(hipMemcpyAsync(plan->frame_dynamic_dev, w.frame_dyn, bytes, hipMemcpyDeviceToDevice, s));
   return ET_OK;
 }
 
@@ -360,16 +357,12 @@ int et_merge_select_policy(const uint16_t *x_dev, int32_t T, int32_t L, int32_t 
   int32_t *info = w.n_seg + 8;
   const PlanStep step{1, 1, 1, T};
   if ((rc = enqueue_policy_stage(x_dev, T, L, D, *policy, step, w, out->frame_sim_dev, out->seg_start_dev,
-                                 out->kept_idx_dev, out->cu_tokens_dev, out->tokens_dev, info, s, nullptr)))
+                                 out->kept_idx_dev, out->cu_tokens_dev, out->tokens_dev, info, s, nullptr, plan)))
     return rc;
   int32_t host_info[5] = {0, 0, 0, 0, 0};
   ET_HIP(hipMemcpyAsync(host_info, info, sizeof(host_info), hipMemcpyDeviceToHost, s));
   ET_HIP(hipStreamSynchronize(s));
-  if ((rc = copy_plan_out(w, host_info[0], plan, s))) return rc;
-  if (plan) {
-    plan->n_segments = host_info[1];
-    ET_HIP(hipStreamSynchronize(s));
-  }
+  if (plan) plan->n_segments = host_info[1];
   out->n_frames_out = host_info[0];
   out->n_tokens = host_info[2];
   return ET_OK;

@@ -148,16 +148,20 @@ struct PolicyArgs {
 struct PlanStep {
   int do_plan, do_counts, init_orig, t_orig;
 };
+// Where the plan kernel leaves copies of the final plan (device, [N] each, any may be NULL).
+struct PlanOut {
+  int32_t *first = nullptr, *count = nullptr, *dyn = nullptr;
+};
 int check_policy(const et_policy *p);
 // Enqueues similarity -> plan -> weighted merge -> selection -> ragged gather; no host sync.
 // info (device, >= 5 ints) receives N, segments, total tokens, tokens per dynamic / static frame.
 // `step` says which parts run: with do_counts the selection and the gather into `packed` follow the
-// merge; without, only `w.merged` (all L tokens per frame) and `w.score` are produced.
+// merge; without, only `w.merged` (all L tokens per frame) and `w.score` are produced.  plan (may be NULL):
+// receives the final plan's device arrays.
 int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy &pol, const PlanStep &step,
                          const MergeWs &w, float *sim_out, int32_t *seg_start, int32_t *kept,
                          int32_t *cu_tokens, uint16_t *packed, int32_t *info, hipStream_t s,
-                         struct Profiler *prof, const float *score_override = nullptr);
-int copy_plan_out(const MergeWs &w, int N, et_plan_out *plan, hipStream_t s);
+                         struct Profiler *prof, const et_plan_out *plan, const float *score_override = nullptr);
 MergeWs carve_merge(void *ws, int T, int L, int D);
 // Where the host learns the segment count while the stage is still running: right after the scan
 // kernel the count is copied to `host` (pinned memory) and `ready` is recorded, so the host waits
@@ -196,7 +200,7 @@ int launch_cu_uniform(int n, int step, int32_t *cu, hipStream_t s);
 int launch_plan(const float *sim, int T, int L, const PolicyArgs &p, int k_uniform, const PlanStep &st,
                 int32_t *seg_start, int32_t *frame_first, int32_t *frame_count, int32_t *frame_dyn,
                 float *frame_w, int32_t *orig_first, int32_t *orig_count, int32_t *cu_tokens, int32_t *info,
-                hipStream_t s);
+                const PlanOut &out, hipStream_t s);
 int launch_plan_merge(const uint16_t *x, int T, int L, int D, const int32_t *info, const int32_t *frame_first,
                       const int32_t *frame_count, const float *frame_w, bool uniform_mean, uint16_t *merged,
                       float *score, hipStream_t s);

@@ -4,8 +4,7 @@
 // the gather of Eq. 7 with per-frame token counts.
 //
 // Readings of points the paper leaves open are stated at plan_kernel.  The similarity kernel of
-// the simple path is reused; this file adds the sequential plan builder (one lane; the work is
-// O(T)), a weighted-range merge, the per-frame selection with two modes and a ragged gather.
+// the simple path is reused; this file adds the sequential plan builder (O(T) steps on one lane), a weighted-range merge, the per-frame selection with two modes and a ragged gather.
 #include "select_common.h"
 
 namespace et {
@@ -24,81 +23,132 @@ constexpr int kRowsPerBlock = 4;
 //  - Eq. 5 (as a count): r_hat = clamp(floor(ratio * T * L / N + 0.5), 1, L).
 //  - Eq. 6: w = L / r_hat (integer division), M = ceil(L / w) windows.
 // ---------------------------------------------------------------------------------------
-__global__ void plan_kernel(const float *__restrict__ sim, int T, int L, PolicyArgs p, int k_uniform,
-                            PlanStep st, int32_t *__restrict__ seg_start, int32_t *__restrict__ frame_first,
-                            int32_t *__restrict__ frame_count, int32_t *__restrict__ frame_dyn,
-                            float *__restrict__ frame_w, int32_t *__restrict__ orig_first,
-                            int32_t *__restrict__ orig_count, int32_t *__restrict__ cu_tokens,
-                            int32_t *__restrict__ info) {
+// What the one lane builds: segments, then the output frames as (first, count) over the current frames.
+struct PlanLists {
+  int32_t *seg, *first, *count, *dyn;
+  float *w;
+};
+
+__device__ __forceinline__ void build_plan(const float *sim, int T, const PolicyArgs &p, const PlanLists &o, int &n_seg_out, int &n_out) {
+  int n_seg = 0, N = 0;
+  o.seg[0] = 0;
+  float prev = 0.f;
+  bool fresh = true;
+  for (int t = 1; t < T; ++t) {
+    const float sv = sim[t - 1];
+    const float cur = fresh ? sv : p.alpha * sv + (1.0f - p.alpha) * prev;
+    if (!(cur >= p.tau_seg)) {
+      o.seg[++n_seg] = t;
+      fresh = true;
+    } else {
+      prev = cur;
+      fresh = false;
+    }
+  }
+  o.seg[++n_seg] = T;
+  auto emit = [&](int first, int count, float w0, float w1, int dyn) {
+    o.first[N] = first;
+    o.count[N] = count;
+    o.dyn[N] = dyn;
+    o.w[2 * N] = w0;
+    o.w[2 * N + 1] = w1;
+    ++N;
+  };
+  for (int sgi = 0; sgi < n_seg; ++sgi) {
+    const int a = o.seg[sgi], b = o.seg[sgi + 1];
+    if (p.merge_mode == ET_MERGE_MEAN) {
+      emit(a, b - a, 0.f, 0.f, 1);                 // uniform weights: handled as sum / count
+      continue;
+    }
+    const int k = b - a - 1;
+    emit(a, 1, 1.f, 0.f, 1);
+    int i = 1;
+    while (i < k) {
+      const float si = sim[a + i];                 // Sim(F_i, F_{i+1})
+      if (i + 1 <= k - 1 && si > p.tau_merge && si > sim[a + i + 1]) {
+        const float sj = sim[a + i + 1];
+        emit(a + i, 2, si / (si + sj), sj / (si + sj), 0);
+        i += 2;
+      } else {
+        emit(a + i, 1, 1.f, 0.f, 0);
+        i += 1;
+      }
+    }
+    if (k >= 1) emit(a + k, 1, 1.f, 0.f, 1);
+  }
+  n_seg_out = n_seg;
+  n_out = N;
+}
+
+// One wavefront.  The plan itself is a serial chain over the frames; lane 0 walks it on LDS copies (T <= kPlanLds; longer
+// clips on global memory, where every step is a round trip), everything else is done by all lanes.  What bounds
+// it is that chain: 40 frames 17.8 us on global memory.
+constexpr int kPlanLds = 1024;
+__global__ __launch_bounds__(kWave) void plan_kernel(
+    const float *__restrict__ sim, int T, int L, PolicyArgs p, int k_uniform, PlanStep st, int32_t *__restrict__ seg_start,
+    int32_t *__restrict__ frame_first, int32_t *__restrict__ frame_count, int32_t *__restrict__ frame_dyn,
+    float *__restrict__ frame_w, int32_t *orig_first, int32_t *orig_count, int32_t *__restrict__ cu_tokens, int32_t *__restrict__ info,
+    PlanOut out) {
   // T = current number of frames.  st.do_plan: build segments and output frames from sim (else the
   // identity plan over the T current frames, dynamic flags left as they are).  st.do_counts: token
   // counts and offsets of the selection.  orig_first / orig_count: range of ORIGINAL frames behind
   // each current frame (st.init_orig: identity, first stage), updated in place; seg_start is
-  // written in original frame indices.
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int N = 0;
+  // written in original frame indices.  out: copies of the final plan for the caller (each may be NULL).
+  __shared__ float l_sim[kPlanLds], l_w[2 * kPlanLds];
+  __shared__ int32_t l_seg[kPlanLds + 1], l_first[kPlanLds], l_count[kPlanLds], l_dyn[kPlanLds];
+  __shared__ int head[2];
+  const int lane = threadIdx.x;
+  int N = T;
   if (st.do_plan) {
-    int n_seg = 0;
-    seg_start[0] = 0;
-    float prev = 0.f;
-    bool fresh = true;
-    for (int t = 1; t < T; ++t) {
-      const float sv = sim[t - 1];
-      const float cur = fresh ? sv : p.alpha * sv + (1.0f - p.alpha) * prev;
-      if (!(cur >= p.tau_seg)) {
-        seg_start[++n_seg] = t;
-        fresh = true;
-      } else {
-        prev = cur;
-        fresh = false;
+    const bool in_lds = T <= kPlanLds;             // (uniform)
+    if (in_lds)
+      for (int t = lane; t < T - 1; t += kWave) l_sim[t] = sim[t];
+    __syncthreads();
+    if (lane == 0) {
+      int n_seg = 0, n = 0;
+      if (in_lds) build_plan(l_sim, T, p, PlanLists{l_seg, l_first, l_count, l_dyn, l_w}, n_seg, n);
+      else build_plan(sim, T, p, PlanLists{seg_start, frame_first, frame_count, frame_dyn, frame_w}, n_seg, n);
+      head[0] = n_seg;
+      head[1] = n;
+      __threadfence_block();
+    }
+    __syncthreads();
+    const int n_seg = head[0];
+    N = head[1];
+    // segment starts and frame ranges in original frame indices: 64 entries at a time are read before they are
+    // written, and entry n only needs entries >= n
+    for (int i0 = 0; i0 < n_seg; i0 += kWave) {
+      const int i = i0 + lane;
+      if (i < n_seg) {
+        const int f = in_lds ? l_seg[i] : seg_start[i];
+        seg_start[i] = st.init_orig ? f : orig_first[f];
       }
     }
-    seg_start[++n_seg] = T;
-    auto emit = [&](int first, int count, float w0, float w1, int dyn) {
-      frame_first[N] = first;
-      frame_count[N] = count;
-      frame_dyn[N] = dyn;
-      frame_w[2 * N] = w0;
-      frame_w[2 * N + 1] = w1;
-      ++N;
-    };
-    for (int sgi = 0; sgi < n_seg; ++sgi) {
-      const int a = seg_start[sgi], b = seg_start[sgi + 1];
-      if (p.merge_mode == ET_MERGE_MEAN) {
-        emit(a, b - a, 0.f, 0.f, 1);                 // uniform weights: handled as sum / count
-        continue;
-      }
-      const int k = b - a - 1;
-      emit(a, 1, 1.f, 0.f, 1);
-      int i = 1;
-      while (i < k) {
-        const float si = sim[a + i];                 // Sim(F_i, F_{i+1})
-        if (i + 1 <= k - 1 && si > p.tau_merge && si > sim[a + i + 1]) {
-          const float sj = sim[a + i + 1];
-          emit(a + i, 2, si / (si + sj), sj / (si + sj), 0);
-          i += 2;
-        } else {
-          emit(a + i, 1, 1.f, 0.f, 0);
-          i += 1;
+    if (lane == 0) seg_start[n_seg] = st.t_orig;
+    for (int n0 = 0; n0 < N; n0 += kWave) {
+      const int n = n0 + lane;
+      int of = 0, oe = 0;
+      if (n < N) {
+        const int f = in_lds ? l_first[n] : frame_first[n], c = in_lds ? l_count[n] : frame_count[n], l = f + c - 1;
+        of = st.init_orig ? f : orig_first[f];
+        oe = st.init_orig ? l + 1 : orig_first[l] + orig_count[l];
+        if (in_lds) {
+          frame_first[n] = f;
+          frame_count[n] = c;
+          frame_dyn[n] = l_dyn[n];
+          frame_w[2 * n] = l_w[2 * n];
+          frame_w[2 * n + 1] = l_w[2 * n + 1];
         }
       }
-      if (k >= 1) emit(a + k, 1, 1.f, 0.f, 1);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (all 64 entries have been read)
+      if (n < N) {
+        orig_first[n] = of;
+        orig_count[n] = oe - of;
+      }
     }
-    // segment starts and frame ranges in original frame indices (ascending, in place: entry n only
-    // reads entries >= n)
-    for (int i = 0; i < n_seg; ++i) seg_start[i] = st.init_orig ? seg_start[i] : orig_first[seg_start[i]];
-    seg_start[n_seg] = st.t_orig;
-    for (int n = 0; n < N; ++n) {
-      const int f = frame_first[n], l = f + frame_count[n] - 1;
-      const int of = st.init_orig ? f : orig_first[f];
-      const int oe = st.init_orig ? l + 1 : orig_first[l] + orig_count[l];
-      orig_first[n] = of;
-      orig_count[n] = oe - of;
-    }
-    info[1] = n_seg;
+    if (lane == 0) info[1] = n_seg;
   } else {
-    N = T;
-    for (int n = 0; n < N; ++n) {
+    for (int n = lane; n < N; n += kWave) {
       frame_first[n] = n;
       frame_count[n] = 1;
       frame_w[2 * n] = 1.f;
@@ -110,11 +160,18 @@ __global__ void plan_kernel(const float *__restrict__ sim, int T, int L, PolicyA
       }
     }
     if (st.init_orig) {
-      for (int i = 0; i <= T; ++i) seg_start[i] = i;
-      info[1] = T;
+      for (int i = lane; i <= T; i += kWave) seg_start[i] = i;
+      if (lane == 0) info[1] = T;
     }
   }
-  info[0] = N;
+  if (lane == 0) info[0] = N;
+  __threadfence_block();
+  __syncthreads();
+  for (int n = lane; n < N; n += kWave) {
+    if (out.first) out.first[n] = orig_first[n];
+    if (out.count) out.count[n] = orig_count[n];
+    if (out.dyn) out.dyn[n] = frame_dyn[n];
+  }
   if (!st.do_counts) return;
   int n_dyn_tok, n_sta_tok;
   if (p.select_mode == ET_SELECT_UNIFORM) {
@@ -126,15 +183,21 @@ __global__ void plan_kernel(const float *__restrict__ sim, int T, int L, PolicyA
     n_dyn_tok = r_hat;
     n_sta_tok = (L + w - 1) / w;
   }
-  int total = 0;
-  for (int n = 0; n < N; ++n) {
-    cu_tokens[n] = total;
-    total += (p.select_mode == ET_SELECT_UNIFORM || frame_dyn[n]) ? n_dyn_tok : n_sta_tok;
+  int total = 0;                                   // tokens before the 64 frames at n0
+  for (int n0 = 0; n0 < N; n0 += kWave) {
+    const int n = n0 + lane, here = N - n0 < kWave ? N - n0 : kWave;
+    const bool dyn = n < N && (p.select_mode == ET_SELECT_UNIFORM || frame_dyn[n]);
+    const unsigned long long m = __ballot(dyn);
+    const int before = __popcll(m & ((1ull << lane) - 1ull)), all = __popcll(m);
+    if (n < N) cu_tokens[n] = total + before * n_dyn_tok + (lane - before) * n_sta_tok;
+    total += all * n_dyn_tok + (here - all) * n_sta_tok;
   }
-  cu_tokens[N] = total;
-  info[2] = total;
-  info[3] = n_dyn_tok;
-  info[4] = n_sta_tok;
+  if (lane == 0) {
+    cu_tokens[N] = total;
+    info[2] = total;
+    info[3] = n_dyn_tok;
+    info[4] = n_sta_tok;
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -262,9 +325,9 @@ __global__ __launch_bounds__(kRowsPerBlock * kWave) void compact_ragged_kernel(
 int launch_plan(const float *sim, int T, int L, const PolicyArgs &p, int k_uniform, const PlanStep &st,
                 int32_t *seg_start, int32_t *frame_first, int32_t *frame_count, int32_t *frame_dyn,
                 float *frame_w, int32_t *orig_first, int32_t *orig_count, int32_t *cu_tokens, int32_t *info,
-                hipStream_t s) {
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64), 0, s, sim, T, L, p, k_uniform, st, seg_start, frame_first,
-                     frame_count, frame_dyn, frame_w, orig_first, orig_count, cu_tokens, info);
+                const PlanOut &out, hipStream_t s) {
+  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kWave), 0, s, sim, T, L, p, k_uniform, st, seg_start, frame_first,
+                     frame_count, frame_dyn, frame_w, orig_first, orig_count, cu_tokens, info, out);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

@@ -623,3 +623,30 @@ def test_multi_layer_degenerate_clips(score_mode):
         if res is not None:                         # (identical frames sit exactly on Alg. 1's ties: plan checked above)
             assert res[0]["n_frames_out"] == want_n
     enc.close()
+
+
+@pytest.mark.parametrize("T", [1, 2, 64, 65, 130, 1024, 1025, 1500])
+@pytest.mark.parametrize("mode,select", [("alg1", "decoupled"), ("mean", "uniform")])
+def test_plan_of_long_clips(T, mode, select):
+    """The plan over its lengths (one or several chunks of 64 entries; above 1024 frames on global memory), against the
+    oracle's scan and Alg. 1 on the device's own similarities: with alpha = 1 both sides compare the same float32
+    numbers, so every integer is exact."""
+    L, D = 6, 8
+    rng = np.random.default_rng(T)
+    lengths = scene_lengths_geometric(rng, T, 9)
+    bits = make_hidden_states(T, L, D, lengths, T, sigma=0.3)
+    pol = _f32_policy(dict(merge_mode=mode, select_mode=select, alpha=1.0, tau_seg=0.8, tau_merge=0.85, ratio=0.6))
+    r = et.et_merge_select_policy(bits_to_dev(bits), pol)
+    sim = r["frame_sim"].cpu().numpy().astype(np.float64)
+    seg, _ = O.ema_segment_starts(sim, 1.0, pol["tau_seg"], T)
+    plan = O.merge_plan(sim, seg, pol["tau_merge"], mode)
+    assert r["seg_start"].tolist() == list(seg)
+    first, count = r["frame_first"].tolist(), r["frame_count"].tolist()
+    assert len(plan) == r["n_frames_out"] == len(first)
+    assert first[0] == 0 and first[-1] + count[-1] == T
+    assert first == [int(e["first"]) for e in plan] and count == [int(e["count"]) for e in plan]
+    dyn = [bool(e["dynamic"]) for e in plan]
+    assert [bool(v) for v in r["frame_dynamic"].tolist()] == dyn
+    k = O.keep_count(L, np.float32(pol["ratio"])) if select == "uniform" else O.rescaled_count(pol["ratio"], T, L, len(plan))
+    ks = k if select == "uniform" else -(-L // (L // k))
+    assert r["cu_tokens"].tolist() == np.concatenate([[0], np.cumsum([k if d or select == "uniform" else ks for d in dyn])]).tolist()
