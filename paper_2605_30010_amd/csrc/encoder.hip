@@ -396,15 +396,20 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
       const MergeWs mw = carve_merge(w.merge, T, L, D);
       int32_t *info = mw.n_seg + 8;
       const PlanStep step{merge_here ? 1 : 0, select_here ? 1 : 0, first_stage ? 1 : 0, T};
+      HostCell cell;
       int rc = enqueue_policy_stage(w.x, n_frames, L, D, *policy, step, mw, first_stage ? out->frame_sim_dev : nullptr,
                                     out->seg_start_dev, out->kept_idx_dev, out->cu_tokens_dev, w.x, info, s,
-                                    &e->prof, select_here ? plan : nullptr, (select_here && by_attention) ? w.att_score : nullptr);
+                                    &e->prof, select_here ? plan : nullptr, cell.ptr, (select_here && by_attention) ? w.att_score : nullptr);
       if (rc) return rc;
       if (!select_here)      // frames keep all L tokens: the merged frames become the residual stream
         ET_HIP(hipMemcpyAsync(w.x, mw.merged, (size_t)n_frames * L * D * 2, hipMemcpyDeviceToDevice, s));
       int32_t hi[5] = {0, 0, 0, 0, 0};
-      ET_HIP(hipMemcpyAsync(hi, info, sizeof(hi), hipMemcpyDeviceToHost, s));
+      if (!cell.ptr) ET_HIP(hipMemcpyAsync(hi, info, sizeof(hi), hipMemcpyDeviceToHost, s));
       ET_HIP(hipStreamSynchronize(s));
+      if (cell.ptr) {
+        memcpy(hi, cell.ptr, sizeof(hi));
+        cell.done = true;
+      }
       if (hi[0] < 1 || hi[0] > n_frames || hi[1] < 1 || hi[1] > T) {
         set_error("plan read back from the device is inconsistent (N = %d, segments = %d)", hi[0], hi[1]);
         return ET_ERR_HIP;
@@ -430,7 +435,7 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
     } else if (select_here) {
       const MergeWs mw = carve_merge(w.merge, T, L, D);
       k = et_keep_count(L, keep_ratio);
-      // The segment count is final after the scan: the host waits for that copy only and enqueues the
+      // The segment count is final after the scan: the host waits for that kernel only and enqueues the
       // next blocks while the merge, the selection and the compaction still run.
       const EarlyCount early{e->count_host, e->count_ready};
       *e->count_host = 0;

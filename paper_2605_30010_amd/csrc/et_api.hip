@@ -58,6 +58,34 @@ static int static_scratch(void **out) {
   return ET_OK;
 }
 
+namespace {
+constexpr int kHostCells = 64, kHostCellInts = 16;
+std::mutex g_cells_mutex;
+int32_t *g_cells = nullptr;        // one pinned page, kept to the process's end
+uint64_t g_cells_used = 0;
+}  // namespace
+
+HostCell::HostCell() : ptr(nullptr) {
+  std::lock_guard<std::mutex> lock(g_cells_mutex);
+  if (!g_cells && hipHostMalloc(reinterpret_cast<void **>(&g_cells), kHostCells * kHostCellInts * sizeof(int32_t),
+                                hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    g_cells = nullptr;
+    return;
+  }
+  if (g_cells_used == ~0ull) return;
+  const int i = __builtin_ctzll(~g_cells_used);
+  g_cells_used |= 1ull << i;
+  ptr = g_cells + i * kHostCellInts;
+  for (int j = 0; j < kHostCellInts; ++j) ptr[j] = 0;
+}
+
+HostCell::~HostCell() {
+  if (!ptr || !done) return;
+  std::lock_guard<std::mutex> lock(g_cells_mutex);
+  g_cells_used &= ~(1ull << ((ptr - g_cells) / kHostCellInts));
+}
+
 // Carves a workspace into 256-byte aligned pieces.
 struct Carver {
   char *base;
@@ -113,11 +141,8 @@ int enqueue_merge_stage(const uint16_t *x, int T, int L, int D, float tau, int k
   float *sim = sim_out ? sim_out : w.sim;
   ET_TIMED_P(prof, ET_K_SIMILARITY, launch_similarity(x, T, L, D, w.cos, w.part, s));
   ET_TIMED_P(prof, ET_K_SCAN, launch_sim_mean_scan(w.part, similarity_blocks(L), T, L, tau, sim, seg_start, w.n_seg,
-                                                   true, true, s));
-  if (early) {
-    ET_HIP(hipMemcpyAsync(early->host, w.n_seg, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    ET_HIP(hipEventRecord(early->ready, s));
-  }
+                                                   early ? early->host : nullptr, true, true, s));
+  if (early && early->ready) ET_HIP(hipEventRecord(early->ready, s));
   ET_TIMED_P(prof, ET_K_MERGE, launch_segment_mean(x, T, L, D, seg_start, w.n_seg, w.merged, w.score, s));
   if (L <= 7680) {     // selection and gather in one launch
     ET_TIMED_P(prof, ET_K_SELECT, launch_topk_gather(w.score, w.merged, T, w.n_seg, L, D, k, kept, cu_tokens, packed, s));
@@ -144,11 +169,12 @@ int check_policy(const et_policy *p) {
 int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy &pol, const PlanStep &step,
                          const MergeWs &w, float *sim_out, int32_t *seg_start, int32_t *kept,
                          int32_t *cu_tokens, uint16_t *packed, int32_t *info, hipStream_t s, Profiler *prof,
-                         const et_plan_out *plan, const float *score_override) {
+                         const et_plan_out *plan, int32_t *header, const float *score_override) {
   float *sim = sim_out ? sim_out : w.sim;
   const PolicyArgs pa{pol.merge_mode, pol.select_mode, pol.alpha, pol.tau_seg, pol.tau_merge, pol.ratio};
   const int k_uniform = et_keep_count(L, pol.ratio);
   PlanOut po;
+  po.header = header;
   if (plan) {
     po.first = plan->frame_first_dev;
     po.count = plan->frame_count_dev;
@@ -157,7 +183,7 @@ int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy
   if (step.do_plan) {
     ET_TIMED_P(prof, ET_K_SIMILARITY, launch_similarity(x, T, L, D, w.cos, w.part, s));
     ET_TIMED_P(prof, ET_K_SCAN, launch_sim_mean_scan(w.part, similarity_blocks(L), T, L, 0.f, sim, nullptr, nullptr,
-                                                     true, false, s));
+                                                     nullptr, true, false, s));
   }
   ET_TIMED_P(prof, ET_K_SCAN, launch_plan(sim, T, L, pa, k_uniform, step, seg_start, w.frame_first, w.frame_count,
                                           w.frame_dyn, w.frame_w, w.orig_first, w.orig_count, cu_tokens, info, po, s));
@@ -254,8 +280,9 @@ static struct StageProfile {
 
 // The stage on a scratch area of at least et_merge_workspace_bytes(T, L, D) bytes; waits for the stream.
 static int merge_select_on(const uint16_t *x_dev, int32_t T, int32_t L, int32_t D, float sim_threshold,
-                           float keep_ratio, void *scratch_dev, hipStream_t s, et_output *out) {
+                           float keep_ratio, void *scratch_dev, hipStream_t s, et_output *out, HostCell *cell) {
   int rc;
+  const EarlyCount count{cell ? cell->ptr : nullptr, nullptr};
   MergeWs w = carve_merge(scratch_dev, T, L, D);
   const int k = et_keep_count(L, keep_ratio);
   const bool timed = g_stage.on;
@@ -265,12 +292,16 @@ static int merge_select_on(const uint16_t *x_dev, int32_t T, int32_t L, int32_t 
   }
   if ((rc = enqueue_merge_stage(x_dev, T, L, D, sim_threshold, k, w, out->frame_sim_dev,
                                 out->seg_start_dev, out->kept_idx_dev, out->cu_tokens_dev,
-                                out->tokens_dev, s, g_stage.p.on ? &g_stage.p : nullptr)))
+                                out->tokens_dev, s, g_stage.p.on ? &g_stage.p : nullptr, &count)))
     return rc;
   if (timed) ET_HIP(hipEventRecord(g_stage.t1, s));
   int32_t n_seg = 0;
-  ET_HIP(hipMemcpyAsync(&n_seg, w.n_seg, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  if (!count.host) ET_HIP(hipMemcpyAsync(&n_seg, w.n_seg, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   ET_HIP(hipStreamSynchronize(s));
+  if (count.host) {
+    n_seg = *count.host;
+    cell->done = true;
+  }
   if (timed) {
     float ms = 0.f;
     ET_HIP(hipEventElapsedTime(&ms, g_stage.t0, g_stage.t1));
@@ -318,7 +349,8 @@ int et_merge_select_static(const uint16_t *x_dev, int32_t T, int32_t L, int32_t 
   }
   void *ptr = nullptr;
   if ((rc = static_scratch(&ptr))) return rc;
-  return merge_select_on(x_dev, T, L, D, sim_threshold, keep_ratio, ptr, static_cast<hipStream_t>(hip_stream), out);
+  return merge_select_on(x_dev, T, L, D, sim_threshold, keep_ratio, ptr, static_cast<hipStream_t>(hip_stream), out,
+                         nullptr);      // (this entry point allocates nothing, not even the page of host cells)
 }
 
 int et_merge_select(const uint16_t *x_dev, int32_t T, int32_t L, int32_t D, float sim_threshold,
@@ -332,8 +364,9 @@ int et_merge_select(const uint16_t *x_dev, int32_t T, int32_t L, int32_t D, floa
     set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, need);
     return ET_ERR_WORKSPACE;
   }
+  HostCell cell;
   return merge_select_on(x_dev, T, L, D, sim_threshold, keep_ratio, workspace_dev,
-                         static_cast<hipStream_t>(hip_stream), out);
+                         static_cast<hipStream_t>(hip_stream), out, &cell);
 }
 
 int et_merge_select_policy(const uint16_t *x_dev, int32_t T, int32_t L, int32_t D, const et_policy *policy,
@@ -356,12 +389,17 @@ int et_merge_select_policy(const uint16_t *x_dev, int32_t T, int32_t L, int32_t 
   MergeWs w = carve_merge(workspace_dev, T, L, D);
   int32_t *info = w.n_seg + 8;
   const PlanStep step{1, 1, 1, T};
+  HostCell cell;
   if ((rc = enqueue_policy_stage(x_dev, T, L, D, *policy, step, w, out->frame_sim_dev, out->seg_start_dev,
-                                 out->kept_idx_dev, out->cu_tokens_dev, out->tokens_dev, info, s, nullptr, plan)))
+                                 out->kept_idx_dev, out->cu_tokens_dev, out->tokens_dev, info, s, nullptr, plan, cell.ptr)))
     return rc;
   int32_t host_info[5] = {0, 0, 0, 0, 0};
-  ET_HIP(hipMemcpyAsync(host_info, info, sizeof(host_info), hipMemcpyDeviceToHost, s));
+  if (!cell.ptr) ET_HIP(hipMemcpyAsync(host_info, info, sizeof(host_info), hipMemcpyDeviceToHost, s));
   ET_HIP(hipStreamSynchronize(s));
+  if (cell.ptr) {
+    memcpy(host_info, cell.ptr, sizeof(host_info));
+    cell.done = true;
+  }
   if (plan) plan->n_segments = host_info[1];
   out->n_frames_out = host_info[0];
   out->n_tokens = host_info[2];
@@ -376,7 +414,7 @@ int et_frame_similarity(const uint16_t *x_dev, int32_t T, int32_t L, int32_t D, 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (T < 2) return ET_OK;
   if ((rc = launch_similarity(x_dev, T, L, D, cos_dev, nullptr, s))) return rc;
-  return launch_sim_mean_scan(cos_dev, L, T, L, 0.f, sim_dev, nullptr, nullptr, true, false, s);
+  return launch_sim_mean_scan(cos_dev, L, T, L, 0.f, sim_dev, nullptr, nullptr, nullptr, true, false, s);
 }
 
 int et_segment_scan(const float *sim_dev, int32_t T, float sim_threshold, int32_t *seg_start_dev,
@@ -386,7 +424,7 @@ int et_segment_scan(const float *sim_dev, int32_t T, float sim_threshold, int32_
   ET_REQUIRE(T == 1 || sim_dev != nullptr, "sim_dev is NULL");
   ET_REQUIRE(!isnan(sim_threshold), "sim_threshold is NaN");
   return launch_sim_mean_scan(nullptr, 0, T, 1, sim_threshold, const_cast<float *>(sim_dev), seg_start_dev,
-                              n_seg_dev, false, true, static_cast<hipStream_t>(hip_stream));
+                              n_seg_dev, nullptr, false, true, static_cast<hipStream_t>(hip_stream));
 }
 
 int et_segment_mean(const uint16_t *x_dev, int32_t T, int32_t L, int32_t D, const int32_t *seg_start_dev,

@@ -148,24 +148,37 @@ struct PolicyArgs {
 struct PlanStep {
   int do_plan, do_counts, init_orig, t_orig;
 };
-// Where the plan kernel leaves copies of the final plan (device, [N] each, any may be NULL).
+// Where the plan kernel leaves copies of the final plan (device, [N] each, any may be NULL) and of its header
+// info[0..4] (pinned host memory, or NULL).
 struct PlanOut {
-  int32_t *first = nullptr, *count = nullptr, *dyn = nullptr;
+  int32_t *first = nullptr, *count = nullptr, *dyn = nullptr, *header = nullptr;
+};
+// Sixteen int32 of pinned host memory that a kernel can write its counts to, so that the host learns them without a
+// copy of its own in the stream.  Taken from one page of 64 such cells that all threads share and given back
+// by the destructor, but only once the stream has been waited for (`done`): a cell that a kernel may still write to is
+// not handed on.  ptr is NULL when no cell is free or pinned memory is not to be had: copy instead.
+struct HostCell {
+  int32_t *ptr;
+  bool done = false;
+  HostCell();
+  ~HostCell();
+  HostCell(const HostCell &) = delete;
+  HostCell &operator=(const HostCell &) = delete;
 };
 int check_policy(const et_policy *p);
 // Enqueues similarity -> plan -> weighted merge -> selection -> ragged gather; no host sync.
 // info (device, >= 5 ints) receives N, segments, total tokens, tokens per dynamic / static frame.
 // `step` says which parts run: with do_counts the selection and the gather into `packed` follow the
 // merge; without, only `w.merged` (all L tokens per frame) and `w.score` are produced.  plan (may be NULL):
-// receives the final plan's device arrays.
+// receives the final plan's device arrays; header (may be NULL): pinned copy of info.
 int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy &pol, const PlanStep &step,
                          const MergeWs &w, float *sim_out, int32_t *seg_start, int32_t *kept,
                          int32_t *cu_tokens, uint16_t *packed, int32_t *info, hipStream_t s,
-                         struct Profiler *prof, const et_plan_out *plan, const float *score_override = nullptr);
+                         struct Profiler *prof, const et_plan_out *plan, int32_t *header, const float *score_override = nullptr);
 MergeWs carve_merge(void *ws, int T, int L, int D);
-// Where the host learns the segment count while the stage is still running: right after the scan
-// kernel the count is copied to `host` (pinned memory) and `ready` is recorded, so the host waits
-// for that event only and enqueues the following blocks under the merge, selection and compaction.
+// Where the host learns the segment count: the scan kernel writes it to `host` (pinned memory) and, if given,
+// `ready` is recorded right behind it, so the host can wait for that event only and enqueue the following blocks under
+// the merge, selection and compaction.
 struct EarlyCount {
   int32_t *host;
   hipEvent_t ready;
@@ -181,7 +194,7 @@ int similarity_blocks(int L);
 int launch_similarity(const uint16_t *x, int T, int L, int D, float *cos_out, float *part, hipStream_t s);
 // sim[t] = (sum of src[t, 0..n_src)) / L (do_mean), then the boundary scan (do_scan)
 int launch_sim_mean_scan(const float *src, int n_src, int T, int L, float tau, float *sim_out,
-                         int32_t *seg_start, int32_t *n_seg, bool do_mean, bool do_scan,
+                         int32_t *seg_start, int32_t *n_seg, int32_t *n_host, bool do_mean, bool do_scan,
                          hipStream_t s);
 int launch_segment_mean(const uint16_t *x, int T, int L, int D, const int32_t *seg_start,
                         const int32_t *n_seg, uint16_t *merged, float *score, hipStream_t s);

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kSimWaves * kWave) void similarity_kernel(
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void sim_mean_scan_kernel(
     const float *__restrict__ src, int n_src, int T, int L, float tau, float *__restrict__ sim,
-    int32_t *__restrict__ seg_start, int32_t *__restrict__ n_seg, int do_mean, int do_scan) {
+    int32_t *__restrict__ seg_start, int32_t *__restrict__ n_seg, int32_t *__restrict__ n_host, int do_mean, int do_scan) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
   if (do_mean) {
     // a wavefront sums four rows at a time, their loads issued together (the kernel is one round trip
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(1024) void sim_mean_scan_kernel(
   if (lane == 0) {
     seg_start[count] = T;
     *n_seg = count;
+    if (n_host) *n_host = count;       // pinned host memory: no copy is enqueued for it
   }
 }
 
@@ -348,10 +349,10 @@ int launch_similarity(const uint16_t *x, int T, int L, int D, float *cos_out, fl
 }
 
 int launch_sim_mean_scan(const float *src, int n_src, int T, int L, float tau, float *sim_out,
-                         int32_t *seg_start, int32_t *n_seg, bool do_mean, bool do_scan,
+                         int32_t *seg_start, int32_t *n_seg, int32_t *n_host, bool do_mean, bool do_scan,
                          hipStream_t s) {
   hipLaunchKernelGGL(sim_mean_scan_kernel, dim3(1), dim3(1024), 0, s, src, n_src, T, L, tau, sim_out,
-                     seg_start, n_seg, do_mean ? 1 : 0, do_scan ? 1 : 0);
+                     seg_start, n_seg, n_host, do_mean ? 1 : 0, do_scan ? 1 : 0);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

@@ -165,6 +165,10 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
     }
   }
   if (lane == 0) info[0] = N;
+  if (lane == 0 && out.header) {
+    out.header[0] = N;
+    out.header[1] = info[1];
+  }
   __threadfence_block();
   __syncthreads();
   for (int n = lane; n < N; n += kWave) {
@@ -197,6 +201,11 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
     info[2] = total;
     info[3] = n_dyn_tok;
     info[4] = n_sta_tok;
+    if (out.header) {
+      out.header[2] = total;
+      out.header[3] = n_dyn_tok;
+      out.header[4] = n_sta_tok;
+    }
   }
 }
 

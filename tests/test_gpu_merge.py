@@ -274,3 +274,33 @@ def test_merge_select_full_size_microbench_workload():
     assert ref["seg_start"].tolist() == np.concatenate([[0], np.cumsum(rec["lengths"])]).tolist()
     r = _run_merge_select(bits, rec["sim_threshold"], rec["keep_ratio"])
     _assert_stage_equal(r, ref)
+
+
+def test_counts_reach_the_calls_of_several_threads():
+    """The frame and token counts travel through host cells that all threads share: eight threads on streams of their
+    own, each with a clip of another segmentation, get their own counts on every call."""
+    import threading
+    L, D, errors = 16, 64, []
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            lengths = [1 + (i + j) % 4 for j in range(3 + i)]
+            bits = make_hidden_states(sum(lengths), L, D, lengths, 50 + i, sigma=0.1)
+            pol = dict(merge_mode="mean", select_mode="uniform", alpha=1.0, tau_seg=0.9, tau_merge=0.9, ratio=0.5)
+            with torch.cuda.stream(stream):
+                x = bits_to_dev(bits)
+                for _ in range(20):
+                    a = et.et_merge_select(x, 0.9, 0.5)
+                    b = et.et_merge_select_policy(x, pol)
+                    if [a["n_frames_out"], a["n_tokens"], b["n_frames_out"], b["n_tokens"]] != [len(lengths), 8 * len(lengths)] * 2:
+                        errors.append((i, a["n_frames_out"], b["n_frames_out"]))
+        except Exception as e:       # noqa: BLE001  (reported by the main thread)
+            errors.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
