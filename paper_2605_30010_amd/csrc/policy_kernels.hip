@@ -80,9 +80,59 @@ __device__ __forceinline__ void build_plan(const float *sim, int T, const Policy
   n_out = N;
 }
 
-// One wavefront.  The plan itself is a serial chain over the frames; lane 0 walks it on LDS copies (T <= kPlanLds; longer
-// clips on global memory, where every step is a round trip), everything else is done by all lanes.  What bounds
-// it is that chain: 40 frames 17.8 us on global memory.
+// The same for up to 64 frames, one per lane: only the smoothing of Eq. 1 is a chain (a few scalar steps per frame); the
+// left-to-right walk of Alg. 1 takes the lowest eligible pair, strikes out its two frames and goes on, on a bit
+// mask; positions are population counts.
+__device__ __forceinline__ void build_plan_64(const float *sim, int T, const PolicyArgs &p, const PlanLists &o, int lane,
+                                              int &n_seg_out, int &n_out) {
+  const float s = lane < T - 1 ? sim[lane] : 0.f;
+  auto of_lane = [&](int t) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), t)); };
+  unsigned long long starts = 1ull;
+  float prev = 0.f;
+  bool fresh = true;
+  for (int t = 1; t < T; ++t) {
+    const float sv = of_lane(t - 1);
+    const float cur = fresh ? sv : p.alpha * sv + (1.0f - p.alpha) * prev;
+    if (!(cur >= p.tau_seg)) {
+      starts |= 1ull << t;
+      fresh = true;
+    } else {
+      prev = cur;
+      fresh = false;
+    }
+  }
+  const unsigned long long below = (1ull << lane) - 1ull, mine = 1ull << lane, later = starts & ~(below | mine);
+  const int b = later ? __builtin_ctzll(later) : T;             // end of this lane's segment
+  const bool head = (starts & mine) != 0, tail = lane == b - 1;
+  const int a = 63 - __builtin_clzll(starts & (below | mine));
+  unsigned long long fused = 0ull, emits = starts;
+  const float s_next = __shfl_down(s, 1);
+  if (p.merge_mode != ET_MERGE_MEAN) {
+    // F_i and F_{i+1} both middle frames
+    unsigned long long left = __ballot(lane < T && lane > a && lane + 1 <= b - 2 && s > p.tau_merge && s > s_next);
+    while (left) {
+      const int i = __builtin_ctzll(left);
+      fused |= 1ull << i;
+      left &= ~(3ull << i);
+    }
+    emits = (T < 64 ? (1ull << T) - 1ull : ~0ull) & ~(fused << 1);
+  }
+  if (emits & mine) {
+    const int n = __popcll(emits & below);
+    const bool pair = (fused & mine) != 0, mean = p.merge_mode == ET_MERGE_MEAN;
+    o.first[n] = lane;
+    o.count[n] = mean ? b - a : (pair ? 2 : 1);
+    o.dyn[n] = head || tail;
+    o.w[2 * n] = mean ? 0.f : (pair ? s / (s + s_next) : 1.f);
+    o.w[2 * n + 1] = pair ? s_next / (s + s_next) : 0.f;
+  }
+  if (head) o.seg[__popcll(starts & below)] = lane;
+  n_seg_out = __popcll(starts);
+  n_out = __popcll(emits);
+}
+
+// One wavefront.  Up to 64 frames are planned by all lanes, longer clips by lane 0 on LDS copies (T <= kPlanLds) or on
+// global memory, where every step is a round trip; the arrays are written by all lanes.
 constexpr int kPlanLds = 1024;
 __global__ __launch_bounds__(kWave) void plan_kernel(
     const float *__restrict__ sim, int T, int L, PolicyArgs p, int k_uniform, PlanStep st, int32_t *__restrict__ seg_start,
@@ -101,10 +151,17 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
   int N = T;
   if (st.do_plan) {
     const bool in_lds = T <= kPlanLds;             // (uniform)
-    if (in_lds)
+    if (in_lds && T > kWave)
       for (int t = lane; t < T - 1; t += kWave) l_sim[t] = sim[t];
     __syncthreads();
-    if (lane == 0) {
+    if (T <= kWave) {
+      int n_seg = 0, n = 0;
+      build_plan_64(sim, T, p, PlanLists{l_seg, l_first, l_count, l_dyn, l_w}, lane, n_seg, n);
+      if (lane == 0) {
+        head[0] = n_seg;
+        head[1] = n;
+      }
+    } else if (lane == 0) {
       int n_seg = 0, n = 0;
       if (in_lds) build_plan(l_sim, T, p, PlanLists{l_seg, l_first, l_count, l_dyn, l_w}, n_seg, n);
       else build_plan(sim, T, p, PlanLists{seg_start, frame_first, frame_count, frame_dyn, frame_w}, n_seg, n);
