@@ -148,13 +148,13 @@ __global__ __launch_bounds__(256) void im2col_kernel(const float *__restrict__ f
 // are read as whole rows (float4, coalesced), kept in LDS as bf16, and the stripe's GX output rows are
 // written as whole 16-byte chunks - both sides of the copy are contiguous, where the kernel above reads
 // P-pixel runs.  Needs W % 4 == 0, 16-byte aligned frames and C * P * W * 2 bytes of LDS.
-__global__ __launch_bounds__(256) void im2col_stripe_kernel(const float *__restrict__ frames, int C, int H, int W, int P,
+__global__ __launch_bounds__(1024) void im2col_stripe_kernel(const float *__restrict__ frames, int C, int H, int W, int P,
                                                             int GX, int GY, int Kreal, int Kpad,
                                                             uint16_t *__restrict__ out) {
   extern __shared__ __align__(16) uint16_t stripe[];           // [C * P][W] bf16
   const int t = blockIdx.x / GY, gy = blockIdx.x % GY;
   const int w4 = W / 4, n4 = C * P * w4;
-  for (int i = threadIdx.x; i < n4; i += 256) {
+  for (int i = threadIdx.x; i < n4; i += blockDim.x) {
     const int r = i / w4, x4 = i % w4, c = r / P, py = r % P;
     const float4 v = *reinterpret_cast<const float4 *>(frames + (((size_t)t * C + c) * H + (gy * P + py)) * W + x4 * 4);
     uint2 o;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void im2col_stripe_kernel(const float *__restr
   __syncthreads();
   const int chunks = Kpad / 8;
   uint16_t *orow = out + ((size_t)t * GY + gy) * GX * Kpad;
-  for (int i = threadIdx.x; i < GX * chunks; i += 256) {
+  for (int i = threadIdx.x; i < GX * chunks; i += blockDim.x) {
     const int gx = i / chunks, ch = i % chunks;
     uint16_t v[8];
 #pragma unroll
@@ -1201,7 +1201,10 @@ int launch_im2col(const float *frames, int T, int C, int H, int W, int P, int Kp
   const int GX = W / P, GY = H / P, L = GX * GY;
   const size_t stripe_bytes = (size_t)C * P * W * sizeof(uint16_t);
   if (W % 4 == 0 && reinterpret_cast<uintptr_t>(frames) % 16 == 0 && stripe_bytes <= 64 * 1024) {
-    hipLaunchKernelGGL(im2col_stripe_kernel, dim3((unsigned)(T * GY)), dim3(256), stripe_bytes, s, frames, C, H, W, P,
+    // A workgroup's copy is a chain of a few loads per thread: more wavefronts per workgroup while there are few
+    // workgroups (256 / 512 / 1024 threads, us: 27 workgroups of 384-pixel images 18 / 12 / 9, 216 21 / 14 / 12, 432
+    // 24 / 19 / 17, 864 33 / 28 / 30, 1728 52 / 46 / 50).
+    hipLaunchKernelGGL(im2col_stripe_kernel, dim3((unsigned)(T * GY)), dim3(T * GY <= 512 ? 1024 : 512), stripe_bytes, s, frames, C, H, W, P,
                        GX, GY, C * P * P, Kpad, out);
     ET_LAUNCH_CHECK();
     return ET_OK;
