@@ -67,11 +67,18 @@ uint64_t g_cells_used = 0;
 
 HostCell::HostCell() : ptr(nullptr) {
   std::lock_guard<std::mutex> lock(g_cells_mutex);
-  if (!g_cells && hipHostMalloc(reinterpret_cast<void **>(&g_cells), kHostCells * kHostCellInts * sizeof(int32_t),
-                                hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-    (void)hipGetLastError();
-    g_cells = nullptr;
-    return;
+  if (!g_cells) {
+    // (relaxed: another thread may be capturing a graph, which forbids allocations in the stricter modes)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t err = hipHostMalloc(reinterpret_cast<void **>(&g_cells), kHostCells * kHostCellInts * sizeof(int32_t),
+                                         hipHostMallocPortable | hipHostMallocMapped);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (err != hipSuccess) {
+      (void)hipGetLastError();
+      g_cells = nullptr;
+      return;
+    }
   }
   if (g_cells_used == ~0ull) return;
   const int i = __builtin_ctzll(~g_cells_used);
