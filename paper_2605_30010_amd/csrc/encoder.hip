@@ -111,7 +111,6 @@ static int upload_f32(et_encoder *e, const float *src, int n, int n_pad, float *
 
 struct EncWs {
   uint16_t *x, *qkv, *att, *hid;
-  int32_t *cu_full;
   void *merge;
   // row statistics and per-head column sums of the attention-received scores.  The statistics of the residual
   // stream live there too, from a residual GEMM to the GEMM that follows it (no scores are computed between):
@@ -138,7 +137,6 @@ static EncWs carve_encoder(const et_encoder *e, void *ws, int T) {
   w.att = static_cast<uint16_t *>(take(R * e->D * 2));
   const size_t hid_cols = (size_t)(e->Mhp > e->Kp_pad ? e->Mhp : e->Kp_pad);
   w.hid = static_cast<uint16_t *>(take(R * hid_cols * 2));
-  w.cu_full = static_cast<int32_t *>(take((size_t)(T + 1) * 4));
   w.merge = take(carve_merge(nullptr, T, e->L, e->D).bytes);
   const size_t score_bytes = attention_scores_workspace_bytes(T, e->L, e->cfg.n_heads), piece_bytes = R * (e->D / 64) * sizeof(float2);
   w.score_ws = take(score_bytes > piece_bytes ? score_bytes : piece_bytes);
@@ -365,13 +363,10 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
 
   int rows = T * L, n_frames = T, max_len = L, k = L;
   (void)k;
-  const int32_t *cu = w.cu_full;
+  const int32_t *cu = nullptr;             // row ranges of the frames, once they differ in length
   if (!compress) {
     ET_TIMED(ET_K_MISC, launch_identity_maps(T, L, out->kept_idx_dev, out->cu_tokens_dev,
                                              out->seg_start_dev, s));
-    cu = out->cu_tokens_dev;
-  } else {
-    ET_TIMED(ET_K_MISC, launch_cu_uniform(T, L, w.cu_full, s));
   }
 
   // patch embedding: x = patches * Wp^T + bp + pos_emb[l]

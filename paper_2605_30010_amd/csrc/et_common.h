@@ -207,7 +207,6 @@ int launch_compact(const uint16_t *merged, const int32_t *kept, int n_rows_max,
                    const int32_t *n_rows_dev, int L, int D, int k, uint16_t *out, hipStream_t s);
 int launch_identity_maps(int T, int L, int32_t *kept, int32_t *cu_tokens, int32_t *seg_start,
                          hipStream_t s);
-int launch_cu_uniform(int n, int step, int32_t *cu, hipStream_t s);
 
 // ---- launchers implemented in policy_kernels.hip ----
 int launch_plan(const float *sim, int T, int L, const PolicyArgs &p, int k_uniform, const PlanStep &st,

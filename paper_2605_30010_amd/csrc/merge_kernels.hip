@@ -326,11 +326,6 @@ __global__ void identity_maps_kernel(int T, int L, int32_t *kept, int32_t *cu_to
   }
 }
 
-__global__ void cu_uniform_kernel(int n, int step, int32_t *cu) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= n) cu[i] = i * step;
-}
-
 }  // namespace
 
 int similarity_blocks(int L) { return (L + kSimWaves - 1) / kSimWaves; }
@@ -407,12 +402,6 @@ int launch_identity_maps(int T, int L, int32_t *kept, int32_t *cu_tokens, int32_
   int n = T * L > T + 1 ? T * L : T + 1;
   hipLaunchKernelGGL(identity_maps_kernel, dim3((n + 255) / 256), dim3(256), 0, s, T, L, kept,
                      cu_tokens, seg_start);
-  ET_LAUNCH_CHECK();
-  return ET_OK;
-}
-
-int launch_cu_uniform(int n, int step, int32_t *cu, hipStream_t s) {
-  hipLaunchKernelGGL(cu_uniform_kernel, dim3((n + 256) / 256), dim3(256), 0, s, n, step, cu);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }
