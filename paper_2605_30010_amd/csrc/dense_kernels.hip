@@ -4,6 +4,7 @@
 // The MFMA operand layouts are described in mfma_common.h.
 #include <atomic>
 
+#include "gemm_choice.h"
 #include "gemm_small.h"
 
 namespace et {
@@ -1216,15 +1217,7 @@ int launch_im2col(const float *frames, int T, int C, int H, int W, int P, int Kp
   return ET_OK;
 }
 
-// Workgroup tilings (tile_config of et_gemm_bf16):
-//   0  256 x 256, 8 wavefronts, persistent, one workgroup per compute unit
-//   1  128 x 128, 4 wavefronts, persistent, two workgroups per compute unit
-//   2   64 x  64, k split over 4 wavefronts, two workgroups per compute unit      (gemm_small.hip)
-//   3  128 x  64, k split over 4 groups of 2 wavefronts                           (gemm_small.hip)
-//   4  128 x 128, k split over 2 groups of 4 wavefronts                           (gemm_small.hip)
-//   5  256 x 128, 8 wavefronts in two alternating halves                          (gemm_small.hip)
-enum { kCfgBig = 0, kCfg128 = 1, kCfgWave = 2, kCfgPair64 = 3, kCfgPair128 = 4, kCfgHalf = 5, kCfgCount = 6 };
-int gemm_config_count() { return kCfgCount; }
+int gemm_config_count() { return kCfgStrip; }     // (what et_gemm_bf16 can ask for)
 
 static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
   switch (cfg) {
@@ -1234,52 +1227,9 @@ static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
     case kCfgPair64: return launch_gemm_pair64(g, s);
     case kCfgPair128: return launch_gemm_pair128(g, s);
     case kCfgHalf: return launch_gemm_half(g, s);
+    case kCfgStrip: return launch_gemm_strip(g, s);
     default: set_error("unknown gemm tile configuration %d", cfg); return ET_ERR_INVALID_ARG;
   }
-}
-
-// Expected time of one launch in microseconds, launch overhead included: a fixed part (first loads,
-// epilogue) plus a part per k-tile of 64 in each round of tiles.  A compute unit is slower when its
-// neighbours work too (shared caches, and the clock falls with the power drawn), hence the terms in
-// t / slots.  Fitted to launches on 256 compute units at the encoder's shapes, 64 to 23328 rows; measured
-// at K = 1152 / 4352:
-//   wave     6.8 / 17 us for one round of 256 tiles, 10.3 / 28 for two, 15 / 42 for three
-//   pair64   9.3 / 25 for one round, 17.5 / 47 for two
-//   pair128  11-12 / 30 (up to 160 tiles), 14 / 36 (234 tiles), 25 / 67 for two rounds
-//   half     16.3 / 45 (up to 100 tiles), 22 / 59 (207), 42 / 120 for two rounds
-//   128      15 / 46 (up to 160 tiles), 20 (324), 23.5 / 64 (414), 36 / 107 (576)
-//   256      26 / 77 (70 tiles), 30 (182), 39 / 108 (230), 4 rounds 133 / 475
-static double gemm_cost(int cfg, long rows, long cols, int K) {
-  const double kt = K / 64;
-  auto tiles = [&](int bm, int bn) { return ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); };
-  auto rounds = [](long t, long slots) { return (double)((t + slots - 1) / slots); };
-  switch (cfg) {
-    case kCfgWave: return 3.2 + rounds(tiles(64, 64), 256) * 0.195 * kt;
-    case kCfgPair64: return 0.5 + rounds(tiles(128, 64), 256) * (2.9 + 0.32 * kt);
-    case kCfgPair128: {
-      const long t = tiles(128, 128);
-      return t <= 256 ? 3.6 + kt * (0.38 + 0.10 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.46 * kt);
-    }
-    case kCfgHalf: {
-      const long t = tiles(256, 128);
-      return t <= 256 ? 6.5 + kt * (0.53 + 0.25 * (double)t / 256.0) : rounds(t, 256) * (6.0 + 0.8 * kt);
-    }
-    case kCfg128: {
-      const long t = tiles(128, 128), last = t % 512;
-      return 2.2 + (double)(t / 512) * (3.5 + 1.05 * kt) + (last ? 2.4 + kt * (0.55 + 0.4 * (double)last / 512.0) : 0.0);
-    }
-    default: {
-      const long t = tiles(256, 256), last = t % 256;
-      return 0.5 + (double)(t / 256) * (4.5 + 1.6 * kt) + (last ? 4.5 + kt * (1.05 + 0.55 * (double)last / 256.0) : 0.0);
-    }
-  }
-}
-
-// Whether gemm_stream_kernel walks one tile per workgroup (the others always do).
-static bool one_round(int cfg, long rows, long cols) {
-  if (cfg == kCfgBig) return ((rows + 255) / 256) * ((cols + 255) / 256) <= 256;
-  if (cfg == kCfg128) return ((rows + 127) / 128) * ((cols + 127) / 128) <= 512;
-  return true;
 }
 
 // Whether a GEMM over `rows` rows is best done in one round of tiles, i.e. takes the statistics of its rows by
@@ -1297,69 +1247,23 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     return ET_ERR_INVALID_ARG;
   }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
-  auto cheapest = [&](long rows, long cols, double *cost) {
-    int best = kCfgWave;
-    double c = gemm_cost(best, rows, cols, g.K);
-    for (int cfg = 0; cfg < kCfgCount; ++cfg) {
-      if (g.stats_in && !one_round(cfg, rows, cols)) continue;
-      const double x = gemm_cost(cfg, rows, cols, g.K);
-      if (x < c) { c = x; best = cfg; }
-    }
-    if (cost) *cost = c;
-    return best;
-  };
-  double best = 0.0;
-  const int cfg = cheapest(g.M, g.n_store, &best);
-  // Big tiles over the whole matrix but the rows or columns that would make a last, nearly empty round
-  // (a partly filled last tile row or column, or the tile rows past a whole number of rounds): those
-  // go to launches of their own with smaller tiles, if that saves at least 3 % and 4 us over the best
-  // single launch.
-  int best_dr = 0, best_dc = 0;
-  const int tm = (g.M + 255) / 256, tn = (g.n_store + 255) / 256;
-  if (!g.stats_in && (long)tm * tn > 256) {
-    const bool rows_splittable = (g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M) && tm > 1;
-    const bool cols_splittable = g.n_store % 256 != 0 && tn > 1;
-    double split_best = best - (best * 0.03 > 4.0 ? best * 0.03 : 4.0);
-    for (int dr = 0; dr <= (rows_splittable ? (tm < 8 ? tm - 1 : 8) : 0); ++dr)
-      for (int dc = 0; dc <= (cols_splittable ? 1 : 0); ++dc) {
-        if (!dr && !dc) continue;
-        const long rm = dr ? (long)(tm - dr) * 256 : g.M, cm = dc ? (long)(tn - dc) * 256 : g.n_store;
-        double right = 0.0, bottom = 0.0;
-        if (dc) cheapest(rm, g.n_store - cm, &right);      // right strip next to the main block
-        if (dr) cheapest(g.M - rm, g.n_store, &bottom);    // bottom strip over the full width
-        const double c = gemm_cost(kCfgBig, rm, cm, g.K) + right + bottom;
-        if (c < split_best - 1e-9) { split_best = c; best_dr = dr; best_dc = dc; }
-      }
+  const GemmPlan plan = plan_gemm(GemmRules{g.K, g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr}, g.M, g.n_store);
+  for (int i = 0; i < plan.n; ++i) {
+    const GemmPart &t = plan.part[i];
+    GemmArgs part = g;
+    part.M = t.rows;
+    part.n_store = t.cols;
+    part.A = g.A + (size_t)t.row0 * g.lda;
+    part.W = g.W + (size_t)t.col0 * g.K;
+    part.bias = g.bias + t.col0;
+    part.C = g.C + (size_t)t.row0 * g.ldc + t.col0;
+    if (g.res) part.res = g.res + (size_t)t.row0 * g.ldr + t.col0;
+    if (g.row_scale) part.row_scale = g.row_scale + t.row0;
+    if (g.stats_out) part.stats_out = g.stats_out + (size_t)(t.col0 / 64) * g.stats_ld + t.row0;
+    const int rc = launch_gemm_id(part, s, t.cfg);
+    if (rc != ET_OK) return rc;
   }
-  if (!best_dr && !best_dc) return launch_gemm_id(g, s, cfg);
-  const int rm = best_dr ? (tm - best_dr) * 256 : g.M, cm = best_dc ? (tn - best_dc) * 256 : g.n_store;
-  GemmArgs part = g;
-  part.M = rm;
-  part.n_store = cm;
-  int rc = launch_gemm_id(part, s, kCfgBig);
-  if (rc == ET_OK && best_dc) {
-    part = g;
-    part.M = rm;
-    part.W = g.W + (size_t)cm * g.K;
-    part.bias = g.bias + cm;
-    part.C = g.C + cm;
-    if (g.res) part.res = g.res + cm;
-    if (g.stats_out) part.stats_out = g.stats_out + (size_t)(cm / 64) * g.stats_ld;
-    part.n_store = g.n_store - cm;
-    rc = launch_gemm(part, s);
-  }
-  if (rc == ET_OK && best_dr) {
-    part = g;
-    part.A = g.A + (size_t)rm * g.lda;
-    part.C = g.C + (size_t)rm * g.ldc;
-    if (g.res) part.res = g.res + (size_t)rm * g.ldr;
-    if (g.row_scale) part.row_scale = g.row_scale + rm;
-    if (g.stats_in) part.stats_in = g.stats_in + rm;
-    if (g.stats_out) part.stats_out = g.stats_out + rm;
-    part.M = g.M - rm;
-    rc = launch_gemm(part, s);
-  }
-  return rc;
+  return ET_OK;
 }
 
 bool head_dim_supported(int hd) {

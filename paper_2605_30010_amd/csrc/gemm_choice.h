@@ -1,0 +1,136 @@
+// Which workgroup tiling each part of a GEMM runs on.  Plain C++ without HIP: launch_gemm carries out what
+// plan_gemm lists, and a test on the CPU checks that list over the sizes.
+//
+// The rows of one matrix are summed over k in one order.  Equal rows (the tokens of a frame that stands still)
+// then have equal bits wherever they lie, so the similarities of equal frames are equal and Alg. 1's strict
+// comparison fuses none of them.  A launch over all rows may use any order; a launch over some of them takes only the
+// tilings that add k-steps in ascending order to one accumulator.
+#pragma once
+
+namespace et {
+
+// Workgroup tilings (tile_config of et_gemm_bf16, up to kCfgHalf):
+//   0  256 x 256, 8 wavefronts, persistent, one workgroup per compute unit
+//   1  128 x 128, 4 wavefronts, persistent, two workgroups per compute unit
+//   2   64 x  64, k split over 4 wavefronts, two workgroups per compute unit      (gemm_small.hip)
+//   3  128 x  64, k split over 4 groups of 2 wavefronts                           (gemm_small.hip)
+//   4  128 x 128, k split over 2 groups of 4 wavefronts                           (gemm_small.hip)
+//   5  256 x 128, 8 wavefronts in two alternating halves                          (gemm_small.hip)
+//   6   64 x  64, 4 wavefronts with a quadrant each, two workgroups per compute unit (gemm_small.hip): the last tile rows only
+enum { kCfgBig = 0, kCfg128 = 1, kCfgWave = 2, kCfgPair64 = 3, kCfgPair128 = 4, kCfgHalf = 5, kCfgStrip = 6, kCfgCount = 7 };
+
+// One accumulator per output element, k ascending.
+inline bool in_k_order(int cfg) { return cfg == kCfgBig || cfg == kCfg128 || cfg == kCfgHalf || cfg == kCfgStrip; }
+
+inline long gemm_tiles(int cfg, long rows, long cols) {
+  static const int bm[kCfgCount] = {256, 128, 64, 128, 128, 256, 64}, bn[kCfgCount] = {256, 128, 64, 64, 128, 128, 64};
+  return ((rows + bm[cfg] - 1) / bm[cfg]) * ((cols + bn[cfg] - 1) / bn[cfg]);
+}
+
+// Expected time of one launch in microseconds, launch overhead included: a fixed part (first loads,
+// epilogue) plus a part per k-tile of 64 in each round of tiles.  A compute unit is slower when its
+// neighbours work too (shared caches, and the clock falls with the power drawn), hence the terms in
+// t / slots.  Fitted to launches on 256 compute units at the encoder's shapes, 64 to 23328 rows; measured
+// at K = 1152 / 4352:
+//   wave     6.8 / 17 us for one round of 256 tiles, 10.3 / 28 for two, 15 / 42 for three
+//   pair64   9.3 / 25 for one round, 17.5 / 47 for two
+//   pair128  11-12 / 30 (up to 160 tiles), 14 / 36 (234 tiles), 25 / 67 for two rounds
+//   half     16.3 / 45 (up to 100 tiles), 22 / 59 (207), 42 / 120 for two rounds
+//   128      15 / 46 (up to 160 tiles), 20 (324), 23.5 / 64 (414), 36 / 107 (576)
+//   256      26 / 77 (70 tiles), 30 (182), 39 / 108 (230), 4 rounds 133 / 475
+//   strip    7.4 (54 tiles) / 18, 8.2 (204), 10.4 (340), 18 / 45 for four and three rounds
+inline double gemm_cost(int cfg, long rows, long cols, int K) {
+  const double kt = K / 64;
+  const long t = gemm_tiles(cfg, rows, cols);
+  auto rounds = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
+  switch (cfg) {
+    case kCfgWave: return 3.2 + rounds(t, 256) * 0.195 * kt;
+    case kCfgPair64: return 0.5 + rounds(t, 256) * (2.9 + 0.32 * kt);
+    case kCfgPair128: return t <= 256 ? 3.6 + kt * (0.38 + 0.10 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.46 * kt);
+    case kCfgHalf: return t <= 256 ? 6.5 + kt * (0.53 + 0.25 * (double)t / 256.0) : rounds(t, 256) * (6.0 + 0.8 * kt);
+    case kCfgStrip: return 3.2 + rounds(t, 256) * 0.205 * kt;
+    case kCfg128: {
+      const long last = t % 512;
+      return 2.2 + (double)(t / 512) * (3.5 + 1.05 * kt) + (last ? 2.4 + kt * (0.55 + 0.4 * (double)last / 512.0) : 0.0);
+    }
+    default: {
+      const long last = t % 256;
+      return 0.5 + (double)(t / 256) * (4.5 + 1.6 * kt) + (last ? 4.5 + kt * (1.05 + 0.55 * (double)last / 256.0) : 0.0);
+    }
+  }
+}
+
+// Whether the persistent kernel walks one tile per workgroup (the others always do).
+inline bool one_round(int cfg, long rows, long cols) {
+  if (cfg == kCfgBig) return gemm_tiles(cfg, rows, cols) <= 256;
+  if (cfg == kCfg128) return gemm_tiles(cfg, rows, cols) <= 512;
+  return true;
+}
+
+struct GemmPart {
+  int row0, rows, col0, cols, cfg;
+};
+struct GemmPlan {
+  static constexpr int kMax = 16;
+  GemmPart part[kMax];
+  int n = 0;
+  void add(long row0, long rows, long col0, long cols, int cfg) {
+    part[n++] = GemmPart{(int)row0, (int)rows, (int)col0, (int)cols, cfg};
+  }
+};
+
+// What plan_gemm may do: split rows off into launches of their own; only tilings that walk one tile per workgroup.
+struct GemmRules {
+  int K;
+  bool rows_splittable, one_tile;
+};
+
+inline int cheapest_tiling(const GemmRules &r, long rows, long cols, bool ordered, double *cost) {
+  int best = ordered ? kCfgStrip : kCfgWave;
+  *cost = gemm_cost(best, rows, cols, r.K);
+  for (int cfg = 0; cfg < kCfgStrip; ++cfg) {
+    if ((ordered && !in_k_order(cfg)) || (r.one_tile && !one_round(cfg, rows, cols))) continue;
+    const double c = gemm_cost(cfg, rows, cols, r.K);
+    if (c < *cost) { *cost = c; best = cfg; }
+  }
+  return best;
+}
+
+// Adds the launches of one part of the matrix; `ordered`: other launches share its columns.
+inline void plan_gemm_part(const GemmRules &r, long row0, long rows, long col0, long cols, bool ordered, GemmPlan &out) {
+  double best = 0.0;
+  const int cfg = cheapest_tiling(r, rows, cols, ordered, &best);
+  // Big tiles over the whole part but the rows or columns that would make a last, nearly empty round
+  // (a partly filled last tile row or column, or the tile rows past a whole number of rounds): those
+  // go to launches of their own with smaller tiles, if that saves at least 3 % and 4 us over the best
+  // single launch.
+  long best_dr = 0, best_dc = 0;
+  const long tm = (rows + 255) / 256, tn = (cols + 255) / 256;
+  if (!r.one_tile && tm * tn > 256 && out.n + 4 <= GemmPlan::kMax) {
+    const long max_dr = r.rows_splittable ? (tm < 8 ? tm - 1 : 8) : 0, max_dc = (cols % 256 != 0 && tn > 1) ? 1 : 0;
+    double split_best = best - (best * 0.03 > 4.0 ? best * 0.03 : 4.0);
+    for (long dr = 0; dr <= max_dr; ++dr)
+      for (long dc = 0; dc <= max_dc; ++dc) {
+        if (!dr && !dc) continue;
+        const long rm = dr ? (tm - dr) * 256 : rows, cm = dc ? (tn - dc) * 256 : cols;
+        double right = 0.0, bottom = 0.0;
+        if (dc) cheapest_tiling(r, rm, cols - cm, ordered || dr > 0, &right);      // right strip next to the main block
+        if (dr) cheapest_tiling(r, rows - rm, cols, true, &bottom);                // bottom strip over the full width
+        const double c = gemm_cost(kCfgBig, rm, cm, r.K) + right + bottom;
+        if (c < split_best - 1e-9) { split_best = c; best_dr = dr; best_dc = dc; }
+      }
+  }
+  if (!best_dr && !best_dc) return out.add(row0, rows, col0, cols, cfg);
+  const long rm = best_dr ? (tm - best_dr) * 256 : rows, cm = best_dc ? (tn - best_dc) * 256 : cols;
+  out.add(row0, rm, col0, cm, kCfgBig);
+  if (best_dc) plan_gemm_part(r, row0, rm, col0 + cm, cols - cm, ordered || best_dr > 0, out);
+  if (best_dr) plan_gemm_part(r, row0 + rm, rows - rm, col0, cols, true, out);
+}
+
+inline GemmPlan plan_gemm(const GemmRules &r, long rows, long cols) {
+  GemmPlan out;
+  plan_gemm_part(r, 0, rows, 0, cols, false, out);
+  return out;
+}
+
+}  // namespace et

@@ -1,6 +1,7 @@
 // GEMM kernels for few rows (a short clip, or the blocks on the kept tokens), where the output has
 // too few tiles to fill the chip: the contraction is split over the wavefronts of a workgroup and
-// the partial sums meet in LDS, so nothing but the result goes through memory.
+// the partial sums meet in LDS, so nothing but the result goes through memory.  (gemm_half_kernel and
+// gemm_strip_kernel split no k: k ascending in one accumulator, as the persistent kernel does it.)
 //
 // What bounds these launches (measured): a launch costs 2.2 us before it does anything; after that
 // a compute unit takes its operands through one 64-byte-per-clock path (59 B/clk reached, and only
@@ -39,16 +40,16 @@ __device__ __forceinline__ uint32_t piece_offset(int row, int src_row, int ld, i
   return (uint32_t)src_row * (uint32_t)ld * 2u + (uint32_t)((slot ^ ((row >> 1) & 7)) * 16) + kOffBias - (uint32_t)(i % 4) * 1024u;
 }
 
-// Sum of the PARTS partial 64 x 64 tiles of one output tile and the epilogue.  Every wavefront has
-// written its accumulators to its own 16 KiB of LDS (fragment order, 16-byte cells); wavefront
-// `rank` of the PARTS finishes 64 / PARTS rows, reading the cells row by row so that residual loads
+// Sum of the SUM partial 64 x 64 tiles of one output tile and the epilogue.  put() writes the wavefront's
+// accumulators to 16 KiB of LDS per partial tile (fragment order, 16-byte cells); wavefront
+// `rank` of the PARTS that share the output tile finishes 64 / PARTS rows, reading the cells row by row so that residual loads
 // and stores are 128-byte row segments.  Partial sums are added in ascending order of the wavefronts:
 // the result does not depend on timing.  rs_tile (LDS): the row scales of the 64 rows, written before the barrier.
 // The cell of (column octet c, lane l) sits at l ^ (c << 1):
 // both the writes (fixed c) and the row-wise reads (8 octets x 8 rows) are then conflict-free.
-template <int PARTS, int STRIDE, int EPI>
-__device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const GemmArgs &g, f32x4 *xch, int wave, int first,
-                                              int rank, int m_tile, int n_tile, int lane, const float *rs_tile) {
+template <int PARTS, int SUM, int STRIDE, int EPI, class Put>
+__device__ __forceinline__ void finish_rows(Put put, const GemmArgs &g, f32x4 *xch, int first, int rank, int m_tile, int n_tile,
+                                            int lane, const float *rs_tile) {
   constexpr int ROWS = 64 / PARTS, PASS = ROWS / 8;
   const int pr = lane >> 3, oct = lane & 7;
   const int n = n_tile + oct * 8, row0 = rank * ROWS + pr;
@@ -66,16 +67,7 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
     b0 = *reinterpret_cast<const f32x4 *>(g.bias + n);
     b1 = *reinterpret_cast<const f32x4 *>(g.bias + n + 4);
   }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = a * 4 + q;
-        xch[wave * 1024 + (b * 8 + c) * 64 + (lane ^ (c << 1))] =
-            f32x4{acc[a][b][q * 4], acc[a][b][q * 4 + 1], acc[a][b][q * 4 + 2], acc[a][b][q * 4 + 3]};
-      }
+  put();
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < PASS; ++p) {
@@ -84,7 +76,7 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
     const f32x4 *cell = xch + first * 1024 + ((ml >> 5) * 8 + oct) * 64;
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll
-    for (int j = 0; j < PARTS; ++j) {
+    for (int j = 0; j < SUM; ++j) {
       lo += cell[j * STRIDE * 1024 + (r ^ (oct << 1))];
       hi += cell[j * STRIDE * 1024 + ((32 + r) ^ (oct << 1))];
     }
@@ -109,6 +101,26 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
       if (oct == 0 && m < g.M && n_ok) g.stats_out[(size_t)(n_tile >> 6) * g.stats_ld + m] = st;
     }
   }
+}
+
+// One 32 x 32 accumulator (columns 32 a, rows 32 b of the 64 x 64 tile) to the cells above.
+__device__ __forceinline__ void put_quadrant(const f32x16 &acc, f32x4 *cells, int a, int b, int lane) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = a * 4 + q;
+    cells[(b * 8 + c) * 64 + (lane ^ (c << 1))] = f32x4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+  }
+}
+template <int PARTS, int STRIDE, int EPI>
+__device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const GemmArgs &g, f32x4 *xch, int wave, int first,
+                                              int rank, int m_tile, int n_tile, int lane, const float *rs_tile) {
+  auto put = [&]() {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) put_quadrant(acc[a][b], xch + wave * 1024, a, b, lane);
+  };
+  finish_rows<PARTS, PARTS, STRIDE, EPI>(put, g, xch, first, rank, m_tile, n_tile, lane, rs_tile);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -196,6 +208,110 @@ __global__ __launch_bounds__(256, 2) void gemm_wave_kernel(GemmArgs g, int tiles
   }
   // (a wavefront's 16 KiB of the exchange are its own slot: no barrier before they are written)
   finish_tile64<NW, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, 0, wave, m0, n0, lane, rs_tile);
+}
+
+// ---------------------------------------------------------------------------------------
+// 64 x 64 tile, 4 wavefronts with a quadrant each, k ascending in one accumulator per element: the order of the persistent
+// kernel and of gemm_half_kernel, for the last tile rows of a matrix whose other rows run there (gemm_choice.h).
+// Four 16 KiB slots, one barrier per k-tile: all fragments of k-tile t are read at once, under the MFMAs of t - 1,
+// and the loads of t + 3 go to the slot that everyone has left.  Bound by the operand path of the compute unit, like the
+// kernel above (256 cycles per k-tile; the matrix unit 256 as well).  Measured per launch against 64 x 128 tiles of the
+// persistent kernel and against the kernel above, which splits k: 32 rows, 3456 x 1152: 12.7 / 6.9 -> 7.4 us; 288 rows,
+// 4352 x 1152: 14.0 / 11.1 -> 10.4; 341 rows, 3584 x 3584: 32.6 / 22.1 -> 21.5; 96 rows, 1152 x 4352: 38.8 / 15.1 -> 18.1.
+// (One wavefront per tile: as slow as the 64 x 128 tile, its SIMD's matrix unit takes 1024 cycles per k-tile.)
+// ---------------------------------------------------------------------------------------
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int ST = 4, SLOT = 8192;                     // slots; elements of one: 64 rows of A, 64 of W, 128 bytes each
+  extern __shared__ __align__(16) uint16_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, r32 = lane & 31, grp = lane >> 5, lrow = lane >> 3, lslot = lane & 7;
+  int m0, n0;
+  small_tile_of(tiles_m, tiles_n, m0, n0);
+  m0 *= 64;
+  n0 *= 64;
+  const int kt_n = g.K / 64;
+  const char *a_base = reinterpret_cast<const char *>(g.A + (size_t)m0 * g.lda) - kOffBias;
+  const char *w_base = reinterpret_cast<const char *>(g.W + (size_t)n0 * g.K) - kOffBias;
+  uint32_t a_off[2], w_off[2];                           // 1 KiB loads 2 wave, 2 wave + 1 of either operand
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = (wave * 2 + i) * 8 + lrow;
+    a_off[i] = piece_offset(row, (m0 + row < g.M) ? row : g.M - 1 - m0, g.lda, lslot, i);   // rows past M: the last row again
+    w_off[i] = piece_offset(row, row, g.K, lslot, i);
+  }
+  auto issue = [&](int slot, int t) {
+    uint16_t *as = lds + slot * SLOT + wave * 1024, *ws = as + 4096;
+    const char *ab = a_base + (size_t)t * 128, *wb = w_base + (size_t)t * 128;
+    asm volatile("" : "+s"(ab), "+s"(wb));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      asm volatile("" : "+v"(a_off[i]));
+      lds_dma16_of4(ab + a_off[i], as, i);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      asm volatile("" : "+v"(w_off[i]));
+      lds_dma16_of4(wb + w_off[i], ws, i);
+    }
+  };
+  float *rs_tile = reinterpret_cast<float *>(lds + ST * SLOT);
+  RowScale<18> scale;
+  const bool scales = EPI != EPI_BIAS_RES && wave == 0;
+  if (scales) scale.fetch(g, m0 + lane);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t)
+    if (t < kt_n) issue(t, t);
+  if (scales) rs_tile[lane] = scale.value(g);
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  const int fx = (r32 >> 1) & 7, a_row = (wm * 32 + r32) * 64, w_row = 4096 + (wn * 32 + r32) * 64;
+  u32x4 fa[2][4], fw[2][4];
+  int slot = 0;
+  // k-tile t into fragment buffer `buf`; the MFMAs of t - 1 (the other buffer) follow the reads
+  auto step = [&](int buf, int t) {
+    if (t + 2 < kt_n) wait_vmcnt<8>();                   // k-tile t has landed (this wavefront's share), two more in flight
+    else if (t + 1 < kt_n) wait_vmcnt<4>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();                        // ... everyone's; and everyone has read k-tile t - 1
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const uint16_t *sp = lds + slot * SLOT;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int ko = ((2 * ks + grp) ^ fx) * 8;
+      fa[buf][ks] = *reinterpret_cast<const u32x4 *>(sp + a_row + ko);
+      fw[buf][ks] = *reinterpret_cast<const u32x4 *>(sp + w_row + ko);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + ST - 1 < kt_n) issue(slot == 0 ? ST - 1 : slot - 1, t + ST - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t > 0) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) acc = mfma32(fw[buf ^ 1][ks], fa[buf ^ 1][ks], acc);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): the reads have returned before the next barrier
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    slot = slot + 1 == ST ? 0 : slot + 1;
+  };
+  for (int t = 0; t < kt_n; t += 2) {
+    step(0, t);
+    if (t + 1 < kt_n) step(1, t + 1);
+  }
+  if (kt_n & 1) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = mfma32(fw[0][ks], fa[0][ks], acc);
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = mfma32(fw[1][ks], fa[1][ks], acc);
+  }
+  __syncthreads();                                       // the slots have been read: their room takes the results
+  f32x4 *xch = reinterpret_cast<f32x4 *>(lds);
+  finish_rows<4, 1, 1, EPI>([&]() { put_quadrant(acc, xch, wn, wm, lane); }, g, xch, 0, wave, m0, n0, lane, rs_tile);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -486,6 +602,16 @@ int launch_gemm_wave(const GemmArgs &g, hipStream_t s) {
     case EPI_BIAS: return launch_small<gemm_wave_kernel<EPI_BIAS>>(g, s, 64, 64, 256, kWaveLds);
     case EPI_BIAS_GELU: return launch_small<gemm_wave_kernel<EPI_BIAS_GELU>>(g, s, 64, 64, 256, kWaveLds);
     case EPI_BIAS_RES: return launch_small<gemm_wave_kernel<EPI_BIAS_RES>>(g, s, 64, 64, 256, kWaveLds);
+    default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
+  }
+}
+
+int launch_gemm_strip(const GemmArgs &g, hipStream_t s) {
+  constexpr size_t bytes = 4 * 16384 + 64 * 4;           // slots and row scales
+  switch (g.epilogue) {
+    case EPI_BIAS: return launch_small<gemm_strip_kernel<EPI_BIAS>>(g, s, 64, 64, 256, bytes);
+    case EPI_BIAS_GELU: return launch_small<gemm_strip_kernel<EPI_BIAS_GELU>>(g, s, 64, 64, 256, bytes);
+    case EPI_BIAS_RES: return launch_small<gemm_strip_kernel<EPI_BIAS_RES>>(g, s, 64, 64, 256, bytes);
     default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
   }
 }

@@ -1,0 +1,74 @@
+"""The list of launches that a GEMM is carried out by (csrc/gemm_choice.h, plain C++), checked on the CPU over the sizes:
+the parts tile the matrix, and rows that share a column are summed over k in one order."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_30010_amd", "csrc")
+IN_ORDER = {0, 1, 5, 6}          # one accumulator, k ascending; 2, 3 and 4 add up 4, 4 and 2 shares of k
+
+SHIM = """
+#include "gemm_choice.h"
+extern "C" int plan(int rows, int cols, int K, int rows_splittable, int one_tile, int *out) {
+  const et::GemmPlan p = et::plan_gemm(et::GemmRules{K, rows_splittable != 0, one_tile != 0}, rows, cols);
+  for (int i = 0; i < p.n; ++i) {
+    const et::GemmPart &t = p.part[i];
+    const int v[5] = {t.row0, t.rows, t.col0, t.cols, t.cfg};
+    for (int j = 0; j < 5; ++j) out[5 * i + j] = v[j];
+  }
+  return p.n;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("gemm_choice")
+    src, lib = str(d / "shim.cpp"), str(d / "shim.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
+    fn = C.CDLL(lib).plan
+    buf = (C.c_int * 80)()
+
+    def call(rows, cols, K, rows_splittable=True, one_tile=False):
+        n = fn(rows, cols, K, int(rows_splittable), int(one_tile), buf)
+        assert 1 <= n <= 16
+        return [tuple(buf[5 * i:5 * i + 5]) for i in range(n)]
+    return call
+
+
+def _sizes():
+    for tokens, mats in ((729, ((3456, 1152), (4352, 1152), (1152, 1152), (1152, 4352), (1152, 640))),
+                         (196, ((2304, 768), (3072, 768), (768, 768), (768, 3072))), (64, ((192, 64), (256, 64), (64, 256)))):
+        for frames in range(1, 65):
+            for keep in (1.0, 0.5, 0.3):
+                for cols, K in mats:
+                    yield frames * max(1, int(tokens * keep)), cols, K
+    rng = random.Random(4)
+    for _ in range(4000):
+        yield int(2 ** rng.uniform(0, 18)), 8 * int(2 ** rng.uniform(0, 13)), 64 * int(2 ** rng.uniform(0, 8))
+
+
+def test_parts_tile_the_matrix_and_keep_one_order_over_its_rows(plan):
+    split = 0
+    for rows, cols, K in _sizes():
+        for rows_splittable in (True, False):
+            parts = plan(rows, cols, K, rows_splittable)
+            assert sum(n * c for _, n, _, c, _ in parts) == rows * cols, (rows, cols, K, parts)
+            for i, (r0, n, c0, c, cfg) in enumerate(parts):
+                assert n > 0 and c > 0 and 0 <= r0 and r0 + n <= rows and 0 <= c0 and c0 + c <= cols
+                assert c0 % 64 == 0 and 0 <= cfg <= 6
+                for r1, n1, c1, m1, _ in parts[:i]:
+                    assert r1 + n1 <= r0 or r0 + n <= r1 or c1 + m1 <= c0 or c0 + c <= c1, (rows, cols, K, parts)
+                assert n == rows or (rows_splittable and cfg in IN_ORDER), (rows, cols, K, parts)
+                split += n < rows
+    assert split > 300           # (the sizes do reach launches over some of the rows)
+
+
+def test_one_tile_launches_are_not_split(plan):
+    for rows, cols, K in _sizes():
+        assert len(plan(rows, cols, K, one_tile=True)) == 1

@@ -313,3 +313,29 @@ def test_attention_split_and_ragged_forms(n_heads, hd, lens):
     for out in got:
         assert rel_l2(dev_to_f64(out), ref) < 6e-3
         assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05
+
+
+@pytest.mark.parametrize("M,N,K,epi", [
+    (729 * 7, 3456, 1152, 0), (729 * 14, 3456, 1152, 0), (729 * 16, 4352, 1152, 1), (729 * 24, 1152, 1152, 2),
+    (729 * 24, 1152, 4352, 2), (729 * 27, 4352, 1152, 1), (729 * 32, 3456, 1152, 0), (729 * 32, 4352, 1152, 1),
+    (729 * 64, 3456, 1152, 0),                                   # a strip of rows and one of columns
+    (729 * 14, 3456, 1216, 0),                                   # an odd number of k-tiles
+    (23040 + 1, 4352, 1152, 1), (23040 + 65, 4352, 1152, 1), (4608 + 63, 3456, 1152, 0),
+    (729 * 5, 1152, 4352, 2), (729, 3456, 1152, 0),              # one launch, its k split over wavefronts
+])
+def test_equal_rows_have_equal_bits_wherever_they_lie(M, N, K, epi):
+    """The library's choice may split the last tile rows off; every row is summed over k in one order all the same: a
+    pattern of 81 rows, repeated through the matrix, gives the same bits in every repeat."""
+    P = 81
+    rng = np.random.default_rng(N + K + epi)
+    a_bits, a = _bf(rng, (P, K))
+    w_bits, w = _bf(rng, (N, K), scale=0.05)
+    r_bits, r = _bf(rng, (P, N))
+    bias = (0.1 * rng.standard_normal(N)).astype(np.float32)
+    rows = torch.arange(M, device="cuda") % P
+    c = et.et_gemm_bf16(bits_to_dev(a_bits)[rows], bits_to_dev(w_bits), torch.from_numpy(bias).cuda(), epi,
+                        residual=bits_to_dev(r_bits)[rows] if epi == 2 else None)
+    assert torch.equal(c.view(torch.int16), c[:P].view(torch.int16)[rows])
+    ref = a @ w.T + bias.astype(np.float64)
+    ref = O.gelu_tanh(ref) if epi == 1 else ref + r if epi == 2 else ref
+    assert rel_l2(dev_to_f64(c[:P]), ref) < 4e-3

@@ -650,3 +650,20 @@ def test_plan_of_long_clips(T, mode, select):
     k = O.keep_count(L, np.float32(pol["ratio"])) if select == "uniform" else O.rescaled_count(pol["ratio"], T, L, len(plan))
     ks = k if select == "uniform" else -(-L // (L // k))
     assert r["cu_tokens"].tolist() == np.concatenate([[0], np.cumsum([k if d or select == "uniform" else ks for d in dyn])]).tolist()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [14, 24, 32])
+def test_siglip_still_clip_keeps_its_frames(T):
+    """Equal frames have equal hidden states after blocks of full size, hence equal similarities, and under the strict
+    comparison of Alg. 1 none of them fuses."""
+    from dataclasses import replace
+    from et_inputs import make_weights
+    shape = replace(SIGLIP, n_layers=3)
+    pol = _f32_policy(dict(merge_mode="alg1", select_mode="decoupled", alpha=0.9, tau_seg=0.8, tau_merge=0.8, ratio=0.5))
+    frames = np.repeat(make_clip(SIGLIP, [1], 5, base="uniform", sigma=0.02), T, axis=0)
+    enc = et.Encoder(shape, make_weights(shape, 5, bf16=True), T)
+    got = enc.encode_policy(torch.from_numpy(frames).cuda(), 2, pol)
+    enc.close()
+    assert got["n_frames_out"] == T
+    assert np.ptp(got["frame_sim"].cpu().numpy()) == 0.0
