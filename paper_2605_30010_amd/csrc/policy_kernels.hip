@@ -29,6 +29,10 @@ struct PlanLists {
   float *w;
 };
 
+// Eq. 1.  The contraction is written out: left to the compiler, which of the two products is rounded first depends on how
+// it unrolls a loop, and a similarity that sits on the threshold would fall on one side or the other with the clip's length.
+__device__ __forceinline__ float smoothed(float alpha, float now, float prev) { return fmaf(1.0f - alpha, prev, alpha * now); }
+
 __device__ __forceinline__ void build_plan(const float *sim, int T, const PolicyArgs &p, const PlanLists &o, int &n_seg_out, int &n_out) {
   int n_seg = 0, N = 0;
   o.seg[0] = 0;
@@ -36,7 +40,7 @@ __device__ __forceinline__ void build_plan(const float *sim, int T, const Policy
   bool fresh = true;
   for (int t = 1; t < T; ++t) {
     const float sv = sim[t - 1];
-    const float cur = fresh ? sv : p.alpha * sv + (1.0f - p.alpha) * prev;
+    const float cur = fresh ? sv : smoothed(p.alpha, sv, prev);
     if (!(cur >= p.tau_seg)) {
       o.seg[++n_seg] = t;
       fresh = true;
@@ -92,7 +96,7 @@ __device__ __forceinline__ void build_plan_64(const float *sim, int T, const Pol
   bool fresh = true;
   for (int t = 1; t < T; ++t) {
     const float sv = of_lane(t - 1);
-    const float cur = fresh ? sv : p.alpha * sv + (1.0f - p.alpha) * prev;
+    const float cur = fresh ? sv : smoothed(p.alpha, sv, prev);
     if (!(cur >= p.tau_seg)) {
       starts |= 1ull << t;
       fresh = true;

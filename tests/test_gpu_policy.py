@@ -667,3 +667,42 @@ def test_siglip_still_clip_keeps_its_frames(T):
     enc.close()
     assert got["n_frames_out"] == T
     assert np.ptp(got["frame_sim"].cpu().numpy()) == 0.0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [40, 64, 65, 100, 1024, 1100])
+@pytest.mark.parametrize("alpha", [0.3, 0.9])
+def test_smoothing_rounds_the_same_at_every_clip_length(T, alpha):
+    """Eq. 1 in float32 is fma(1 - alpha, previous, round(alpha * s_t)), whichever way the plan is built (one lane per
+    frame, on LDS copies, on global memory).  The threshold is put on smoothed values for which the other order of
+    rounding gives another number: the segment starts tell the two apart."""
+    L, D = 4, 8
+    rng = np.random.default_rng(T)
+    base, noise = rng.standard_normal((1, L, D)), rng.standard_normal((T, L, D))
+    bits = f64_to_bits(base + np.linspace(0.02, 1.2, T)[:, None, None] * noise)      # similarities that fall, with jitter
+    x = bits_to_dev(bits)
+    pol = dict(merge_mode="mean", select_mode="uniform", alpha=alpha, tau_seg=-2.0, tau_merge=0.5, ratio=1.0)
+    sim = et.et_merge_select_policy(x, pol)["frame_sim"].cpu().numpy()
+    a, wide = np.float32(alpha), np.longdouble
+    b = np.float32(1) - a
+
+    def smoothed(order):
+        out = [sim[0]]
+        for s in sim[1:]:
+            now, old = (a, s), (b, out[-1])
+            rounded, fused = (now, old) if order == 0 else (old, now)
+            out.append(np.float32(wide(fused[0]) * wide(fused[1]) + wide(np.float32(rounded[0] * rounded[1]))))
+        return np.array(out)
+
+    mine, other = smoothed(0), smoothed(1)
+    tried = 0
+    for t in range(1, T - 1):
+        tau = max(mine[t], other[t])
+        if mine[t] == other[t] or np.min(mine[:t]) < tau or np.min(other[:t]) < tau:
+            continue                                   # (a segment that starts earlier would restart the smoothing)
+        starts = et.et_merge_select_policy(x, dict(pol, tau_seg=float(tau)))["seg_start"].tolist()
+        assert ((t + 1) in starts) == bool(mine[t] < tau), t
+        tried += 1
+        if tried == 12:
+            break
+    assert tried >= 1
