@@ -561,16 +561,9 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
   constexpr size_t lds_bytes = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t) +
                                (size_t)WAVES_M * WAVES_N * 32 * 64 * sizeof(uint16_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget");
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0;
-    ET_HIP(hipGetDevice(&dev));
-    ET_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    if (n_cu <= 0) n_cu = 256;
-  }
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.n_store + BN - 1) / BN;
   const int n_tiles = tiles_m * tiles_n;
-  const int slots = n_cu * MINB;
+  const int slots = device_cus() * MINB;
   const dim3 grid(n_tiles < slots ? n_tiles : slots), block(NT);
   if (g.stats_in && n_tiles > slots) {
     set_error("gemm: row statistics by pieces need one tile per workgroup (%d tiles, %d slots)", n_tiles, slots);
@@ -1172,6 +1165,20 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
 
 }  // namespace
 
+int device_cus() {
+  static std::atomic<int> known[64];       // by device; 0: not asked yet
+  int dev = 0, n = 0;
+  const bool have_dev = hipGetDevice(&dev) == hipSuccess;
+  std::atomic<int> &slot = known[dev & 63];
+  if (have_dev && (n = slot.load(std::memory_order_relaxed)) > 0) return n;
+  if (!have_dev || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  slot.store(n, std::memory_order_relaxed);
+  return n;
+}
+
 int launch_layernorm(const uint16_t *x, const float *g, const float *b, float eps, int rows, int D,
                      uint16_t *y, hipStream_t s) {
   if (rows <= 0) return ET_OK;
@@ -1234,7 +1241,7 @@ static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
 
 // Whether a GEMM over `rows` rows is best done in one round of tiles, i.e. takes the statistics of its rows by
 // pieces (launch_gemm accepts them for any size; beyond one round the row scales' own launch is cheaper).
-bool gemm_takes_pieces(int rows, int cols) { return one_round(kCfgBig, rows, cols); }
+bool gemm_takes_pieces(int rows, int cols) { return one_round(kCfgBig, rows, cols, device_cus()); }
 
 int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
   if (g.M <= 0) return ET_OK;
@@ -1247,7 +1254,7 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     return ET_ERR_INVALID_ARG;
   }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
-  const GemmPlan plan = plan_gemm(GemmRules{g.K, g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr}, g.M, g.n_store);
+  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr}, g.M, g.n_store);
   for (int i = 0; i < plan.n; ++i) {
     const GemmPart &t = plan.part[i];
     GemmArgs part = g;
@@ -1268,15 +1275,6 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
 
 bool head_dim_supported(int hd) {
   return hd == 16 || hd == 32 || hd == 64 || hd == 72 || hd == 80 || hd == 96 || hd == 128;
-}
-
-static int attention_cus() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
-    (void)hipGetLastError();
-    return 256;
-  }
-  return n;
 }
 
 template <int HD, int KG>
@@ -1302,7 +1300,7 @@ template <int HD>
 static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_frames, int len, int n_heads, uint16_t *out,
                                hipStream_t s) {
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
-  const long long pairs = (long long)n_heads * n_frames, cus = attention_cus();
+  const long long pairs = (long long)n_heads * n_frames, cus = device_cus();
   const int n = cu ? 0 : len;
   auto blocks = [&](int rows) { return (len + rows - 1) / rows; };
   // Key tiles split over groups of wavefronts while that still makes one workgroup per compute unit at most, and

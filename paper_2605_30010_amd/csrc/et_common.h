@@ -253,6 +253,7 @@ int launch_rowstats(const uint16_t *x, float eps, int rows, int D, float *rstd, 
 int launch_piece_stats(const uint16_t *x, int rows, int D, int ld, float2 *stats, hipStream_t s);
 int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg = -1);
 bool gemm_takes_pieces(int rows, int cols);
+int device_cus();          // compute units of the current device
 int gemm_config_count();
 int launch_attention(const uint16_t *qkv, const int32_t *cu, int n_frames, int max_len, int n_heads,
                      int head_dim, uint16_t *out, hipStream_t s);

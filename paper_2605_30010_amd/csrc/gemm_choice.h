@@ -60,10 +60,12 @@ inline double gemm_cost(int cfg, long rows, long cols, int K) {
   }
 }
 
-// Whether the persistent kernel walks one tile per workgroup (the others always do).
-inline bool one_round(int cfg, long rows, long cols) {
-  if (cfg == kCfgBig) return gemm_tiles(cfg, rows, cols) <= 256;
-  if (cfg == kCfg128) return gemm_tiles(cfg, rows, cols) <= 512;
+// Whether the persistent kernel walks one tile per workgroup on `cus` compute units (the others always do).  What it
+// refuses otherwise depends on this, so the device's own count is asked for; the costs above only rank the tilings
+// and keep the 256 units that they were measured on.
+inline bool one_round(int cfg, long rows, long cols, int cus) {
+  if (cfg == kCfgBig) return gemm_tiles(cfg, rows, cols) <= cus;
+  if (cfg == kCfg128) return gemm_tiles(cfg, rows, cols) <= 2L * cus;
   return true;
 }
 
@@ -81,7 +83,7 @@ struct GemmPlan {
 
 // What plan_gemm may do: split rows off into launches of their own; only tilings that walk one tile per workgroup.
 struct GemmRules {
-  int K;
+  int K, cus;
   bool rows_splittable, one_tile;
 };
 
@@ -89,7 +91,7 @@ inline int cheapest_tiling(const GemmRules &r, long rows, long cols, bool ordere
   int best = ordered ? kCfgStrip : kCfgWave;
   *cost = gemm_cost(best, rows, cols, r.K);
   for (int cfg = 0; cfg < kCfgStrip; ++cfg) {
-    if ((ordered && !in_k_order(cfg)) || (r.one_tile && !one_round(cfg, rows, cols))) continue;
+    if ((ordered && !in_k_order(cfg)) || (r.one_tile && !one_round(cfg, rows, cols, r.cus))) continue;
     const double c = gemm_cost(cfg, rows, cols, r.K);
     if (c < *cost) { *cost = c; best = cfg; }
   }

@@ -326,15 +326,12 @@ int launch_attention_scores(const uint16_t *qkv, int n_frames, int L, int n_head
   // (2 above head_dim 96), and the one-dimensional grid stays far below its limit.
   if (L <= 32 * kPassWaves * (ksteps <= 6 ? 3 : 2) && n_frames <= 65535 && n_heads <= 65535 && (long)n_frames * n_heads <= (1L << 20)) {
     const int nb = (L + 32 * kPassWaves - 1) / (32 * kPassWaves), n_qb = (L + 31) / 32;
-    int n_cu = 0, dev = 0;
-    ET_HIP(hipGetDevice(&dev));
-    ET_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     // Shares per (frame, head): the fewest query blocks on the busiest compute unit, a workgroup's own start
     // (K fragments from memory, reduction of the column sums) counted as two.
     int splits = 1;
     long best = -1;
     for (int sp = 1; sp <= kMaxSplits && sp <= n_qb; ++sp) {
-      const long slots = (long)(n_cu > 0 ? n_cu : 256), wgs = (long)n_frames * n_heads * sp;
+      const long slots = device_cus(), wgs = (long)n_frames * n_heads * sp;
       const long cost = ((wgs + slots - 1) / slots) * ((n_qb + sp - 1) / sp + 2);
       if (best < 0 || cost < best) { best = cost; splits = sp; }
     }

@@ -12,8 +12,8 @@ IN_ORDER = {0, 1, 5, 6}          # one accumulator, k ascending; 2, 3 and 4 add 
 
 SHIM = """
 #include "gemm_choice.h"
-extern "C" int plan(int rows, int cols, int K, int rows_splittable, int one_tile, int *out) {
-  const et::GemmPlan p = et::plan_gemm(et::GemmRules{K, rows_splittable != 0, one_tile != 0}, rows, cols);
+extern "C" int plan(int rows, int cols, int K, int cus, int rows_splittable, int one_tile, int *out) {
+  const et::GemmPlan p = et::plan_gemm(et::GemmRules{K, cus, rows_splittable != 0, one_tile != 0}, rows, cols);
   for (int i = 0; i < p.n; ++i) {
     const et::GemmPart &t = p.part[i];
     const int v[5] = {t.row0, t.rows, t.col0, t.cols, t.cfg};
@@ -34,8 +34,8 @@ def plan(tmp_path_factory):
     fn = C.CDLL(lib).plan
     buf = (C.c_int * 80)()
 
-    def call(rows, cols, K, rows_splittable=True, one_tile=False):
-        n = fn(rows, cols, K, int(rows_splittable), int(one_tile), buf)
+    def call(rows, cols, K, rows_splittable=True, one_tile=False, cus=256):
+        n = fn(rows, cols, K, cus, int(rows_splittable), int(one_tile), buf)
         assert 1 <= n <= 16
         return [tuple(buf[5 * i:5 * i + 5]) for i in range(n)]
     return call
@@ -69,6 +69,11 @@ def test_parts_tile_the_matrix_and_keep_one_order_over_its_rows(plan):
     assert split > 300           # (the sizes do reach launches over some of the rows)
 
 
-def test_one_tile_launches_are_not_split(plan):
+@pytest.mark.parametrize("cus", [32, 64, 128, 256])
+def test_launches_with_row_statistics_walk_one_tile_per_workgroup(plan, cus):
+    """The persistent kernel takes row statistics only where each workgroup has one tile (one 256 x 256 or two 128 x 128
+    per compute unit); it refuses the call otherwise, so on no device, whole or partitioned, may it be chosen there."""
     for rows, cols, K in _sizes():
-        assert len(plan(rows, cols, K, one_tile=True)) == 1
+        (_, _, _, _, cfg), = plan(rows, cols, K, one_tile=True, cus=cus)
+        assert cfg != 0 or -(-rows // 256) * -(-cols // 256) <= cus, (rows, cols, K)
+        assert cfg != 1 or -(-rows // 128) * -(-cols // 128) <= 2 * cus, (rows, cols, K)
