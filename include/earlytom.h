@@ -288,11 +288,11 @@ int et_attention(const uint16_t *qkv_dev, const int32_t *cu_tokens_dev, int32_t 
 int et_attention_uniform(const uint16_t *qkv_dev, int32_t n_frames, int32_t len, int32_t n_heads,
                          int32_t head_dim, uint16_t *out_dev, void *hip_stream);
 
-/* The first two launches of encoder block `layer` on caller-supplied hidden states x_dev (bf16
- * [rows, D]), exactly as et_encode_clip issues them: the row scales 1 / sqrt(var + eps) of
- * LayerNorm 1 into rstd_dev (float32 [rows]) and the fused projection with the LayerNorm folded in
- * into qkv_dev (bf16 [rows, 3D], q | k | v).  Lets a test rank attention-received scores on the very
- * q and k the encoder used.  Errors: INVALID_ARG, HIP. */
+/* The start of encoder block `layer` on caller-supplied hidden states x_dev (bf16 [rows, D]), with the
+ * bits that et_encode_clip gets: the row scales 1 / sqrt(var + eps) of LayerNorm 1 into rstd_dev
+ * (float32 [rows]) and the fused projection with the LayerNorm folded in into qkv_dev (bf16
+ * [rows, 3D], q | k | v).  Lets a test rank attention-received scores on the very q and k the
+ * encoder used.  Errors: INVALID_ARG, HIP. */
 int et_encoder_block_qkv(et_encoder *enc, int32_t layer, const uint16_t *x_dev, int32_t rows,
                          float *rstd_dev, uint16_t *qkv_dev, void *hip_stream);
 

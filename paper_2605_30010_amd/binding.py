@@ -465,7 +465,7 @@ def et_encode_clip(handle, frames, merge_layer, sim_threshold, keep_ratio, L, D,
 
 def et_encoder_block_qkv(handle, layer, x, stream=None):
     """Row scales and fused q | k | v projection of encoder block `layer` on x (bf16 CUDA [rows, D]),
-    as the encode calls launch them.  Returns (qkv bf16 [rows, 3D], rstd float32 [rows])."""
+    with the bits that the encode calls get.  Returns (qkv bf16 [rows, 3D], rstd float32 [rows])."""
     lib = load_library()
     _dev(x, torch.bfloat16, "x")
     rows, D = x.shape

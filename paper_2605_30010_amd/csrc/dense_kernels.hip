@@ -113,6 +113,29 @@ __global__ __launch_bounds__(kLnRows * kWave) void piece_stats_kernel(const uint
   }
 }
 
+// The row scales that RowScale combines from those pieces, in the same order.
+template <int NV>
+__global__ __launch_bounds__(kLnRows * kWave) void piece_scale_kernel(const uint16_t *__restrict__ x, float eps, int rows, int D,
+                                                                      float *__restrict__ rstd_out) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * kLnRows + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  uint4 raw[NV];
+  load_row<NV>(x + (size_t)row * D, D, lane, raw);
+  PieceSum sum(0.f);
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const float2 st = piece_moments(u32x4{raw[j].x, raw[j].y, raw[j].z, raw[j].w});
+    if (j == 0) sum.ref = __shfl(st.x, 0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float2 p = make_float2(__shfl(st.x, u * 8), __shfl(st.y, u * 8));
+      if (j * 8 + u < D / 64) sum.add(p);
+    }
+  }
+  if (lane == 0) rstd_out[row] = sum.scale(D / 64, eps);
+}
+
 // ---------------------------------------------------------------------------------------
 // Patch extraction: frames fp32 [T, C, H, W] -> bf16 [T * L, Kpad]; row (t, gy, gx), column
 // (c, py, px) flattened; columns >= C*P*P are zero.  One thread writes 8 columns (16 bytes).
@@ -1204,6 +1227,14 @@ int launch_piece_stats(const uint16_t *x, int rows, int D, int ld, float2 *stats
   return ET_OK;
 }
 
+int launch_piece_scale(const uint16_t *x, float eps, int rows, int D, float *rstd, hipStream_t s) {
+  if (rows <= 0) return ET_OK;
+  dim3 grid((rows + kLnRows - 1) / kLnRows), block(kLnRows * kWave);
+  ET_DISPATCH_NV(D, hipLaunchKernelGGL(piece_scale_kernel<NV>, grid, block, 0, s, x, eps, rows, D, rstd));
+  ET_LAUNCH_CHECK();
+  return ET_OK;
+}
+
 int launch_im2col(const float *frames, int T, int C, int H, int W, int P, int Kpad, uint16_t *out,
                   hipStream_t s) {
   const int GX = W / P, GY = H / P, L = GX * GY;
@@ -1254,7 +1285,7 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     return ET_ERR_INVALID_ARG;
   }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
-  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr}, g.M, g.n_store);
+  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr || g.one_tile}, g.M, g.n_store);
   for (int i = 0; i < plan.n; ++i) {
     const GemmPart &t = plan.part[i];
     GemmArgs part = g;

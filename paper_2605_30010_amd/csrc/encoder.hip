@@ -557,8 +557,14 @@ int et_encoder_block_qkv(et_encoder *e, int32_t layer, const uint16_t *x_dev, in
   const int D = e->D;
   const LayerDev &lw = e->layers[layer];
   int rc;
-  if ((rc = launch_rowstats(x_dev, e->cfg.ln_eps, rows, D, rstd_dev, s))) return rc;
-  const GemmArgs g{x_dev, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, qkv_dev, 3 * D, rows, 3 * D, D, EPI_BIAS, rstd_dev};
+  // run_block's two ways to the row scales; where it takes them from the pieces of a row, they are combined here by a kernel
+  // of its own, with the same arithmetic, and the projection runs in the tiling that takes pieces
+  const bool by_pieces = takes_pieces(e, rows);
+  if (by_pieces) rc = launch_piece_scale(x_dev, e->cfg.ln_eps, rows, D, rstd_dev, s);
+  else rc = launch_rowstats(x_dev, e->cfg.ln_eps, rows, D, rstd_dev, s);
+  if (rc) return rc;
+  GemmArgs g{x_dev, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, qkv_dev, 3 * D, rows, 3 * D, D, EPI_BIAS, rstd_dev};
+  g.one_tile = by_pieces;
   return launch_gemm(g, s);
 }
 

@@ -86,10 +86,25 @@ __device__ __forceinline__ float2 piece_moments(u32x4 v) {
   return make_float2(mean, sum_of_8_lanes(q));
 }
 
+// Combines the pieces of one row, in ascending order.  The pieces' means are taken relative to the first one's: nothing
+// cancels when the row's mean is many standard deviations.
+struct PieceSum {
+  float ref, s1 = 0.f, s2 = 0.f;
+  __device__ __forceinline__ explicit PieceSum(float first_mean) : ref(first_mean) {}
+  __device__ __forceinline__ void add(float2 p) {
+    const float d = p.x - ref;
+    s1 += d;
+    s2 = fmaf(64.f * d, d, s2 + p.y);
+  }
+  __device__ __forceinline__ float scale(int pieces, float eps) const {       // 1 / sqrt(var + eps)
+    const float n = (float)pieces, m2 = fmaf(-64.f * s1, s1 / n, s2);
+    return 1.0f / sqrtf((m2 < 0.f ? 0.f : m2) / (64.f * n) + eps);             // (NaN stays NaN)
+  }
+};
+
 // Row scale of one row per lane: 1 / sqrt(var + eps) from the statistics of the row's pieces, or g.row_scale, or 1
 // (fma(1, acc, bias) == acc + bias exactly).  fetch() issues the loads, value() combines them, so that a kernel
-// can put its first operand loads between.  The pieces' means are taken relative to the first one's: nothing
-// cancels when the row's mean is many standard deviations.
+// can put its first operand loads between.
 template <int BATCH>                                    // pieces in flight
 struct RowScale {
   float2 v[BATCH];
@@ -111,25 +126,18 @@ struct RowScale {
   __device__ __forceinline__ float value(const GemmArgs &g) {
     if (!g.stats_in) return v[0].x;
     const int pieces = g.K / 64;
-    const float ref = v[0].x, n = (float)pieces;
-    float s1 = 0.f, s2 = 0.f;
-    auto add = [&](float2 p) {
-      const float d = p.x - ref;
-      s1 += d;
-      s2 = fmaf(64.f * d, d, s2 + p.y);
-    };
+    PieceSum sum(v[0].x);
     for (int c = 0;;) {
 #pragma unroll
       for (int u = 0; u < BATCH; ++u)
-        if (c + u < pieces) add(v[u]);
+        if (c + u < pieces) sum.add(v[u]);
       c += BATCH;
       if (c >= pieces) break;
 #pragma unroll
       for (int u = 0; u < BATCH; ++u)
         if (c + u < pieces) v[u] = piece(g, c + u);
     }
-    const float m2 = s2 - 64.f * s1 * (s1 / n);
-    return 1.0f / sqrtf((m2 < 0.f ? 0.f : m2) / (64.f * n) + g.ln_eps);   // (NaN stays NaN)
+    return sum.scale(pieces, g.ln_eps);
   }
 };
 

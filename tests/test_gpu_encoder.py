@@ -340,3 +340,31 @@ def test_row_statistics_taken_along_by_the_gemms(d, heads, mlp, side, T):
     ref = O.encode_clip(shape, w, frames, -1, 0.9, 1.0)["tokens"]
     err = np.linalg.norm(dev_to_f64(got) - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= 3e-2, err.max()
+
+
+@pytest.mark.parametrize("d,heads,mlp,side,T", [(64, 4, 72, 28, 3), (576, 8, 320, 112, 8), (1152, 16, 4304, 182, 7), (1152, 16, 64, 182, 20),
+                                                (192, 2, 256, 224, 24), (64, 4, 64, 448, 90)])
+def test_block_qkv_has_the_bits_of_the_encoder(d, heads, mlp, side, T):
+    """et_encoder_block_qkv on the hidden states in front of a block gives the projection that the encoder itself used: read
+    from the encoder's workspace (the residual stream, then q | k | v; each piece 256-byte aligned) after a call of one
+    block.  The hidden states come from an encoder whose block adds nothing.  Rows by pieces in several tilings,
+    and (the last) rows whose scales have a launch of their own."""
+    from et_inputs import EncoderShape
+    shape = EncoderShape(n_layers=1, d_model=d, n_heads=heads, d_mlp=mlp, patch=14, image_h=side, image_w=side, has_final_ln=0)
+    w = make_weights(shape, seed=d + T, bf16=True)
+    frames = np.random.default_rng(T).standard_normal((T, 3, side, side)).astype(np.float32)
+    nothing = dict(w, layers=[dict(w["layers"][0], **{k: 0 * w["layers"][0][k] for k in ("wo", "bo", "w2", "b2")})])
+    plain = et.Encoder(shape, nothing, T)
+    x = _encode(plain, frames, -1, 0.9, 1.0)["tokens"]
+    plain.close()
+    enc = et.Encoder(shape, w, T)
+    _encode(enc, frames, -1, 0.9, 1.0)
+    torch.cuda.synchronize()
+    rows = x.shape[0]
+    start = (rows * d * 2 + 255) // 256 * 256
+    inside = enc._ws[start:start + rows * 3 * d * 2].view(torch.int16).reshape(rows, 3 * d)
+    qkv, rstd = et.et_encoder_block_qkv(enc.handle, 0, x)
+    assert torch.equal(qkv.view(torch.int16), inside)
+    enc.close()
+    want = 1.0 / np.sqrt(dev_to_f64(x).var(axis=1) + shape.ln_eps)
+    assert np.max(np.abs(rstd.cpu().numpy() / want - 1.0)) < 1e-5
