@@ -122,11 +122,11 @@ __global__ __launch_bounds__(kLnRows * kWave) void piece_scale_kernel(const uint
   if (row >= rows) return;
   uint4 raw[NV];
   load_row<NV>(x + (size_t)row * D, D, lane, raw);
-  PieceSum sum(0.f);
+  PieceSum sum;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const float2 st = piece_moments(u32x4{raw[j].x, raw[j].y, raw[j].z, raw[j].w});
-    if (j == 0) sum.ref = __shfl(st.x, 0);
+    if (j == 0) sum.start(__shfl(st.x, 0));
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const float2 p = make_float2(__shfl(st.x, u * 8), __shfl(st.y, u * 8));

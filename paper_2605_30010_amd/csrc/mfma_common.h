@@ -87,17 +87,18 @@ __device__ __forceinline__ float2 piece_moments(u32x4 v) {
 }
 
 // Combines the pieces of one row, in ascending order.  The pieces' means are taken relative to the first one's: nothing
-// cancels when the row's mean is many standard deviations.
+// cancels when the row's mean is many standard deviations.  Where a square or a piece's sum leaves float32 (values beyond
+// 1e18) the variance is infinite and the scale 0, as in rowstats_kernel; a NaN or an infinity in the row gives NaN.
 struct PieceSum {
-  float ref, s1 = 0.f, s2 = 0.f;
-  __device__ __forceinline__ explicit PieceSum(float first_mean) : ref(first_mean) {}
+  float ref = 0.f, s1 = 0.f, s2 = 0.f;
+  __device__ __forceinline__ void start(float first_mean) { ref = fabsf(first_mean) < INFINITY ? first_mean : 0.f; }
   __device__ __forceinline__ void add(float2 p) {
     const float d = p.x - ref;
     s1 += d;
     s2 = fmaf(64.f * d, d, s2 + p.y);
   }
   __device__ __forceinline__ float scale(int pieces, float eps) const {       // 1 / sqrt(var + eps)
-    const float n = (float)pieces, m2 = fmaf(-64.f * s1, s1 / n, s2);
+    const float n = (float)pieces, m2 = s2 == INFINITY ? s2 : fmaf(-64.f * s1, s1 / n, s2);
     return 1.0f / sqrtf((m2 < 0.f ? 0.f : m2) / (64.f * n) + eps);             // (NaN stays NaN)
   }
 };
@@ -126,7 +127,8 @@ struct RowScale {
   __device__ __forceinline__ float value(const GemmArgs &g) {
     if (!g.stats_in) return v[0].x;
     const int pieces = g.K / 64;
-    PieceSum sum(v[0].x);
+    PieceSum sum;
+    sum.start(v[0].x);
     for (int c = 0;;) {
 #pragma unroll
       for (int u = 0; u < BATCH; ++u)

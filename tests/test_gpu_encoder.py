@@ -368,3 +368,19 @@ def test_block_qkv_has_the_bits_of_the_encoder(d, heads, mlp, side, T):
     enc.close()
     want = 1.0 / np.sqrt(dev_to_f64(x).var(axis=1) + shape.ln_eps)
     assert np.max(np.abs(rstd.cpu().numpy() / want - 1.0)) < 1e-5
+
+
+@pytest.mark.parametrize("size", [1e20, 3e36, 1e37])
+def test_row_whose_variance_leaves_float32(size):
+    """A token whose two halves are -size and +size: the squares overflow, the variance is infinite, the LayerNorm leaves
+    its shift only.  The other tokens of the frame stay finite; the token's own output is the final LayerNorm's shift."""
+    from et_inputs import EncoderShape
+    shape = EncoderShape(n_layers=2, d_model=128, n_heads=4, d_mlp=200, patch=14, image_h=56, image_w=56)
+    w = make_weights(shape, seed=11, bf16=True)
+    w["pos_emb"] = w["pos_emb"].copy()
+    w["pos_emb"][3] = np.where(np.arange(128) < 64, -size, size)
+    enc = et.Encoder(shape, w, 1)
+    got = dev_to_f64(_encode(enc, np.random.default_rng(3).standard_normal((1, 3, 56, 56)).astype(np.float32), -1, 0.9, 1.0)["tokens"])
+    enc.close()
+    assert np.all(np.isfinite(got))
+    assert np.array_equal(got[3], w["final_ln_b"].astype(np.float64))
