@@ -692,6 +692,9 @@ struct AttentionRows {
   u32x4 qf[QB][NC];
   f32x16 o_acc[QB][NDB];
   float m_ref[QB], l_run[QB];
+  // Lanes whose query has met no logit above minus infinity yet (wave-uniform mask; all of them before the first keys).
+  // Their reference stays 0 and their accumulators 0; the first such logit sets the reference without a rescaling.
+  unsigned long long fresh[QB];
 
   // Q is scaled by log2(e) / sqrt(head_dim) once, here, and rounded back to bf16: the logits leave
   // the MFMA already in the exponent's units.  A wavefront owns QB blocks of 32 queries: every K and
@@ -714,6 +717,7 @@ struct AttentionRows {
 #pragma unroll
         for (int i = 0; i < 16; ++i) o_acc[j][b][i] = 0.f;
       m_ref[j] = l_run[j] = 0.f;
+      fresh[j] = ~0ull;
     }
   }
 
@@ -729,9 +733,30 @@ struct AttentionRows {
     return v;
   }
 
-  // The 32 keys kv0 + 32 kb .. of the 64-key tile at kv0, whose K and V rows lie at ks and vs.  `first`: nothing
-  // has been accumulated yet (the block then holds a valid key).
-  __device__ __forceinline__ void block(const uint16_t *ks, const uint16_t *vs, int kb, int kv0, int n, bool first, int lane) {
+  // Moves the reference of block j to the maximum mx of the new logits s (relative to the old one).
+  template <class Logits>
+  __device__ __forceinline__ void move_reference(int j, float mx, int lane, Logits subtract) {
+    const bool mine = (fresh[j] >> lane) & 1ull, none = mine && mx == -INFINITY;
+    // (keys past the frame can make a block of minus infinities: it moves nothing)
+    float target = m_ref[j] + (none ? 0.f : mine ? mx : fmaxf(mx, 0.f));
+    if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
+    const float delta = target - m_ref[j];
+    if (fresh[j] != ~0ull) {               // (something accumulated: delta >= 0 in those lanes)
+      const float alpha = mine ? 1.0f : __builtin_amdgcn_exp2f(-delta);
+      l_run[j] *= alpha;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o_acc[j][b][i] *= alpha;
+    }
+    subtract(delta);
+    m_ref[j] = target;
+    if (REF_IN_PAD && (lane >> 5)) qf[j][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
+    fresh[j] = __ballot(none);
+  }
+
+  // The 32 keys kv0 + 32 kb .. of the 64-key tile at kv0, whose K and V rows lie at ks and vs.
+  __device__ __forceinline__ void block(const uint16_t *ks, const uint16_t *vs, int kb, int kv0, int n, int lane) {
     const int r32 = lane & 31, grp = lane >> 5;
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // S^T = K Q^T.  K fragments are double-buffered: the LDS read of contraction chunk c+1 is
@@ -780,28 +805,19 @@ struct AttentionRows {
       mx[j] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));   // relative to m_ref
     }
     bool over = false;
+    unsigned long long any_fresh = 0ull;
 #pragma unroll
-    for (int j = 0; j < QB; ++j) over = over || mx[j] > kLazy;
-    if (first || __any(over)) {              // wave-uniform: move the references
+    for (int j = 0; j < QB; ++j) {
+      over = over || mx[j] > kLazy;
+      any_fresh |= fresh[j];
+    }
+    if (any_fresh || __any(over)) {          // wave-uniform: move the references
 #pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        // a block of the last tile may hold no valid key at all (mx = -inf): it moves nothing
-        float target = m_ref[j] + (first ? mx[j] : fmaxf(mx[j], 0.f));
-        if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
-        const float delta = target - m_ref[j];
-        if (!first) {                        // (nothing accumulated yet in the first block; later delta >= 0)
-          const float alpha = __builtin_amdgcn_exp2f(-delta);
-          l_run[j] *= alpha;
+      for (int j = 0; j < QB; ++j)
+        move_reference(j, mx[j], lane, [&](float delta) {
 #pragma unroll
-          for (int b = 0; b < NDB; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) o_acc[j][b][i] *= alpha;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s_acc[j][i] -= delta;
-        m_ref[j] = target;
-        if (REF_IN_PAD && grp) qf[j][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
-      }
+          for (int i = 0; i < 16; ++i) s_acc[j][i] -= delta;
+        });
     }
     u32x4 pf[QB][2];
 #pragma unroll
@@ -841,10 +857,10 @@ struct AttentionRows {
   // the softmax chain follow one another.  Both 32-key blocks are then taken together: all K fragments are read up
   // front, the two MFMA chains fill each other's gaps, one maximum and one reference check serve 64 keys (heads of 72,
   // 8 x 729: 35.8 -> 34.0 us per launch, 5 x 729: 26.4 -> 25.0).
-  __device__ __forceinline__ void tile(const uint16_t *ks, const uint16_t *vs, int kv0, int n, bool first, int lane) {
+  __device__ __forceinline__ void tile(const uint16_t *ks, const uint16_t *vs, int kv0, int n, int lane) {
     if constexpr (QB > 1) {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) block(ks, vs, kb, kv0, n, first && kb == 0, lane);
+      for (int kb = 0; kb < 2; ++kb) block(ks, vs, kb, kv0, n, lane);
     } else {
       const int r32 = lane & 31, grp = lane >> 5;
       const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -887,25 +903,13 @@ struct AttentionRows {
       const uint32_t mb = __float_as_uint(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
       const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
       const float mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));      // relative to m_ref
-      if (first || __any(mx > kLazy)) {      // wave-uniform: move the reference
-        float target = m_ref[0] + (first ? mx : fmaxf(mx, 0.f));
-        if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
-        const float delta = target - m_ref[0];
-        if (!first) {                        // (nothing accumulated yet in the first tile; later delta >= 0)
-          const float alpha = __builtin_amdgcn_exp2f(-delta);
-          l_run[0] *= alpha;
+      if (fresh[0] || __any(mx > kLazy))     // wave-uniform: move the reference
+        move_reference(0, mx, lane, [&](float delta) {
 #pragma unroll
-          for (int b = 0; b < NDB; ++b)
+          for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o_acc[0][b][i] *= alpha;
-        }
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
-        m_ref[0] = target;
-        if (REF_IN_PAD && grp) qf[0][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
-      }
+            for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
+        });
       // P V by 16-key chunks: the exponentials of chunk c + 1 run beside the MFMAs of chunk c
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -1034,7 +1038,7 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     asm volatile("" ::: "memory");
     if (t + 1 < n_tiles) issue(stage ^ 1);
     const uint16_t *ks = lds + stage * STAGE;
-    rows.tile(ks, ks + K_ELEMS, kv0, n, t == 0, lane);
+    rows.tile(ks, ks + K_ELEMS, kv0, n, lane);
   }
 
 #pragma unroll
@@ -1142,12 +1146,12 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
     if (t + KG < n_tiles) issue(t + KG, stage ^ 1);
     if (t < n_tiles) {
       const uint16_t *ks = mem + stage * 2 * S::TILE;
-      rows.tile(ks, ks + S::TILE, t * kAttBKV, n, t0 == 0, lane);
+      rows.tile(ks, ks + S::TILE, t * kAttBKV, n, lane);
     }
   }
-  const bool any = grp_k < n_tiles;
   const float l = rows.denominator(0, r32);
-  if (grp == 0) ml[wave][r32] = any ? make_float2(rows.m_ref[0], l) : make_float2(-INFINITY, 0.f);
+  // (a group without a tile, or with nothing but minus infinities, has no part in the sum)
+  if (grp == 0) ml[wave][r32] = ((rows.fresh[0] >> lane) & 1ull) ? make_float2(-INFINITY, 0.f) : make_float2(rows.m_ref[0], l);
   __syncthreads();                                     // the stages have been read
   float *part = reinterpret_cast<float *>(lds);
 #pragma unroll

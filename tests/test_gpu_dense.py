@@ -339,3 +339,33 @@ def test_equal_rows_have_equal_bits_wherever_they_lie(M, N, K, epi):
     ref = a @ w.T + bias.astype(np.float64)
     ref = O.gelu_tanh(ref) if epi == 1 else ref + r if epi == 2 else ref
     assert rel_l2(dev_to_f64(c[:P]), ref) < 4e-3
+
+
+@pytest.mark.parametrize("n_heads,hd,lens,dead", [
+    (16, 72, [729], (64, 128)), (4, 64, [300], (64, 128)), (2, 16, [300], (128, 192)),       # first tile of one of four groups
+    (16, 72, [729], (64, 200)), (2, 32, [130], (0, 64)),                                     # ... and more of its tiles; of the first group
+    (16, 72, [729, 700], (64, 128)), (2, 96, [330], (64, 128)), (2, 80, [400, 321], (0, 130)),       # two groups
+    (16, 72, [729] * 5, (0, 64)), (16, 64, [130] * 30, (0, 100)), (2, 128, [70], (0, 32)),           # one block of 32 queries per wavefront
+    (16, 72, [150] * 96, (0, 96)), (16, 16, [70] * 96, (0, 32)), (16, 80, [129] * 96, (0, 64)),      # two blocks
+])
+@pytest.mark.parametrize("shift", [0.0, -16.0])
+def test_attention_with_logits_of_minus_infinity(n_heads, hd, lens, dead, shift):
+    """Keys whose logits are minus infinity for every query have probability 0, wherever they lie: the first 32 keys, the
+    whole first key tile of a frame or of a group of wavefronts.  With `shift` all other logits are below -150, where a
+    reference maximum that had stayed at 0 would leave no probability.  Bounds as in the oracle test."""
+    rng = np.random.default_rng(n_heads * hd + len(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, D = int(cu[-1]), n_heads * hd
+    qkv = rng.standard_normal((rows, 3 * D))
+    qkv[:, :D] = np.abs(qkv[:, :D]) + 0.5
+    qkv[:, D:2 * D] += shift
+    for f in range(len(lens)):
+        qkv[cu[f] + dead[0]:min(cu[f] + dead[1], cu[f + 1]), D:2 * D] = -3.0e38
+    bits = f32_to_bf16_bits(qkv.astype(np.float32))
+    ref = _attention_ref(bf16_bits_to_f32(bits).astype(np.float64), cu, n_heads, hd)
+    got = [et.et_attention(bits_to_dev(bits), torch.from_numpy(cu).cuda(), max(lens), n_heads, hd)]
+    if len(set(lens)) == 1:
+        got.append(et.et_attention_uniform(bits_to_dev(bits), len(lens), lens[0], n_heads, hd))
+    for out in got:
+        assert rel_l2(dev_to_f64(out), ref) < 6e-3
+        assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05
