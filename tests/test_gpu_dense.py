@@ -139,7 +139,7 @@ def test_attention_matches_oracle(n_heads, hd):
                                                         (4, 16, 8, 64), (4, 16, 2, 32), (2, 64, 3, 130),
                                                         (2, 128, 2, 70), (3, 32, 2, 1), (2, 80, 2, 129),
                                                         (2, 96, 2, 65), (16, 72, 1, 218),
-                                                        # enough workgroups for two query blocks per wavefront
+                                                        # several rounds of workgroups
                                                         (16, 72, 11, 729), (4, 16, 130, 70), (2, 80, 90, 300)])
 def test_attention_uniform_matches_oracle(n_heads, hd, n_frames, length):
     rng = np.random.default_rng(n_heads * hd + length)
@@ -294,7 +294,7 @@ def test_gemm_split_over_wavefronts(cfg, M, N, K):
     (2, 16, [300] * 3), (3, 32, [511, 64]), (1, 72, [70]),
     (16, 72, [729, 700]),                 # two groups
     (2, 80, [400, 321]), (2, 96, [330]), (1, 128, [577]),
-    (16, 72, [729, 33, 515, 256, 1, 700, 257, 640, 90, 729, 600]),   # ragged, two query blocks per wavefront
+    (16, 72, [729, 33, 515, 256, 1, 700, 257, 640, 90, 729, 600]),   # ragged, several rounds of workgroups
 ])
 def test_attention_split_and_ragged_forms(n_heads, hd, lens):
     """Same bounds as the oracle test above: probabilities pass through bf16 once, the output is rounded once; partial
@@ -361,6 +361,29 @@ def test_attention_with_logits_of_minus_infinity(n_heads, hd, lens, dead, shift)
     qkv[:, D:2 * D] += shift
     for f in range(len(lens)):
         qkv[cu[f] + dead[0]:min(cu[f] + dead[1], cu[f + 1]), D:2 * D] = -3.0e38
+    bits = f32_to_bf16_bits(qkv.astype(np.float32))
+    ref = _attention_ref(bf16_bits_to_f32(bits).astype(np.float64), cu, n_heads, hd)
+    got = [et.et_attention(bits_to_dev(bits), torch.from_numpy(cu).cuda(), max(lens), n_heads, hd)]
+    if len(set(lens)) == 1:
+        got.append(et.et_attention_uniform(bits_to_dev(bits), len(lens), lens[0], n_heads, hd))
+    for out in got:
+        assert rel_l2(dev_to_f64(out), ref) < 6e-3
+        assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05
+
+
+@pytest.mark.parametrize("n_heads,hd,lens", [
+    (16, 72, [729] * 32), (16, 16, [70] * 96), (12, 64, [129] * 130), (16, 32, [64] * 96), (16, 80, [1] * 96),
+    (16, 72, [257, 0, 1, 255, 64, 33] * 9), (24, 80, [300] * 33), (16, 64, [256, 31] * 48),
+])
+def test_attention_with_two_query_blocks_per_wavefront(n_heads, hd, lens):
+    """From 1536 workgroups of 256 queries on (six per compute unit) a wavefront owns two blocks of 32 queries, in frames of
+    one length and in ragged ones.  Bounds as in the oracle test."""
+    assert -(-max(lens) // 256) * n_heads * len(lens) >= 1536
+    rng = np.random.default_rng(n_heads * hd + len(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, D = int(cu[-1]), n_heads * hd
+    _, qkv = _bf(rng, (rows, 3 * D))
+    qkv[:, :D] *= 2.0
     bits = f32_to_bf16_bits(qkv.astype(np.float32))
     ref = _attention_ref(bf16_bits_to_f32(bits).astype(np.float64), cu, n_heads, hd)
     got = [et.et_attention(bits_to_dev(bits), torch.from_numpy(cu).cuda(), max(lens), n_heads, hd)]

@@ -318,10 +318,14 @@ def test_full_size_64_frame_clip(siglip_weights):
 
 
 @pytest.mark.parametrize("d,heads,mlp,side,T", [(64, 4, 72, 28, 3), (128, 4, 200, 56, 1), (192, 2, 128, 56, 5), (192, 2, 256, 224, 24),
-                                                (576, 8, 320, 112, 8), (2176, 17, 64, 56, 2)])
+                                                (576, 8, 320, 112, 8), (2176, 17, 64, 56, 2),
+                                                (1152, 16, 4304, 84, 33), (1152, 16, 4304, 98, 37), (1152, 16, 4304, 112, 37),
+                                                (1152, 16, 4304, 140, 36)])
 def test_row_statistics_taken_along_by_the_gemms(d, heads, mlp, side, T):
     """The LayerNorm statistics travel from the GEMM that writes a row to the one that reads it, by pieces of 64
-    columns: 1, 2, 3, 9 and 34 pieces, ragged row counts, few rows and enough for the large tiles.  A wrong scale
+    columns: 1, 2, 3, 9, 18 and 34 pieces, ragged row counts.  The small shapes run in the tilings that split k; the four
+    of width 1152 (1188, 1813, 2368 and 3600 rows) take statistics in 128 x 128 and 256 x 128, 256 x 128 and 128 x 128,
+    256 x 256 and 256 x 256 (QKV and fc1), the last also leaves them from 128 x 128 and 256 x 128.  A wrong scale
     shows in its row: every row within 3e-2 (the residual stream is rounded to bf16 five times; a row of mean 4 standard
     deviations, the largest here, has steps of 2^-7 of one, so below 1e-2 each).  With a selection that keeps everything
     in between, the statistics come from their own kernel: identical bits."""
