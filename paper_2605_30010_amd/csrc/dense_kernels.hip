@@ -330,17 +330,16 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
 // waits are explicit (vmcnt) because the loads are asynchronous to the wavefront: a tile is
 // complete once this wavefront's loads have landed AND the workgroup barrier after that wait has
 // been passed.
-// ---------------------------------------------------------------------------------------
-// ---------------------------------------------------------------------------------------
+//
 // The kernel is persistent: one workgroup per compute-unit slot walks over its output tiles
 // t = b, b + G, b + 2G, ... and treats their k-tiles as ONE stream through the LDS stages, so the
 // loads of the next output tile are already in flight (and its first fragments already in
 // registers) while the finished tile's epilogue runs.  That removes the per-tile prologue latency
 // and the workgroup relaunch between tiles.
 // ---------------------------------------------------------------------------------------
-// STATS, residual epilogue: leaves g.stats_out.  STATS, others: the row scales come from g.stats_in: one wavefront per 64 rows combines them (a row per lane) before the
-// k-loop and leaves them, with the last k-tile, in the epilogue slices of the wavefronts that need them.  Only for
-// launches of one tile per workgroup: further tiles' scales cost more than a launch that computes them
+// STATS, residual epilogue: leaves g.stats_out.  STATS, others: the row scales come from g.stats_in: one wavefront per
+// 64 rows combines them (a row per lane) before the k-loop and leaves them, with the last k-tile, in the epilogue slices
+// of the wavefronts that need them.  Only for launches of one tile per workgroup: further tiles' scales cost more than a launch that computes them
 // (fetched beside the k-loop, 46656 rows: QKV 292 -> 324 us, fc1 445 -> 475).
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool STATS>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kernel(GemmArgs g, int tiles_m, int tiles_n) {

@@ -425,7 +425,7 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
         selected = true;
         e->prof.phase = 1;
       } else {
-        rows = n_frames * L;     // still L tokens per frame: the uniform offsets stay valid
+        rows = n_frames * L;     // still L tokens per frame
       }
     } else if (select_here) {
       const MergeWs mw = carve_merge(w.merge, T, L, D);

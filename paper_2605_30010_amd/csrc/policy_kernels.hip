@@ -4,7 +4,8 @@
 // the gather of Eq. 7 with per-frame token counts.
 //
 // Readings of points the paper leaves open are stated at plan_kernel.  The similarity kernel of
-// the simple path is reused; this file adds the sequential plan builder (O(T) steps on one lane), a weighted-range merge, the per-frame selection with two modes and a ragged gather.
+// the simple path is reused; this file adds the plan builder (all lanes of a wavefront up to 64 frames, O(T) steps on
+// one lane above), a weighted-range merge, the per-frame selection with two modes and a ragged gather.
 #include "select_common.h"
 
 namespace et {
