@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kLnRows * kWave) void piece_scale_kernel(const uint
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const float2 st = piece_moments(u32x4{raw[j].x, raw[j].y, raw[j].z, raw[j].w});
-    if (j == 0) sum.start(__shfl(st.x, 0));
+    if (j == 0) sum.ref = __shfl(st.x, 0);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const float2 p = make_float2(__shfl(st.x, u * 8), __shfl(st.y, u * 8));
@@ -1277,7 +1277,7 @@ static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
 // pieces (launch_gemm accepts them for any size; beyond one round the row scales' own launch is cheaper).
 bool gemm_takes_pieces(int rows, int cols) { return one_round(kCfgBig, rows, cols, device_cus()); }
 
-int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
+int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg, bool one_tile) {
   if (g.M <= 0) return ET_OK;
   if (g.K % 64 != 0 || g.n_store % 8 != 0) {
     set_error("gemm: K = %d must be a multiple of 64 and n_store = %d of 8", g.K, g.n_store);
@@ -1288,7 +1288,7 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg) {
     return ET_ERR_INVALID_ARG;
   }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
-  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr || g.one_tile}, g.M, g.n_store);
+  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr || one_tile}, g.M, g.n_store);
   for (int i = 0; i < plan.n; ++i) {
     const GemmPart &t = plan.part[i];
     GemmArgs part = g;

@@ -563,9 +563,8 @@ int et_encoder_block_qkv(et_encoder *e, int32_t layer, const uint16_t *x_dev, in
   if (by_pieces) rc = launch_piece_scale(x_dev, e->cfg.ln_eps, rows, D, rstd_dev, s);
   else rc = launch_rowstats(x_dev, e->cfg.ln_eps, rows, D, rstd_dev, s);
   if (rc) return rc;
-  GemmArgs g{x_dev, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, qkv_dev, 3 * D, rows, 3 * D, D, EPI_BIAS, rstd_dev};
-  g.one_tile = by_pieces;
-  return launch_gemm(g, s);
+  const GemmArgs g{x_dev, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, qkv_dev, 3 * D, rows, 3 * D, D, EPI_BIAS, rstd_dev};
+  return launch_gemm(g, s, -1, by_pieces);
 }
 
 int et_layernorm(const uint16_t *x_dev, const float *gamma_dev, const float *beta_dev, float eps,

@@ -246,7 +246,6 @@ struct GemmArgs {
   const float2 *stats_in = nullptr;
   int stats_ld = 0;
   float ln_eps = 0.f;
-  bool one_tile = false;      // row_scale, in the tiling that stats_in would take (the same bits)
 };
 // 1 / sqrt(var + eps) of every row of x [rows, D] bf16 (biased variance, fp32 two-pass like layernorm_kernel).
 int launch_rowstats(const uint16_t *x, float eps, int rows, int D, float *rstd, hipStream_t s);
@@ -254,7 +253,8 @@ int launch_rowstats(const uint16_t *x, float eps, int rows, int D, float *rstd, 
 int launch_piece_stats(const uint16_t *x, int rows, int D, int ld, float2 *stats, hipStream_t s);
 // The row scales that a GEMM derives from those pieces, bit for bit.
 int launch_piece_scale(const uint16_t *x, float eps, int rows, int D, float *rstd, hipStream_t s);
-int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg = -1);
+// one_tile: with row_scale, but in the tiling that stats_in would take (the same bits).
+int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg = -1, bool one_tile = false);
 bool gemm_takes_pieces(int rows, int cols);
 int device_cus();          // compute units of the current device
 int gemm_config_count();

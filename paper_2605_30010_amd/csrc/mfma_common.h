@@ -67,7 +67,8 @@ __device__ __forceinline__ float dpp_plus(float v) {
 }
 __device__ __forceinline__ float sum_of_8_lanes(float v) { return dpp_plus<0x141>(dpp_plus<0x4E>(dpp_plus<0xB1>(v))); }
 
-// (mean, sum of squares about it) of the 64 bf16 values that eight lanes hold, eight each.
+// (mean, sum of squares about it) of the 64 bf16 values that eight lanes hold, eight each.  A mean that has left float32
+// is given as 0, so that means can be subtracted; the sum of squares is infinite then, or NaN where a value is not finite.
 __device__ __forceinline__ float2 piece_moments(u32x4 v) {
   float x[8], s = 0.f, q = 0.f;
 #pragma unroll
@@ -83,15 +84,14 @@ __device__ __forceinline__ float2 piece_moments(u32x4 v) {
     const float d = x[e] - mean;
     q = fmaf(d, d, q);
   }
-  return make_float2(mean, sum_of_8_lanes(q));
+  return make_float2(fabsf(mean) < INFINITY ? mean : 0.f, sum_of_8_lanes(q));
 }
 
 // Combines the pieces of one row, in ascending order.  The pieces' means are taken relative to the first one's: nothing
 // cancels when the row's mean is many standard deviations.  Where a square or a piece's sum leaves float32 (values beyond
 // 1e18) the variance is infinite and the scale 0, as in rowstats_kernel; a NaN or an infinity in the row gives NaN.
 struct PieceSum {
-  float ref = 0.f, s1 = 0.f, s2 = 0.f;
-  __device__ __forceinline__ void start(float first_mean) { ref = fabsf(first_mean) < INFINITY ? first_mean : 0.f; }
+  float ref = 0.f, s1 = 0.f, s2 = 0.f;                   // ref: the first piece's mean, set by the caller
   __device__ __forceinline__ void add(float2 p) {
     const float d = p.x - ref;
     s1 += d;
@@ -128,7 +128,7 @@ struct RowScale {
     if (!g.stats_in) return v[0].x;
     const int pieces = g.K / 64;
     PieceSum sum;
-    sum.start(v[0].x);
+    sum.ref = v[0].x;
     for (int c = 0;;) {
 #pragma unroll
       for (int u = 0; u < BATCH; ++u)
