@@ -3,6 +3,7 @@
 //
 // The MFMA operand layouts are described in mfma_common.h.
 #include <atomic>
+#include <type_traits>
 
 #include "gemm_choice.h"
 #include "gemm_small.h"
@@ -216,50 +217,47 @@ __global__ __launch_bounds__(1024) void im2col_stripe_kernel(const float *__rest
 // (columns = m): each lane then owns 4 consecutive n of one output row m per accumulator
 // quad, which packs to an 8-byte bf16 piece.
 // ---------------------------------------------------------------------------------------
-// acc[a][b] is the 32 x 32 tile at rows n_base + 32a (MFMA rows = output columns n) and columns
-// m_base + 32b: the lane owns output row m = .. + r32 and, per accumulator quad q, the four
-// consecutive columns n = .. + 8q + 4grp + (0..3).
+// acc[a][b] is the 16 x 16 tile at columns n_base + 16 a (MFMA rows) and rows m_base + 16 b (MFMA columns): the lane owns
+// output row m = .. + lane % 16 and the four consecutive columns n = .. + 4 (lane / 16) + (0..3).
 // Epilogue for wavefront tiles 64 columns wide, staged through a private 4 KiB LDS slice per
 // wavefront so that every global access is a full 128-byte row segment (8 lanes x 16 bytes)
-// instead of 8-byte pieces scattered over 32 rows.  Per 32-row block: (residual only) the
+// instead of 8-byte pieces scattered over 16 rows.  Per 32-row block: (residual only) the
 // residual block is fetched coalesced into the slice; each lane then adds bias (+GELU | +its
 // residual values read back from the slice) in fp32, rounds once to bf16 and writes its 4-column
 // pieces to the slice; finally the slice is read row-wise and stored.  16-byte slots of a row are
 // XOR-swizzled by (row >> 1) & 7.  LDS operations of one wavefront execute in order, so the phases
 // need no barrier.
-// STATS: the residual epilogue leaves the rows' statistics; for the others the row scales of the wavefront's FM * 32
+// STATS: the residual epilogue leaves the rows' statistics; for the others the row scales of the wavefront's MS * 16
 // rows lie at the start of the slice as floats.
-template <int EPI, bool STATS, int FM, int FN>
-__device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const GemmArgs &g, int m_base,
+template <int EPI, bool STATS, int MS, int NS>
+__device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const GemmArgs &g, int m_base,
                                                   int n_base, int lane, uint16_t *slice) {
-  static_assert(FN % 2 == 0, "the staged epilogue handles 64-column pieces of the wavefront tile");
-  const int r32 = lane & 31, grp = lane >> 5;
+  static_assert(NS == 4 && MS % 2 == 0, "the staged epilogue handles 64-column wavefront tiles in blocks of 32 rows");
+  const int r16 = lane & 15, g4 = lane >> 4;
   const int prow = lane >> 3, pch = lane & 7;                 // row-wise phase: 8 rows x 8 chunks per pass
-  const int wsw = (r32 >> 1) & 7;
-  float rsv[FM];                                              // row scales of this lane's rows, fetched up front
+  float rsv[MS];                                              // row scales of this lane's rows, fetched up front
 #pragma unroll
-  for (int b = 0; b < FM; ++b) {
-    const int m = m_base + b * 32 + r32;
+  for (int b = 0; b < MS; ++b) {
+    const int m = m_base + b * 16 + r16;
     if (EPI == EPI_BIAS_RES) rsv[b] = 1.0f;                   // (no LayerNorm in front of these)
-    else if (STATS) rsv[b] = reinterpret_cast<const float *>(slice)[b * 32 + r32];
+    else if (STATS) rsv[b] = reinterpret_cast<const float *>(slice)[b * 16 + r16];
     else rsv[b] = (g.row_scale && m < g.M) ? g.row_scale[m] : 1.0f;   // (fma(1, acc, bias) == acc + bias exactly)
   }
   if (STATS) asm volatile("" ::: "memory");                   // read before the slice takes the results
-#pragma unroll
-  for (int half = 0; half < FN / 2; ++half) {
-  const int nb = n_base + half * 64;
-  const int n_lane = nb + pch * 8;
+  const int n_lane = n_base + pch * 8;
   const bool n_ok = n_lane < g.n_store;                       // n_store is a multiple of 8 on this path
-  float4 bi[2][4];                                            // this lane's bias values for the 64 columns
+  float4 bi[NS];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NS; ++a) {
+    const int n = n_base + a * 16 + g4 * 4;
+    bi[a] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n < g.n_store) bi[a] = *reinterpret_cast<const float4 *>(g.bias + n);
+  }
+  // (waited for on every path: a load still pending at the k-loop's head would be waited for there, each time round)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int n = nb + a * 32 + q * 8 + grp * 4;
-      bi[a][q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (n < g.n_store) bi[a][q] = *reinterpret_cast<const float4 *>(g.bias + n);
-    }
-  // residual rows of a 32-row block, fetched coalesced one block ahead of their use
+  for (int a = 0; a < NS; ++a) asm volatile("" : "+v"(bi[a].x), "+v"(bi[a].y), "+v"(bi[a].z), "+v"(bi[a].w));
+#pragma unroll
+  for (int b = 0; b < MS; ++b) asm volatile("" : "+v"(rsv[b]));
   u32x4 rv[4];
   auto fetch_res = [&](int b) {
 #pragma unroll
@@ -272,29 +270,30 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
   };
   if (EPI == EPI_BIAS_RES) fetch_res(0);
 #pragma unroll
-  for (int b = 0; b < FM; ++b) {
+  for (int b = 0; b < MS / 2; ++b) {
     const int mb = m_base + b * 32;
     if (mb >= g.M) break;                                     // wave-uniform: whole block past the last row
-    const float rs = rsv[b];
     if (EPI == EPI_BIAS_RES) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int row = j * 8 + prow;
         *reinterpret_cast<u32x4 *>(slice + row * 64 + ((pch ^ ((row >> 1) & 7)) * 8)) = rv[j];
       }
-      if (b + 1 < FM) fetch_res(b + 1);
+      if (b + 1 < MS / 2) fetch_res(b + 1);
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const f32x16 av = acc[half * 2 + a][b];
+    for (int h = 0; h < 2; ++h) {
+      const int row = h * 16 + r16;
+      const float rs = rsv[b * 2 + h];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v0 = fmaf(rs, av[q * 4 + 0], bi[a][q].x), v1 = fmaf(rs, av[q * 4 + 1], bi[a][q].y);
-        float v2 = fmaf(rs, av[q * 4 + 2], bi[a][q].z), v3 = fmaf(rs, av[q * 4 + 3], bi[a][q].w);
+      for (int a = 0; a < NS; ++a) {
+        const f32x4 av = acc[a][b * 2 + h];
+        float v0 = fmaf(rs, av[0], bi[a].x), v1 = fmaf(rs, av[1], bi[a].y);
+        float v2 = fmaf(rs, av[2], bi[a].z), v3 = fmaf(rs, av[3], bi[a].w);
         if (EPI == EPI_BIAS_GELU) {
           v0 = gelu_tanh_f(v0); v1 = gelu_tanh_f(v1); v2 = gelu_tanh_f(v2); v3 = gelu_tanh_f(v3);
         }
-        uint2 *cell = reinterpret_cast<uint2 *>(slice + r32 * 64 + (((a * 4 + q) ^ wsw) * 8) + grp * 4);
+        uint2 *cell = reinterpret_cast<uint2 *>(slice + row * 64 + (((a * 2 + (g4 >> 1)) ^ ((row >> 1) & 7)) * 8) + (g4 & 1) * 4);
         if (EPI == EPI_BIAS_RES) {
           const uint2 rr = *cell;
           v0 += bf16lo_to_f32(rr.x); v1 += bf16hi_to_f32(rr.x);
@@ -313,12 +312,28 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
       if (m < g.M && n_ok) *reinterpret_cast<u32x4 *>(g.C + (size_t)m * g.ldc + n_lane) = v;
       if (EPI == EPI_BIAS_RES && STATS) {                     // (n_store is a multiple of 64 then)
         const float2 st = piece_moments(v);
-        if (pch == 0 && m < g.M && n_ok) g.stats_out[(size_t)(nb >> 6) * g.stats_ld + m] = st;
+        if (pch == 0 && m < g.M && n_ok) g.stats_out[(size_t)(n_base >> 6) * g.stats_ld + m] = st;
         asm volatile("" ::: "memory");                          // (one piece at a time: the accumulators leave no registers)
       }
     }
   }
+}
+
+// Order of a quarter of gemm_stream_kernel's k-tile: one MFMA in front of each LDS read, then the direct loads GAP MFMAs apart, the rest behind them.
+template <int READS, int LOADS, int MFMAS>
+__device__ __forceinline__ void mfma_between() {
+  constexpr int GAP = LOADS ? ((MFMAS - READS) / (LOADS + 1) > 0 ? (MFMAS - READS) / (LOADS + 1) : 1) : 0;
+#pragma unroll
+  for (int i = 0; i < READS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
   }
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, GAP, 0);
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+  }
+  if constexpr (MFMAS - READS - LOADS * GAP > 0) __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - READS - LOADS * GAP, 0);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -326,44 +341,43 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x16 (&acc)[FN][FM], const G
 // registers and no LDS write instructions.  One wavefront load moves 64 x 16 bytes to 1 KiB of
 // consecutive LDS, i.e. 8 tile rows of 64 bf16; lane L lands at row L / 8, slot L % 8 and fetches
 // the global 16-byte chunk (slot ^ swz(row)), an XOR swizzle that spreads the MFMA fragment reads
-// (same k-chunk, consecutive rows) over the banks.  STAGES k-tiles are in flight (one per stage);
-// waits are explicit (vmcnt) because the loads are asynchronous to the wavefront: a tile is
-// complete once this wavefront's loads have landed AND the workgroup barrier after that wait has
-// been passed.
+// (same k-chunk, consecutive rows) over the banks.  Waits are explicit (vmcnt) because the loads are
+// asynchronous to the wavefront: a piece is complete once this wavefront's loads have landed AND the
+// workgroup barrier after that wait has been passed.
 //
 // The kernel is persistent: one workgroup per compute-unit slot walks over its output tiles
-// t = b, b + G, b + 2G, ... and treats their k-tiles as ONE stream through the LDS stages, so the
+// t = b, b + G, b + 2G, ... and treats their k-tiles as ONE stream through two LDS stages, so the
 // loads of the next output tile are already in flight (and its first fragments already in
 // registers) while the finished tile's epilogue runs.  That removes the per-tile prologue latency
 // and the workgroup relaunch between tiles.
+//
+// A wavefront goes over its 64-deep k-tile in quarters: (upper half of its rows, k 0-31), (upper, 32-63), (lower, 0-31),
+// (lower, 32-63); the fragments of a quarter are read from LDS under the MFMAs of the one before.  The weight fragments of
+// both k-steps stay in registers for the whole k-tile, so after the first quarter the weights and the upper rows of the
+// stage have been read by everyone and are refilled with the k-tile after the next, two loads per wavefront and quarter
+// among the MFMAs: a compute unit takes 58 bytes of operands per clock, 1100 clocks per k-tile, and a burst of loads
+// blocks whoever issues it.  The lower rows follow in the next k-tile's first quarter.  Two barriers per k-tile, a few
+// MFMAs before a quarter's end, so that these are at hand behind them.
+// Bound: the board's power cap where all compute units work; in launches of one round the fixed parts (launch 1-4 us,
+// first loads 3 us, epilogue 3-7 us) and the barriers (120 of 600 clocks per quarter pair).  Measured against
+// 32x32x16 MFMAs with whole stages refilled in one burst, us per launch (one box): 23328 rows, QKV 184.8 -> 176.8, fc1
+// 238.7 -> 227.4, out-projection 73.5 -> 69.3, fc2 231.4 -> 215.3; 3276 rows, QKV 35.5 -> 33.5, fc1 39.6 -> 38.3.
 // ---------------------------------------------------------------------------------------
 // STATS, residual epilogue: leaves g.stats_out.  STATS, others: the row scales come from g.stats_in: one wavefront per
 // 64 rows combines them (a row per lane) before the k-loop and leaves them, with the last k-tile, in the epilogue slices
 // of the wavefronts that need them.  Only for launches of one tile per workgroup: further tiles' scales cost more than a launch that computes them
 // (fetched beside the k-loop, 46656 rows: QKV 292 -> 324 us, fc1 445 -> 475).
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int MINB, int EPI, bool STATS>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB, int EPI, bool STATS>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int BK = 64, STAGES = 2;
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  constexpr int FM = WTM / 32, FN = WTN / 32;
-  constexpr int CPR = BK / 8;
-  constexpr int RPB = 64 / CPR;
-  constexpr int SWZ = (BK == 64) ? 1 : 2;
-  // With two wavefronts per SIMD (8 wavefronts, one workgroup per compute unit) only the upper half
-  // of the wavefronts issues the direct loads.  The address unit takes 64 bytes per clock, so the
-  // 64 KiB of a k-tile keep it busy for ~1000 cycles and block whoever issues them; the wavefront
-  // that shares the SIMD and issues none goes straight on with its MFMAs, and the loader does its
-  // own while the other one waits at the next barrier.
-  constexpr bool SPLIT_LOADERS = (NW == 8 && MINB == 1);
-  constexpr int LW = SPLIT_LOADERS ? NW / 2 : NW;                    // wavefronts that load
-  constexpr int A_BLK = BM / RPB / LW, W_BLK = BN / RPB / LW;
-  constexpr int LOADS = A_BLK + W_BLK;
+  constexpr int MS = WTM / 16, NS = WTN / 16, MH = MS / 2;
   constexpr int STAGE_ELEMS = (BM + BN) * BK;
-  constexpr int KS = BK / 16;
-  static_assert(BK == 64 || BK == 32, "k-tile is 64 or 32");
-  static_assert(WTN % 64 == 0, "the staged epilogue handles 64-column pieces of the wavefront tile");
-  static_assert(BM % (RPB * LW) == 0 && BN % (RPB * LW) == 0, "tile rows must split evenly over the loading wavefronts");
-  static_assert(A_BLK % 4 == 0 || A_BLK < 4, "loads are issued in groups of four sharing one M0 value");
+  constexpr int WL = BN / 8 / NW, AL = BM / 16 / NW;                 // 1 KiB loads per wavefront: of the weight tile, of either half of the activation tile
+  constexpr int LOADS = WL + 2 * AL;
+  static_assert(WTN == 64, "the staged epilogue handles 64-column wavefront tiles");
+  static_assert(WL == 4 && AL == 2 && (WTM / 2) % (8 * AL) == 0, "loads are issued two per quarter, in groups that share one M0 value");
   extern __shared__ __align__(16) uint16_t lds[];
 
   const int n_tiles = tiles_m * tiles_n;
@@ -372,10 +386,8 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS destinations of the loads stay scalar
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int r32 = lane & 31, grp = lane >> 5;
-  const int lrow = lane / CPR, lslot = lane % CPR;
-  const bool is_loader = !SPLIT_LOADERS || wave >= NW / 2;
-  const int lwave = SPLIT_LOADERS ? (wave >= NW / 2 ? wave - NW / 2 : 0) : wave;   // index among the loading wavefronts
+  const int r16 = lane & 15, g4 = lane >> 4;
+  const int lrow = lane >> 3, lslot = lane & 7;
 
   // j-th tile of this workgroup.  Tiles are ordered in bands of 8 tile rows, inside a band in
   // column blocks of 4 tile columns, inside a block row-major; within a round of G tiles each XCD
@@ -406,11 +418,14 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
   // origins are lowered by it).
   constexpr uint32_t kOffBias = 4096;
   const char *a_base = nullptr, *w_base = nullptr;
-  uint32_t a_off[A_BLK], w_off[W_BLK];
+  uint32_t a_off[2 * AL], w_off[WL];
+  // activation rows of this wavefront's loads: half h (rows h * WTM / 2 .. of every wavefront tile), i-th load
+  constexpr int WPH = WTM / 2 / (8 * AL);                         // wavefronts that load one wavefront row's half
+  const int a_row0 = (wave / WPH) * WTM + (wave % WPH) * 8 * AL;  // half 0; half 1: + WTM / 2
 #pragma unroll
-  for (int i = 0; i < W_BLK; ++i) {
-    const int row = (lwave * W_BLK + i) * RPB + lrow;
-    w_off[i] = (uint32_t)(((size_t)row * g.K + ((lslot ^ ((row >> SWZ) & (CPR - 1))) * 8)) * 2) + kOffBias - (i % 4) * 1024;
+  for (int i = 0; i < WL; ++i) {
+    const int row = (wave * WL + i) * 8 + lrow;
+    w_off[i] = (uint32_t)(((size_t)row * g.K + ((lslot ^ ((row >> 1) & 7)) * 8)) * 2) + kOffBias - i * 1024;
   }
   auto set_load_tile = [&](int j) {
     int m0, n0;
@@ -419,38 +434,33 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
     w_base = reinterpret_cast<const char *>(g.W + (size_t)n0 * g.K) - kOffBias;
     asm volatile("" : "+s"(a_base), "+s"(w_base));      // (keeps the bias out of the loads' address expressions)
 #pragma unroll
-    for (int i = 0; i < A_BLK; ++i) {
-      const int row = (lwave * A_BLK + i) * RPB + lrow;
+    for (int i = 0; i < 2 * AL; ++i) {
+      const int row = a_row0 + (i / AL) * (WTM / 2) + (i % AL) * 8 + lrow;
       const int rc = (m0 + row < g.M) ? row : g.M - 1 - m0;       // m0 < M always
-      a_off[i] = (uint32_t)(((size_t)rc * g.lda + ((lslot ^ ((row >> SWZ) & (CPR - 1))) * 8)) * 2) + kOffBias - (i % 4) * 1024;
+      a_off[i] = (uint32_t)(((size_t)rc * g.lda + ((lslot ^ ((row >> 1) & 7)) * 8)) * 2) + kOffBias - (i % AL) * 1024;
     }
   };
   const int kt_n = g.K / BK;
   int load_tile = 0, load_kt = 0;                   // next k-tile of the stream to be fetched
-  auto issue_one = [&](int stage, int i) {          // i-th 1 KiB load of this wavefront for the next k-tile
-    uint16_t *as = lds + stage * STAGE_ELEMS;
-    uint16_t *ws = as + BM * BK;
-    const size_t ko = (size_t)load_kt * (BK * 2);
-    // (the empty asm keeps the offset a 32-bit register at this point, so that the load is selected
-    // with the scalar base + 32-bit offset form instead of a widened 64-bit vector address)
-    const char *src;
-    uint16_t *dst;
-    if (i < A_BLK) {
-      asm volatile("" : "+v"(a_off[i]));
-      src = a_base + ko + a_off[i];
-      dst = as + (lwave * A_BLK + (i & ~3)) * 512;
-    } else {
-      const int j = i - A_BLK;
-      asm volatile("" : "+v"(w_off[j]));
-      src = w_base + ko + w_off[j];
-      dst = ws + (lwave * W_BLK + (j & ~3)) * 512;
-    }
-    lds_dma16_of4(src, dst, i < A_BLK ? i : i - A_BLK);
-  };
-  auto issue_next = [&](int stage) {
-    if (!is_loader) return;
+  auto load_w = [&](int stage, int i0, int i1) {
+    const char *b = w_base + (size_t)load_kt * (BK * 2);
+    uint16_t *dst = lds + stage * STAGE_ELEMS + BM * BK + wave * WL * 512;
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) issue_one(stage, i);
+    for (int i = i0; i < i1; ++i) {
+      asm volatile("" : "+v"(w_off[i]));
+      lds_dma16_of4(b + w_off[i], dst, i);
+    }
+  };
+  auto load_a = [&](int stage, int h) {
+    const char *b = a_base + (size_t)load_kt * (BK * 2);
+    uint16_t *dst = lds + stage * STAGE_ELEMS + (a_row0 + h * (WTM / 2)) * 64;
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+      asm volatile("" : "+v"(a_off[h * AL + i]));
+      lds_dma16_of4(b + a_off[h * AL + i], dst, i);
+    }
+  };
+  auto advance = [&]() {
     if (++load_kt == kt_n) {                        // past the stream's end the last k-tile is re-read (unused)
       if (load_tile + 1 < n_my) {
         load_kt = 0;
@@ -461,126 +471,144 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
     }
   };
 
-  const int fx = (r32 >> SWZ) & (CPR - 1);
-  int koff[KS];
+  const int fx = (r16 >> 1) & 7;
+  int a_addr[2], w_addr[2];                         // element offsets of this lane's fragments, by k-step
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) koff[ks] = (((2 * ks + grp) ^ fx) * 8);
-  const int a_row = (wm * WTM + r32) * BK, w_row = (wn * WTN + r32) * BK;
+  for (int ks = 0; ks < 2; ++ks) {
+    const int ko = ((4 * ks + g4) ^ fx) * 8;
+    a_addr[ks] = (wm * WTM + r16) * 64 + ko;
+    w_addr[ks] = BM * BK + (wn * WTN + r16) * 64 + ko;
+  }
 
-  f32x16 acc[FN][FM];
+  f32x4 acc[NS][MS];
   auto clear_acc = [&]() {
 #pragma unroll
-    for (int a = 0; a < FN; ++a)
+    for (int a = 0; a < NS; ++a)
 #pragma unroll
-      for (int b = 0; b < FM; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+      for (int b = 0; b < MS; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
   constexpr bool LNF = STATS && EPI != EPI_BIAS_RES;
   static_assert(!LNF || (WTM % 64 == 0 && BM / 64 <= NW), "one wavefront per 64 rows");
   float my_scale = 1.0f;
-  RowScale<6> scale;
+  RowScale<18> scale;
   if (LNF && wave < BM / 64) {
     int m0, n0;
     tile_of(0, m0, n0);
     scale.fetch(g, m0 + wave * 64 + lane);
   }
-  if (is_loader) set_load_tile(0);
+  set_load_tile(0);
 #pragma unroll
-  for (int st = 0; st < STAGES; ++st) issue_next(st);
+  for (int st = 0; st < 2; ++st) {
+    load_w(st, 0, WL);
+    load_a(st, 0);
+    if (st == 0) {
+      load_a(st, 1);
+      advance();
+    }
+  }
+
+  u32x4 fw[2][NS], fa[2][MH];
+  auto read_w = [&](int stage, int ks) {
+    const uint16_t *p = lds + stage * STAGE_ELEMS + w_addr[ks];
+#pragma unroll
+    for (int a = 0; a < NS; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(p + a * 16 * 64);
+  };
+  auto read_a = [&](int buf, int stage, int h, int ks) {
+    const uint16_t *p = lds + stage * STAGE_ELEMS + a_addr[ks] + h * (WTM / 2) * 64;
+#pragma unroll
+    for (int b = 0; b < MH; ++b) fa[buf][b] = *reinterpret_cast<const u32x4 *>(p + b * 16 * 64);
+  };
+  auto mfma_rows = [&](int buf, int h, int ks, int b0, int b1) {
+#pragma unroll
+    for (int b = b0; b < b1; ++b)
+#pragma unroll
+      for (int a = 0; a < NS; ++a) acc[a][h * MH + b] = mfma16(fw[ks][a], fa[buf][b], acc[a][h * MH + b]);
+  };
+  constexpr int N_ST = (MS / 2) * 4;                 // global stores per wavefront in the staged epilogue
+  int relax = 0;
+  auto landed = [&](auto newest) {                              // all but the newest LOADS loads of this wavefront, then everyone's
+    if (relax > 0) {
+      wait_vmcnt<decltype(newest)::value + N_ST>();
+      --relax;
+    } else {
+      wait_vmcnt<decltype(newest)::value>();
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  wait_vmcnt<LOADS>();
+  __builtin_amdgcn_sched_barrier(0);
   if (LNF && wave < BM / 64) {
     my_scale = scale.value(g);
     asm volatile("" : "+v"(my_scale));
   }
   clear_acc();
-
-  // Fragments are double-buffered in registers: the LDS reads of k-step s+1 are issued under the
-  // MFMAs of step s, also across k-tiles (the one barrier per tile sits before the tile's last step).
-  u32x4 fa[2][FM], fw[2][FN];
-  auto read_frags = [&](int buf, int stage, int ks) {
-    const uint16_t *as = lds + stage * STAGE_ELEMS;
-    const uint16_t *ws = as + BM * BK;
-#pragma unroll
-    for (int b = 0; b < FM; ++b) fa[buf][b] = *reinterpret_cast<const u32x4 *>(as + a_row + b * 32 * BK + koff[ks]);
-#pragma unroll
-    for (int a = 0; a < FN; ++a) fw[buf][a] = *reinterpret_cast<const u32x4 *>(ws + w_row + a * 32 * BK + koff[ks]);
-  };
-  auto mfma_step = [&](int buf) {
-#pragma unroll
-    for (int a = 0; a < FN; ++a)
-#pragma unroll
-      for (int b = 0; b < FM; ++b) acc[a][b] = mfma32(fw[buf][a], fa[buf][b], acc[a][b]);
-  };
-  // scheduling hint for one step: alternate MFMA / LDS read until the reads are placed
-  auto interleave = [&]() {
-#pragma unroll
-    for (int i = 0; i < FM + FN; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - (FM + FN), 0);
-  };
-
-  wait_vmcnt<(STAGES - 1) * LOADS>();    // k-tile 0 has landed
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  read_frags(0, 0, 0);
+  read_w(0, 0);
+  read_a(0, 0, 0, 0);
 
-  int stage = 0, kt = 0, my_tile = 0, relax = 0;
-  constexpr int N_ST = FM * (FN / 2) * 4;            // global stores per wavefront in the staged epilogue
+  int stage = 0, kt = 0, my_tile = 0;
   const int units = n_my * kt_n;
   uint16_t *const slices = lds + STAGES * STAGE_ELEMS;
   for (int u = 0; u < units; ++u) {
-#pragma unroll
-    for (int ks = 0; ks < KS - 1; ++ks) {
-      read_frags((ks + 1) & 1, stage, ks + 1);
-      mfma_step(ks & 1);
-      interleave();
-    }
-    // Last step of k-tile u: tile u+1 must have landed (at most STAGES-2 newer tiles outstanding) and
-    // this wavefront's reads of tile u must have returned before its stage is handed to the loads.
-    // Vector-memory operations retire in issue order.  For STAGES - 1 units after the epilogue of
-    // an interior tile (every lane stored: exactly N_ST store instructions per wavefront) those
-    // stores are younger than the loads awaited here, so they may stay in flight and drain under
-    // the next tile's MFMAs.
-    if (relax > 0) {
-      wait_vmcnt<(STAGES - 2) * LOADS + N_ST>();
-      --relax;
-    } else {
-      wait_vmcnt<(STAGES - 2) * LOADS>();
-    }
+    read_a(1, stage, 0, 1);
+    read_w(stage, 1);
+    load_a(stage ^ 1, 1);
+    mfma_rows(0, 0, 0, 0, MH - 1);
+    mfma_between<MH + NS, AL, NS * (MH - 1)>();
+    __builtin_amdgcn_sched_barrier(0);
+    advance();
+    landed(std::integral_constant<int, LOADS>());
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_rows(0, 0, 0, MH - 1, MH);
+    read_a(0, stage, 1, 0);
+    load_w(stage, 0, 2);
+    mfma_rows(1, 0, 1, 0, MH);
+    __builtin_amdgcn_sched_group_barrier(0x008, NS, 0);
+    mfma_between<MH, 2, NS * MH>();
+    __builtin_amdgcn_sched_barrier(0);
+    read_a(1, stage, 1, 1);
+    load_w(stage, 2, 4);
+    mfma_rows(0, 1, 0, 0, MH - 1);
+    mfma_between<MH, 2, NS * (MH - 1)>();
+    __builtin_amdgcn_sched_barrier(0);
     if (LNF && wave < BM / 64 && kt + 1 == kt_n) {
       uint16_t *dst = slices + (wave * 64 / WTM) * WAVES_N * (32 * 64);
 #pragma unroll
       for (int w = 0; w < WAVES_N; ++w) reinterpret_cast<float *>(dst + w * (32 * 64))[(wave * 64) % WTM + lane] = my_scale;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const int next_stage = (stage + 1 == STAGES) ? 0 : stage + 1;
-    issue_next(stage);
-    read_frags(KS & 1, next_stage, 0);
-    mfma_step((KS - 1) & 1);
-    interleave();
-    stage = next_stage;
+    landed(std::integral_constant<int, LOADS - AL>());
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_rows(0, 1, 0, MH - 1, MH);
+    read_w(stage ^ 1, 0);
+    read_a(0, stage ^ 1, 0, 0);
+    load_a(stage, 0);
+    mfma_rows(1, 1, 1, 0, MH);
+    __builtin_amdgcn_sched_group_barrier(0x008, NS, 0);
+    mfma_between<MH + NS, AL, NS * MH>();
+    __builtin_amdgcn_sched_barrier(0);
+    stage ^= 1;
     if (++kt == kt_n) {                             // an output tile is complete
       int m0, n0;
       tile_of(my_tile, m0, n0);
-      gemm_epilogue_lds<EPI, STATS, FM, FN>(acc, g, m0 + wm * WTM, n0 + wn * WTN, lane, slices + wave * (32 * 64));
-      if (m0 + BM <= g.M && n0 + BN <= g.n_store) relax = STAGES - 1;
+      gemm_epilogue_lds<EPI, STATS, MS, NS>(acc, g, m0 + wm * WTM, n0 + wn * WTN, lane, slices + wave * (32 * 64));
+      if (m0 + BM <= g.M && n0 + BN <= g.n_store) relax = 2;
+      if (++my_tile == n_my) break;
       kt = 0;
-      ++my_tile;
       clear_acc();
     }
   }
   wait_vmcnt<0>();                     // drain the padding loads before the workgroup's LDS is released
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int MINB = 1>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB>
 int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
   constexpr int NT = WAVES_M * WAVES_N * 64;
-  // k-tile stages plus one 4 KiB epilogue slice per wavefront
-  constexpr size_t lds_bytes = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t) +
+  // two k-tile stages plus one 4 KiB epilogue slice per wavefront
+  constexpr size_t lds_bytes = (size_t)2 * (BM + BN) * 64 * sizeof(uint16_t) +
                                (size_t)WAVES_M * WAVES_N * 32 * 64 * sizeof(uint16_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget");
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.n_store + BN - 1) / BN;
@@ -593,7 +621,7 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
   }
 #define ET_GEMM_LAUNCH(E, STATS)                                                                  \
   {                                                                                              \
-    auto kern = gemm_stream_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, MINB, E, STATS>;        \
+    auto kern = gemm_stream_kernel<BM, BN, WAVES_M, WAVES_N, MINB, E, STATS>;        \
     static bool attr_set = false;                                                                \
     if (!attr_set) {                                                                             \
       ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                           \
@@ -1262,8 +1290,8 @@ int gemm_config_count() { return kCfgStrip; }     // (what et_gemm_bf16 can ask 
 
 static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
   switch (cfg) {
-    case kCfgBig: return launch_gemm_stream_cfg<256, 256, 64, 2, 4, 2>(g, s);
-    case kCfg128: return launch_gemm_stream_cfg<128, 128, 64, 2, 2, 2, 2>(g, s);
+    case kCfgBig: return launch_gemm_stream_cfg<256, 256, 2, 4, 1>(g, s);
+    case kCfg128: return launch_gemm_stream_cfg<128, 128, 2, 2, 2>(g, s);
     case kCfgWave: return launch_gemm_wave(g, s);
     case kCfgPair64: return launch_gemm_pair64(g, s);
     case kCfgPair128: return launch_gemm_pair128(g, s);

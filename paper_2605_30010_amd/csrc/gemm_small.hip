@@ -111,6 +111,11 @@ __device__ __forceinline__ void put_quadrant(const f32x16 &acc, f32x4 *cells, in
     cells[(b * 8 + c) * 64 + (lane ^ (c << 1))] = f32x4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
   }
 }
+// One 16 x 16 accumulator (columns 16 a, rows 16 b of the 64 x 64 tile) to the same cells.
+__device__ __forceinline__ void put_tile16(const f32x4 &acc, f32x4 *cells, int a, int b, int lane) {
+  const int r = (b & 1) * 16 + (lane & 15), g4 = lane >> 4, c = a * 2 + (g4 >> 1);
+  cells[((b >> 1) * 8 + c) * 64 + (((g4 & 1) * 32 + r) ^ (c << 1))] = acc;
+}
 template <int PARTS, int STRIDE, int EPI>
 __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const GemmArgs &g, f32x4 *xch, int wave, int first,
                                               int rank, int m_tile, int n_tile, int lane, const float *rs_tile) {
@@ -225,7 +230,7 @@ __global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tile
   constexpr int ST = 4, SLOT = 8192;                     // slots; elements of one: 64 rows of A, 64 of W, 128 bytes each
   extern __shared__ __align__(16) uint16_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1, r32 = lane & 31, grp = lane >> 5, lrow = lane >> 3, lslot = lane & 7;
+  const int wm = wave >> 1, wn = wave & 1, r16 = lane & 15, g4 = lane >> 4, lrow = lane >> 3, lslot = lane & 7;
   int m0, n0;
   small_tile_of(tiles_m, tiles_n, m0, n0);
   m0 *= 64;
@@ -264,11 +269,21 @@ __global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tile
   for (int t = 0; t < ST - 1; ++t)
     if (t < kt_n) issue(t, t);
   if (scales) rs_tile[lane] = scale.value(g);
-  f32x16 acc;
+  f32x4 acc[2][2];                                       // [16 columns][16 rows] of the quadrant
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  const int fx = (r32 >> 1) & 7, a_row = (wm * 32 + r32) * 64, w_row = 4096 + (wn * 32 + r32) * 64;
-  u32x4 fa[2][4], fw[2][4];
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fx = (r16 >> 1) & 7, a_row = (wm * 32 + r16) * 64, w_row = 4096 + (wn * 32 + r16) * 64;
+  u32x4 fa[2][2][2], fw[2][2][2];                        // [buffer][k-step][16 rows or columns]
+  auto mfmas = [&](int buf) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = mfma16(fw[buf][ks][a], fa[buf][ks][b], acc[a][b]);
+  };
   int slot = 0;
   // k-tile t into fragment buffer `buf`; the MFMAs of t - 1 (the other buffer) follow the reads
   auto step = [&](int buf, int t) {
@@ -280,18 +295,18 @@ __global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tile
     __builtin_amdgcn_sched_barrier(0);
     const uint16_t *sp = lds + slot * SLOT;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int ko = ((2 * ks + grp) ^ fx) * 8;
-      fa[buf][ks] = *reinterpret_cast<const u32x4 *>(sp + a_row + ko);
-      fw[buf][ks] = *reinterpret_cast<const u32x4 *>(sp + w_row + ko);
+    for (int ks = 0; ks < 2; ++ks) {
+      const int ko = ((4 * ks + g4) ^ fx) * 8;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[buf][ks][i] = *reinterpret_cast<const u32x4 *>(sp + a_row + i * 1024 + ko);
+        fw[buf][ks][i] = *reinterpret_cast<const u32x4 *>(sp + w_row + i * 1024 + ko);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (t + ST - 1 < kt_n) issue(slot == 0 ? ST - 1 : slot - 1, t + ST - 1);
     __builtin_amdgcn_sched_barrier(0);
-    if (t > 0) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) acc = mfma32(fw[buf ^ 1][ks], fa[buf ^ 1][ks], acc);
-    }
+    if (t > 0) mfmas(buf ^ 1);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): the reads have returned before the next barrier
     asm volatile("" ::: "memory");
@@ -302,16 +317,17 @@ __global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tile
     step(0, t);
     if (t + 1 < kt_n) step(1, t + 1);
   }
-  if (kt_n & 1) {
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) acc = mfma32(fw[0][ks], fa[0][ks], acc);
-  } else {
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) acc = mfma32(fw[1][ks], fa[1][ks], acc);
-  }
+  if (kt_n & 1) mfmas(0);
+  else mfmas(1);
   __syncthreads();                                       // the slots have been read: their room takes the results
   f32x4 *xch = reinterpret_cast<f32x4 *>(lds);
-  finish_rows<4, 1, 1, EPI>([&]() { put_quadrant(acc, xch, wn, wm, lane); }, g, xch, 0, wave, m0, n0, lane, rs_tile);
+  auto put = [&]() {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) put_tile16(acc[a][b], xch, wn * 2 + a, wm * 2 + b, lane);
+  };
+  finish_rows<4, 1, 1, EPI>(put, g, xch, 0, wave, m0, n0, lane, rs_tile);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -476,7 +492,7 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
   extern __shared__ __align__(16) uint16_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = wave >> 2, wm = wave >> 1, wn = wave & 1;
-  const int r32 = lane & 31, grp = lane >> 5, lrow = lane >> 3, lslot = lane & 7;
+  const int r16 = lane & 15, g4 = lane >> 4, lrow = lane >> 3, lslot = lane & 7;
   int m0, n0;
   small_tile_of(tiles_m, tiles_n, m0, n0);
   m0 *= BM;
@@ -519,16 +535,14 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
   for (int t = 0; t < ST - 1; ++t)
     if (t < kt_n) issue(t, t);
   if (scales) rs_tile[wave * 64 + lane] = scale.value(g);
-  const int fx = (r32 >> 1) & 7;
-  const int a_row = (wm * 64 + r32) * 64, w_row = BM * 64 + (wn * 64 + r32) * 64;
-  f32x16 acc[2][2];
+  const int fx = (r16 >> 1) & 7;
+  const int a_row = (wm * 64 + r16) * 64, w_row = BM * 64 + (wn * 64 + r16) * 64;
+  f32x4 acc[4][4];                                       // [16 columns][16 rows] of the wavefront tile
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-  u32x4 fa[4][2], fw[4][2];
+    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 fa[2][4], fw[2][4];
   // k-tile t has landed (this wavefront's share); the loads of t + 1 may still be in flight
   auto wait_tile = [&](int t) {
     if (t + 1 < kt_n) wait_vmcnt<LOADS>();
@@ -548,12 +562,12 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
   for (int t = 0; t < kt_n; ++t) {
     const uint16_t *sp = lds + stage * STAGE;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int ko = ((2 * ks + grp) ^ fx) * 8;
+    for (int ks = 0; ks < 2; ++ks) {
+      const int ko = ((4 * ks + g4) ^ fx) * 8;
 #pragma unroll
-      for (int b = 0; b < 2; ++b) fa[ks][b] = *reinterpret_cast<const u32x4 *>(sp + a_row + b * 2048 + ko);
+      for (int b = 0; b < 4; ++b) fa[ks][b] = *reinterpret_cast<const u32x4 *>(sp + a_row + b * 1024 + ko);
 #pragma unroll
-      for (int a = 0; a < 2; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(sp + w_row + a * 2048 + ko);
+      for (int a = 0; a < 4; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(sp + w_row + a * 1024 + ko);
     }
     // (both halves have read k-tile t - 1 by now: its stage takes t + 2)
     if (t + ST - 1 < kt_n) issue(stage == 0 ? ST - 1 : stage - 1, t + ST - 1);
@@ -562,11 +576,11 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
     phase_end();
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = mfma32(fw[ks][a], fa[ks][b], acc[a][b]);
+        for (int b = 0; b < 4; ++b) acc[a][b] = mfma16(fw[ks][a], fa[ks][b], acc[a][b]);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
     if (!half && t + 1 < kt_n) wait_tile(t + 1);
@@ -574,7 +588,14 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
     stage = (stage + 1 == ST) ? 0 : stage + 1;
   }
   if (!half) phase_end();
-  finish_tile64<1, 1, EPI>(acc, g, reinterpret_cast<f32x4 *>(lds), wave, wave, 0, m0 + wm * 64, n0 + wn * 64, lane, rs_tile + wm * 64);
+  f32x4 *xch = reinterpret_cast<f32x4 *>(lds);
+  auto put = [&]() {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) put_tile16(acc[a][b], xch + wave * 1024, a, b, lane);
+  };
+  finish_rows<1, 1, 1, EPI>(put, g, xch, wave, 0, m0 + wm * 64, n0 + wn * 64, lane, rs_tile + wm * 64);
 }
 
 }  // namespace

@@ -1,11 +1,17 @@
 // Device helpers shared by the matrix kernels: MFMA and conversion wrappers, direct global -> LDS
 // loads, explicit waits, the GELU of the fused epilogues.  Device code only.
 //
-// MFMA shape used throughout: v_mfma_f32_32x32x16_bf16.  Per 64-lane wavefront, with
-// g = lane / 32 and r = lane % 32:
+// MFMA shapes, per 64-lane wavefront:
+// v_mfma_f32_32x32x16_bf16, with g = lane / 32 and r = lane % 32:
 //   operand "A" (32 x 16): lane holds row r,    k = 8g .. 8g+7   (8 bf16 = one 16-byte vector)
 //   operand "B" (16 x 32): lane holds column r, k = 8g .. 8g+7
 //   accumulator (32 x 32): lane holds column r, rows (i / 4) * 8 + 4g + (i % 4), i = 0..15
+// v_mfma_f32_16x16x32_bf16, with g = lane / 16 and r = lane % 16:
+//   operand "A" (16 x 32): lane holds row r,    k = 8g .. 8g+7
+//   operand "B" (32 x 16): lane holds column r, k = 8g .. 8g+7
+//   accumulator (16 x 16): lane holds column r, rows 4g + i, i = 0..3
+// The second one takes less power per multiply-add: in a loop of MFMAs alone on all compute units the board's cap
+// holds 1.83 GHz with the first shape (1.87 PFLOP/s) and 2.06 GHz with the second (2.06 PFLOP/s).
 #pragma once
 #include "et_common.h"
 
@@ -27,6 +33,10 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
 __device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
 __device__ __forceinline__ float gelu_tanh_f(float u) {
@@ -118,8 +128,7 @@ struct RowScale {
     off = (uint32_t)mc * (uint32_t)sizeof(float2);
     if (g.stats_in) {
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u)
-        if (u < g.K / 64) v[u] = piece(g, u);
+      for (int u = 0; u < BATCH; ++u) v[u] = piece(g, u < g.K / 64 ? u : g.K / 64 - 1);   // (no branch; past the end unused)
     } else {
       v[0].x = g.row_scale ? g.row_scale[mc] : 1.0f;
     }

@@ -209,6 +209,26 @@ def test_gemm_persistent_configs_walk_several_tiles_per_workgroup(cfg):
         assert rel_l2(got, ref) < 4e-3, epi
 
 
+@pytest.mark.parametrize("M,N,K", [(4500, 4304, 64), (4500, 4304, 128), (4353, 4168, 192), (511, 264, 576)])
+def test_gemm_short_contractions_in_a_stream_of_tiles(M, N, K):
+    """One, two and three k-tiles per output tile (the operand stream crosses an output tile at every one, two or
+    three of them, the stores of a tile still in flight), an odd and an even count; the tilings in k order agree bit for
+    bit.  Exact products, float32 sums of K terms (K * 2^-24 of their absolute sum, below 1e-5 here), one rounding to bf16."""
+    rng = np.random.default_rng(M + K)
+    a_bits, a = _bf(rng, (M, K))
+    w_bits, w = _bf(rng, (N, K), scale=0.05)
+    bias = (0.1 * rng.standard_normal(N)).astype(np.float32)
+    r_bits, r = _bf(rng, (M, N))
+    lin = (a.astype(np.float32) @ w.astype(np.float32).T + bias).astype(np.float64)
+    a_d, w_d, b_d, r_d = bits_to_dev(a_bits), bits_to_dev(w_bits), torch.from_numpy(bias).cuda(), bits_to_dev(r_bits)
+    for epi, ref in ((0, lin), (2, lin + r)):
+        outs = [et.et_gemm_bf16(a_d, w_d, b_d, epi, residual=r_d if epi == 2 else None, tile_config=cfg) for cfg in (0, 1, 5)]
+        got = dev_to_f64(outs[0])
+        assert np.max(np.abs(got - ref) - 2 ** -8 * np.abs(ref)) < 5e-4, epi
+        for other in outs[1:]:
+            assert torch.equal(outs[0].view(torch.int16), other.view(torch.int16)), epi
+
+
 def test_gemm_fc2_shape_with_residual_at_encoder_row_counts():
     """The fc2 step as the encoder runs it (K = 4304, bias + residual) on the kept-token and the all-token
     row counts: every element against exact products summed in float64."""
