@@ -309,7 +309,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const Ge
     for (int j = 0; j < 4; ++j) {
       const int row = j * 8 + prow, m = mb + row;
       const u32x4 v = *reinterpret_cast<const u32x4 *>(slice + row * 64 + ((pch ^ ((row >> 1) & 7)) * 8));
-      if (m < g.M && n_ok) *reinterpret_cast<u32x4 *>(g.C + (size_t)m * g.ldc + n_lane) = v;
+      if (m < g.M && n_ok) store16_through(g.C + (size_t)m * g.ldc + n_lane, v);
       if (EPI == EPI_BIAS_RES && STATS) {                     // (n_store is a multiple of 64 then)
         const float2 st = piece_moments(v);
         if (pch == 0 && m < g.M && n_ok) g.stats_out[(size_t)(n_base >> 6) * g.stats_ld + m] = st;

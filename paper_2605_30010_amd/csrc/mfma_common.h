@@ -152,6 +152,14 @@ struct RowScale {
   }
 };
 
+// Stores 16 bytes past the XCD's L2 (write-through).  Results left dirty there are written back when the kernel ends, in
+// front of the next one: 22 MB of them cost 2.2 us.  For whole 128-byte segments only (the memory side merges nothing).
+// (The s_nop keeps the data registers from being overwritten in the very next cycle, which the compiler sees to for
+// stores that it knows.)
+__device__ __forceinline__ void store16_through(uint16_t *p, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+}
+
 // Waits until at most N of this wavefront's vector-memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
