@@ -668,8 +668,8 @@ __device__ __forceinline__ int xcd_contiguous_index() {
 }
 
 // ---------------------------------------------------------------------------------------
-// attention_dma_kernel: the K tile is brought in by direct global -> LDS loads and the V tile
-// through registers, one tile ahead, two LDS stages, one barrier per 64-key tile.  Frames have
+// attention_dma_kernel: K and V tiles are brought in by direct global -> LDS loads, one tile ahead, two
+// LDS stages, one barrier per 64-key tile; three workgroups share a compute unit (168 registers).  Frames have
 // equal length n (frame f = rows f n ..) or, with `cu` given, the row ranges cu[f] .. cu[f+1]
 // (decoupled selection: the grid is sized for the longest frame and workgroups past a frame's
 // end leave at once).
@@ -682,6 +682,11 @@ __device__ __forceinline__ int xcd_contiguous_index() {
 // those slots carry the reference maximum (see below).  O^T row blocks past head_dim read
 // whatever follows a V row; that only reaches accumulator rows >= head_dim, which are never
 // stored (MFMA output rows are independent).
+// No maximum is kept over the tiles (quick_block); a workgroup whose first reference did not last walks its tiles again
+// with an online maximum (tile).  Bound: the board's power cap on many frames (1.63 GHz; matrix unit busy 58 % of the
+// clocks), on few the chain of a wavefront.  Measured against an online maximum in every tile (heads of 72, us per launch):
+// 64 x 729 320 -> 285, 32 x 729 140 -> 125, 23 x 729 99 -> 89, 8 x 729 36.9 -> 34.1, 9 x 364 16.7 -> 15.0; heads of 64,
+// 16 x 196 12.3 -> 11.7.  (Two query blocks per wavefront spill: 170.)
 // ---------------------------------------------------------------------------------------
 // LDS transpose read: every lane of a 16-lane group supplies the address of four consecutive 16-bit
 // elements; lane j of the group receives element j % 4 of the lanes j / 4, 4 + j / 4, 8 + j / 4 and
@@ -697,8 +702,18 @@ __device__ __forceinline__ uint2 lds_read_tr16(const uint16_t *p) {
 #endif
 }
 
-// What one wavefront keeps and does for its QB blocks of 32 queries, shared by the kernels below.
-template <int HD, int QB>
+// A flag in LDS that any wavefront of the workgroup can raise: cleared at the kernel's start by one thread, whose write
+// is waited for in front of the first barrier; read behind a later one.
+__device__ __forceinline__ void clear_flag(int &flag) {
+  if (threadIdx.x == 0) flag = 0;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+__device__ __forceinline__ void raise_flag(int &flag, bool mine) {
+  if (__any(mine) && (threadIdx.x & 63) == 0) flag = 1;
+}
+
+// What one wavefront keeps and does for its 32 queries, shared by the kernels below.
+template <int HD>
 struct AttentionRows {
   static constexpr int NC = (HD + 15) / 16;
   static constexpr int NDB = (HD + 31) / 32;
@@ -716,264 +731,235 @@ struct AttentionRows {
   // REF_IN_PAD it is kept bf16-representable (any reference serves as long as numerator and
   // denominator use the same one).
   static constexpr float kLazy = 8.0f;
-  u32x4 qf[QB][NC];
-  f32x16 o_acc[QB][NDB];
-  float m_ref[QB], l_run[QB];
+  u32x4 qf[NC];
+  f32x16 o_acc[NDB];
+  float m_ref, l_run;
   // Lanes whose query has met no logit above minus infinity yet (wave-uniform mask; all of them before the first keys).
   // Their reference stays 0 and their accumulators 0; the first such logit sets the reference without a rescaling.
-  unsigned long long fresh[QB];
+  unsigned long long fresh;
 
   // Q is scaled by log2(e) / sqrt(head_dim) once, here, and rounded back to bf16: the logits leave
-  // the MFMA already in the exponent's units.  A wavefront owns QB blocks of 32 queries: every K and
-  // V^T fragment it reads from LDS feeds QB MFMAs.
+  // the MFMA already in the exponent's units.
   __device__ __forceinline__ void start(const uint16_t *qbase, int q_first, int n, int ld, float scale_log2, int r32, int grp) {
+    const int q = q_first + r32;
 #pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      const int q = q_first + j * 32 + r32;
+    for (int c = 0; c < NC; ++c) {
+      const int d = c * 16 + grp * 8;
+      u32x4 raw = u32x4{0u, 0u, 0u, 0u};
+      if (q < n && d < HD) raw = *reinterpret_cast<const u32x4 *>(qbase + (size_t)q * ld + d);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int d = c * 16 + grp * 8;
-        u32x4 raw = u32x4{0u, 0u, 0u, 0u};
-        if (q < n && d < HD) raw = *reinterpret_cast<const u32x4 *>(qbase + (size_t)q * ld + d);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          qf[j][c][e] = cvt_pk_bf16(bf16lo_to_f32(raw[e]) * scale_log2, bf16hi_to_f32(raw[e]) * scale_log2);
-      }
-#pragma unroll
-      for (int b = 0; b < NDB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o_acc[j][b][i] = 0.f;
-      m_ref[j] = l_run[j] = 0.f;
-      fresh[j] = ~0ull;
+      for (int e = 0; e < 4; ++e)
+        qf[c][e] = cvt_pk_bf16(bf16lo_to_f32(raw[e]) * scale_log2, bf16hi_to_f32(raw[e]) * scale_log2);
     }
+#pragma unroll
+    for (int b = 0; b < NDB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o_acc[b][i] = 0.f;
+    m_ref = l_run = 0.f;
+    fresh = ~0ull;
   }
 
+  // Order of the keys: row r of a 32-row MFMA tile is key key_of_row(r) of its 32.  The keys of the four rows that half a
+  // wavefront's transpose read touches, rows 8 h + 4 g + (0..3) of a 16-row chunk, lie KEY_STEP apart, so that their
+  // 64-byte pieces fall into different banks (row strides of 36, 40, 48 and 16 banks; 64 and 128 take no order).
+  static constexpr int KEY_STEP = HD == 72 ? 4 : HD == 80 ? 2 : 1;
+  static __device__ __forceinline__ constexpr int key_of_row(int r) {
+    const int j = r & 3, g = (r >> 2) & 1, h = (r >> 3) & 1;
+    return (r & 16) + (KEY_STEP == 4 ? 4 * j + 2 * h + g : KEY_STEP == 2 ? 2 * j + g + 8 * h : r & 15);
+  }
   // V^T fragment of 16-key chunk c, row block b = two transpose reads.  P's k-slots 0-3 of lane group
-  // grp are keys 16 c + 4 grp + (0..3), slots 4-7 keys 16 c + 8 + 4 grp + (0..3); lane s of a 16-lane
-  // group points at key + s / 4, features 32 b + 16 (group % 2) + 4 (s % 4) .. + 3.
+  // grp are rows 16 c + 4 grp + (0..3), slots 4-7 rows 16 c + 8 + 4 grp + (0..3); lane s of a 16-lane
+  // group points at the key of row + s / 4, features 32 b + 16 (group % 2) + 4 (s % 4) .. + 3.
   static __device__ __forceinline__ u32x4 read_vfrag(const uint16_t *vs, int c, int b, int lane) {
-    const int vr_off = (4 * (lane >> 5) + ((lane & 15) >> 2)) * HD + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    const int vr_off = key_of_row(4 * (lane >> 5) + ((lane & 15) >> 2)) * HD + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
     const uint16_t *p = vs + vr_off + c * 16 * HD + b * 32;
-    const uint2 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 8 * HD);
+    const uint2 lo = lds_read_tr16(p), hi = lds_read_tr16(p + key_of_row(8) * HD);
     u32x4 v = u32x4{lo.x, lo.y, hi.x, hi.y};
     if (SUM_BY_MFMA && b == NDB - 1 && (lane & 31) == HD % 32) v = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
     return v;
   }
 
-  // Moves the reference of block j to the maximum mx of the new logits s (relative to the old one).
+  // Moves the reference to the maximum mx of the new logits s (relative to the old one).
   template <class Logits>
-  __device__ __forceinline__ void move_reference(int j, float mx, int lane, Logits subtract) {
-    const bool mine = (fresh[j] >> lane) & 1ull, none = mine && mx == -INFINITY;
+  __device__ __forceinline__ void move_reference(float mx, int lane, Logits subtract) {
+    const bool mine = (fresh >> lane) & 1ull, none = mine && mx == -INFINITY;
     // (keys past the frame can make a block of minus infinities: it moves nothing)
-    float target = m_ref[j] + (none ? 0.f : mine ? mx : fmaxf(mx, 0.f));
+    float target = m_ref + (none ? 0.f : mine ? mx : fmaxf(mx, 0.f));
     if (REF_IN_PAD) target = bf16lo_to_f32(cvt_pk_bf16(target, 0.f));
-    const float delta = target - m_ref[j];
-    if (fresh[j] != ~0ull) {               // (something accumulated: delta >= 0 in those lanes)
+    const float delta = target - m_ref;
+    if (fresh != ~0ull) {               // (something accumulated: delta >= 0 in those lanes)
       const float alpha = mine ? 1.0f : __builtin_amdgcn_exp2f(-delta);
-      l_run[j] *= alpha;
+      l_run *= alpha;
 #pragma unroll
       for (int b = 0; b < NDB; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o_acc[j][b][i] *= alpha;
+        for (int i = 0; i < 16; ++i) o_acc[b][i] *= alpha;
     }
     subtract(delta);
-    m_ref[j] = target;
-    if (REF_IN_PAD && (lane >> 5)) qf[j][NC - 1][0] = cvt_pk_bf16(-target, 0.f);
-    fresh[j] = __ballot(none);
+    m_ref = target;
+    if (REF_IN_PAD && (lane >> 5)) qf[NC - 1][0] = cvt_pk_bf16(-target, 0.f);
+    fresh = __ballot(none);
   }
 
-  // The 32 keys kv0 + 32 kb .. of the 64-key tile at kv0, whose K and V rows lie at ks and vs.
-  __device__ __forceinline__ void block(const uint16_t *ks, const uint16_t *vs, int kb, int kv0, int n, int lane) {
+  // A whole 64-key tile.  A wavefront alone is bound by latency: LDS reads, dependent MFMAs and
+  // the softmax chain follow one another.  Both 32-key blocks are taken together: all K fragments are read up
+  // front, the two MFMA chains fill each other's gaps, one maximum and one reference check serve 64 keys.
+  __device__ __forceinline__ void tile(const uint16_t *ks, const uint16_t *vs, int kv0, int n, int lane) {
     const int r32 = lane & 31, grp = lane >> 5;
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // S^T = K Q^T.  K fragments are double-buffered: the LDS read of contraction chunk c+1 is
-    // issued before the MFMAs of chunk c (scheduling barriers keep that order); the query blocks
-    // are independent MFMA chains.
-    f32x16 s_acc[QB];
-    u32x4 kf[2];
-    kf[0] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + grp * 8);
+    u32x4 kf[NC][2];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if (c + 1 < NC)
-        kf[(c + 1) & 1] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + (c + 1) * 16 + grp * 8);
-      u32x4 kk = kf[c & 1];
-      if (REF_IN_PAD && c == NC - 1 && grp) kk = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
-      __builtin_amdgcn_sched_barrier(0);
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int j = 0; j < QB; ++j) s_acc[j] = mfma32(kk, qf[j][c], c == 0 ? zero16 : s_acc[j]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // V^T fragments of the block's first 16 keys: fetched now, consumed after the softmax arithmetic
+      for (int kb = 0; kb < 2; ++kb) {
+        kf[c][kb] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + key_of_row(r32)) * HD + c * 16 + grp * 8);
+        if (REF_IN_PAD && c == NC - 1 && grp) kf[c][kb] = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
+      }
     u32x4 vf[2][NDB];
 #pragma unroll
-    for (int b = 0; b < NDB; ++b)
-      vf[0][b] = read_vfrag(vs, 2 * kb, b, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    float mx[QB];
+    for (int b = 0; b < NDB; ++b) vf[0][b] = read_vfrag(vs, 0, b, lane);
+    f32x16 s[2];
 #pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      if (!REF_IN_PAD) {
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s_acc[j][i] -= m_ref[j];
+      for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32(kf[c][kb], qf[c], c == 0 ? zero16 : s[kb]);
+    if (!REF_IN_PAD) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[kb][i] -= m_ref;
+    }
+    if (kv0 + kAttBKV > n) {               // only the last tile can hold keys past the frame
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kv0 + kb * 32 + key_of_row((i >> 2) * 8 + grp * 4 + (i & 3)) >= n) s[kb][i] = -INFINITY;
+    }
+    float m4[4];                           // four chains of maxima
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m4[u] = s[u >> 1][(u & 1) * 8];
+#pragma unroll
+    for (int i = 1; i < 8; ++i)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m4[u] = fmaxf(m4[u], s[u >> 1][(u & 1) * 8 + i]);
+    const uint32_t mb = __float_as_uint(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
+    const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
+    const float mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));      // relative to m_ref
+    if (fresh || __any(mx > kLazy))     // wave-uniform: move the reference
+      move_reference(mx, lane, [&](float delta) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
+      });
+    // P V by 16-key chunks: the exponentials of chunk c + 1 run beside the MFMAs of chunk c
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (c + 1 < 4) {
+#pragma unroll
+        for (int b = 0; b < NDB; ++b) vf[(c + 1) & 1][b] = read_vfrag(vs, c + 1, b, lane);
       }
-      if (kv0 + kAttBKV > n) {               // only the last tile can hold keys past the frame
+      float p[8];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int key = kv0 + kb * 32 + (i >> 2) * 8 + grp * 4 + (i & 3);
-          if (key >= n) s_acc[j][i] = -INFINITY;
-        }
+      for (int i = 0; i < 8; ++i) {
+        p[i] = __builtin_amdgcn_exp2f(s[c >> 1][(c & 1) * 8 + i]);
+        if (!SUM_BY_MFMA) l_run += p[i];
       }
-      float m = s_acc[j][0];
+      u32x4 pf;
+      pf.x = cvt_pk_bf16(p[0], p[1]); pf.y = cvt_pk_bf16(p[2], p[3]);
+      pf.z = cvt_pk_bf16(p[4], p[5]); pf.w = cvt_pk_bf16(p[6], p[7]);
 #pragma unroll
-      for (int i = 1; i < 16; ++i) m = fmaxf(m, s_acc[j][i]);
-      // maximum over the two lane halves (the other 16 keys of the same query), without an LDS round trip
+      for (int b = 0; b < NDB; ++b) o_acc[b] = mfma32(vf[c & 1][b], pf, o_acc[b]);
+    }
+  }
+
+  // The 32 keys kv0 + 32 kb .. without an online maximum: the reference is the maximum of the first such block (`first`) and
+  // stays.  A probability is then 2^(s - reference), whatever its size: float32 and bf16 carry the exponent, so nothing is
+  // lost until a later logit exceeds the first block's maximum by some 2^60, which `sound` finds out at the end.  This
+  // leaves one exponential and half a conversion per logit on the vector unit.  EDGE: the first tile, and the last one,
+  // which can hold keys past the frame.
+  template <bool EDGE>
+  __device__ __forceinline__ void quick_block(const uint16_t *ks, const uint16_t *vs, int kb, int kv0, int n, int lane, bool first) {
+    const int r32 = lane & 31, grp = lane >> 5;
+    u32x4 kf[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      kf[c] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + key_of_row(r32)) * HD + c * 16 + grp * 8);
+      if (REF_IN_PAD && c == NC - 1 && grp) kf[c] = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
+    }
+    u32x4 vf[2][NDB];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int b = 0; b < NDB; ++b) vf[hh][b] = read_vfrag(vs, 2 * kb + hh, b, lane);
+    f32x16 s;                                // (where no slot is spare the reference is subtracted in the accumulator)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = REF_IN_PAD ? 0.f : -m_ref;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) s = mfma32(kf[c], qf[c], s);
+    if (EDGE && kv0 + kAttBKV > n) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (kv0 + kb * 32 + key_of_row((i >> 2) * 8 + grp * 4 + (i & 3)) >= n) s[i] = -INFINITY;
+    }
+    if (EDGE && first) {
+      float m = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) m = fmaxf(m, s[i]);
       const uint32_t mb = __float_as_uint(m);
       const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
-      mx[j] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));   // relative to m_ref
+      m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+      if (!(fabsf(m) < INFINITY)) m = 0.f;      // (no finite maximum: `sound` finds a later one, or a NaN or an infinity)
+      if (REF_IN_PAD) m = bf16lo_to_f32(cvt_pk_bf16(m, 0.f));
+      m_ref = m;
+      if (REF_IN_PAD && grp) qf[NC - 1][0] = cvt_pk_bf16(-m, 0.f);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] -= m;
     }
-    bool over = false;
-    unsigned long long any_fresh = 0ull;
+    float p[16];
 #pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      over = over || mx[j] > kLazy;
-      any_fresh |= fresh[j];
+    for (int i = 0; i < 16; ++i) {
+      p[i] = __builtin_amdgcn_exp2f(s[i]);
+      if (!SUM_BY_MFMA) l_run += p[i];
     }
-    if (any_fresh || __any(over)) {          // wave-uniform: move the references
-#pragma unroll
-      for (int j = 0; j < QB; ++j)
-        move_reference(j, mx[j], lane, [&](float delta) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s_acc[j][i] -= delta;
-        });
-    }
-    u32x4 pf[QB][2];
-#pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      float p[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        p[i] = __builtin_amdgcn_exp2f(s_acc[j][i]);
-        if (!SUM_BY_MFMA) l_run[j] += p[i];
-      }
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        u32x4 v;
-        v.x = cvt_pk_bf16(p[hh * 8 + 0], p[hh * 8 + 1]); v.y = cvt_pk_bf16(p[hh * 8 + 2], p[hh * 8 + 3]);
-        v.z = cvt_pk_bf16(p[hh * 8 + 4], p[hh * 8 + 5]); v.w = cvt_pk_bf16(p[hh * 8 + 6], p[hh * 8 + 7]);
-        pf[j][hh] = v;
-      }
-    }
-    // O^T += V^T P^T; row blocks and query blocks are independent MFMA chains.
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      if (hh == 0) {
+      u32x4 pf;
+      pf.x = cvt_pk_bf16(p[hh * 8 + 0], p[hh * 8 + 1]); pf.y = cvt_pk_bf16(p[hh * 8 + 2], p[hh * 8 + 3]);
+      pf.z = cvt_pk_bf16(p[hh * 8 + 4], p[hh * 8 + 5]); pf.w = cvt_pk_bf16(p[hh * 8 + 6], p[hh * 8 + 7]);
 #pragma unroll
-        for (int b = 0; b < NDB; ++b)
-          vf[1][b] = read_vfrag(vs, 2 * kb + 1, b, lane);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int b = 0; b < NDB; ++b)
-#pragma unroll
-        for (int j = 0; j < QB; ++j) o_acc[j][b] = mfma32(vf[hh][b], pf[j][hh], o_acc[j][b]);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int b = 0; b < NDB; ++b) o_acc[b] = mfma32(vf[hh][b], pf, o_acc[b]);
     }
   }
 
-  // A whole 64-key tile.  One query block alone (QB = 1) is bound by latency, not by issue: LDS reads, dependent MFMAs and
-  // the softmax chain follow one another.  Both 32-key blocks are then taken together: all K fragments are read up
-  // front, the two MFMA chains fill each other's gaps, one maximum and one reference check serve 64 keys (heads of 72,
-  // 8 x 729: 35.8 -> 34.0 us per launch, 5 x 729: 26.4 -> 25.0).
-  __device__ __forceinline__ void tile(const uint16_t *ks, const uint16_t *vs, int kv0, int n, int lane) {
-    if constexpr (QB > 1) {
+  // Whether quick_block's result stands: the weights' sums are of ordinary size and everything is finite.
+  __device__ __forceinline__ bool sound(int r32) const {
+    const float l = denominator(r32);
+    float z = 0.f;
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) block(ks, vs, kb, kv0, n, lane);
-    } else {
-      const int r32 = lane & 31, grp = lane >> 5;
-      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      u32x4 kf[NC][2];
+    for (int b = 0; b < NDB; ++b)
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          kf[c][kb] = *reinterpret_cast<const u32x4 *>(ks + (kb * 32 + r32) * HD + c * 16 + grp * 8);
-          if (REF_IN_PAD && c == NC - 1 && grp) kf[c][kb] = u32x4{0x3F80u, 0u, 0u, 0u};   // slot head_dim reads 1, the rest 0
-        }
-      u32x4 vf[2][NDB];
-#pragma unroll
-      for (int b = 0; b < NDB; ++b) vf[0][b] = read_vfrag(vs, 0, b, lane);
-      f32x16 s[2];
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32(kf[c][kb], qf[0][c], c == 0 ? zero16 : s[kb]);
-      if (!REF_IN_PAD) {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s[kb][i] -= m_ref[0];
-      }
-      if (kv0 + kAttBKV > n) {               // only the last tile can hold keys past the frame
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (kv0 + kb * 32 + (i >> 2) * 8 + grp * 4 + (i & 3) >= n) s[kb][i] = -INFINITY;
-      }
-      float m4[4];                           // four chains of maxima
-#pragma unroll
-      for (int u = 0; u < 4; ++u) m4[u] = s[u >> 1][(u & 1) * 8];
-#pragma unroll
-      for (int i = 1; i < 8; ++i)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) m4[u] = fmaxf(m4[u], s[u >> 1][(u & 1) * 8 + i]);
-      const uint32_t mb = __float_as_uint(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
-      const auto r = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
-      const float mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));      // relative to m_ref
-      if (fresh[0] || __any(mx > kLazy))     // wave-uniform: move the reference
-        move_reference(0, mx, lane, [&](float delta) {
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s[kb][i] -= delta;
-        });
-      // P V by 16-key chunks: the exponentials of chunk c + 1 run beside the MFMAs of chunk c
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (c + 1 < 4) {
-#pragma unroll
-          for (int b = 0; b < NDB; ++b) vf[(c + 1) & 1][b] = read_vfrag(vs, c + 1, b, lane);
-        }
-        float p[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          p[i] = __builtin_amdgcn_exp2f(s[c >> 1][(c & 1) * 8 + i]);
-          if (!SUM_BY_MFMA) l_run[0] += p[i];
-        }
-        u32x4 pf;
-        pf.x = cvt_pk_bf16(p[0], p[1]); pf.y = cvt_pk_bf16(p[2], p[3]);
-        pf.z = cvt_pk_bf16(p[4], p[5]); pf.w = cvt_pk_bf16(p[6], p[7]);
-#pragma unroll
-        for (int b = 0; b < NDB; ++b) o_acc[0][b] = mfma32(vf[c & 1][b], pf, o_acc[0][b]);
-      }
-    }
+      for (int i = 0; i < 16; ++i)
+        if (b * 32 + (i >> 2) * 8 < HD) z = fmaf(o_acc[b][i], 0.f, z);          // (rows past head_dim hold anything)
+    return l > 0x1p-60f && l < 0x1p60f && z == 0.f;
   }
 
-  // Softmax denominator of this lane's query of block j.
-  __device__ __forceinline__ float denominator(int j, int r32) const {
+  // Softmax denominator of this lane's query.
+  __device__ __forceinline__ float denominator(int r32) const {
     if (SUM_BY_MFMA) {                        // accumulator row head_dim of O^T: lane group (row % 8) / 4, register (row / 8) * 4 + row % 4
       constexpr int ROW = HD % 32;
-      return __shfl(o_acc[j][NDB - 1][(ROW / 8) * 4 + (ROW % 4)], r32 + 32 * ((ROW % 8) / 4), 64);
+      return __shfl(o_acc[NDB - 1][(ROW / 8) * 4 + (ROW % 4)], r32 + 32 * ((ROW % 8) / 4), 64);
     }
-    return l_run[j] + __shfl_xor(l_run[j], 32, 64);
+    return l_run + __shfl_xor(l_run, 32, 64);
   }
 };
 
-template <int HD, int QB, int MINB>
+template <int HD, int MINB>
 __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     const uint16_t *__restrict__ qkv, const int32_t *__restrict__ cu, int n, int n_heads, int n_qblk, float scale_log2,
     uint16_t *__restrict__ out) {
-  using Rows = AttentionRows<HD, QB>;
+  using Rows = AttentionRows<HD>;
   constexpr int NDB = Rows::NDB;
   constexpr int STAGES = 2;
   constexpr int T_LOADS = HD / 8;            // 1 KiB pieces of a K (or V) tile: 64 keys * HD * 2 bytes
@@ -984,11 +970,13 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
   // behind the tile (rounded up generously).
   constexpr int PAD = (NDB * 32 - HD) * kAttBKV + 64;
   __shared__ __align__(16) uint16_t lds[STAGES * STAGE + PAD];
+  __shared__ int redo;
+  clear_flag(redo);
 
   // One-dimensional grid over (frame, head, query block), query block fastest, so that the query blocks
   // of one (frame, head) - which read the same K and V - run on one XCD and share its L2.
   const int v = xcd_contiguous_index();
-  const int q0 = (v % n_qblk) * (kAttBQ * QB), h = (v / n_qblk) % n_heads, f = v / (n_qblk * n_heads);
+  const int q0 = (v % n_qblk) * kAttBQ, h = (v / n_qblk) % n_heads, f = v / (n_qblk * n_heads);
   int start = f * n;
   if (cu) {                                            // ragged frames (workgroup-uniform)
     start = cu[f];
@@ -1003,91 +991,77 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
   const uint16_t *kbase = qbase + D;                    // (V: + D again)
   const int n_tiles = (n + kAttBKV - 1) / kAttBKV;
 
-  // Pieces j = wave, wave + 4, ... of a tile belong to this wavefront.  The K tile comes in by direct
-  // global -> LDS loads, the V tile through registers (ordinary loads now, written to LDS one tile
-  // later): a compute unit keeps only about 20 KiB of direct loads in flight (measured: the 19th
-  // 1-KiB load of a wavefront, or the 6th of each of four, blocks until the first has landed), and
-  // two workgroups' K and V tiles, 36 KiB per step, kept the wavefronts blocked at the issue.
-  // Per-lane source pointers advance by a constant per tile; the last tile has pointers of its own,
-  // with the key rows clamped to the frame (masked later, in bounds).  V's pointers are K's + D.
-  const uint16_t *cur[PW], *src_last[PW];
-  int dst_off[PW];                           // elements into the K (or V) tile
-  bool mine[PW];
+  // Pieces j = wave, wave + 4, ... of a tile belong to this wavefront: K and V by direct global -> LDS loads.  A scalar
+  // origin that advances by a constant per tile plus 32-bit lane offsets; the last tile has offsets of its own, with the
+  // key rows clamped to the frame (masked later, in bounds).  V's origin is K's + D.
+  uint32_t off[PW], off_last[PW];            // bytes from the tile's origin
 #pragma unroll
   for (int j = 0; j < PW; ++j) {
-    const int ld_id = j * kAttWaves + wave;
-    mine[j] = ld_id < T_LOADS;               // wave-uniform
-    const int q = (mine[j] ? ld_id : 0) * 64 + lane, key = q / (HD / 8), ch = q % (HD / 8);
-    int kl = (n_tiles - 1) * kAttBKV + key;
-    if (kl >= n) kl = n - 1;
-    cur[j] = kbase + (size_t)key * ld + ch * 8;
-    src_last[j] = kbase + (size_t)kl * ld + ch * 8;
-    dst_off[j] = (mine[j] ? ld_id : 0) * 512;
-    if (n_tiles == 1) cur[j] = src_last[j];
+    const int q = min(j * kAttWaves + wave, T_LOADS - 1) * 64 + lane, key = q / (HD / 8), ch = q % (HD / 8);
+    off[j] = (uint32_t)(key * ld + ch * 8) * 2u;
+    off_last[j] = (uint32_t)(min(key, n - 1 - (n_tiles - 1) * kAttBKV) * ld + ch * 8) * 2u;
   }
-  u32x4 vreg[PW];
-  int next_tile = 0;
-  auto issue = [&](int stage) {                        // tile `next_tile`: K into `stage`, V into registers
-    const int sb = stage * STAGE;
+  auto issue = [&](int t) {                            // tile t into stage t % 2
+    const uint16_t *k0 = kbase + (size_t)t * kAttBKV * ld;
+    uint16_t *dst = lds + (t & 1) * STAGE;
+    const bool last = t + 1 == n_tiles;
 #pragma unroll
-    for (int j = 0; j < PW; ++j)
-      if (mine[j]) ET_LDS_DMA16(cur[j], lds + sb + dst_off[j]);
-#pragma unroll
-    for (int j = 0; j < PW; ++j)
-      if (mine[j]) vreg[j] = *reinterpret_cast<const u32x4 *>(cur[j] + D);
-    ++next_tile;
-    if (next_tile == n_tiles - 1) {
-#pragma unroll
-      for (int j = 0; j < PW; ++j) cur[j] = src_last[j];
-    } else if (next_tile < n_tiles - 1) {
-#pragma unroll
-      for (int j = 0; j < PW; ++j) cur[j] += kAttBKV * ld;
+    for (int j = 0; j < PW; ++j) {
+      const int piece = j * kAttWaves + wave;          // (wave-uniform)
+      if (piece < T_LOADS) {
+        const uint32_t o = last ? off_last[j] : off[j];
+        lds_dma16_untracked(k0, o, dst + piece * 512);
+        lds_dma16_untracked(k0 + D, o, dst + K_ELEMS + piece * 512);
+      }
     }
   };
-  auto write_v = [&](int stage) {                      // the V tile in registers -> `stage`
-    uint16_t *vd = lds + stage * STAGE + K_ELEMS + lane * 8;
-#pragma unroll
-    for (int j = 0; j < PW; ++j)
-      if (mine[j]) *reinterpret_cast<u32x4 *>(vd + dst_off[j]) = vreg[j];
-  };
-
-  issue(0);
-
   Rows rows;
-  rows.start(qbase, q0 + wave * QB * 32, n, ld, scale_log2, r32, grp);
-
-  for (int t = 0; t < n_tiles; ++t) {
-    const int kv0 = t * kAttBKV, stage = t & 1;
-    wait_vmcnt<0>();                           // tile t: K has landed in LDS, V in registers
-    write_v(stage);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();              // ... for every wavefront; everyone is done with tile t-1
-    asm volatile("" ::: "memory");
-    if (t + 1 < n_tiles) issue(stage ^ 1);
-    const uint16_t *ks = lds + stage * STAGE;
-    rows.tile(ks, ks + K_ELEMS, kv0, n, lane);
-  }
-
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-    const float inv = 1.0f / rows.denominator(j, r32);
-    const int q = q0 + (wave * QB + j) * 32 + r32;
-    if (q < n) {
-      uint16_t *orow = out + ((size_t)start + q) * D + h * HD;
-#pragma unroll
-      for (int b = 0; b < NDB; ++b)
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          const int d = b * 32 + qd * 8 + grp * 4;
-          if (d < HD) {
-            const f32x16 &o = rows.o_acc[j][b];
-            uint2 w;
-            w.x = cvt_pk_bf16(o[qd * 4 + 0] * inv, o[qd * 4 + 1] * inv);
-            w.y = cvt_pk_bf16(o[qd * 4 + 2] * inv, o[qd * 4 + 3] * inv);
-            *reinterpret_cast<uint2 *>(orow + d) = w;
-          }
-        }
+  // One pass over the key tiles; tile(t, K, V) takes them in order.
+  auto pass = [&](auto tile) {
+    issue(0);
+    rows.start(qbase, q0 + wave * 32, n, ld, scale_log2, r32, grp);
+    for (int t = 0; t < n_tiles; ++t) {
+      wait_vmcnt<0>();                         // tile t has landed
+      __builtin_amdgcn_s_barrier();            // ... for every wavefront; everyone is done with tile t-1
+      asm volatile("" ::: "memory");
+      if (t + 1 < n_tiles) issue(t + 1);
+      const uint16_t *ks = lds + (t & 1) * STAGE;
+      tile(t, ks, ks + K_ELEMS);
     }
+  };
+  auto careful = [&](int t, const uint16_t *ks, const uint16_t *vs) { rows.tile(ks, vs, t * kAttBKV, n, lane); };
+  pass([&](int t, const uint16_t *ks, const uint16_t *vs) {
+    const int kv0 = t * kAttBKV;
+    const bool edge = t == 0 || t + 1 == n_tiles;
+    if (edge) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
+    } else {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+    }
+  });
+  raise_flag(redo, !rows.sound(r32));
+  __syncthreads();
+  if (__builtin_expect(redo, 0)) pass(careful);
+
+  const float inv = 1.0f / rows.denominator(r32);
+  const int q = q0 + wave * 32 + r32;
+  if (q < n) {
+    uint16_t *orow = out + ((size_t)start + q) * D + h * HD;
+#pragma unroll
+    for (int b = 0; b < NDB; ++b)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        const int d = b * 32 + qd * 8 + grp * 4;
+        if (d < HD) {
+          const f32x16 &o = rows.o_acc[b];
+          uint2 w;
+          w.x = cvt_pk_bf16(o[qd * 4 + 0] * inv, o[qd * 4 + 1] * inv);
+          w.y = cvt_pk_bf16(o[qd * 4 + 2] * inv, o[qd * 4 + 3] * inv);
+          *reinterpret_cast<uint2 *>(orow + d) = w;
+        }
+      }
   }
 }
 
@@ -1096,7 +1070,8 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
 // one after the other (1.4 us per tile): the 8 wavefronts of a workgroup form KG groups; a group takes 256 / KG
 // queries, one block of 32 per wavefront, and every KG-th key tile, with LDS stages of its own.  The groups'
 // partial results (reference maximum, denominator, O^T) meet in LDS; a thread finishes 8 features of a query
-// and stores 16 bytes.  (One query block per workgroup, its tiles split over 4 wavefronts with private slots, loads every
+// and stores 16 bytes.  (Without the online maximum: 1 x 729 12.1 -> 11.4 us, 2 x 729 16.4 -> 14.9, 3 x 364 10.5 -> 10.0.)
+// (One query block per workgroup, its tiles split over 4 wavefronts with private slots, loads every
 // tile once per 32 queries: 729 tokens x 16 heads 18.0 -> 13.6 us, and slower than the kernel above from two frames on.)
 // ---------------------------------------------------------------------------------------
 template <int HD, int KG>
@@ -1106,7 +1081,7 @@ struct GroupShape {
   static constexpr int O_LD = NDB * 32 + 4;                 // floats of a query's partial row: no bank conflicts on 16-byte cells
   static constexpr size_t kStages = (size_t)KG * GROUP * 2, kPartials = (size_t)8 * 32 * O_LD * 4;
   static constexpr size_t kLdsBytes = kStages > kPartials ? kStages : kPartials;
-  static constexpr bool kFits = kLdsBytes + 8 * 32 * sizeof(float2) <= 160 * 1024;
+  static constexpr bool kFits = kLdsBytes + 8 * 32 * sizeof(float2) + sizeof(int) <= 160 * 1024;
 };
 
 template <int HD, int KG>
@@ -1114,10 +1089,12 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
     const uint16_t *__restrict__ qkv, const int32_t *__restrict__ cu, int n, int n_heads, int n_qblk, float scale_log2,
     uint16_t *__restrict__ out) {
   using S = GroupShape<HD, KG>;
-  using Rows = AttentionRows<HD, 1>;
+  using Rows = AttentionRows<HD>;
   constexpr int WPG = S::WPG, T_LOADS = HD / 8, PW = (T_LOADS + WPG - 1) / WPG;
   extern __shared__ __align__(16) uint16_t lds[];
   __shared__ float2 ml[8][32];
+  __shared__ int redo;
+  clear_flag(redo);
   const int v = xcd_contiguous_index();
   const int q0 = (v % n_qblk) * (32 * WPG), h = (v / n_qblk) % n_heads, f = v / (n_qblk * n_heads);
   int start = f * n;
@@ -1136,56 +1113,75 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
   const int n_tiles = (n + kAttBKV - 1) / kAttBKV;
   uint16_t *mem = lds + grp_k * S::GROUP;
 
-  // Pieces wi, wi + WPG, ... of the group's tiles: K by direct loads, V through registers (see above).  Key rows past
-  // the frame are clamped to its last one (masked later).
-  u32x4 vreg[PW];
+  // Pieces wi, wi + WPG, ... of the group's tiles by direct loads (see above).  Key rows past the frame are clamped to
+  // its last one (masked later).
+  uint32_t off[PW], off_last[PW];                      // bytes from the tile's origin
+#pragma unroll
+  for (int j = 0; j < PW; ++j) {
+    const int piece = min(j * WPG + wi, T_LOADS - 1) * 64 + lane, key = piece / (HD / 8), ch = piece % (HD / 8);
+    off[j] = (uint32_t)(key * ld + ch * 8) * 2u;
+    off_last[j] = (uint32_t)(min(key, n - 1 - (n_tiles - 1) * kAttBKV) * ld + ch * 8) * 2u;
+  }
   auto issue = [&](int t, int stage) {
-    const uint16_t *src[PW];
+    const uint16_t *k0 = kbase + (size_t)t * kAttBKV * ld;
+    uint16_t *dst = mem + stage * 2 * S::TILE;
+    const bool last = t + 1 == n_tiles;
 #pragma unroll
     for (int j = 0; j < PW; ++j) {
-      const int id = j * WPG + wi, q = (id < T_LOADS ? id : 0) * 64 + lane, key = q / (HD / 8), ch = q % (HD / 8);
-      const int row = t * kAttBKV + key;
-      src[j] = kbase + (size_t)(row < n ? row : n - 1) * ld + ch * 8;
+      const int piece = j * WPG + wi;                  // (wave-uniform)
+      if (piece < T_LOADS) {
+        const uint32_t o = last ? off_last[j] : off[j];
+        lds_dma16_untracked(k0, o, dst + piece * 512);
+        lds_dma16_untracked(k0 + D, o, dst + S::TILE + piece * 512);
+      }
     }
-#pragma unroll
-    for (int j = 0; j < PW; ++j)
-      if (j * WPG + wi < T_LOADS) ET_LDS_DMA16(src[j], mem + stage * 2 * S::TILE + (j * WPG + wi) * 512);
-#pragma unroll
-    for (int j = 0; j < PW; ++j)
-      if (j * WPG + wi < T_LOADS) vreg[j] = *reinterpret_cast<const u32x4 *>(src[j] + D);
   };
-  if (grp_k < n_tiles) issue(grp_k, 0);
   Rows rows;
-  rows.start(qbase, q0 + wi * 32, n, ld, scale_log2, r32, grp);
-  int stage = 0;
-  for (int t0 = 0; t0 < n_tiles; t0 += KG, stage ^= 1) {
-    const int t = t0 + grp_k;
-    wait_vmcnt<0>();                                   // tile t: K has landed in LDS, V in registers
-    if (t < n_tiles) {
-#pragma unroll
-      for (int j = 0; j < PW; ++j)
-        if (j * WPG + wi < T_LOADS)
-          *reinterpret_cast<u32x4 *>(mem + (stage * 2 + 1) * S::TILE + (j * WPG + wi) * 512 + lane * 8) = vreg[j];
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();                      // ... for every wavefront; everyone is done with the other stage
-    asm volatile("" ::: "memory");
-    if (t + KG < n_tiles) issue(t + KG, stage ^ 1);
-    if (t < n_tiles) {
+  const bool has_tiles = grp_k < n_tiles;              // (wave-uniform)
+  auto pass = [&](auto tile) {
+    if (has_tiles) issue(grp_k, 0);
+    rows.start(qbase, q0 + wi * 32, n, ld, scale_log2, r32, grp);
+    int stage = 0;
+    for (int t0 = 0; t0 < n_tiles; t0 += KG, stage ^= 1) {
+      const int t = t0 + grp_k;
+      wait_vmcnt<0>();                                 // tile t has landed
+      __builtin_amdgcn_s_barrier();                    // ... for every wavefront; everyone is done with the other stage
+      asm volatile("" ::: "memory");
+      if (t + KG < n_tiles) issue(t + KG, stage ^ 1);
       const uint16_t *ks = mem + stage * 2 * S::TILE;
-      rows.tile(ks, ks + S::TILE, t * kAttBKV, n, lane);
+      if (t < n_tiles) tile(t, ks, ks + S::TILE);
     }
-  }
-  const float l = rows.denominator(0, r32);
+  };
+  pass([&](int t, const uint16_t *ks, const uint16_t *vs) {
+    const int kv0 = t * kAttBKV;
+    const bool edge = t == grp_k || t + 1 == n_tiles;
+    if (edge) {
+#pragma unroll 1                                       // (code that runs once or twice is kept short: it comes in cold)
+      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == grp_k && kb == 0);
+    } else {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+    }
+  });
   // (a group without a tile, or with nothing but minus infinities, has no part in the sum)
-  if (grp == 0) ml[wave][r32] = ((rows.fresh[0] >> lane) & 1ull) ? make_float2(-INFINITY, 0.f) : make_float2(rows.m_ref[0], l);
+  auto leave = [&](bool nothing) {
+    const float l = rows.denominator(r32);
+    if (grp == 0) ml[wave][r32] = nothing ? make_float2(-INFINITY, 0.f) : make_float2(rows.m_ref, l);
+  };
+  leave(!has_tiles);
+  raise_flag(redo, has_tiles && !rows.sound(r32));
   __syncthreads();                                     // the stages have been read
+  if (__builtin_expect(redo, 0)) {
+    pass([&](int t, const uint16_t *ks, const uint16_t *vs) { rows.tile(ks, vs, t * kAttBKV, n, lane); });
+    leave((rows.fresh >> lane) & 1ull);
+    __syncthreads();
+  }
   float *part = reinterpret_cast<float *>(lds);
 #pragma unroll
   for (int b = 0; b < S::NDB; ++b)
 #pragma unroll
     for (int qd = 0; qd < 4; ++qd) {
-      const f32x16 &a = rows.o_acc[0][b];
+      const f32x16 &a = rows.o_acc[b];
       *reinterpret_cast<f32x4 *>(part + (wave * 32 + r32) * S::O_LD + b * 32 + qd * 8 + grp * 4) =
           f32x4{a[qd * 4], a[qd * 4 + 1], a[qd * 4 + 2], a[qd * 4 + 3]};
     }
@@ -1379,17 +1375,8 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
     if (n_tiles >= 5 && blocks(128) * pairs <= cus)
       return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s);
   }
-  if (HD <= 80 && blocks(2 * kAttBQ) * pairs >= 6 * cus) {
-    // Two query blocks per wavefront (half the LDS reads and loads per query) from three rounds of workgroups on; below,
-    // three smaller workgroups per compute unit win (heads of 72, one / two blocks, us per launch: 64 x 729
-    // 285 / 274, 32 x 729 152 / 150, 23 x 729 94 / 104, 12 x 729 54 / 66, 32 x 364 39 / 48, 16 x 364 23 / 28; ragged 13 frames of
-    // 700-729 55 / 65).
-    hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 80 ? 2 : 1), 2>), dim3((unsigned)(blocks(2 * kAttBQ) * pairs)),
-                       dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(2 * kAttBQ), scale_log2, out);
-  } else {
-    hipLaunchKernelGGL((attention_dma_kernel<HD, 1, (HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
-                       dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(kAttBQ), scale_log2, out);
-  }
+  hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 80 ? 3 : HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
+                     dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(kAttBQ), scale_log2, out);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

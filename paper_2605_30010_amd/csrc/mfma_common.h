@@ -59,6 +59,18 @@ __device__ __forceinline__ float gelu_tanh_f(float u) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
                                    (__attribute__((address_space(3))) void *)(lptr), 16, (imm), 0)
 
+// The same load, unknown to the compiler: it has every LDS transpose read behind a direct load that it knows wait for that
+// load (as if the read could overlap it), which undoes a prefetch.  The caller's own waits (wait_vmcnt) cover it; the
+// compiler's waits for its own loads stay right, since an operation that it does not count only makes them longer.  M0 is
+// written behind its back: not beside the macros above in one kernel.
+__device__ __forceinline__ void lds_dma16_untracked(const uint16_t *base, uint32_t byte_off, uint16_t *dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)dst;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
+               ::"v"(byte_off), "s"(__builtin_amdgcn_readfirstlane(to)), "s"(base) : "memory");
+#endif
+}
+
 // The i-th of a group of four loads that share one LDS base (M0 cannot be rewritten before the
 // previous load has read it): `src` has to be lowered by (i % 4) KiB by the caller.
 __device__ __forceinline__ void lds_dma16_of4(const char *src, uint16_t *dst, int i) {

@@ -412,3 +412,33 @@ def test_attention_with_two_query_blocks_per_wavefront(n_heads, hd, lens):
     for out in got:
         assert rel_l2(dev_to_f64(out), ref) < 6e-3
         assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05
+
+
+@pytest.mark.parametrize("n_heads,hd,lens", [
+    (16, 72, [729] * 11), (16, 72, [729]), (16, 72, [729, 700]),        # 128 queries per workgroup; four and two groups
+    (12, 64, [196] * 30), (4, 64, [65, 1, 129]), (2, 16, [300] * 3), (3, 32, [511, 64]), (2, 80, [400, 321]), (2, 96, [330]),
+    (1, 128, [577]),
+])
+@pytest.mark.parametrize("jump,v_scale", [(100.0, 1.0), (28.0, 1.0e28), (-100.0, 1.0)])
+def test_attention_where_the_first_reference_does_not_last(n_heads, hd, lens, jump, v_scale):
+    """The reference maximum is the one of a frame's (or of a group of wavefronts') first 32 keys.  Later keys of every
+    second query exceed it by e^100 (the weights' sum leaves its range), by e^28 with values of 1e28 (the sum stays, the
+    weighted values leave float32), or lie e^100 below (nothing happens): the result is the oracle's in all of them.
+    Bounds as in the oracle test, relative to the values' scale."""
+    rng = np.random.default_rng(n_heads * hd + len(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, D = int(cu[-1]), n_heads * hd
+    qkv = rng.standard_normal((rows, 3 * D))
+    late = np.concatenate([np.arange(n) >= n * 0.55 for n in lens])
+    heads = qkv.reshape(rows, 3, n_heads, hd)
+    heads[:, 0, :, 0] = np.where(np.arange(rows) % 2 == 0, 8.0, 0.0)[:, None]      # q . u
+    heads[:, 1, :, 0] = np.where(late, jump * math.sqrt(hd) / 8.0, 0.0)[:, None]   # k . u: the logit is shifted by `jump`
+    heads[:, 2] *= v_scale
+    bits = f32_to_bf16_bits(qkv.astype(np.float32))
+    ref = _attention_ref(bf16_bits_to_f32(bits).astype(np.float64), cu, n_heads, hd)
+    got = [et.et_attention(bits_to_dev(bits), torch.from_numpy(cu).cuda(), max(lens), n_heads, hd)]
+    if len(set(lens)) == 1:
+        got.append(et.et_attention_uniform(bits_to_dev(bits), len(lens), lens[0], n_heads, hd))
+    for out in got:
+        assert rel_l2(dev_to_f64(out), ref) < 6e-3
+        assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05 * v_scale
