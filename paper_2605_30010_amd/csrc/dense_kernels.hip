@@ -319,23 +319,6 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const Ge
   }
 }
 
-// Order of a quarter of gemm_stream_kernel's k-tile: one MFMA in front of each LDS read, then the direct loads GAP MFMAs apart, the rest behind them.
-template <int READS, int LOADS, int MFMAS>
-__device__ __forceinline__ void mfma_between() {
-  constexpr int GAP = LOADS ? ((MFMAS - READS) / (LOADS + 1) > 0 ? (MFMAS - READS) / (LOADS + 1) : 1) : 0;
-#pragma unroll
-  for (int i = 0; i < READS; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < LOADS; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, GAP, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-  }
-  if constexpr (MFMAS - READS - LOADS * GAP > 0) __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - READS - LOADS * GAP, 0);
-}
-
 // ---------------------------------------------------------------------------------------
 // Operands are brought in by direct global -> LDS loads (global_load_lds_dwordx4): no staging
 // registers and no LDS write instructions.  One wavefront load moves 64 x 16 bytes to 1 KiB of
@@ -1033,12 +1016,10 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
   pass([&](int t, const uint16_t *ks, const uint16_t *vs) {
     const int kv0 = t * kAttBKV;
     const bool edge = t == 0 || t + 1 == n_tiles;
-    if (edge) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
-    } else {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+#pragma unroll                                         // (in this form the registers suffice: no spill in the loop)
+    for (int kb = 0; kb < 2; ++kb) {
+      if (edge) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
+      else rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
     }
   });
   raise_flag(redo, !rows.sound(r32));
@@ -1375,7 +1356,8 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
     if (n_tiles >= 5 && blocks(128) * pairs <= cus)
       return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s);
   }
-  hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 80 ? 3 : HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
+  // three workgroups per compute unit where that spills nothing (heads of 80: 17.1 us with three, 15.1 with two, 8 x 364)
+  hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 72 ? 3 : HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
                      dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(kAttBQ), scale_log2, out);
   ET_LAUNCH_CHECK();
   return ET_OK;

@@ -172,6 +172,23 @@ __device__ __forceinline__ void store16_through(uint16_t *p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
 }
 
+// Order of a quarter of a k-tile (gemm_stream_kernel, gemm_duo_kernel): one MFMA in front of each LDS read, then the direct loads GAP MFMAs apart, the rest behind them.
+template <int READS, int LOADS, int MFMAS>
+__device__ __forceinline__ void mfma_between() {
+  constexpr int GAP = LOADS ? ((MFMAS - READS) / (LOADS + 1) > 0 ? (MFMAS - READS) / (LOADS + 1) : 1) : 0;
+#pragma unroll
+  for (int i = 0; i < READS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, GAP, 0);
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+  }
+  if constexpr (MFMAS - READS - LOADS * GAP > 0) __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - READS - LOADS * GAP, 0);
+}
+
 // Waits until at most N of this wavefront's vector-memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
