@@ -13,7 +13,7 @@ namespace et {
 //   0  256 x 256, 8 wavefronts, persistent, one workgroup per compute unit
 //   1  128 x 128, 4 wavefronts, persistent, two workgroups per compute unit
 //   2   64 x  64, k split over 4 wavefronts, two workgroups per compute unit      (gemm_small.hip)
-//   3  128 x  64, k split over 4 groups of 2 wavefronts                           (gemm_small.hip)
+//   3  128 x  64, k split over 2 groups of 4 wavefronts (4 of 2 where k-tiles are odd) (gemm_small.hip)
 //   4  128 x 128, k split over 2 groups of 4 wavefronts                           (gemm_small.hip)
 //   5  256 x 128, 8 wavefronts in two alternating halves                          (gemm_small.hip)
 //   6   64 x  64, 4 wavefronts with a quadrant each, two workgroups per compute unit (gemm_small.hip): the last tile rows only

@@ -21,7 +21,7 @@ namespace {
 // (bands of 8 tile rows, column by column inside a band), so that the tiles an XCD works on at
 // once share operand slices through its L2.
 __device__ __forceinline__ void small_tile_of(int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int total = gridDim.x, per = total / 8, rem = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  const int total = tiles_m * tiles_n, per = total / 8, rem = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
   const int v = xcd * per + (xcd < rem ? xcd : rem) + slot;
   const int band = v / (8 * tiles_n), r = v - band * 8 * tiles_n;
   const int hb = (tiles_m - band * 8 < 8) ? (tiles_m - band * 8) : 8;
@@ -477,6 +477,176 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g, int tiles
 }
 
 // ---------------------------------------------------------------------------------------
+// 128 x 64 tile for an even number of k-tiles, 8 wavefronts in two groups that take the k-tiles in turn, each with two LDS
+// stages of its own; the four wavefronts of a group as 2 x 2 with 64 x 32 wavefront tiles.  The k-loop is
+// gemm_stream_kernel's (quarters of a k-tile, half stages refilled among the MFMAs, two barriers), one k-tile of either
+// group at a time, so that the loads are never in a burst.  Bound: the operand path, 24 KiB per k-tile at 58 bytes per
+// clock, 424 clocks against 256 of the matrix unit.  Measured per launch against gemm_pair_kernel<128, 64>: 1092 rows, 1152 x
+// 1152: 9.7 -> 8.4 us; 1152 x 4352: 26.7 -> 25.7; 686 rows, 2304 x 768: 8.5 -> 7.8.  (As 128 x 128 tiles against
+// gemm_pair_kernel<128, 128>: 3276 rows, 1152 x 4352 level, 2184 rows 32.6 -> 34.7: there the operand path, LDS and the
+// matrix unit are all about as long.)
+// ---------------------------------------------------------------------------------------
+struct DuoShape {
+  static constexpr int BM = 128, BN = 64, STAGE = (BM + BN) * 64, GROUP = 2 * STAGE;      // elements
+  static constexpr int SCALES = 2 * GROUP;                       // the row scales lie behind the stages
+  static constexpr size_t kLdsBytes = (size_t)SCALES * 2 + BM * sizeof(float);
+  static_assert(kLdsBytes <= 160 * 1024 && SCALES >= 4 * 8192, "stages fit, and the exchange fits over them");
+};
+
+template <int EPI>
+__global__ __launch_bounds__(512, 1) void gemm_duo_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  using S = DuoShape;
+  constexpr int BM = S::BM, BN = S::BN, MS = 4, MH = 2, NS = BN / 32;
+  constexpr int WL = BN / 32, AL = 2, LOADS = WL + 2 * AL;       // 1 KiB loads per wavefront: of the weight tile, of either half of the activation tile
+  extern __shared__ __align__(16) uint16_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave >> 2, w = wave & 3, wm = w >> 1, wn = w & 1;
+  const int r16 = lane & 15, g4 = lane >> 4, lrow = lane >> 3, lslot = lane & 7;
+  int m0, n0;
+  small_tile_of(tiles_m, tiles_n, m0, n0);
+  m0 *= BM;
+  n0 *= BN;
+  const int units = g.K / 128;
+  uint16_t *mem = lds + group * S::GROUP;
+  const char *a_base = reinterpret_cast<const char *>(g.A + (size_t)m0 * g.lda + group * 64) - kOffBias;
+  const char *w_base = reinterpret_cast<const char *>(g.W + (size_t)n0 * g.K + group * 64) - kOffBias;
+  const int a_row0 = wm * 64 + wn * 16;                          // half 0 of the activation rows; half 1: + 32
+  uint32_t a_off[2 * AL], w_off[WL];
+#pragma unroll
+  for (int i = 0; i < 2 * AL; ++i) {
+    const int row = a_row0 + (i / AL) * 32 + (i % AL) * 8 + lrow;
+    a_off[i] = piece_offset(row, (m0 + row < g.M) ? row : g.M - 1 - m0, g.lda, lslot, i % AL);
+  }
+#pragma unroll
+  for (int i = 0; i < WL; ++i) {
+    const int row = (w * WL + i) * 8 + lrow;
+    w_off[i] = piece_offset(row, row, g.K, lslot, i);
+  }
+  int load_u = 0;                                                // next k-tile of this group to be fetched
+  auto load_w = [&](int stage, int i0, int i1) {
+    const char *b = w_base + (size_t)load_u * 256;
+    uint16_t *dst = mem + stage * S::STAGE + BM * 64 + w * WL * 512;
+    asm volatile("" : "+s"(b));
+#pragma unroll
+    for (int i = i0; i < i1; ++i) {
+      asm volatile("" : "+v"(w_off[i]));
+      lds_dma16_of4(b + w_off[i], dst, i);
+    }
+  };
+  auto load_a = [&](int stage, int h) {
+    const char *b = a_base + (size_t)load_u * 256;
+    uint16_t *dst = mem + stage * S::STAGE + (a_row0 + h * 32) * 64;
+    asm volatile("" : "+s"(b));
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+      asm volatile("" : "+v"(a_off[h * AL + i]));
+      lds_dma16_of4(b + a_off[h * AL + i], dst, i);
+    }
+  };
+  auto advance = [&]() { load_u = load_u + 1 < units ? load_u + 1 : load_u; };     // (past the end the last one is re-read, unused)
+  RowScale<18> scale;
+  float my_scale = 1.0f;
+  const bool scales = EPI != EPI_BIAS_RES && wave < BM / 64;
+  if (scales) scale.fetch(g, m0 + wave * 64 + lane);
+  __builtin_amdgcn_sched_barrier(0);
+  load_w(0, 0, WL);
+  load_a(0, 0);
+  load_a(0, 1);
+  advance();
+  load_w(1, 0, WL);
+  load_a(1, 0);
+
+  const int fx = (r16 >> 1) & 7;
+  int a_addr[2], w_addr[2];                                      // element offsets of this lane's fragments, by k-step
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int ko = ((4 * ks + g4) ^ fx) * 8;
+    a_addr[ks] = (wm * 64 + r16) * 64 + ko;
+    w_addr[ks] = BM * 64 + (wn * (BN / 2) + r16) * 64 + ko;
+  }
+  f32x4 acc[NS][MS];
+#pragma unroll
+  for (int a = 0; a < NS; ++a)
+#pragma unroll
+    for (int b = 0; b < MS; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 fw[2][NS], fa[2][MH];
+  auto read_w = [&](int stage, int ks) {
+    const uint16_t *p = mem + stage * S::STAGE + w_addr[ks];
+#pragma unroll
+    for (int a = 0; a < NS; ++a) fw[ks][a] = *reinterpret_cast<const u32x4 *>(p + a * 1024);
+  };
+  auto read_a = [&](int buf, int stage, int h, int ks) {
+    const uint16_t *p = mem + stage * S::STAGE + a_addr[ks] + h * 32 * 64;
+#pragma unroll
+    for (int b = 0; b < MH; ++b) fa[buf][b] = *reinterpret_cast<const u32x4 *>(p + b * 1024);
+  };
+  auto mfma_quarter = [&](int buf, int h, int ks) {
+#pragma unroll
+    for (int b = 0; b < MH; ++b)
+#pragma unroll
+      for (int a = 0; a < NS; ++a) acc[a][h * MH + b] = mfma16(fw[ks][a], fa[buf][b], acc[a][h * MH + b]);
+  };
+  auto meet = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  wait_vmcnt<LOADS>();
+  __builtin_amdgcn_sched_barrier(0);
+  if (scales) my_scale = scale.value(g);
+  asm volatile("" : "+v"(my_scale));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read_w(0, 0);
+  read_a(0, 0, 0, 0);
+  int stage = 0;
+  for (int u = 0; u < units; ++u) {
+    read_a(1, stage, 0, 1);
+    read_w(stage, 1);
+    load_a(stage ^ 1, 1);
+    mfma_quarter(0, 0, 0);
+    mfma_between<NS * MH - AL, AL, NS * MH>();
+    __builtin_amdgcn_sched_barrier(0);
+    advance();
+    wait_vmcnt<LOADS>();                                         // the lower rows of this k-tile have landed
+    meet();                                                      // ... everyone's; weights and upper rows have been read
+    read_a(0, stage, 1, 0);
+    load_w(stage, 0, WL / 2);
+    mfma_quarter(1, 0, 1);
+    mfma_between<MH, WL / 2, NS * MH>();
+    __builtin_amdgcn_sched_barrier(0);
+    read_a(1, stage, 1, 1);
+    load_w(stage, WL / 2, WL);
+    mfma_quarter(0, 1, 0);
+    mfma_between<MH, WL / 2, NS * MH>();
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<LOADS - AL>();                                    // the next k-tile's weights and upper rows have landed
+    meet();                                                      // ... everyone's; the lower rows have been read
+    read_w(stage ^ 1, 0);
+    read_a(0, stage ^ 1, 0, 0);
+    load_a(stage, 0);
+    mfma_quarter(1, 1, 1);
+    mfma_between<NS * MH - AL, AL, NS * MH>();
+    __builtin_amdgcn_sched_barrier(0);
+    stage ^= 1;
+  }
+  wait_vmcnt<0>();                                               // (the loads past the end)
+  __syncthreads();                                               // the stages take the partial sums
+  float *rs_tile = reinterpret_cast<float *>(lds + S::SCALES);
+  if (scales) rs_tile[wave * 64 + lane] = my_scale;
+  f32x4 *xch = reinterpret_cast<f32x4 *>(lds);
+  const int tile = group * 2 + wm;                               // the 64 x 64 partial tile that this wavefront writes half of
+  auto put = [&]() {
+#pragma unroll
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+      for (int b = 0; b < MS; ++b) put_tile16(acc[a][b], xch + tile * 1024, wn * NS + a, b, lane);
+  };
+  finish_rows<4, 2, 2, EPI>(put, g, xch, wm, group * 2 + wn, m0 + wm * 64, n0, lane, rs_tile + wm * 64);
+}
+
+// ---------------------------------------------------------------------------------------
 // 256 x 128 tile, 8 wavefronts with 64 x 64 wavefront tiles, one k-tile stream for all: half 0 owns the
 // upper 128 rows, half 1 the lower ones.  The halves alternate as above (phase 2 u: half 0 reads
 // k-tile u while half 1 runs the MFMAs of u - 1; phase 2 u + 1: the other way round), so the load path
@@ -656,7 +826,15 @@ int launch_gemm_half(const GemmArgs &g, hipStream_t s) {
     default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
   }
 }
+static int launch_duo(const GemmArgs &g, hipStream_t s) {
+  switch (g.epilogue) {
+    case EPI_BIAS: return launch_small<gemm_duo_kernel<EPI_BIAS>>(g, s, 128, 64, 512, DuoShape::kLdsBytes);
+    case EPI_BIAS_GELU: return launch_small<gemm_duo_kernel<EPI_BIAS_GELU>>(g, s, 128, 64, 512, DuoShape::kLdsBytes);
+    case EPI_BIAS_RES: return launch_small<gemm_duo_kernel<EPI_BIAS_RES>>(g, s, 128, 64, 512, DuoShape::kLdsBytes);
+    default: set_error("unknown epilogue %d", g.epilogue); return ET_ERR_INVALID_ARG;
+  }
+}
 int launch_gemm_pair128(const GemmArgs &g, hipStream_t s) { return launch_pair_shape<128, 128>(g, s); }
-int launch_gemm_pair64(const GemmArgs &g, hipStream_t s) { return launch_pair_shape<128, 64>(g, s); }
+int launch_gemm_pair64(const GemmArgs &g, hipStream_t s) { return g.K % 128 == 0 ? launch_duo(g, s) : launch_pair_shape<128, 64>(g, s); }
 
 }  // namespace et

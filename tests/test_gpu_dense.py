@@ -308,6 +308,13 @@ def test_gemm_split_over_wavefronts(cfg, M, N, K):
         assert rel_l2(got, ref) < 4e-3
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (63, 72, 128), (129, 64, 256), (257, 200, 384), (300, 136, 1152)])
+def test_gemm_two_groups_of_wavefronts_in_turn(M, N, K):
+    """128 x 64 tiles with an even number of k-tiles (one, two, three and nine per group of wavefronts), ragged rows and
+    columns; in fp64 against bf16 inputs, bounds as above."""
+    test_gemm_split_over_wavefronts(3, M, N, K)
+
+
 @pytest.mark.parametrize("n_heads,hd,lens", [
     (16, 72, [729]),                      # key tiles over four groups of wavefronts, uneven shares, ragged last tile
     (4, 64, [65, 0, 1, 128, 129]),        # the same: fewer tiles than groups, an empty and a one-token frame
