@@ -644,9 +644,9 @@ constexpr int kAttBKV = 64;
 
 // Workgroups go to the 8 XCDs round-robin by index.  A one-dimensional grid whose order puts
 // workgroups that share data next to each other is therefore remapped first: XCD x takes the x-th
-// contiguous run of the order (a bijection of [0, gridDim.x)), and neighbours share an L2.
-__device__ __forceinline__ int xcd_contiguous_index() {
-  const int total = gridDim.x, per = total / 8, rem = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+// contiguous run of the order (a bijection of [0, total)), and neighbours share an L2.
+__device__ __forceinline__ int xcd_contiguous_index(int total) {
+  const int per = total / 8, rem = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
   return xcd * per + (xcd < rem ? xcd : rem) + slot;
 }
 
@@ -958,7 +958,7 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
 
   // One-dimensional grid over (frame, head, query block), query block fastest, so that the query blocks
   // of one (frame, head) - which read the same K and V - run on one XCD and share its L2.
-  const int v = xcd_contiguous_index();
+  const int v = xcd_contiguous_index(gridDim.x);
   const int q0 = (v % n_qblk) * kAttBQ, h = (v / n_qblk) % n_heads, f = v / (n_qblk * n_heads);
   int start = f * n;
   if (cu) {                                            // ragged frames (workgroup-uniform)
@@ -1046,6 +1046,24 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
   }
 }
 
+// Workgroup `idx` of `count` reads its share of the ranges, eight 16-byte loads per thread in flight.
+__device__ __forceinline__ void read_ahead(const WarmRanges &w, int idx, int count) {
+#pragma unroll 1
+  for (int r = 0; r < WarmRanges::kMax; ++r) {
+    const u32x4 *p = static_cast<const u32x4 *>(w.ptr[r]);
+    const uint32_t n = w.bytes[r] / 16u, step = (uint32_t)count * blockDim.x;
+    if (n == 0) continue;
+#pragma unroll 1
+    for (uint32_t i = (uint32_t)idx * blockDim.x + threadIdx.x; i < n; i += 8 * step) {
+      u32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[min(i + u * step, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) asm volatile("" ::"v"(v[u]));
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // The same for few queries, where a workgroup per 128 queries leaves most of the chip idle and walks all key tiles
 // one after the other (1.4 us per tile): the 8 wavefronts of a workgroup form KG groups; a group takes 256 / KG
@@ -1068,7 +1086,7 @@ struct GroupShape {
 template <int HD, int KG>
 __global__ __launch_bounds__(512, 1) void attention_group_kernel(
     const uint16_t *__restrict__ qkv, const int32_t *__restrict__ cu, int n, int n_heads, int n_qblk, float scale_log2,
-    uint16_t *__restrict__ out) {
+    uint16_t *__restrict__ out, WarmRanges warm, int n_work) {
   using S = GroupShape<HD, KG>;
   using Rows = AttentionRows<HD>;
   constexpr int WPG = S::WPG, T_LOADS = HD / 8, PW = (T_LOADS + WPG - 1) / WPG;
@@ -1076,7 +1094,8 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
   __shared__ float2 ml[8][32];
   __shared__ int redo;
   clear_flag(redo);
-  const int v = xcd_contiguous_index();
+  if ((int)blockIdx.x >= n_work) return read_ahead(warm, blockIdx.x - n_work, gridDim.x - n_work);
+  const int v = xcd_contiguous_index(n_work);
   const int q0 = (v % n_qblk) * (32 * WPG), h = (v / n_qblk) % n_heads, f = v / (n_qblk * n_heads);
   int start = f * n;
   if (cu) {                                            // ragged frames (workgroup-uniform)
@@ -1318,7 +1337,7 @@ bool head_dim_supported(int hd) {
 
 template <int HD, int KG>
 static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n, int n_heads, int n_qblk, long long pairs,
-                                  float scale_log2, uint16_t *out, hipStream_t s) {
+                                  float scale_log2, uint16_t *out, hipStream_t s, const WarmRanges *warm) {
   constexpr size_t bytes = GroupShape<HD, KG>::kLdsBytes;
   static std::atomic<uint64_t> allowed{0};
   int dev = 0;
@@ -1329,7 +1348,13 @@ static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n,
     ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
     allowed.fetch_or(bit, std::memory_order_relaxed);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(n_qblk * pairs)), dim3(512), bytes, s, qkv, cu, n, n_heads, n_qblk, scale_log2, out);
+  // One workgroup per compute unit: the idle ones read ahead.  The weights of a block (31 MB at a width of 1152) otherwise
+  // come from HBM, the encoder's together being more than the last-level cache holds: us per block, 1 x 729 tokens 68.1
+  // -> 63.7, 2 x 364 65.6 -> 63.1, 3 x 364 82.7 -> 80.4, the attention launch itself +1.2 ... +3.6.  (Where it has several
+  // workgroups per compute unit, or beside the QKV projection, reading ahead costs what it gives.)
+  const int work = (int)(n_qblk * pairs), idle = device_cus() - work;
+  const int more = warm && idle >= 16 ? idle : 0;
+  hipLaunchKernelGGL(kern, dim3(work + more), dim3(512), bytes, s, qkv, cu, n, n_heads, n_qblk, scale_log2, out, warm ? *warm : WarmRanges{}, work);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }
@@ -1337,7 +1362,7 @@ static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n,
 // cu == nullptr: frames of `len` rows each; else row ranges cu[f] .. cu[f + 1] of at most `len` rows.
 template <int HD>
 static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_frames, int len, int n_heads, uint16_t *out,
-                               hipStream_t s) {
+                               hipStream_t s, const WarmRanges *warm) {
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
   const long long pairs = (long long)n_heads * n_frames, cus = device_cus();
   const int n = cu ? 0 : len;
@@ -1350,11 +1375,11 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
   const int n_tiles = blocks(kAttBKV);
   if constexpr (GroupShape<HD, 4>::kFits) {
     if (n_tiles >= 2 && blocks(64) * pairs <= cus)
-      return launch_attention_group<HD, 4>(qkv, cu, n, n_heads, blocks(64), pairs, scale_log2, out, s);
+      return launch_attention_group<HD, 4>(qkv, cu, n, n_heads, blocks(64), pairs, scale_log2, out, s, warm);
   }
   if constexpr (GroupShape<HD, 2>::kFits) {
     if (n_tiles >= 5 && blocks(128) * pairs <= cus)
-      return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s);
+      return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s, warm);
   }
   // three workgroups per compute unit where that spills nothing (heads of 80: 17.1 us with three, 15.1 with two, 8 x 364)
   hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 72 ? 3 : HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
@@ -1364,22 +1389,23 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
 }
 
 int launch_attention(const uint16_t *qkv, const int32_t *cu, int n_frames, int len, int n_heads, int head_dim, uint16_t *out,
-                     hipStream_t s) {
+                     hipStream_t s, const WarmRanges *warm) {
   if (n_frames <= 0 || len <= 0) return ET_OK;
   switch (head_dim) {
-    case 16: return launch_attention_hd<16>(qkv, cu, n_frames, len, n_heads, out, s);
-    case 32: return launch_attention_hd<32>(qkv, cu, n_frames, len, n_heads, out, s);
-    case 64: return launch_attention_hd<64>(qkv, cu, n_frames, len, n_heads, out, s);
-    case 72: return launch_attention_hd<72>(qkv, cu, n_frames, len, n_heads, out, s);
-    case 80: return launch_attention_hd<80>(qkv, cu, n_frames, len, n_heads, out, s);
-    case 96: return launch_attention_hd<96>(qkv, cu, n_frames, len, n_heads, out, s);
-    case 128: return launch_attention_hd<128>(qkv, cu, n_frames, len, n_heads, out, s);
+    case 16: return launch_attention_hd<16>(qkv, cu, n_frames, len, n_heads, out, s, warm);
+    case 32: return launch_attention_hd<32>(qkv, cu, n_frames, len, n_heads, out, s, warm);
+    case 64: return launch_attention_hd<64>(qkv, cu, n_frames, len, n_heads, out, s, warm);
+    case 72: return launch_attention_hd<72>(qkv, cu, n_frames, len, n_heads, out, s, warm);
+    case 80: return launch_attention_hd<80>(qkv, cu, n_frames, len, n_heads, out, s, warm);
+    case 96: return launch_attention_hd<96>(qkv, cu, n_frames, len, n_heads, out, s, warm);
+    case 128: return launch_attention_hd<128>(qkv, cu, n_frames, len, n_heads, out, s, warm);
     default: set_error("head_dim %d is not instantiated", head_dim); return ET_ERR_UNSUPPORTED;
   }
 }
 
-int launch_attention_uniform(const uint16_t *qkv, int n_frames, int len, int n_heads, int head_dim, uint16_t *out, hipStream_t s) {
-  return launch_attention(qkv, nullptr, n_frames, len, n_heads, head_dim, out, s);
+int launch_attention_uniform(const uint16_t *qkv, int n_frames, int len, int n_heads, int head_dim, uint16_t *out, hipStream_t s,
+                             const WarmRanges *warm) {
+  return launch_attention(qkv, nullptr, n_frames, len, n_heads, head_dim, out, s, warm);
 }
 
 }  // namespace et

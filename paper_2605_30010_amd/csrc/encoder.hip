@@ -157,10 +157,11 @@ static bool takes_pieces(const et_encoder *e, int rows) {
 // have_pieces: w.pieces holds the statistics of w.x (only looked at where takes_pieces(rows)).
 // with_scores: also leave the attention each token receives in this block in w.att_score (frames of
 // equal length only).
-static int run_block(et_encoder *e, const LayerDev &lw, const EncWs &w, int rows, const int32_t *cu,
+static int run_block(et_encoder *e, int layer, const EncWs &w, int rows, const int32_t *cu,
                      int n_frames, int max_len, bool ragged, bool have_pieces, hipStream_t s, bool with_scores = false) {
   const et_config &c = e->cfg;
   const int D = e->D;
+  const LayerDev &lw = e->layers[layer];
   // LayerNorm 1 and 2 are folded into the QKV and fc1 weights (fold_layernorm): only the row scales are needed.  On
   // few rows (`by_pieces`) the GEMMs that write the residual stream leave its statistics by pieces of 64 columns
   // and the next GEMM combines them; after a merge or selection the pieces are computed here.  On many rows the scales
@@ -189,10 +190,17 @@ static int run_block(et_encoder *e, const LayerDev &lw, const EncWs &w, int rows
   ET_TIMED(ET_K_GEMM_QKV, launch_gemm(g, s));
   if (with_scores)
     ET_TIMED(ET_K_SCORE, launch_attention_scores(w.qkv, n_frames, max_len, c.n_heads, e->hd, w.score_ws, w.att_score, s));
+  // the weights that the launches behind the attention read, for its idle compute units
+  const uint32_t mlp_bytes = (uint32_t)D * e->Mhp * 2u;
+  WarmRanges warm{{lw.wo, lw.w1, lw.w2, nullptr}, {(uint32_t)D * D * 2u, mlp_bytes, mlp_bytes, 0u}};
+  if (layer + 1 < c.n_layers) {
+    warm.ptr[3] = e->layers[layer + 1].wqkv;
+    warm.bytes[3] = 3u * D * D * 2u;
+  }
   if (ragged) {   // frames of different lengths (decoupled selection): row ranges from cu
-    ET_TIMED(ET_K_ATTENTION, launch_attention(w.qkv, cu, n_frames, max_len, c.n_heads, e->hd, w.att, s));
+    ET_TIMED(ET_K_ATTENTION, launch_attention(w.qkv, cu, n_frames, max_len, c.n_heads, e->hd, w.att, s, &warm));
   } else {        // every frame has max_len tokens
-    ET_TIMED(ET_K_ATTENTION, launch_attention_uniform(w.qkv, n_frames, max_len, c.n_heads, e->hd, w.att, s));
+    ET_TIMED(ET_K_ATTENTION, launch_attention_uniform(w.qkv, n_frames, max_len, c.n_heads, e->hd, w.att, s, &warm));
   }
   g = leaving_pieces(GemmArgs{w.att, D, lw.wo, lw.bo, w.x, D, rows, w.x, D, rows, D, D, EPI_BIAS_RES});
   ET_TIMED(ET_K_GEMM_OUT, launch_gemm(g, s));
@@ -453,7 +461,7 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
     if (i < c.n_layers) {
       const bool with_scores = by_attention && !selected && i == merge_layer - 1;
       int rc;
-      if ((rc = run_block(e, e->layers[i], w, rows, cu, n_frames, max_len, ragged, have_pieces, s, with_scores))) return rc;
+      if ((rc = run_block(e, i, w, rows, cu, n_frames, max_len, ragged, have_pieces, s, with_scores))) return rc;
       have_pieces = true;
     }
   }
