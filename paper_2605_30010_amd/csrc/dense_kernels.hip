@@ -1312,7 +1312,7 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg, bool one_tile) 
     return ET_ERR_INVALID_ARG;
   }
   if (force_cfg >= 0) return launch_gemm_id(g, s, force_cfg);
-  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr || one_tile}, g.M, g.n_store);
+  const GemmPlan plan = plan_gemm(GemmRules{g.K, device_cus(), g.epilogue != EPI_BIAS_RES || g.res_mod >= g.M, g.stats_in != nullptr || one_tile, g.epilogue == EPI_BIAS_RES}, g.M, g.n_store);
   for (int i = 0; i < plan.n; ++i) {
     const GemmPart &t = plan.part[i];
     GemmArgs part = g;

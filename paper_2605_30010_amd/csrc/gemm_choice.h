@@ -30,32 +30,38 @@ inline long gemm_tiles(int cfg, long rows, long cols) {
 // Expected time of one launch in microseconds, launch overhead included: a fixed part (first loads,
 // epilogue) plus a part per k-tile of 64 in each round of tiles.  A compute unit is slower when its
 // neighbours work too (shared caches, and the clock falls with the power drawn), hence the terms in
-// t / slots.  Fitted to launches on 256 compute units at the encoder's shapes, 64 to 23328 rows; measured
-// at K = 1152 / 4352:
-//   wave     6.8 / 17 us for one round of 256 tiles, 10.3 / 28 for two, 15 / 42 for three
-//   pair64   9.3 / 25 for one round, 17.5 / 47 for two
-//   pair128  11-12 / 30 (up to 160 tiles), 14 / 36 (234 tiles), 25 / 67 for two rounds
-//   half     16.3 / 45 (up to 100 tiles), 22 / 59 (207), 42 / 120 for two rounds
-//   128      15 / 46 (up to 160 tiles), 20 (324), 23.5 / 64 (414), 36 / 107 (576)
-//   256      26 / 77 (70 tiles), 30 (182), 39 / 108 (230), 4 rounds 133 / 475
+// t / slots.  Fitted to launches on 256 compute units at widths of 768 to 4352, 64 to 13122 rows, weights
+// from HBM; measured at K = 1152 / 4352:
+//   wave     6.5-7 / 15-17 us for one round of 256 tiles, 10 / 28 for two, 14 / 40 for three
+//   pair64   8.3 / 23 for one round, 15.4 / 43 for two
+//   pair128  11-12.5 / 30-33 for one round, 22 / 63 for two
+//   half     17 / 47 (135 tiles), 18.3 / 52 (207-243), 34 / 103 for two rounds, 50 for three
+//   128      half rounds of 256 tiles: 13.8, 18, 26, 33.5, 40.5, .. 56 for seven; with a residual 17.5 / 52.5, 21.3 / 62.5, 36 /
+//            110, 40 / 133 (the loads of the residual rows wait for the next tile's operands)
+//   256      25 / 80 (70 tiles), 26 (182), 30.5 (252), 33 / 98 (230, residual), 55 (448), 87 (728)
 //   strip    7.4 (54 tiles) / 18, 8.2 (204), 10.4 (340), 18 / 45 for four and three rounds
-inline double gemm_cost(int cfg, long rows, long cols, int K) {
+inline double gemm_cost(int cfg, long rows, long cols, int K, bool residual = false) {
   const double kt = K / 64;
   const long t = gemm_tiles(cfg, rows, cols);
   auto rounds = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
   switch (cfg) {
     case kCfgWave: return 3.2 + rounds(t, 256) * 0.195 * kt;
-    case kCfgPair64: return 0.5 + rounds(t, 256) * (2.9 + 0.32 * kt);
-    case kCfgPair128: return t <= 256 ? 3.6 + kt * (0.38 + 0.10 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.46 * kt);
-    case kCfgHalf: return t <= 256 ? 6.5 + kt * (0.53 + 0.25 * (double)t / 256.0) : rounds(t, 256) * (6.0 + 0.8 * kt);
+    case kCfgPair64: return 0.5 + rounds(t, 256) * (2.2 + 0.305 * kt);
+    case kCfgPair128: return t <= 256 ? 3.6 + kt * (0.36 + 0.09 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.42 * kt);
+    case kCfgHalf: return t <= 256 ? 5.5 + kt * (0.56 + 0.16 * (double)t / 256.0) : rounds(t, 256) * (2.2 + 0.82 * kt);
     case kCfgStrip: return 3.2 + rounds(t, 256) * 0.205 * kt;
     case kCfg128: {
-      const long last = t % 512;
-      return 2.2 + (double)(t / 512) * (3.5 + 1.05 * kt) + (last ? 2.4 + kt * (0.55 + 0.4 * (double)last / 512.0) : 0.0);
+      const double h = rounds(t, 256);                     // half rounds: two workgroups share a compute unit
+      // (rated some 5 % above what was measured: it moves more operand bytes than 256 x 256, which costs clock elsewhere)
+      if (!residual) return h < 2 ? 2.6 + 0.6 * kt : 4.2 + 0.8 * kt + (h - 2) * (0.9 + 0.45 * kt);
+      const long pairs = (long)h / 2;
+      const double single = (long)h % 2 ? 1.0 : 0.0;
+      if (pairs == 0) return 3.5 + 0.72 * kt;
+      return 6.5 + 0.82 * kt + (double)(pairs - 1) * (0.6 + 1.02 * kt) + single * (3.0 + 0.66 * kt);
     }
     default: {
       const long last = t % 256;
-      return 0.5 + (double)(t / 256) * (4.5 + 1.6 * kt) + (last ? 4.5 + kt * (1.05 + 0.55 * (double)last / 256.0) : 0.0);
+      return (double)(t / 256) * (1.5 + 1.47 * kt) + (last ? 4.0 + kt * (1.0 + 0.42 * (double)last / 256.0) : 2.5);
     }
   }
 }
@@ -85,14 +91,15 @@ struct GemmPlan {
 struct GemmRules {
   int K, cus;
   bool rows_splittable, one_tile;
+  bool residual = false;                   // the launch has the residual epilogue (its cost only)
 };
 
 inline int cheapest_tiling(const GemmRules &r, long rows, long cols, bool ordered, double *cost) {
   int best = ordered ? kCfgStrip : kCfgWave;
-  *cost = gemm_cost(best, rows, cols, r.K);
+  *cost = gemm_cost(best, rows, cols, r.K, r.residual);
   for (int cfg = 0; cfg < kCfgStrip; ++cfg) {
     if ((ordered && !in_k_order(cfg)) || (r.one_tile && !one_round(cfg, rows, cols, r.cus))) continue;
-    const double c = gemm_cost(cfg, rows, cols, r.K);
+    const double c = gemm_cost(cfg, rows, cols, r.K, r.residual);
     if (c < *cost) { *cost = c; best = cfg; }
   }
   return best;
@@ -118,7 +125,7 @@ inline void plan_gemm_part(const GemmRules &r, long row0, long rows, long col0, 
         double right = 0.0, bottom = 0.0;
         if (dc) cheapest_tiling(r, rm, cols - cm, ordered || dr > 0, &right);      // right strip next to the main block
         if (dr) cheapest_tiling(r, rows - rm, cols, true, &bottom);                // bottom strip over the full width
-        const double c = gemm_cost(kCfgBig, rm, cm, r.K) + right + bottom;
+        const double c = gemm_cost(kCfgBig, rm, cm, r.K, r.residual) + right + bottom;
         if (c < split_best - 1e-9) { split_best = c; best_dr = dr; best_dc = dc; }
       }
   }
