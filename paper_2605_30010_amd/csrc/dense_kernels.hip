@@ -999,6 +999,7 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     }
   };
   Rows rows;
+  const bool active = q0 + wave * 32 < n;              // (wave-uniform: past the frame's queries a wavefront only loads)
   // One pass over the key tiles; tile(t, K, V) takes them in order.
   auto pass = [&](auto tile) {
     issue(0);
@@ -1009,7 +1010,7 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
       asm volatile("" ::: "memory");
       if (t + 1 < n_tiles) issue(t + 1);
       const uint16_t *ks = lds + (t & 1) * STAGE;
-      tile(t, ks, ks + K_ELEMS);
+      if (active) tile(t, ks, ks + K_ELEMS);
     }
   };
   auto careful = [&](int t, const uint16_t *ks, const uint16_t *vs) { rows.tile(ks, vs, t * kAttBKV, n, lane); };
@@ -1018,11 +1019,14 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     const bool edge = t == 0 || t + 1 == n_tiles;
 #pragma unroll                                         // (in this form the registers suffice: no spill in the loop)
     for (int kb = 0; kb < 2; ++kb) {
-      if (edge) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
-      else rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+      if (edge) {
+        if (kb == 0 || kv0 + 32 < n) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
+      } else {
+        rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+      }
     }
   });
-  raise_flag(redo, !rows.sound(r32));
+  raise_flag(redo, active && !rows.sound(r32));
   __syncthreads();
   if (__builtin_expect(redo, 0)) pass(careful);
 
@@ -1157,7 +1161,7 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
     const bool edge = t == grp_k || t + 1 == n_tiles;
     if (edge) {
 #pragma unroll 1                                       // (code that runs once or twice is kept short: it comes in cold)
-      for (int kb = 0; kb < 2; ++kb) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == grp_k && kb == 0);
+      for (int kb = 0; kb < (kv0 + 32 < n ? 2 : 1); ++kb) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == grp_k && kb == 0);
     } else {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
