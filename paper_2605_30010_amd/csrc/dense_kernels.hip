@@ -227,37 +227,27 @@ __global__ __launch_bounds__(1024) void im2col_stripe_kernel(const float *__rest
 // pieces to the slice; finally the slice is read row-wise and stored.  16-byte slots of a row are
 // XOR-swizzled by (row >> 1) & 7.  LDS operations of one wavefront execute in order, so the phases
 // need no barrier.
-// STATS: the residual epilogue leaves the rows' statistics; for the others the row scales of the wavefront's MS * 16
-// rows lie at the start of the slice as floats.
+// Bias and row scales of the tile come to the slice before (see fetch_constants in the kernel).  STATS: the residual epilogue
+// leaves the rows' statistics; for the others the row scales are written by a wavefront that has combined them.
+constexpr int kBiasInSlice = 512;            // floats
 template <int EPI, bool STATS, int MS, int NS>
 __device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const GemmArgs &g, int m_base,
                                                   int n_base, int lane, uint16_t *slice) {
   static_assert(NS == 4 && MS % 2 == 0, "the staged epilogue handles 64-column wavefront tiles in blocks of 32 rows");
   const int r16 = lane & 15, g4 = lane >> 4;
   const int prow = lane >> 3, pch = lane & 7;                 // row-wise phase: 8 rows x 8 chunks per pass
-  float rsv[MS];                                              // row scales of this lane's rows, fetched up front
+  // Bias and row scales lie in the slice (bias_at floats from its start, and from its start); read before it takes results.
+  const float *in_slice = reinterpret_cast<const float *>(slice);
+  float rsv[MS];                                              // row scales of this lane's rows
 #pragma unroll
-  for (int b = 0; b < MS; ++b) {
-    const int m = m_base + b * 16 + r16;
-    if (EPI == EPI_BIAS_RES) rsv[b] = 1.0f;                   // (no LayerNorm in front of these)
-    else if (STATS) rsv[b] = reinterpret_cast<const float *>(slice)[b * 16 + r16];
-    else rsv[b] = (g.row_scale && m < g.M) ? g.row_scale[m] : 1.0f;   // (fma(1, acc, bias) == acc + bias exactly)
-  }
-  if (STATS) asm volatile("" ::: "memory");                   // read before the slice takes the results
+  for (int b = 0; b < MS; ++b)                                // (no LayerNorm in front of a residual GEMM; fma(1, acc, bias) == acc + bias)
+    rsv[b] = EPI != EPI_BIAS_RES && (STATS || g.row_scale) ? in_slice[b * 16 + r16] : 1.0f;
   const int n_lane = n_base + pch * 8;
   const bool n_ok = n_lane < g.n_store;                       // n_store is a multiple of 8 on this path
   float4 bi[NS];
 #pragma unroll
-  for (int a = 0; a < NS; ++a) {
-    const int n = n_base + a * 16 + g4 * 4;
-    bi[a] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (n < g.n_store) bi[a] = *reinterpret_cast<const float4 *>(g.bias + n);
-  }
-  // (waited for on every path: a load still pending at the k-loop's head would be waited for there, each time round)
-#pragma unroll
-  for (int a = 0; a < NS; ++a) asm volatile("" : "+v"(bi[a].x), "+v"(bi[a].y), "+v"(bi[a].z), "+v"(bi[a].w));
-#pragma unroll
-  for (int b = 0; b < MS; ++b) asm volatile("" : "+v"(rsv[b]));
+  for (int a = 0; a < NS; ++a) bi[a] = *reinterpret_cast<const float4 *>(in_slice + kBiasInSlice + a * 16 + g4 * 4);
+  asm volatile("" ::: "memory");
   u32x4 rv[4];
   auto fetch_res = [&](int b) {
 #pragma unroll
@@ -479,6 +469,23 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
     tile_of(0, m0, n0);
     scale.fetch(g, m0 + wave * 64 + lane);
   }
+  // The bias of the wavefront's 64 columns and the scales of its rows, by direct loads into its epilogue slice while the
+  // tile's k-loop runs: fetched in the epilogue they cost its wavefronts a trip to memory, behind all operand loads in flight.
+  uint16_t *const slices = lds + STAGES * STAGE_ELEMS;
+  uint16_t *const slice = slices + wave * (32 * 64);
+  auto fetch_constants = [&](int j) {
+    int m0, n0;
+    tile_of(j, m0, n0);
+    ET_LDS_DMA4(g.bias + n0 + wn * WTN + lane, slice + kBiasInSlice * 2);
+    if (EPI != EPI_BIAS_RES && !STATS && g.row_scale) {
+#pragma unroll
+      for (int i = 0; i < WTM / 64; ++i) {
+        const int m = m0 + wm * WTM + i * 64 + lane;
+        ET_LDS_DMA4(g.row_scale + (m < g.M ? m : g.M - 1), slice + i * 128);
+      }
+    }
+  };
+  fetch_constants(0);
   set_load_tile(0);
 #pragma unroll
   for (int st = 0; st < 2; ++st) {
@@ -535,7 +542,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
 
   int stage = 0, kt = 0, my_tile = 0;
   const int units = n_my * kt_n;
-  uint16_t *const slices = lds + STAGES * STAGE_ELEMS;
   for (int u = 0; u < units; ++u) {
     read_a(1, stage, 0, 1);
     read_w(stage, 1);
@@ -577,9 +583,11 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kerne
     if (++kt == kt_n) {                             // an output tile is complete
       int m0, n0;
       tile_of(my_tile, m0, n0);
-      gemm_epilogue_lds<EPI, STATS, MS, NS>(acc, g, m0 + wm * WTM, n0 + wn * WTN, lane, slices + wave * (32 * 64));
+      wait_vmcnt<LOADS>();                          // (the tile's bias and row scales are older than its last k-tile's loads)
+      gemm_epilogue_lds<EPI, STATS, MS, NS>(acc, g, m0 + wm * WTM, n0 + wn * WTN, lane, slice);
       if (m0 + BM <= g.M && n0 + BN <= g.n_store) relax = 2;
       if (++my_tile == n_my) break;
+      fetch_constants(my_tile);
       kt = 0;
       clear_acc();
     }

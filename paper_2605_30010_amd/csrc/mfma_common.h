@@ -55,6 +55,11 @@ __device__ __forceinline__ float gelu_tanh_f(float u) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
                                    (__attribute__((address_space(3))) void *)(lptr), 16, 0, 0)
 
+// The same with 4 bytes per lane.
+#define ET_LDS_DMA4(gptr, lptr)                                                              \
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
+                                   (__attribute__((address_space(3))) void *)(lptr), 4, 0, 0)
+
 #define ET_LDS_DMA16_OFF(gptr, lptr, imm)                                                    \
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
                                    (__attribute__((address_space(3))) void *)(lptr), 16, (imm), 0)
