@@ -46,14 +46,14 @@ inline double gemm_cost(int cfg, long rows, long cols, int K, bool residual = fa
   auto rounds = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
   switch (cfg) {
     case kCfgWave: return 3.2 + rounds(t, 256) * 0.195 * kt;
-    case kCfgPair64: return 0.5 + rounds(t, 256) * (2.2 + 0.305 * kt);
+    case kCfgPair64: return 0.5 + rounds(t, 256) * (2.7 + 0.298 * kt);
     case kCfgPair128: return t <= 256 ? 3.6 + kt * (0.36 + 0.09 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.42 * kt);
     case kCfgHalf: return t <= 256 ? 5.5 + kt * (0.56 + 0.16 * (double)t / 256.0) : rounds(t, 256) * (2.2 + 0.82 * kt);
     case kCfgStrip: return 3.2 + rounds(t, 256) * 0.205 * kt;
     case kCfg128: {
       const double h = rounds(t, 256);                     // half rounds: two workgroups share a compute unit
       // (rated some 5 % above what was measured: it moves more operand bytes than 256 x 256, which costs clock elsewhere)
-      if (!residual) return h < 2 ? 2.6 + 0.6 * kt : 4.2 + 0.8 * kt + (h - 2) * (0.9 + 0.45 * kt);
+      if (!residual) return h < 2 ? 4.2 + 0.5 * kt : 4.2 + 0.8 * kt + (h - 2) * (0.9 + 0.45 * kt);
       const long pairs = (long)h / 2;
       const double single = (long)h % 2 ? 1.0 : 0.0;
       if (pairs == 0) return 3.5 + 0.72 * kt;
