@@ -299,7 +299,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const Ge
     for (int j = 0; j < 4; ++j) {
       const int row = j * 8 + prow, m = mb + row;
       const u32x4 v = *reinterpret_cast<const u32x4 *>(slice + row * 64 + ((pch ^ ((row >> 1) & 7)) * 8));
-      if (m < g.M && n_ok) store16_through(g.C + (size_t)m * g.ldc + n_lane, v);
+      if (m < g.M && n_ok) store16(g.C + (size_t)m * g.ldc + n_lane, v, g.through);
       if (EPI == EPI_BIAS_RES && STATS) {                     // (n_store is a multiple of 64 then)
         const float2 st = piece_moments(v);
         if (pch == 0 && m < g.M && n_ok) g.stats_out[(size_t)(n_base >> 6) * g.stats_ld + m] = st;
@@ -1313,7 +1313,10 @@ static int launch_gemm_id(const GemmArgs &g, hipStream_t s, int cfg) {
 // pieces (launch_gemm accepts them for any size; beyond one round the row scales' own launch is cheaper).
 bool gemm_takes_pieces(int rows, int cols) { return one_round(kCfgBig, rows, cols, device_cus()); }
 
-int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg, bool one_tile) {
+int launch_gemm(const GemmArgs &args, hipStream_t s, int force_cfg, bool one_tile) {
+  GemmArgs g = args;
+  // from 1 MB of results on (0.7 MB: two launches 19.3 us without, 19.7 with; 1.7 to 6.3 MB, a 27-block encoder: 1984, 1930)
+  g.through = (size_t)g.M * g.n_store * sizeof(uint16_t) >= (1u << 20);
   if (g.M <= 0) return ET_OK;
   if (g.K % 64 != 0 || g.n_store % 8 != 0) {
     set_error("gemm: K = %d must be a multiple of 64 and n_store = %d of 8", g.K, g.n_store);

@@ -246,6 +246,7 @@ struct GemmArgs {
   const float2 *stats_in = nullptr;
   int stats_ld = 0;
   float ln_eps = 0.f;
+  bool through = false;                    // results are stored past the L2; set by launch_gemm
 };
 // 1 / sqrt(var + eps) of every row of x [rows, D] bf16 (biased variance, fp32 two-pass like layernorm_kernel).
 int launch_rowstats(const uint16_t *x, float eps, int rows, int D, float *rstd, hipStream_t s);

@@ -95,7 +95,7 @@ __device__ __forceinline__ void finish_rows(Put put, const GemmArgs &g, f32x4 *x
       }
       o[e] = cvt_pk_bf16(x0, x1);
     }
-    if (m < g.M && n_ok) store16_through(g.C + (size_t)m * g.ldc + n, o);
+    if (m < g.M && n_ok) store16(g.C + (size_t)m * g.ldc + n, o, g.through);
     if (EPI == EPI_BIAS_RES && g.stats_out) {              // (n_store is a multiple of 64 then)
       const float2 st = piece_moments(o);
       if (oct == 0 && m < g.M && n_ok) g.stats_out[(size_t)(n_tile >> 6) * g.stats_ld + m] = st;

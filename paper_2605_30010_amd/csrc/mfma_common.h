@@ -49,13 +49,8 @@ __device__ __forceinline__ float gelu_tanh_f(float u) {
   return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
-// One wavefront moves 64 x 16 bytes to 1 KiB of consecutive LDS (no staging registers).  The
+// Direct global -> LDS loads (no staging registers): one wavefront moves 64 x 4 or 64 x 16 bytes to consecutive LDS.  The
 // immediate offset moves the global AND the LDS address and has to be a literal.
-#define ET_LDS_DMA16(gptr, lptr)                                                             \
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
-                                   (__attribute__((address_space(3))) void *)(lptr), 16, 0, 0)
-
-// The same with 4 bytes per lane.
 #define ET_LDS_DMA4(gptr, lptr)                                                              \
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr),   \
                                    (__attribute__((address_space(3))) void *)(lptr), 4, 0, 0)
@@ -67,11 +62,12 @@ __device__ __forceinline__ float gelu_tanh_f(float u) {
 // The same load, unknown to the compiler: it has every LDS transpose read behind a direct load that it knows wait for that
 // load (as if the read could overlap it), which undoes a prefetch.  The caller's own waits (wait_vmcnt) cover it; the
 // compiler's waits for its own loads stay right, since an operation that it does not count only makes them longer.  M0 is
-// written behind its back: not beside the macros above in one kernel.
+// written behind its back: not beside the macros above in one kernel.  (s_nop: the wait states that the base needs if a
+// vector instruction has just written it, and M0, which the compiler sees to for loads that it knows.)
 __device__ __forceinline__ void lds_dma16_untracked(const uint16_t *base, uint32_t byte_off, uint16_t *dst) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)dst;
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %2"
                ::"v"(byte_off), "s"(__builtin_amdgcn_readfirstlane(to)), "s"(base) : "memory");
 #endif
 }
@@ -169,12 +165,14 @@ struct RowScale {
   }
 };
 
-// Stores 16 bytes past the XCD's L2 (write-through).  Results left dirty there are written back when the kernel ends, in
-// front of the next one: 22 MB of them cost 2.2 us.  For whole 128-byte segments only (the memory side merges nothing).
+// Stores 16 bytes of a result, past the XCD's L2 (write-through) if `through` (the same for the whole launch).  Results left
+// dirty there are written back when the kernel ends, in front of the next one: 22 MB of them cost 2.2 us; a store past
+// it is waited for longer at a wavefront's end.  For whole 128-byte segments only (the memory side merges nothing).
 // (The s_nop keeps the data registers from being overwritten in the very next cycle, which the compiler sees to for
 // stores that it knows.)
-__device__ __forceinline__ void store16_through(uint16_t *p, u32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+__device__ __forceinline__ void store16(uint16_t *p, u32x4 v, bool through) {
+  if (through) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+  else *reinterpret_cast<u32x4 *>(p) = v;
 }
 
 // Order of a quarter of a k-tile (gemm_stream_kernel, gemm_duo_kernel): one MFMA in front of each LDS read, then the direct loads GAP MFMAs apart, the rest behind them.
