@@ -168,10 +168,10 @@ struct RowScale {
 // Stores 16 bytes of a result, past the XCD's L2 (write-through) if `through` (the same for the whole launch).  Results left
 // dirty there are written back when the kernel ends, in front of the next one: 22 MB of them cost 2.2 us; a store past
 // it is waited for longer at a wavefront's end.  For whole 128-byte segments only (the memory side merges nothing).
-// (The s_nop keeps the data registers from being overwritten in the very next cycle, which the compiler sees to for
-// stores that it knows.)
+// (s_nop: the store reads its data after it has issued, so two wait states have to pass before a vector instruction may
+// overwrite them; the compiler sees to that for stores that it knows.)
 __device__ __forceinline__ void store16(uint16_t *p, u32x4 v, bool through) {
-  if (through) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+  if (through) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
   else *reinterpret_cast<u32x4 *>(p) = v;
 }
 

@@ -1,0 +1,100 @@
+"""Wait states around the instructions that csrc/mfma_common.h writes as inline assembly.  The compiler keeps the distances
+that the hardware asks for between instructions that it knows; an inline instruction carries its own.  Small kernels
+are compiled for gfx950 and the distances counted in the assembly (no GPU)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_30010_amd.build import FLAGS, HIPCC
+
+KERNELS = """
+#include "mfma_common.h"
+namespace et {
+template <bool THROUGH>
+__global__ void overwrite_behind_store(uint16_t *p, const u32x4 *src) {
+  u32x4 v = src[threadIdx.x], w = src[threadIdx.x + 64];
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(v), "+v"(w)::"memory");
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint16_t *q = p + (threadIdx.x + 64 * i) * 8;
+    if (THROUGH) store16(q, v, true);
+    else *reinterpret_cast<u32x4 *>(q) = v;
+    __builtin_amdgcn_sched_barrier(0);
+    v ^= w;
+    asm volatile("" : "+v"(v));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+template __global__ void overwrite_behind_store<true>(uint16_t *, const u32x4 *);
+template __global__ void overwrite_behind_store<false>(uint16_t *, const u32x4 *);
+}
+"""
+
+
+def wait_states(instruction):
+    m = re.match(r"s_nop (\d+)", instruction)
+    return int(m.group(1)) + 1 if m else 1
+
+
+def registers(operand):
+    m = re.match(r"([vs])\[(\d+):(\d+)\]|([vs])(\d+)$", operand.strip().rstrip(","))
+    if not m:
+        return set()
+    if m.group(4):
+        return {m.group(4) + m.group(5)}
+    return {m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)}
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Instructions by kernel: those between its label and s_endpgm."""
+    d = tmp_path_factory.mktemp("wait_states")
+    src, asm = str(d / "k.hip"), str(d / "k.s")
+    with open(src, "w") as f:
+        f.write(KERNELS)
+    subprocess.run([HIPCC] + FLAGS + ["--offload-device-only", "-S", src, "-o", asm], check=True, capture_output=True)
+    out, name = {}, None
+    for line in open(asm):
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            name = m.group(1)
+            out[name] = []
+        code = line.split(";")[0].strip()
+        if name and line[0] in " \t" and code and code[0] != ".":
+            out[name].append(code)
+            if code == "s_endpgm":
+                name = None
+    return out
+
+
+def of(kernels, *parts):
+    (body,) = [v for k, v in kernels.items() if all(p in k for p in parts)]
+    return body
+
+
+def distances_to_overwrite(body):
+    """Wait states between each 16-byte store and the next vector instruction that writes one of its data registers."""
+    out = []
+    for i, code in enumerate(body):
+        if not code.startswith("global_store_dwordx4"):
+            continue
+        data, states = registers(code.split()[2]), 0
+        assert len(data) == 4, code
+        for later in body[i + 1:]:
+            if later.startswith("v_") and registers(later.split()[1]) & data:
+                out.append(states)
+                break
+            states += wait_states(later)
+    return out
+
+
+def test_data_of_a_write_through_store_outlive_it(kernels):
+    """A store of more than 8 bytes reads its data after it has issued: two wait states on gfx950, which the compiler's own
+    stores show, whatever instruction follows (none of the ones behind it in the kernels counts here)."""
+    known = distances_to_overwrite(of(kernels, "overwrite_behind_store", "Lb0E"))
+    written = distances_to_overwrite(of(kernels, "overwrite_behind_store", "Lb1E"))
+    assert len(known) >= 3 and len(written) >= 3
+    assert min(known) == 2
+    assert min(written) >= 2, written
