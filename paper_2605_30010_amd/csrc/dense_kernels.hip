@@ -1013,8 +1013,8 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     issue(0);
     rows.start(qbase, q0 + wave * 32, n, ld, scale_log2, r32, grp);
     for (int t = 0; t < n_tiles; ++t) {
-      wait_vmcnt<0>();                         // tile t has landed
-      __builtin_amdgcn_s_barrier();            // ... for every wavefront; everyone is done with tile t-1
+      wait_all();                              // tile t has landed, and the reads of tile t-1 have returned
+      __builtin_amdgcn_s_barrier();            // ... for every wavefront: the loads behind it may overwrite tile t-1
       asm volatile("" ::: "memory");
       if (t + 1 < n_tiles) issue(t + 1);
       const uint16_t *ks = lds + (t & 1) * STAGE;
@@ -1156,8 +1156,8 @@ __global__ __launch_bounds__(512, 1) void attention_group_kernel(
     int stage = 0;
     for (int t0 = 0; t0 < n_tiles; t0 += KG, stage ^= 1) {
       const int t = t0 + grp_k;
-      wait_vmcnt<0>();                                 // tile t has landed
-      __builtin_amdgcn_s_barrier();                    // ... for every wavefront; everyone is done with the other stage
+      wait_all();                                      // tile t has landed, and the reads of the other stage have returned
+      __builtin_amdgcn_s_barrier();                    // ... for every wavefront: the loads behind it may overwrite that stage
       asm volatile("" ::: "memory");
       if (t + KG < n_tiles) issue(t + KG, stage ^ 1);
       const uint16_t *ks = mem + stage * 2 * S::TILE;

@@ -198,5 +198,8 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// Waits until all of its vector-memory and LDS operations are done.  In front of a barrier behind which LDS is refilled: that
+// a read's result is used in front of the barrier in the source does not keep its wait there.
+__device__ __forceinline__ void wait_all() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
 }  // namespace et

@@ -7,7 +7,7 @@ import subprocess
 
 import pytest
 
-from paper_2605_30010_amd.build import FLAGS, HIPCC
+from paper_2605_30010_amd.build import CSRC, FLAGS, HIPCC
 
 KERNELS = """
 #include "mfma_common.h"
@@ -47,13 +47,8 @@ def registers(operand):
     return {m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)}
 
 
-@pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """Instructions by kernel: those between its label and s_endpgm."""
-    d = tmp_path_factory.mktemp("wait_states")
-    src, asm = str(d / "k.hip"), str(d / "k.s")
-    with open(src, "w") as f:
-        f.write(KERNELS)
+def assemble(src, asm):
+    """Labels and instructions by kernel."""
     subprocess.run([HIPCC] + FLAGS + ["--offload-device-only", "-S", src, "-o", asm], check=True, capture_output=True)
     out, name = {}, None
     for line in open(asm):
@@ -62,11 +57,20 @@ def kernels(tmp_path_factory):
             name = m.group(1)
             out[name] = []
         code = line.split(";")[0].strip()
-        if name and line[0] in " \t" and code and code[0] != ".":
+        if name and code and (line[0] in " \t" and code[0] != "." or code.startswith(".LBB")):
             out[name].append(code)
-            if code == "s_endpgm":
-                name = None
+        if line.startswith(".Lfunc_end"):
+            name = None
     return out
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    d = tmp_path_factory.mktemp("wait_states")
+    src = str(d / "k.hip")
+    with open(src, "w") as f:
+        f.write(KERNELS)
+    return assemble(src, str(d / "k.s"))
 
 
 def of(kernels, *parts):
@@ -98,3 +102,22 @@ def test_data_of_a_write_through_store_outlive_it(kernels):
     assert len(known) >= 3 and len(written) >= 3
     assert min(known) == 2
     assert min(written) >= 2, written
+
+
+def test_attention_waits_for_its_lds_reads_in_front_of_each_barrier(tmp_path):
+    """The key tiles are refilled behind a barrier by direct loads that the compiler does not know: the reads of the tile
+    before have to have returned in front of it, by a wait that stands right there."""
+    dense = assemble(os.path.join(CSRC, "dense_kernels.hip"), str(tmp_path / "dense.s"))
+    barriers = 0
+    for name, body in dense.items():
+        if "attention" not in name:
+            continue
+        for i, code in enumerate(body):
+            if code != "s_barrier":
+                continue
+            barriers += 1
+            for before in reversed(body[:i]):
+                if before.startswith("s_waitcnt") and "lgkmcnt(0)" in before:
+                    break
+                assert not re.match(r"ds_|\.LBB|s_c?branch", before), (name, body[max(0, i - 8):i + 1])
+    assert barriers >= 40
