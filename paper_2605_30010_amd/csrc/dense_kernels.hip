@@ -612,13 +612,8 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
   }
 #define ET_GEMM_LAUNCH(E, STATS)                                                                  \
   {                                                                                              \
-    auto kern = gemm_stream_kernel<BM, BN, WAVES_M, WAVES_N, MINB, E, STATS>;        \
-    static bool attr_set = false;                                                                \
-    if (!attr_set) {                                                                             \
-      ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                           \
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));   \
-      attr_set = true;                                                                           \
-    }                                                                                            \
+    constexpr auto kern = gemm_stream_kernel<BM, BN, WAVES_M, WAVES_N, MINB, E, STATS>;          \
+    if (int rc = allow_lds<kern>(lds_bytes)) return rc;                                          \
     hipLaunchKernelGGL(kern, grid, block, lds_bytes, s, g, tiles_m, tiles_n);                    \
   }
   switch (g.epilogue) {
@@ -1354,15 +1349,8 @@ template <int HD, int KG>
 static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n, int n_heads, int n_qblk, long long pairs,
                                   float scale_log2, uint16_t *out, hipStream_t s, const WarmRanges *warm) {
   constexpr size_t bytes = GroupShape<HD, KG>::kLdsBytes;
-  static std::atomic<uint64_t> allowed{0};
-  int dev = 0;
-  ET_HIP(hipGetDevice(&dev));
-  const uint64_t bit = 1ull << (dev & 63);
-  auto kern = attention_group_kernel<HD, KG>;
-  if (!(allowed.load(std::memory_order_relaxed) & bit)) {
-    ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    allowed.fetch_or(bit, std::memory_order_relaxed);
-  }
+  constexpr auto kern = attention_group_kernel<HD, KG>;
+  if (int rc = allow_lds<kern>(bytes)) return rc;
   // One workgroup per compute unit: the idle ones read ahead.  The weights of a block (31 MB at a width of 1152) otherwise
   // come from HBM, the encoder's together being more than the last-level cache holds: us per block, 1 x 729 tokens 68.1
   // -> 63.7, 2 x 364 65.6 -> 63.1, 3 x 364 82.7 -> 80.4, the attention launch itself +1.2 ... +3.6.  (Where it has several

@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <stdarg.h>
 
+#include <atomic>
 #include <vector>
 
 #include "earlytom.h"
@@ -32,6 +33,20 @@ int hip_fail(hipError_t e, const char *what, const char *file, int line);
       return ET_ERR_INVALID_ARG;       \
     }                                  \
   } while (0)
+
+// Allows the kernel KERN `bytes` of dynamic LDS on the current device: more than 64 KiB have to be asked for, by kernel
+// and device.  Asked once for each; several host threads may be here at the same time.
+template <auto KERN>
+int allow_lds(size_t bytes) {
+  static std::atomic<uint64_t> allowed{0};
+  int dev = 0;
+  ET_HIP(hipGetDevice(&dev));
+  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+  if (allowed.load(std::memory_order_relaxed) & bit) return ET_OK;
+  ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  allowed.fetch_or(bit, std::memory_order_relaxed);
+  return ET_OK;
+}
 
 // ---- device-side bf16 <-> fp32 (bit-level, round to nearest even) ----
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {

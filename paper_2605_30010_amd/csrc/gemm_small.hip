@@ -9,7 +9,6 @@
 // 512 per 128 x 128 x 64, against 128 and 512 cycles of the matrix unit.  What cost the time before
 // was neither: a 64 x 128 workgroup tile walked its k-tiles one after the other, each a chain of
 // barrier, LDS reads waited for one by one, two MFMAs per wait (0.6-1.2 us per k-tile).
-#include <atomic>
 
 #include "gemm_small.h"
 
@@ -770,17 +769,9 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
 
 }  // namespace
 
-// Launches KERN with its dynamic LDS size allowed once per device.
 template <void (*KERN)(GemmArgs, int, int)>
 static int launch_small(const GemmArgs &g, hipStream_t s, int bm, int bn, int threads, size_t lds_bytes) {
-  static std::atomic<uint64_t> allowed{0};
-  int dev = 0;
-  ET_HIP(hipGetDevice(&dev));
-  const uint64_t bit = 1ull << (dev & 63);
-  if (!(allowed.load(std::memory_order_relaxed) & bit)) {
-    ET_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
-    allowed.fetch_or(bit, std::memory_order_relaxed);
-  }
+  if (int rc = allow_lds<KERN>(lds_bytes)) return rc;
   const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.n_store + bn - 1) / bn;
   hipLaunchKernelGGL(KERN, dim3(tiles_m * tiles_n), dim3(threads), lds_bytes, s, g, tiles_m, tiles_n);
   ET_LAUNCH_CHECK();
