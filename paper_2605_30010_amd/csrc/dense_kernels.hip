@@ -1346,18 +1346,17 @@ bool head_dim_supported(int hd) {
 }
 
 template <int HD, int KG>
-static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n, int n_heads, int n_qblk, long long pairs,
+static int launch_attention_group(const uint16_t *qkv, const int32_t *cu, int n, int n_tiles, int n_heads, int n_qblk, long long pairs,
                                   float scale_log2, uint16_t *out, hipStream_t s, const WarmRanges *warm) {
   constexpr size_t bytes = GroupShape<HD, KG>::kLdsBytes;
   constexpr auto kern = attention_group_kernel<HD, KG>;
   if (int rc = allow_lds<kern>(bytes)) return rc;
-  // One workgroup per compute unit: the idle ones read ahead.  The weights of a block (31 MB at a width of 1152) otherwise
-  // come from HBM, the encoder's together being more than the last-level cache holds: us per block, 1 x 729 tokens 68.1
-  // -> 63.7, 2 x 364 65.6 -> 63.1, 3 x 364 82.7 -> 80.4, the attention launch itself +1.2 ... +3.6.  (Where it has several
+  // One workgroup per compute unit: the idle ones read ahead what read_ahead_of allows them.  (Where the attention has several
   // workgroups per compute unit, or beside the QKV projection, reading ahead costs what it gives.)
   const int work = (int)(n_qblk * pairs), idle = device_cus() - work;
-  const int more = warm && idle >= 16 ? idle : 0;
-  hipLaunchKernelGGL(kern, dim3(work + more), dim3(512), bytes, s, qkv, cu, n, n_heads, n_qblk, scale_log2, out, warm ? *warm : WarmRanges{}, work);
+  const WarmRanges ahead = warm ? read_ahead_of(*warm, idle, (n_tiles + KG - 1) / KG) : WarmRanges{};
+  const int more = ahead.bytes[0] ? idle : 0;
+  hipLaunchKernelGGL(kern, dim3(work + more), dim3(512), bytes, s, qkv, cu, n, n_heads, n_qblk, scale_log2, out, ahead, work);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }
@@ -1378,11 +1377,11 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
   const int n_tiles = blocks(kAttBKV);
   if constexpr (GroupShape<HD, 4>::kFits) {
     if (n_tiles >= 2 && blocks(64) * pairs <= cus)
-      return launch_attention_group<HD, 4>(qkv, cu, n, n_heads, blocks(64), pairs, scale_log2, out, s, warm);
+      return launch_attention_group<HD, 4>(qkv, cu, n, n_tiles, n_heads, blocks(64), pairs, scale_log2, out, s, warm);
   }
   if constexpr (GroupShape<HD, 2>::kFits) {
     if (n_tiles >= 5 && blocks(128) * pairs <= cus)
-      return launch_attention_group<HD, 2>(qkv, cu, n, n_heads, blocks(128), pairs, scale_log2, out, s, warm);
+      return launch_attention_group<HD, 2>(qkv, cu, n, n_tiles, n_heads, blocks(128), pairs, scale_log2, out, s, warm);
   }
   // three workgroups per compute unit where that spills nothing (heads of 80: 17.1 us with three, 15.1 with two, 8 x 364)
   hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 72 ? 3 : HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "earlytom.h"
+#include "read_ahead.h"
 
 namespace et {
 
@@ -274,13 +275,6 @@ int launch_gemm(const GemmArgs &g, hipStream_t s, int force_cfg = -1, bool one_t
 bool gemm_takes_pieces(int rows, int cols);
 int device_cus();          // compute units of the current device
 int gemm_config_count();
-// Memory that the launches after this one read and that is in no cache yet (weights): where an attention launch leaves
-// compute units idle, further workgroups of it read these ranges once, so that they come from the last-level cache then.
-struct WarmRanges {
-  static constexpr int kMax = 4;
-  const void *ptr[kMax] = {};
-  uint32_t bytes[kMax] = {};               // multiples of 16
-};
 int launch_attention(const uint16_t *qkv, const int32_t *cu, int n_frames, int max_len, int n_heads,
                      int head_dim, uint16_t *out, hipStream_t s, const WarmRanges *warm = nullptr);
 bool head_dim_supported(int hd);
