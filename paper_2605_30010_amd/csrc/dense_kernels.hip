@@ -655,7 +655,7 @@ __device__ __forceinline__ int xcd_contiguous_index(int total) {
 
 // ---------------------------------------------------------------------------------------
 // attention_dma_kernel: K and V tiles are brought in by direct global -> LDS loads, one tile ahead, two
-// LDS stages, one barrier per 64-key tile; three workgroups share a compute unit (168 registers).  Frames have
+// LDS stages, one barrier per 64-key tile; up to three workgroups share a compute unit (168 registers).  Frames have
 // equal length n (frame f = rows f n ..) or, with `cu` given, the row ranges cu[f] .. cu[f+1]
 // (decoupled selection: the grid is sized for the longest frame and workgroups past a frame's
 // end leave at once).
@@ -941,7 +941,8 @@ struct AttentionRows {
   }
 };
 
-template <int HD, int MINB>
+// QUICK: the pass without an online maximum first (see launch_attention_hd).
+template <int HD, int MINB, bool QUICK>
 __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     const uint16_t *__restrict__ qkv, const int32_t *__restrict__ cu, int n, int n_heads, int n_qblk, float scale_log2,
     uint16_t *__restrict__ out) {
@@ -957,7 +958,7 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
   constexpr int PAD = (NDB * 32 - HD) * kAttBKV + 64;
   __shared__ __align__(16) uint16_t lds[STAGES * STAGE + PAD];
   __shared__ int redo;
-  clear_flag(redo);
+  if (QUICK) clear_flag(redo);
 
   // One-dimensional grid over (frame, head, query block), query block fastest, so that the query blocks
   // of one (frame, head) - which read the same K and V - run on one XCD and share its L2.
@@ -1017,21 +1018,25 @@ __global__ __launch_bounds__(kAttWaves * 64, MINB) void attention_dma_kernel(
     }
   };
   auto careful = [&](int t, const uint16_t *ks, const uint16_t *vs) { rows.tile(ks, vs, t * kAttBKV, n, lane); };
-  pass([&](int t, const uint16_t *ks, const uint16_t *vs) {
-    const int kv0 = t * kAttBKV;
-    const bool edge = t == 0 || t + 1 == n_tiles;
+  if constexpr (QUICK) {
+    pass([&](int t, const uint16_t *ks, const uint16_t *vs) {
+      const int kv0 = t * kAttBKV;
+      const bool edge = t == 0 || t + 1 == n_tiles;
 #pragma unroll                                         // (in this form the registers suffice: no spill in the loop)
-    for (int kb = 0; kb < 2; ++kb) {
-      if (edge) {
-        if (kb == 0 || kv0 + 32 < n) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
-      } else {
-        rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+      for (int kb = 0; kb < 2; ++kb) {
+        if (edge) {
+          if (kb == 0 || kv0 + 32 < n) rows.template quick_block<true>(ks, vs, kb, kv0, n, lane, t == 0 && kb == 0);
+        } else {
+          rows.template quick_block<false>(ks, vs, kb, kv0, n, lane, false);
+        }
       }
-    }
-  });
-  raise_flag(redo, active && !rows.sound(r32));
-  __syncthreads();
-  if (__builtin_expect(redo, 0)) pass(careful);
+    });
+    raise_flag(redo, active && !rows.sound(r32));
+    __syncthreads();
+    if (__builtin_expect(redo, 0)) pass(careful);
+  } else {
+    pass(careful);
+  }
 
   const float inv = 1.0f / rows.denominator(r32);
   const int q = q0 + wave * 32 + r32;
@@ -1383,9 +1388,22 @@ static int launch_attention_hd(const uint16_t *qkv, const int32_t *cu, int n_fra
     if (n_tiles >= 5 && blocks(128) * pairs <= cus)
       return launch_attention_group<HD, 2>(qkv, cu, n, n_tiles, n_heads, blocks(128), pairs, scale_log2, out, s, warm);
   }
-  // three workgroups per compute unit where that spills nothing (heads of 80: 17.1 us with three, 15.1 with two, 8 x 364)
-  hipLaunchKernelGGL((attention_dma_kernel<HD, (HD <= 72 ? 3 : HD <= 96 ? 2 : 1)>), dim3((unsigned)(blocks(kAttBQ) * pairs)),
-                     dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(kAttBQ), scale_log2, out);
+  // Three workgroups per compute unit where the registers suffice without a spill: with both passes up to heads of 72, with the
+  // online maximum alone also heads of 80 (150 registers; both passes take 186, held to 168 they spill).  Those take it from the
+  // first workgroup that two per compute unit leave waiting.  us per launch, two with both passes / three with one: 47 x 59
+  // (12 heads) 9.3 / 7.7, 18 x 172 17.5 / 14.0, 15 x 325 21.0 / 18.6, 29 x 322 32.2 / 29.8, 57 x 829 (12 heads) 227 / 216, 9 x
+  // 761 46.6 / 48.5, 11 x 678 (12 heads) 41.4 / 42.5; up to two per compute unit two are the faster ones (5 x 777, 12 heads,
+  // 23.7 / 26.4; 11 x 148 10.1 / 10.7).
+  const long long work = blocks(kAttBQ) * pairs;
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)work), dim3(kAttWaves * 64), 0, s, qkv, cu, n, n_heads, blocks(kAttBQ), scale_log2, out);
+  };
+  bool three = false;
+  if constexpr (HD == 80) {
+    three = work > 2 * cus;
+    if (three) launch(attention_dma_kernel<HD, 3, false>);
+  }
+  if (!three) launch(attention_dma_kernel<HD, (HD <= 72 ? 3 : HD <= 96 ? 2 : 1), true>);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

@@ -322,6 +322,7 @@ def test_gemm_two_groups_of_wavefronts_in_turn(M, N, K):
     (16, 72, [729, 700]),                 # two groups
     (2, 80, [400, 321]), (2, 96, [330]), (1, 128, [577]),
     (16, 72, [729, 33, 515, 256, 1, 700, 257, 640, 90, 729, 600]),   # ragged, several rounds of workgroups
+    (2, 80, [70] * 256), (2, 80, [70] * 257), (4, 80, [129, 33] * 32), (4, 80, [129, 33] * 33),   # heads of 80: two and three workgroups per compute unit
 ])
 def test_attention_split_and_ragged_forms(n_heads, hd, lens):
     """Same bounds as the oracle test above: probabilities pass through bf16 once, the output is rounded once; partial
