@@ -33,7 +33,8 @@ inline long gemm_tiles(int cfg, long rows, long cols) {
 // t / slots.  Fitted to launches on 256 compute units at widths of 768 to 4352, 64 to 13122 rows, weights
 // from HBM; measured at K = 1152 / 4352:
 //   wave     6.5-7 / 15-17 us for one round of 256 tiles, 10 / 28 for two, 14 / 40 for three
-//   pair64   8.3 / 23 for one round, 15.4 / 43 for two
+//   pair64   8.3 / 23 for one round, 15.4 / 43 for two; an odd number of k-tiles, one round at 5, 7, 11, 17, 69 of them, 7.2, 7.8, 9.0, 11.0,
+//            26.0 where 6, 8, 12, 18, 68 take 6.8, 7.2, 8.5, 10.1, 24.4
 //   pair128  11-12.5 / 30-33 for one round, 22 / 63 for two
 //   half     17 / 47 (135 tiles), 18.3 / 52 (207-243), 34 / 103 for two rounds, 50 for three
 //   128      half rounds of 256 tiles: 13.8, 18, 26, 33.5, 40.5, .. 56 for seven; with a residual 17.5 / 52.5, 21.3 / 62.5, 36 /
@@ -46,7 +47,8 @@ inline double gemm_cost(int cfg, long rows, long cols, int K, bool residual = fa
   auto rounds = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
   switch (cfg) {
     case kCfgWave: return 3.2 + rounds(t, 256) * 0.195 * kt;
-    case kCfgPair64: return 0.5 + rounds(t, 256) * (2.7 + 0.298 * kt);
+    case kCfgPair64:                                       // (two kernels, see above)
+      return 0.5 + rounds(t, 256) * ((K / 64) % 2 ? 2.9 + 0.32 * kt : 2.7 + 0.298 * kt);
     case kCfgPair128: return t <= 256 ? 3.6 + kt * (0.36 + 0.09 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.42 * kt);
     case kCfgHalf: return t <= 256 ? 5.5 + kt * (0.56 + 0.16 * (double)t / 256.0) : rounds(t, 256) * (2.2 + 0.82 * kt);
     case kCfgStrip: return 3.2 + rounds(t, 256) * 0.205 * kt;

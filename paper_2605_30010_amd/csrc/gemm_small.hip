@@ -336,8 +336,9 @@ __global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tile
 // a group, so the load path carries half (128 x 128) or three quarters (128 x 64) of what four
 // 64 x 64 tiles would.  A set of k-tiles (one per group of a half) is loaded four phases ahead (three
 // stages: two phases).  Measured, one workgroup per compute unit (before: 64 x 128 workgroup tile):
-//   729 rows, 3456 x 1152 (162 workgroups of 128 x 128): 14.0 -> 12.0 us; 1092 rows, 1152 x 4352 (162 of
-//   128 x 64): 51 -> 26 us; 3276 rows, 1152 x 4352 (234 of 128 x 128): 54 -> 38 us.
+//   729 rows, 3456 x 1152 (162 workgroups of 128 x 128): 14.0 -> 12.0 us; 3276 rows, 1152 x 4352 (234 of 128 x 128): 54 -> 38 us.
+// As 128 x 64 it serves odd numbers of k-tiles only (gemm_duo_kernel below the even ones): 2048 rows, 1024 x 1088, 11.0 us; there
+// with 1152, 10.1.
 // ---------------------------------------------------------------------------------------
 template <int BM, int BN>
 struct PairShape {

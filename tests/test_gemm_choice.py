@@ -8,12 +8,12 @@ import subprocess
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_30010_amd", "csrc")
-IN_ORDER = {0, 1, 5, 6}          # one accumulator, k ascending; 2, 3 and 4 add up 4, 4 and 2 shares of k
+IN_ORDER = {0, 1, 5, 6}          # one accumulator, k ascending; 2, 3 and 4 add up 4, 2 (of an odd number of k-tiles 4) and 2 shares of k
 
 SHIM = """
 #include "gemm_choice.h"
-extern "C" int plan(int rows, int cols, int K, int cus, int rows_splittable, int one_tile, int *out) {
-  const et::GemmPlan p = et::plan_gemm(et::GemmRules{K, cus, rows_splittable != 0, one_tile != 0}, rows, cols);
+extern "C" int plan(int rows, int cols, int K, int cus, int rows_splittable, int one_tile, int residual, int *out) {
+  const et::GemmPlan p = et::plan_gemm(et::GemmRules{K, cus, rows_splittable != 0, one_tile != 0, residual != 0}, rows, cols);
   for (int i = 0; i < p.n; ++i) {
     const et::GemmPart &t = p.part[i];
     const int v[5] = {t.row0, t.rows, t.col0, t.cols, t.cfg};
@@ -21,21 +21,29 @@ extern "C" int plan(int rows, int cols, int K, int cus, int rows_splittable, int
   }
   return p.n;
 }
+extern "C" double cost(int cfg, int rows, int cols, int K) { return et::gemm_cost(cfg, rows, cols, K); }
 """
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def shim(tmp_path_factory):
     d = tmp_path_factory.mktemp("gemm_choice")
     src, lib = str(d / "shim.cpp"), str(d / "shim.so")
     with open(src, "w") as f:
         f.write(SHIM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
-    fn = C.CDLL(lib).plan
+    shim = C.CDLL(lib)
+    shim.cost.restype = C.c_double
+    return shim
+
+
+@pytest.fixture(scope="module")
+def plan(shim):
+    fn = shim.plan
     buf = (C.c_int * 80)()
 
-    def call(rows, cols, K, rows_splittable=True, one_tile=False, cus=256):
-        n = fn(rows, cols, K, cus, int(rows_splittable), int(one_tile), buf)
+    def call(rows, cols, K, rows_splittable=True, one_tile=False, cus=256, residual=False):
+        n = fn(rows, cols, K, cus, int(rows_splittable), int(one_tile), int(residual), buf)
         assert 1 <= n <= 16
         return [tuple(buf[5 * i:5 * i + 5]) for i in range(n)]
     return call
@@ -77,3 +85,12 @@ def test_launches_with_row_statistics_walk_one_tile_per_workgroup(plan, cus):
         (_, _, _, _, cfg), = plan(rows, cols, K, one_tile=True, cus=cus)
         assert cfg != 0 or -(-rows // 256) * -(-cols // 256) <= cus, (rows, cols, K)
         assert cfg != 1 or -(-rows // 128) * -(-cols // 128) <= 2 * cus, (rows, cols, K)
+
+
+def test_an_odd_number_of_k_tiles_is_rated_by_its_own_kernel(plan, shim):
+    """128 x 64 tiles run another kernel where K / 64 is odd, which takes longer than the other one's next larger K (256
+    workgroups, 5 to 19 k-tiles: 7.2, 6.8, 7.8, 7.2, .., 11.0, 10.1, 11.5 us)."""
+    for kt in range(5, 18, 2):
+        assert shim.cost(3, 2048, 1024, 64 * kt) > shim.cost(3, 2048, 1024, 64 * (kt + 1)), kt
+    assert [p[4] for p in plan(1261, 3264, 1088)] == [5]              # 17.2 us; as 128 x 64 tiles 18.6
+    assert [p[4] for p in plan(2787, 1472, 1472, residual=True)] == [5]   # 22.7; 23.9
