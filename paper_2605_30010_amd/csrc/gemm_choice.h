@@ -37,6 +37,7 @@ inline long gemm_tiles(int cfg, long rows, long cols) {
 //            26.0 where 6, 8, 12, 18, 68 take 6.8, 7.2, 8.5, 10.1, 24.4
 //   pair128  11-12.5 / 30-33 for one round, 22 / 63 for two
 //   half     17 / 47 (135 tiles), 18.3 / 52 (207-243), 34 / 103 for two rounds, 50 for three
+//            5 to 8 k-tiles, a round of several: 8.9-10.8 (5), 10.4-11.8 (7), 12.3-13.5 (8)
 //   128      half rounds of 256 tiles: 13.8, 18, 26, 33.5, 40.5, .. 56 for seven; with a residual 17.5 / 52.5, 21.3 / 62.5, 36 /
 //            110, 40 / 133 (the loads of the residual rows wait for the next tile's operands)
 //   256      25 / 80 (70 tiles), 26 (182), 30.5 (252), 33 / 98 (230, residual), 55 (448), 87 (728)
@@ -50,7 +51,9 @@ inline double gemm_cost(int cfg, long rows, long cols, int K, bool residual = fa
     case kCfgPair64:                                       // (two kernels, see above)
       return 0.5 + rounds(t, 256) * ((K / 64) % 2 ? 2.9 + 0.32 * kt : 2.7 + 0.298 * kt);
     case kCfgPair128: return t <= 256 ? 3.6 + kt * (0.36 + 0.09 * (double)t / 256.0) : 0.5 + rounds(t, 256) * (3.2 + 0.42 * kt);
-    case kCfgHalf: return t <= 256 ? 5.5 + kt * (0.56 + 0.16 * (double)t / 256.0) : rounds(t, 256) * (2.2 + 0.82 * kt);
+    case kCfgHalf:                                         // (of several rounds each pays its own first loads and epilogue: short k-loops)
+      if (t > 256) return rounds(t, 256) * (kt > 4 && kt < 11 ? 5.0 + 0.56 * kt : 2.2 + 0.82 * kt);
+      return 5.5 + kt * (0.56 + 0.16 * (double)t / 256.0);
     case kCfgStrip: return 3.2 + rounds(t, 256) * 0.205 * kt;
     case kCfg128: {
       const double h = rounds(t, 256);                     // half rounds: two workgroups share a compute unit

@@ -94,3 +94,10 @@ def test_an_odd_number_of_k_tiles_is_rated_by_its_own_kernel(plan, shim):
         assert shim.cost(3, 2048, 1024, 64 * kt) > shim.cost(3, 2048, 1024, 64 * (kt + 1)), kt
     assert [p[4] for p in plan(1261, 3264, 1088)] == [5]              # 17.2 us; as 128 x 64 tiles 18.6
     assert [p[4] for p in plan(2787, 1472, 1472, residual=True)] == [5]   # 22.7; 23.9
+
+
+def test_short_contractions_of_several_rounds_run_on_the_persistent_kernel(plan):
+    """256 x 128 tiles fetch and finish anew in each round, which short k-loops do not hide (us per launch, that tiling / the
+    persistent kernel): 23709 x 1344, 7 k-tiles, 43.4 / 34.3; 15395 x 1536, 8, 34.7 / 29.8; 13409 x 1152, 6, 21.1 / 17.8."""
+    for rows, cols, K in ((23709, 1344, 448), (15395, 1536, 512), (13409, 1152, 384), (16057, 1344, 448)):
+        assert {p[4] for p in plan(rows, cols, K)} <= {0, 1}, (rows, cols, K)
