@@ -57,7 +57,10 @@ inline double gemm_cost(int cfg, long rows, long cols, int K, bool residual = fa
     case kCfgStrip: return 3.2 + rounds(t, 256) * 0.205 * kt;
     case kCfg128: {
       const double h = rounds(t, 256);                     // half rounds: two workgroups share a compute unit
-      // (rated some 5 % above what was measured: it moves more operand bytes than 256 x 256, which costs clock elsewhere)
+      // (Dearer by design than 256 x 256: this formula gives 0.9 to 1.0 of what a launch takes by itself, that one 0.75 at short K, 0.8
+      // to 0.9 at 12 to 24 k-tiles and 0.95 beyond, with a residual, which it has no term for, and without.  128 x 128 moves more
+      // operand bytes, which costs clock in the launches beside it.  Over 130 launches of 1500 to 24000 rows what is chosen takes
+      // 1.6 % longer than the fastest single tiling, with a residual at most 8 %.)
       if (!residual) return h < 2 ? 4.2 + 0.5 * kt : 4.2 + 0.8 * kt + (h - 2) * (0.9 + 0.45 * kt);
       const long pairs = (long)h / 2;
       const double single = (long)h % 2 ? 1.0 : 0.0;

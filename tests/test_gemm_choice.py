@@ -61,11 +61,12 @@ def _sizes():
         yield int(2 ** rng.uniform(0, 18)), 8 * int(2 ** rng.uniform(0, 13)), 64 * int(2 ** rng.uniform(0, 8))
 
 
-def test_parts_tile_the_matrix_and_keep_one_order_over_its_rows(plan):
+@pytest.mark.parametrize("residual", [False, True])
+def test_parts_tile_the_matrix_and_keep_one_order_over_its_rows(plan, residual):
     split = 0
     for rows, cols, K in _sizes():
         for rows_splittable in (True, False):
-            parts = plan(rows, cols, K, rows_splittable)
+            parts = plan(rows, cols, K, rows_splittable, residual=residual)
             assert sum(n * c for _, n, _, c, _ in parts) == rows * cols, (rows, cols, K, parts)
             for i, (r0, n, c0, c, cfg) in enumerate(parts):
                 assert n > 0 and c > 0 and 0 <= r0 and r0 + n <= rows and 0 <= c0 and c0 + c <= cols
@@ -77,12 +78,13 @@ def test_parts_tile_the_matrix_and_keep_one_order_over_its_rows(plan):
     assert split > 300           # (the sizes do reach launches over some of the rows)
 
 
+@pytest.mark.parametrize("residual", [False, True])
 @pytest.mark.parametrize("cus", [32, 64, 128, 256])
-def test_launches_with_row_statistics_walk_one_tile_per_workgroup(plan, cus):
+def test_launches_with_row_statistics_walk_one_tile_per_workgroup(plan, cus, residual):
     """The persistent kernel takes row statistics only where each workgroup has one tile (one 256 x 256 or two 128 x 128
     per compute unit); it refuses the call otherwise, so on no device, whole or partitioned, may it be chosen there."""
     for rows, cols, K in _sizes():
-        (_, _, _, _, cfg), = plan(rows, cols, K, one_tile=True, cus=cus)
+        (_, _, _, _, cfg), = plan(rows, cols, K, one_tile=True, cus=cus, residual=residual)
         assert cfg != 0 or -(-rows // 256) * -(-cols // 256) <= cus, (rows, cols, K)
         assert cfg != 1 or -(-rows // 128) * -(-cols // 128) <= 2 * cus, (rows, cols, K)
 
