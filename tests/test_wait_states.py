@@ -29,6 +29,17 @@ __global__ void overwrite_behind_store(uint16_t *p, const u32x4 *src) {
 }
 template __global__ void overwrite_behind_store<true>(uint16_t *, const u32x4 *);
 template __global__ void overwrite_behind_store<false>(uint16_t *, const u32x4 *);
+
+// The origin comes out of a vector register right in front of the load.
+__global__ void load_from_a_fresh_base(const uint16_t *const *rows, uint16_t *out) {
+  __shared__ __align__(16) uint16_t lds[512];
+  const uint64_t a = (uint64_t)rows[threadIdx.x];
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)), lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  __builtin_amdgcn_sched_barrier(0);
+  lds_dma16_untracked((const uint16_t *)(((uint64_t)hi << 32) | lo), threadIdx.x * 16, lds);
+  wait_all();
+  *reinterpret_cast<u32x4 *>(out + threadIdx.x * 8) = *reinterpret_cast<const u32x4 *>(lds + threadIdx.x * 8);
+}
 }
 """
 
@@ -102,6 +113,26 @@ def test_data_of_a_write_through_store_outlive_it(kernels):
     assert len(known) >= 3 and len(written) >= 3
     assert min(known) == 2
     assert min(written) >= 2, written
+
+
+def test_scalar_base_of_an_untracked_load_is_there_when_it_reads_it(kernels):
+    """A vector-memory instruction may read a scalar register five wait states after a vector instruction has written it, and
+    M0 one after a scalar move: the load that the compiler does not know brings these along."""
+    body = of(kernels, "load_from_a_fresh_base")
+    (at,) = [i for i, code in enumerate(body) if code.startswith("global_load_lds_dwordx4")]
+    base = registers(body[at].split()[2])
+    assert len(base) == 2, body[at]
+    states, m0 = 0, None
+    for before in reversed(body[:at]):
+        if before.startswith("s_mov_b32 m0"):
+            m0 = states
+        if before.startswith("v_readfirstlane") and registers(before.split()[1]) & base:
+            break
+        assert not registers(before.split()[1] if " " in before else "") & base, before      # (copied by a scalar instruction since)
+        states += wait_states(before)
+    else:
+        pytest.fail("no vector instruction writes the base: %s" % body[:at + 1])
+    assert states >= 5 and m0 is not None and m0 >= 1, body[max(0, at - 8):at + 1]
 
 
 def test_attention_waits_for_its_lds_reads_in_front_of_each_barrier(tmp_path):
