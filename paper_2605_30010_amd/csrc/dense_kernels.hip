@@ -236,7 +236,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const Ge
   static_assert(NS == 4 && MS % 2 == 0, "the staged epilogue handles 64-column wavefront tiles in blocks of 32 rows");
   const int r16 = lane & 15, g4 = lane >> 4;
   const int prow = lane >> 3, pch = lane & 7;                 // row-wise phase: 8 rows x 8 chunks per pass
-  // Bias and row scales lie in the slice (bias_at floats from its start, and from its start); read before it takes results.
+  // Bias and row scales lie in the slice (kBiasInSlice floats from its start, and at its start); read before it takes results.
   const float *in_slice = reinterpret_cast<const float *>(slice);
   float rsv[MS];                                              // row scales of this lane's rows
 #pragma unroll
@@ -635,11 +635,11 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
 
 // ---------------------------------------------------------------------------------------
 // Attention: softmax(Q K^T / sqrt(hd)) V inside one frame, one head per workgroup column.
-// Flash-style streaming over 64-key tiles with an online softmax.  Everything is computed
-// transposed: S^T = K Q^T puts the query on the accumulator's lane axis, so the running
-// maximum, the running sum and the rescale factor are per-lane scalars, and the exponentiated
-// accumulator registers are, without any data movement, MFMA operand "B" of
-// O^T = V^T P^T.
+// Flash-style streaming over 64-key tiles.  Everything is computed transposed: S^T = K Q^T puts the
+// query on the accumulator's lane axis, so the exponentials' reference and the running sum are per-lane
+// scalars, and the exponentiated accumulator registers are, without any data movement, MFMA operand "B" of
+// O^T = V^T P^T.  The reference is the maximum of the first keys and stays (quick_block); where that does not
+// serve, a second pass takes a running maximum and rescales (tile).
 // ---------------------------------------------------------------------------------------
 constexpr int kAttWaves = 4;
 constexpr int kAttBQ = kAttWaves * 32;
@@ -672,7 +672,10 @@ __device__ __forceinline__ int xcd_contiguous_index(int total) {
 // with an online maximum (tile).  Bound: the board's power cap on many frames (1.63 GHz; matrix unit busy 58 % of the
 // clocks), on few the chain of a wavefront.  Measured against an online maximum in every tile (heads of 72, us per launch):
 // 64 x 729 320 -> 285, 32 x 729 140 -> 125, 23 x 729 99 -> 89, 8 x 729 36.9 -> 34.1, 9 x 364 16.7 -> 15.0; heads of 64,
-// 16 x 196 12.3 -> 11.7.  (Two query blocks per wavefront spill: 170.)
+// 16 x 196 12.3 -> 11.7.  (Two query blocks per wavefront spill: 170.)  The second pass, per workgroup that has a query with a
+// later logit some 41 (2^60 in weight) above its first 32, or anything that is not finite; launches in which every workgroup
+// has one, against a single pass with an online maximum: 64 x 729 288 -> 481, 8 x 729 36 -> 58, 2 x 729 16.9 -> 26.0, 1 x 729 12.8 ->
+// 18.5, heads of 64, 16 x 196, 12.8 -> 18.8; up to that jump nothing (by 30: 36.4 -> 33.1, 12.7 -> 11.4).
 // ---------------------------------------------------------------------------------------
 // LDS transpose read: every lane of a 16-lane group supplies the address of four consecutive 16-bit
 // elements; lane j of the group receives element j % 4 of the lanes j / 4, 4 + j / 4, 8 + j / 4 and

@@ -162,12 +162,12 @@ def test_attention_uniform_matches_oracle(n_heads, hd, n_frames, length):
 
 @pytest.mark.parametrize("order", ["rising", "falling", "negative_first", "spike_last"])
 def test_attention_uniform_moving_maxima(order):
-    """The online softmax keeps a reference maximum that it moves only when a 64-key tile exceeds it by
-    2^8; these inputs make the row maxima climb by far more than that from tile to tile (rising), never
-    move after the first tile (falling), start far below zero (negative_first), or jump in the last,
-    partly filled tile (spike_last)."""
+    """The exponentials refer to the maximum of the first 32 keys.  These inputs make the row maxima climb past it by some 2^47 over
+    the frame (rising) or by 2^41 in the last, partly filled tile (spike_last), which the weights carry without another reference, never
+    exceed it (falling), or start so far below the rest (negative_first) that the weights leave their range and the tiles are walked
+    again with an online maximum."""
     n_heads, hd, length = 16, 72, 729
-    n_frames = 11 if order in ("rising", "spike_last") else 2    # 11 frames: two query blocks per wavefront
+    n_frames = 11 if order in ("rising", "spike_last") else 2    # 11 frames: 128 queries per workgroup; two: groups of wavefronts
     rng = np.random.default_rng({"rising": 1, "falling": 2, "negative_first": 3, "spike_last": 4}[order])
     D, rows = n_heads * hd, n_frames * length
     _, qkv = _bf(rng, (rows, 3 * D))
@@ -373,8 +373,8 @@ def test_equal_rows_have_equal_bits_wherever_they_lie(M, N, K, epi):
     (16, 72, [729], (64, 128)), (4, 64, [300], (64, 128)), (2, 16, [300], (128, 192)),       # first tile of one of four groups
     (16, 72, [729], (64, 200)), (2, 32, [130], (0, 64)),                                     # ... and more of its tiles; of the first group
     (16, 72, [729, 700], (64, 128)), (2, 96, [330], (64, 128)), (2, 80, [400, 321], (0, 130)),       # two groups
-    (16, 72, [729] * 5, (0, 64)), (16, 64, [130] * 30, (0, 100)), (2, 128, [70], (0, 32)),           # one block of 32 queries per wavefront
-    (16, 72, [150] * 96, (0, 96)), (16, 16, [70] * 96, (0, 32)), (16, 80, [129] * 96, (0, 64)),      # two blocks
+    (16, 72, [729] * 5, (0, 64)), (16, 64, [130] * 30, (0, 100)), (2, 128, [70], (0, 32)),           # 128 queries per workgroup
+    (16, 72, [150] * 96, (0, 96)), (16, 16, [70] * 96, (0, 32)), (16, 80, [129] * 96, (0, 64)),      # ... and many rounds of workgroups
 ])
 @pytest.mark.parametrize("shift", [0.0, -16.0])
 def test_attention_with_logits_of_minus_infinity(n_heads, hd, lens, dead, shift):
@@ -403,10 +403,10 @@ def test_attention_with_logits_of_minus_infinity(n_heads, hd, lens, dead, shift)
     (16, 72, [729] * 32), (16, 16, [70] * 96), (12, 64, [129] * 130), (16, 32, [64] * 96), (16, 80, [1] * 96),
     (16, 72, [257, 0, 1, 255, 64, 33] * 9), (24, 80, [300] * 33), (16, 64, [256, 31] * 48),
 ])
-def test_attention_with_two_query_blocks_per_wavefront(n_heads, hd, lens):
-    """From 1536 workgroups of 256 queries on (six per compute unit) a wavefront owns two blocks of 32 queries, in frames of
-    one length and in ragged ones.  Bounds as in the oracle test."""
-    assert -(-max(lens) // 256) * n_heads * len(lens) >= 1536
+def test_attention_over_several_rounds_of_workgroups(n_heads, hd, lens):
+    """More workgroups of 128 queries than the compute units hold at a time (three each), in frames of one length and in ragged
+    ones: wavefronts past a frame's queries, workgroups past its end, frames of a few tokens.  Bounds as in the oracle test."""
+    assert -(-max(lens) // 128) * n_heads * len(lens) >= 1536
     rng = np.random.default_rng(n_heads * hd + len(lens))
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     rows, D = int(cu[-1]), n_heads * hd
@@ -450,3 +450,50 @@ def test_attention_where_the_first_reference_does_not_last(n_heads, hd, lens, ju
     for out in got:
         assert rel_l2(dev_to_f64(out), ref) < 6e-3
         assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05 * v_scale
+
+
+@pytest.mark.parametrize("n_heads,hd,lens,stride", [
+    (16, 72, [729], 4), (16, 72, [729, 700], 2), (16, 72, [729] * 11, 1),          # four and two groups of wavefronts; 128 queries per workgroup
+    (4, 64, [729], 4), (12, 64, [330] * 30, 1), (2, 16, [729] * 3, 4), (16, 16, [380] * 40, 1), (3, 32, [729], 4), (12, 32, [380] * 40, 1),
+    (2, 80, [729], 2), (16, 80, [380] * 7, 1), (16, 80, [380] * 10, 1),            # the latter: the online maximum alone
+    (2, 96, [729], 2), (16, 96, [380] * 6, 1), (1, 128, [729], 2), (16, 128, [380] * 6, 1),
+])
+def test_attention_rescales_what_still_counts(n_heads, hd, lens, stride):
+    """The pass with an online maximum (a key far above the first reference forces it: the last key, for every 32nd query) moves its
+    reference when a key tile exceeds it by 2^8, and rescales what it has summed up.  The other queries' logits climb by 7 (2^10)
+    in every third tile of a group of wavefronts, there in one key only, so that the keys below it keep a share s of the weight of
+    0.15 to 0.25; their values are 1, the high key's -1.  The scaled q is rounded to bf16, and here one component of it makes the
+    whole step: 7 * 2^-9 in the logit, the same for all keys of a level, with another 2^-8 from the probabilities' own rounding.  That moves the result 1 - 2s by
+    2 s (1 - s) * 0.018, 1.3 % of it at s = 0.25; with the oracle test's 6e-3 the bound is 2e-2.  An oracle whose keys below the last
+    step are left out, or are not scaled down, is ten times further off."""
+    rng = np.random.default_rng(n_heads * hd + len(lens))
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows, D = int(cu[-1]), n_heads * hd
+    pos = np.concatenate([np.arange(n) for n in lens])
+    last = np.concatenate([np.arange(n) == n - 1 for n in lens])
+    tile = pos // 64 // stride                                     # tiles of a group in its own order
+    step = (tile % 3 == 2) & (pos % 64 == 5)                       # the key that leads to the next level
+    level = tile // 3 + step
+    forced = pos % 32 == 7
+    heads = (0.2 * rng.standard_normal((rows, 3, n_heads, hd)))
+    heads[:, 0, :, 0] = np.where(forced, 8.0, 0.0)[:, None]
+    heads[:, 1, :, 0] = np.where(last, 100.0 * math.sqrt(hd) / 8.0, 0.0)[:, None]
+    heads[:, 0, :, 1] = np.where(forced, 0.0, 8.0)[:, None]
+    heads[:, 1, :, 1] = np.where(last, 0.0, 7.0 * level * math.sqrt(hd) / 8.0)[:, None]
+    heads[:, 2] += np.where(step, -1.0, 1.0)[:, None, None]
+    bits = f32_to_bf16_bits(heads.reshape(rows, 3 * D).astype(np.float32))
+    qkv = bf16_bits_to_f32(bits).astype(np.float64)
+    ref = _attention_ref(qkv, cu, n_heads, hd)
+    got = [et.et_attention(bits_to_dev(bits), torch.from_numpy(cu).cuda(), max(lens), n_heads, hd)]
+    if len(set(lens)) == 1:
+        got.append(et.et_attention_uniform(bits_to_dev(bits), len(lens), lens[0], n_heads, hd))
+    for out in got:
+        assert rel_l2(dev_to_f64(out), ref) < 2e-2
+        assert np.max(np.abs(dev_to_f64(out) - ref)) < 0.05
+    top = np.concatenate([np.full(n, level[cu[f]:cu[f + 1]].max()) for f, n in enumerate(lens)])
+    below = level < top
+    for wrong in (-60.0, 7.0 * math.sqrt(hd) / 8.0):               # the last rescaling by 0, and by 1
+        planted = qkv.copy()
+        planted.reshape(rows, 3, n_heads, hd)[below & ~last, 1, :, 1] += wrong
+        mistaken = _attention_ref(planted, cu, n_heads, hd)
+        assert rel_l2(mistaken[~forced], ref[~forced]) > 0.2
