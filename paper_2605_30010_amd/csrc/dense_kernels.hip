@@ -669,8 +669,9 @@ __device__ __forceinline__ int xcd_contiguous_index(int total) {
 // whatever follows a V row; that only reaches accumulator rows >= head_dim, which are never
 // stored (MFMA output rows are independent).
 // No maximum is kept over the tiles (quick_block); a workgroup whose first reference did not last walks its tiles again
-// with an online maximum (tile).  Bound: the board's power cap on many frames (1.63 GHz; matrix unit busy 58 % of the
-// clocks), on few the chain of a wavefront.  Measured against an online maximum in every tile (heads of 72, us per launch):
+// with an online maximum (tile).  Bound on many frames: the matrix and the vector unit are busy 40 % of the cycles each, 38 %
+// of the former at the same time, with the board near its power cap (back to back 1370 of 1400 W at 1.9 GHz); on few
+// the chain of a wavefront.  Measured against an online maximum in every tile (heads of 72, us per launch):
 // 64 x 729 320 -> 285, 32 x 729 140 -> 125, 23 x 729 99 -> 89, 8 x 729 36.9 -> 34.1, 9 x 364 16.7 -> 15.0; heads of 64,
 // 16 x 196 12.3 -> 11.7.  (Two query blocks per wavefront spill: 170.)  The second pass, per workgroup that has a query with a
 // later logit some 41 (2^60 in weight) above its first 32, or anything that is not finite; launches in which every workgroup
