@@ -678,20 +678,6 @@ __device__ __forceinline__ int xcd_contiguous_index(int total) {
 // has one, against a single pass with an online maximum: 64 x 729 288 -> 481, 8 x 729 36 -> 58, 2 x 729 16.9 -> 26.0, 1 x 729 12.8 ->
 // 18.5, heads of 64, 16 x 196, 12.8 -> 18.8; up to that jump nothing (by 30: 36.4 -> 33.1, 12.7 -> 11.4).
 // ---------------------------------------------------------------------------------------
-// LDS transpose read: every lane of a 16-lane group supplies the address of four consecutive 16-bit
-// elements; lane j of the group receives element j % 4 of the lanes j / 4, 4 + j / 4, 8 + j / 4 and
-// 12 + j / 4 (layout checked on the device).  With lane s of a group pointing at row s / 4, columns
-// 4 (s % 4) .. + 3 of a row-major matrix, lane j gets column j of four consecutive rows.
-__device__ __forceinline__ uint2 lds_read_tr16(const uint16_t *p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-  return __builtin_bit_cast(uint2, v);
-#else
-  return make_uint2(0u, 0u);
-#endif
-}
-
 // A flag in LDS that any wavefront of the workgroup can raise: cleared at the kernel's start by one thread, whose write
 // is waited for in front of the first barrier; read behind a later one.
 __device__ __forceinline__ void clear_flag(int &flag) {

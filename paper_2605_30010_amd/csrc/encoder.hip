@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "et_common.h"
+#include "gemm_choice.h"
 
 namespace et {
 
@@ -34,6 +35,7 @@ struct et_encoder {
   uint16_t *patch_w = nullptr, *pos_emb = nullptr;
   float *patch_b = nullptr, *final_g = nullptr, *final_b = nullptr;
   std::vector<et::LayerDev> layers;
+  char *narrow_pack = nullptr;          // see pack_narrow (NULL: not a narrow encoder)
   et::Profiler prof;
   int32_t *count_host = nullptr;        // pinned: segment count read back in the middle of the compression stage
   hipEvent_t count_ready = nullptr;
@@ -212,6 +214,69 @@ static int run_block(et_encoder *e, int layer, const EncWs &w, int rows, const i
   return ET_OK;
 }
 
+// Whether every frame of the encoder fits the kernel that takes a frame through a run of blocks (narrow_blocks.hip).  A rule
+// on the encoder, not on the call: the stages of one clip, and et_encoder_block_qkv, see the same arithmetic throughout.
+// An encoder of 4 blocks and 64 tokens per frame, merge after two, us per call by launches / by frames: 1 frame 149 / 79, 8 frames 158 / 84, 64 frames
+// 160 / 88.
+static bool is_narrow(const et_encoder *e) {
+  return e->D == kNarrowWidth && e->L <= kNarrowTokens && e->Mhp <= kNarrowMlp && (e->hd == 16 || e->hd == 32 || e->hd == 64);
+}
+
+// Blocks first .. last - 1 on the frames of w.x; leaves the stream in `out`, normalised if `final_norm`, and q | k | v of
+// the last block in w.qkv.
+static int run_narrow_blocks(et_encoder *e, int first, int last, const EncWs &w, const int32_t *cu, int n_frames, int max_len, bool final_norm,
+                             uint16_t *out, hipStream_t s) {
+  NarrowArgs a{};
+  a.pack = e->narrow_pack + (size_t)first * NarrowPack::bytes(e->Mhp);
+  a.n_layers = last - first;
+  a.x = w.x;
+  a.out = out;
+  a.qkv = w.qkv;
+  a.cu = cu;
+  a.len = max_len;
+  a.mlp = e->Mhp;
+  a.ln_eps = e->cfg.ln_eps;
+  a.scale_log2 = 1.4426950408889634f / sqrtf((float)e->hd);
+  if (final_norm) {
+    a.final_g = e->final_g;
+    a.final_b = e->final_b;
+  }
+  ET_TIMED(ET_K_MISC, launch_narrow_blocks(a, n_frames, e->cfg.n_heads, s));
+  return ET_OK;
+}
+
+// The parameters of all blocks once more, as that kernel reads them.
+static int pack_narrow(et_encoder *e) {
+  const int mlp = e->Mhp, D = kNarrowWidth;
+  std::vector<char> host((size_t)e->cfg.n_layers * NarrowPack::bytes(mlp));
+  std::vector<uint16_t> plain((size_t)mlp * D > (size_t)3 * D * D ? (size_t)mlp * D : (size_t)3 * D * D);
+  for (int i = 0; i < e->cfg.n_layers; ++i) {
+    char *p = host.data() + (size_t)i * NarrowPack::bytes(mlp);
+    const LayerDev &l = e->layers[i];
+    const struct { int off; const uint16_t *src; int rows, cols; } mats[] = {{NarrowPack::wqkv(), l.wqkv, 3 * D, D}, {NarrowPack::wo(), l.wo, D, D},
+                                                                             {NarrowPack::w1(), l.w1, mlp, D}, {NarrowPack::w2(mlp), l.w2, D, mlp}};
+    for (const auto &m : mats) {
+      ET_HIP(hipMemcpy(plain.data(), m.src, (size_t)m.rows * m.cols * 2, hipMemcpyDeviceToHost));
+      for (int r = 0; r < m.rows; ++r)
+        for (int c = 0; c < m.cols; c += 8)
+          memcpy(p + m.off + ((r / 16) * (m.cols / 32) + c / 32) * 1024 + ((c / 8 % 4) * 16 + r % 16) * 16, plain.data() + (size_t)r * m.cols + c, 16);
+    }
+    const struct { int off; const float *src; int n; } biases[] = {{NarrowPack::bqkv(mlp), l.bqkv, 3 * D}, {NarrowPack::bo(mlp), l.bo, D},
+                                                                   {NarrowPack::b1(mlp), l.b1, mlp}, {NarrowPack::b2(mlp), l.b2, D}};
+    for (const auto &b : biases) ET_HIP(hipMemcpy(p + b.off, b.src, (size_t)b.n * 4, hipMemcpyDeviceToHost));
+  }
+  void *d = nullptr;
+  if (hipMalloc(&d, host.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    set_error("device allocation of %zu bytes failed", host.size());
+    return ET_ERR_ALLOC;
+  }
+  e->allocs.push_back(d);
+  e->narrow_pack = static_cast<char *>(d);
+  ET_HIP(hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice));
+  return ET_OK;
+}
+
 }  // namespace et
 
 using namespace et;
@@ -295,6 +360,7 @@ int et_encoder_create(const et_config *config, const et_weights *weights, int32_
     ET_TRY(upload_bf16(e, weights->w2[i], D, c.d_mlp, Dn, e->Mhp, &l.w2));
     ET_TRY(upload_f32(e, weights->b2[i], D, Dn, &l.b2));
   }
+  if (is_narrow(e) && c.n_layers > 0) ET_TRY(pack_narrow(e));
 #undef ET_TRY
   if (hipEventCreateWithFlags(&e->count_ready, hipEventDisableTiming) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void **>(&e->count_host), 64, hipHostMallocDefault) != hipSuccess) {
@@ -377,11 +443,13 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
                                              out->seg_start_dev, s));
   }
 
+  const bool narrow = is_narrow(e);
+  bool finished = false;                   // out->tokens_dev is written
   // patch embedding: x = patches * Wp^T + bp + pos_emb[l]
   ET_TIMED(ET_K_IM2COL, launch_im2col(frames_dev, T, c.channels, c.image_h, c.image_w, c.patch, e->Kp_pad, w.hid, s));
   {
     GemmArgs g{w.hid, e->Kp_pad, e->patch_w, e->patch_b, e->pos_emb, D, L, w.x, D, T * L, D, e->Kp_pad, EPI_BIAS_RES};
-    if (takes_pieces(e, T * L)) {
+    if (!narrow && takes_pieces(e, T * L)) {
       g.stats_out = w.pieces;
       g.stats_ld = w.piece_ld;
     }
@@ -391,9 +459,10 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
   bool ragged = false, selected = false, first_stage = true;
   bool have_pieces = true;         // w.pieces belongs to w.x: not after a stage has replaced it
   int n_segments = T, next_merge = 0;
+  auto merges_at = [&](int i) { return compress && policy && !selected && next_merge < n_merge && merge_layers[next_merge] == i; };
+  auto selects_at = [&](int i) { return compress && !selected && i == merge_layer; };
   for (int i = 0; i <= c.n_layers; ++i) {
-    const bool merge_here = compress && policy && !selected && next_merge < n_merge && merge_layers[next_merge] == i;
-    const bool select_here = compress && !selected && i == merge_layer;
+    const bool merge_here = merges_at(i), select_here = selects_at(i);
     if (merge_here || select_here) have_pieces = false;
     if (policy && (merge_here || select_here)) {
       const MergeWs mw = carve_merge(w.merge, T, L, D);
@@ -458,7 +527,16 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
       selected = true;
       e->prof.phase = 1;
     }
-    if (i < c.n_layers) {
+    if (i < c.n_layers && narrow) {        // all blocks up to the next stage
+      int last = i + 1;
+      while (last < c.n_layers && !merges_at(last) && !selects_at(last)) ++last;
+      finished = last == c.n_layers && !merges_at(last) && !selects_at(last);
+      int rc = run_narrow_blocks(e, i, last, w, ragged ? cu : nullptr, n_frames, max_len, finished && c.has_final_ln, finished ? out->tokens_dev : w.x, s);
+      if (rc) return rc;
+      if (by_attention && !selected && last == merge_layer)
+        ET_TIMED(ET_K_SCORE, launch_attention_scores(w.qkv, n_frames, max_len, c.n_heads, e->hd, w.score_ws, w.att_score, s));
+      i = last - 1;
+    } else if (i < c.n_layers) {
       const bool with_scores = by_attention && !selected && i == merge_layer - 1;
       int rc;
       if ((rc = run_block(e, i, w, rows, cu, n_frames, max_len, ragged, have_pieces, s, with_scores))) return rc;
@@ -466,7 +544,9 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
     }
   }
   if (plan) plan->n_segments = n_segments;
-  if (c.has_final_ln) {
+  if (finished) {
+    // (by the last run of blocks)
+  } else if (c.has_final_ln) {
     ET_TIMED(ET_K_LAYERNORM, launch_layernorm(w.x, e->final_g, e->final_b, c.ln_eps, rows, D,
                                               out->tokens_dev, s));
   } else {
@@ -565,6 +645,10 @@ int et_encoder_block_qkv(et_encoder *e, int32_t layer, const uint16_t *x_dev, in
   const int D = e->D;
   const LayerDev &lw = e->layers[layer];
   int rc;
+  if (is_narrow(e)) {                      // (the arithmetic of narrow_blocks_kernel)
+    if ((rc = launch_piece_scale(x_dev, e->cfg.ln_eps, rows, D, rstd_dev, s))) return rc;
+    return launch_gemm(GemmArgs{x_dev, D, lw.wqkv, lw.bqkv, nullptr, 0, 1, qkv_dev, 3 * D, rows, 3 * D, D, EPI_BIAS, rstd_dev}, s, kCfgStrip);
+  }
   // run_block's two ways to the row scales; where it takes them from the pieces of a row, they are combined here by a kernel
   // of its own, with the same arithmetic, and the projection runs in the tiling that takes pieces
   const bool by_pieces = takes_pieces(e, rows);

@@ -282,6 +282,34 @@ bool head_dim_supported(int hd);
 int launch_attention_uniform(const uint16_t *qkv, int n_frames, int len, int n_heads, int head_dim,
                              uint16_t *out, hipStream_t s, const WarmRanges *warm = nullptr);
 
+// narrow_blocks.hip: runs of blocks of narrow encoders, a workgroup per frame
+constexpr int kNarrowWidth = 64, kNarrowTokens = 64, kNarrowMlp = 256;
+// Byte offsets in the parameters of one block: weights bf16 and biases fp32, the LayerNorms folded in; mlp: padded to a
+// multiple of 64.  A weight matrix lies as MFMA operands: 1 KiB per 16 outputs and 32 inputs, 16 bytes per lane (output lane %
+// 16, inputs 8 (lane / 16) ..), the inputs' steps of one group of outputs one after the other.
+struct NarrowPack {
+  static constexpr int wqkv() { return 0; }
+  static constexpr int wo() { return wqkv() + 3 * kNarrowWidth * kNarrowWidth * 2; }
+  static constexpr int w1() { return wo() + kNarrowWidth * kNarrowWidth * 2; }
+  static constexpr int w2(int mlp) { return w1() + mlp * kNarrowWidth * 2; }
+  static constexpr int bqkv(int mlp) { return w2(mlp) + mlp * kNarrowWidth * 2; }
+  static constexpr int bo(int mlp) { return bqkv(mlp) + 3 * kNarrowWidth * 4; }
+  static constexpr int b1(int mlp) { return bo(mlp) + kNarrowWidth * 4; }
+  static constexpr int b2(int mlp) { return b1(mlp) + mlp * 4; }
+  static constexpr int bytes(int mlp) { return b2(mlp) + kNarrowWidth * 4; }
+};
+struct NarrowArgs {
+  const char *pack;                        // the blocks' parameters, one after the other
+  int n_layers;
+  const uint16_t *x;                       // residual stream [rows, 64]
+  uint16_t *out, *qkv;                     // the stream behind the blocks (may be x); q | k | v of the last block [rows, 192]
+  const int32_t *cu;                       // NULL: frames of `len` rows each; else row ranges cu[f] .. cu[f + 1] of at most `len` rows
+  int len, mlp;                            // mlp: padded to a multiple of 64
+  float ln_eps, scale_log2;                // scale_log2: log2(e) / sqrt(head dim)
+  const float *final_g, *final_b;          // a LayerNorm in front of `out`, or NULL
+};
+int launch_narrow_blocks(const NarrowArgs &a, int n_frames, int n_heads, hipStream_t s);
+
 // score_kernels.hip: attention received per token, equal-length frames
 size_t attention_scores_workspace_bytes(int n_frames, int L, int n_heads);
 int launch_attention_scores(const uint16_t *qkv, int n_frames, int L, int n_heads, int head_dim, void *stats_ws,

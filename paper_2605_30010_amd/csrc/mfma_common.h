@@ -49,6 +49,20 @@ __device__ __forceinline__ float gelu_tanh_f(float u) {
   return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
+// LDS transpose read: every lane of a 16-lane group supplies the address of four consecutive 16-bit
+// elements; lane j of the group receives element j % 4 of the lanes j / 4, 4 + j / 4, 8 + j / 4 and
+// 12 + j / 4 (layout checked on the device).  With lane s of a group pointing at row s / 4, columns
+// 4 (s % 4) .. + 3 of a row-major matrix, lane j gets column j of four consecutive rows.
+__device__ __forceinline__ uint2 lds_read_tr16(const uint16_t *p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
+  return __builtin_bit_cast(uint2, v);
+#else
+  return make_uint2(0u, 0u);
+#endif
+}
+
 // Direct global -> LDS loads (no staging registers): one wavefront moves 64 x 4 or 64 x 16 bytes to consecutive LDS.  The
 // immediate offset moves the global AND the LDS address and has to be a literal.
 #define ET_LDS_DMA4(gptr, lptr)                                                              \

@@ -388,3 +388,27 @@ def test_row_whose_variance_leaves_float32(size):
     enc.close()
     assert np.all(np.isfinite(got))
     assert np.array_equal(got[3], w["final_ln_b"].astype(np.float64))
+
+
+@pytest.mark.parametrize("heads,mlp,side,T,layers", [(4, 256, 112, 5, 2), (2, 200, 98, 3, 2), (1, 64, 14, 2, 2), (4, 72, 70, 9, 2), (1, 256, 112, 70, 2),
+                                                     (2, 65, 56, 1, 35)])
+def test_narrow_encoders_run_by_frames(heads, mlp, side, T, layers):
+    """The kernel that takes a frame through a run of blocks: every head size, frames of 1 to 64 tokens (a last tile of 16 that is full,
+    nearly empty, or the only one), MLP widths on both sides of a multiple of 64, more blocks than one launch holds; and the same rows
+    through a merge in the middle, whose hidden states et_encoder_block_qkv's projection has to match as well.
+    Bound: seven roundings to bf16 per block, each 2^-9 relative at most and independent, two blocks 0.0073."""
+    from et_inputs import EncoderShape
+    shape = EncoderShape(n_layers=layers, d_model=64, n_heads=heads, d_mlp=mlp, patch=14, image_h=side, image_w=side)
+    w = make_weights(shape, seed=3 * side + T, bf16=True)
+    frames = make_clip(shape, [1] * T, T, base="uniform", sigma=0.02)
+    enc = et.Encoder(shape, w, T)
+    got = _encode(enc, frames, -1, 0.9, 1.0)
+    ref = O.encode_clip(shape, w, frames, -1, 0.9, 1.0)
+    err = rel_l2(dev_to_f64(got["tokens"]), ref["tokens"])
+    print("narrow encoder", heads, mlp, side, T, layers, "rel-L2 %.4f" % err)
+    assert err <= 2.0 ** -9 * np.sqrt(7 * layers)
+    cut = _encode(enc, frames, 1, -2.0, 1.0)                  # one segment, all tokens: the mean frame after the first block
+    assert cut["n_frames_out"] == 1
+    ref = O.encode_clip(shape, w, frames, 1, -2.0, 1.0)
+    assert rel_l2(dev_to_f64(cut["tokens"]), ref["tokens"]) <= TOL
+    enc.close()
