@@ -14,6 +14,8 @@
 // heads * L (no atomics anywhere: bit-reproducible).  The two-pass kernels load their fragments
 // straight from global memory (16-byte pieces of q / k rows); the head dimension is padded to a
 // multiple of 16 with zero fragments.
+#include <type_traits>
+
 #include "mfma_common.h"
 
 namespace et {
@@ -33,31 +35,29 @@ __device__ __forceinline__ u32x4 load_piece(const uint16_t *row, int chunk, int 
 // One pass.  A workgroup of 8 wavefronts owns one (frame, head) and a contiguous share of the 32-query
 // blocks; wavefront w owns the NB 32-key blocks w, w + 8, ..., whose K fragments stay in registers.
 // Per query block every wavefront computes S^T = K Q^T for its keys (the query on the accumulator's
-// lane axis), exponentiates against its OWN maximum, and leaves (maximum, sum) per query in LDS; after
-// one barrier each knows the factor exp2(m_w - m) / l that turns its exponentials into probabilities and
-// adds them to its column sums, which stay in registers to the end: one exponential and one logit per
-// (query, key) instead of two.  The query block (KSTEPS * 1 KiB) is staged in LDS, zero padded, one
-// block ahead; its row stride is an odd number of 16-byte slots (no bank conflicts).
-// Bound by the vector unit: per 16 accumulator values 16 exponentials at quarter rate, 2 fma, an add and half a max
-// each (about 480 cycles against 160 of the matrix unit).  The logits of the next block are issued behind the
-// barrier, so the matrix unit works under the combination (116 -> 109 us).  K and Q are read once per workgroup.
-// Measured against the two passes (all launches of a call): 32 frames x 16 heads x 729 tokens of 72: 373 -> 99 us;
-// 16 x 16 x 600 of 80: 139 -> 50; 8 x 16 x 729: 114 -> 41; one frame: 63 -> 33; 32 x 12 x 200 of 64: 38 -> 20.
+// lane axis), exponentiates, and leaves the sum per query in LDS; after one barrier each knows the factor 1 / l
+// that turns its exponentials into probabilities and adds them to its column sums, which stay in registers to the
+// end: one exponential and one logit per (query, key) instead of two.  The exponentials take the reference 0 as long as
+// every query's l stays within 2^+-60 (logits within some 41 of 0: float32 loses nothing there); a workgroup that finds
+// another l starts again with each wavefront's OWN maximum as its reference, leaves (maximum, sum), and uses the factor
+// exp2(m_w - m) / l.  The query blocks come to LDS as fragments (KSTEPS * 1 KiB) by direct loads, three blocks ahead.
+// Bound by the vector unit: per 16 accumulator values 16 multiplications, exponentials (at half rate), additions and
+// fma, 320 clocks against 160 of the matrix unit, which works on the next block in between; of a workgroup's 95 000 clocks at 729
+// tokens 10 000 are its keys' way from memory (one compute unit takes 40 KB per us), 83 000 the loop.  K and Q are read once per workgroup.
+// Measured against the two passes (all launches of a call): 32 frames x 16 heads x 729 tokens of 72: 373 -> 94 us (with a maximum
+// per block 98, sums over the lanes value by value at the end another 4 more); 16 x 16 x 600 of 80: 139 -> 50; 8 x 16 x 729: 114 -> 41;
+// one frame: 63 -> 33; 32 x 12 x 200 of 64: 38 -> 20.
 // ---------------------------------------------------------------------------------------
 constexpr int kPassWaves = 8;
 constexpr int kMaxSplits = 3;        // shares of a (frame, head)'s queries: their partial sums take the room of the two-pass statistics
 
-// Sum over the 32 lanes of each half of the wavefront, complete in lanes 31 and 63.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+// Sum over each row of 16 lanes, in all of them.
+template <int CTRL>
+__device__ __forceinline__ float dpp_rotated(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float half_wave_sum(float v) {
-  v = dpp_add<0x111, 0xf>(v);          // row_shr:1
-  v = dpp_add<0x112, 0xf>(v);          // row_shr:2
-  v = dpp_add<0x114, 0xf>(v);          // row_shr:4
-  v = dpp_add<0x118, 0xf>(v);          // row_shr:8
-  return dpp_add<0x142, 0xa>(v);       // row_bcast:15 into rows 1 and 3
+__device__ __forceinline__ float row_sum(float v) {       // row_ror:8, 4, 2, 1
+  return dpp_rotated<0x121>(dpp_rotated<0x122>(dpp_rotated<0x124>(dpp_rotated<0x128>(v))));
 }
 // {this lane's value, the value of the same query in the other lane half}, in half order
 __device__ __forceinline__ float2 both_halves(float v) {
@@ -69,8 +69,8 @@ template <int KSTEPS, int NB>
 __global__ __launch_bounds__(kPassWaves * 64, NB == 1 ? 4 : 2) void attn_score_kernel(
     const uint16_t *__restrict__ qkv, int L, int D, int n_heads, int head_dim, float scale_log2, int splits,
     float *__restrict__ partial) {
-  constexpr int QS = 2 * KSTEPS + 1;                     // 16-byte slots of a staged query row
-  __shared__ __align__(16) u32x4 qs[2][32 * QS];
+  constexpr int RING = 4;                                // query blocks in LDS
+  __shared__ __align__(16) uint16_t qs[RING][KSTEPS * 512];          // fragments, 1 KiB each, 16 bytes per lane
   __shared__ float2 ex[2][kPassWaves][32];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, grp = lane >> 5;
@@ -82,16 +82,25 @@ __global__ __launch_bounds__(kPassWaves * 64, NB == 1 ? 4 : 2) void attn_score_k
   const size_t row_stride = (size_t)3 * D;
   const uint16_t *head = qkv + (size_t)f * L * row_stride + (size_t)h * head_dim;
 
-  // one 16-byte piece of a query block per thread (32 rows x 2 KSTEPS pieces <= 512); zeros past L and head_dim
-  const int prow = tid / (2 * KSTEPS), pch = tid % (2 * KSTEPS);
-  auto fetch = [&](int qb) {
-    const int q = qb * 32 + prow;
-    u32x4 piece = u32x4{0u, 0u, 0u, 0u};
-    if (prow < 32 && q < L) piece = load_piece(head + (size_t)q * row_stride, pch, head_dim);
-    return piece;
+  // The fragments of a query block come by direct loads, one per wavefront, three blocks ahead; nothing else is loaded in
+  // the loop and the waits are explicit.  (Through registers, one block ahead, the loop waited for memory: 2 us per block.)
+  // Rows past the frame are its last one; pieces past head_dim are taken from inside the row and zeroed behind LDS.
+  const int n_pieces = head_dim / 8;
+  const bool loads = wave < KSTEPS, pad_last = n_pieces < 2 * KSTEPS;
+  const uint32_t piece_off = (uint32_t)min(2 * wave + grp, n_pieces - 1) * 16u;
+  const uint32_t off_full = (uint32_t)r32 * (uint32_t)row_stride * 2u + piece_off;
+  const uint32_t off_last = (uint32_t)min(r32, L - 1 - (n_qb - 1) * 32) * (uint32_t)row_stride * 2u + piece_off;
+  auto issue = [&](int qb) {
+    const int block = min(qb, n_qb - 1);                 // (past the share's end: loaded and not used)
+    const uint64_t base = (uint64_t)(uintptr_t)(head + (size_t)block * 32 * row_stride);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base), hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+    if (loads)
+      lds_dma16_untracked(reinterpret_cast<const uint16_t *>((uintptr_t)((uint64_t)hi << 32 | lo)), block == n_qb - 1 ? off_last : off_full,
+                          qs[(qb - qb0) % RING] + wave * 512);
   };
-  u32x4 piece = fetch(qb0);
   u32x4 kf[NB][KSTEPS];
+#pragma unroll
+  for (int i = 0; i < RING - 1; ++i) issue(qb0 + i);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int k = (wave + b * kPassWaves) * 32 + r32;
@@ -101,91 +110,147 @@ __global__ __launch_bounds__(kPassWaves * 64, NB == 1 ? 4 : 2) void attn_score_k
       if (k < L) kf[b][ks] = load_piece(head + (size_t)k * row_stride + D, 2 * ks + grp, head_dim);
     }
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), known to the compiler: it has no waits for the keys in the loop
   float col[NB][16];
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) col[b][i] = 0.f;
   const bool any_key = wave * 32 < L;                    // wave-uniform; a wavefront without keys only keeps the barriers
-  if (prow < 32) qs[0][prow * QS + pch] = piece;
-  __syncthreads();
-
   f32x16 acc[NB];
-  auto logits = [&](int buf) {
+  auto query = [&](int turn, int ks) {
+    u32x4 q = *reinterpret_cast<const u32x4 *>(qs[turn] + ks * 512 + lane * 8);
+    if (ks == KSTEPS - 1 && pad_last && grp) q = u32x4{0u, 0u, 0u, 0u};
+    return q;
+  };
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // One pass over the share's query blocks, whose first fragments have landed.  QUICK: exponentials against the reference 0;
+  // returns whether every query's denominator is of ordinary size (all wavefronts with keys find the same denominators).
+  auto pass = [&](auto quick) {
+    constexpr bool QUICK = decltype(quick)::value;
+    bool sound = true;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      const u32x4 q = qs[buf][r32 * QS + 2 * ks + grp];
-#pragma unroll
-      for (int b = 0; b < NB; ++b) acc[b] = mfma32(kf[b][ks], q, acc[b]);
-    }
-  };
-  if (any_key) logits(0);
-  for (int qb = qb0, buf = 0; qb < qb1; ++qb, buf ^= 1) {
-    if (qb + 1 < qb1) piece = fetch(qb + 1);
-    float p[NB][16];
-    float m = -INFINITY, l = 0.f;
-    if (any_key) {
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int k0 = (wave + b * kPassWaves) * 32;
-        if (k0 + 32 > L) {                               // (wave-uniform) keys past the frame
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (k0 + (i / 4) * 8 + 4 * grp + (i % 4) >= L) acc[b][i] = -INFINITY;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[b][i]);
-      }
-      // The wavefront's reference is a whole number, so the factor between two wavefronts' references is an
-      // exact power of two.
-      const float2 mm = both_halves(m);
-      m = ceilf(fmaxf(mm.x, mm.y) * scale_log2);         // (scale_log2 > 0: the order is kept)
-      const float m_ref = m == -INFINITY ? 0.f : m;      // no finite logit here: exponentials are 0, not NaN
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          p[b][i] = __builtin_amdgcn_exp2f(fmaf(acc[b][i], scale_log2, -m_ref));
-          l += p[b][i];
-        }
-      const float2 ll = both_halves(l);
-      l = ll.x + ll.y;
-    }
-    if (grp == 0) ex[buf][wave][r32] = make_float2(m, l);
-    if (prow < 32 && qb + 1 < qb1) qs[buf ^ 1][prow * QS + pch] = piece;
+      for (int i = 0; i < 16; ++i) col[b][i] = 0.f;
     __syncthreads();
-    // (ex[buf] is written again two blocks on, behind the next barrier; qs[buf] likewise)
     if (any_key) {
-      if (qb + 1 < qb1) logits(buf ^ 1);                 // the matrix unit works under the arithmetic below
-      float2 o[4];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) o[w] = ex[buf][grp * 4 + w][r32];      // each lane half combines four wavefronts
-      const float2 mm = both_halves(fmaxf(fmaxf(o[0].x, o[1].x), fmaxf(o[2].x, o[3].x)));
-      const float mt = fmaxf(mm.x, mm.y);
-      float lt = 0.f;
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        const u32x4 q = query(0, ks);
 #pragma unroll
-      for (int w = 0; w < 4; ++w) lt += o[w].y * __builtin_amdgcn_exp2f(o[w].x - mt);
-      const float2 ll = both_halves(lt);
-      const float fac = qb * 32 + r32 < L ? __builtin_amdgcn_exp2f(m - mt) / (ll.x + ll.y) : 0.f;   // queries past L add nothing
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) col[b][i] = fmaf(p[b][i], fac, col[b][i]);
+        for (int b = 0; b < NB; ++b) acc[b] = mfma32(kf[b][ks], q, ks ? acc[b] : zero16);
+      }
     }
+    for (int qb = qb0, buf = 0; qb < qb1; ++qb, buf ^= 1) {
+      issue(qb + RING - 1);
+      float p[NB][16];
+      float m = -INFINITY, l = 0.f;
+      // One step of the next block's logits of key block b (past the share's end unused).
+      const int next = (qb + 1 - qb0) % RING;
+      u32x4 q_now;
+      auto step = [&](int b, int ks) {
+        acc[b] = mfma32(kf[b][ks], q_now, ks ? acc[b] : zero16);
+        q_now = query(next, ks + 1 < KSTEPS ? ks + 1 : 0);
+      };
+      if (any_key) {
+        q_now = query(next, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const int k0 = (wave + b * kPassWaves) * 32;
+          if (k0 + 32 > L) {                             // (wave-uniform) keys past the frame
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              if (k0 + (i / 4) * 8 + 4 * grp + (i % 4) >= L) acc[b][i] = -INFINITY;
+          }
+          if (!QUICK) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[b][i]);
+          }
+        }
+        float m_ref = 0.f;
+        if (!QUICK) {
+          // The wavefront's reference is a whole number, so the factor between two wavefronts' references is an
+          // exact power of two.
+          const float2 mm = both_halves(m);
+          m = ceilf(fmaxf(mm.x, mm.y) * scale_log2);     // (scale_log2 > 0: the order is kept)
+          m_ref = m == -INFINITY ? 0.f : m;              // no finite logit here: exponentials are 0, not NaN
+        }
+        // The matrix unit works on the next block under the exponentials: of key block b - 1 as soon as its logits are used.
+        float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int ks = 0; ks < KSTEPS; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (b > 0) step(b - 1, ks);
+#pragma unroll
+            for (int i = 16 * ks / KSTEPS; i < 16 * (ks + 1) / KSTEPS; ++i) {
+              p[b][i] = __builtin_amdgcn_exp2f(QUICK ? acc[b][i] * scale_log2 : fmaf(acc[b][i], scale_log2, -m_ref));
+              part[i & 3] += p[b][i];
+            }
+          }
+        __builtin_amdgcn_sched_barrier(0);
+        const float2 ll = both_halves((part[0] + part[1]) + (part[2] + part[3]));
+        l = ll.x + ll.y;
+      }
+      if (grp == 0) ex[buf][wave][r32] = make_float2(m, l);
+      wait_vmcnt<RING - 3>();                            // the fragment of the block after the next has landed
+      __syncthreads();
+      // (ex[buf] is written again two blocks on, behind the next barrier; a query block's room is loaded again behind the
+      // barrier that follows its last read)
+      if (any_key) {
+        float2 o[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) o[w] = ex[buf][grp * 4 + w][r32];    // each lane half combines four wavefronts
+        const bool valid = qb * 32 + r32 < L;            // queries past L add nothing
+        float fac;
+        if (QUICK) {
+          const float2 ll = both_halves((o[0].y + o[1].y) + (o[2].y + o[3].y));
+          const float lt = ll.x + ll.y;
+          sound = sound && (!valid || (lt > 0x1p-60f && lt < 0x1p60f));
+          fac = valid ? 1.0f / lt : 0.f;
+        } else {
+          const float2 mm = both_halves(fmaxf(fmaxf(o[0].x, o[1].x), fmaxf(o[2].x, o[3].x)));
+          const float mt = fmaxf(mm.x, mm.y);
+          float lt = 0.f;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) lt += o[w].y * __builtin_amdgcn_exp2f(o[w].x - mt);
+          const float2 ll = both_halves(lt);
+          fac = valid ? __builtin_amdgcn_exp2f(m - mt) / (ll.x + ll.y) : 0.f;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+          __builtin_amdgcn_sched_barrier(0);
+          step(NB - 1, ks);
+#pragma unroll
+          for (int i = NB * 16 * ks / KSTEPS; i < NB * 16 * (ks + 1) / KSTEPS; ++i) col[i / 16][i % 16] = fmaf(p[i / 16][i % 16], fac, col[i / 16][i % 16]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    wait_vmcnt<0>();                                     // (the loads past the end)
+    return sound;
+  };
+  const bool sound = pass(std::true_type());
+  if (__syncthreads_or(any_key && !sound)) {             // (and everyone has left the buffers)
+#pragma unroll
+    for (int i = 0; i < RING - 1; ++i) issue(qb0 + i);
+    wait_vmcnt<0>();
+    pass(std::false_type());
   }
+  // Sums over the 32 queries of each lane half.  Two values of a key block share a register after the first exchange
+  // (accumulator rows i in the even, i + 8 in the odd rows of 16 lanes); lane j of a row then stores the j-th sum.
   float *dst = partial + (((size_t)f * n_heads + h) * splits + sp) * L;
+  const int j = lane & 15, odd_row = (lane >> 4) & 1;
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
+  for (int b = 0; b < NB; ++b) {
+    float mine = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float c = half_wave_sum(col[b][i]);
-      const int k = (wave + b * kPassWaves) * 32 + (i / 4) * 8 + 4 * grp + (i % 4);
-      if (r32 == 31 && k < L) dst[k] = c;
+    for (int i = 0; i < 8; ++i) {
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(col[b][i]), __float_as_uint(col[b][i + 8]), false, false);
+      const float c = row_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+      mine = j == i ? c : mine;
     }
+    const int k = (wave + b * kPassWaves) * 32 + odd_row * 16 + (j >> 2) * 8 + 4 * grp + (j & 3);
+    if (j < 8 && k < L) dst[k] = mine;
+  }
 }
 
 // Pass 1.  grid (ceil(L / 128), heads, frames), 4 wavefronts, 32 queries per wavefront.

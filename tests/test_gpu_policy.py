@@ -529,6 +529,28 @@ def test_attention_scores_over_the_sizes(F, n, H, hd):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n,H,hd,size", [(40, 2, 72, 3.0), (300, 2, 72, 6.0), (729, 1, 80, 6.0), (520, 2, 16, 8.0), (200, 1, 128, 4.0)])
+def test_attention_scores_of_large_logits(n, H, hd, size):
+    """Denominators on both sides of what the exponentials' fixed reference serves (2^+-60): frames with ordinary queries, queries
+    whose largest logit is some hundreds, and queries that are far below 0 for every key.  A float32 logit s is off by a
+    few 2^-24 |s|, a probability by that relative error."""
+    rng = np.random.default_rng(n)
+    D = H * hd
+    x = rng.standard_normal((3, n, 3 * D))
+    x[1] *= size
+    x[2, :, :D] = -np.abs(x[2, :, :D]) * size
+    x[2, :, D:2 * D] = np.abs(x[2, :, D:2 * D]) + 1.0
+    bits = f64_to_bits(x.reshape(3 * n, 3 * D))
+    got = et.et_attention_scores(bits_to_dev(bits), 3, n, H, hd).cpu().numpy().astype(np.float64)
+    qk = bf16_bits_to_f32(bits).astype(np.float64).reshape(3, n, 3 * D)
+    q, k = qk[..., :D].reshape(3, n, H, hd), qk[..., D:2 * D].reshape(3, n, H, hd)
+    largest = max(np.abs(np.matmul(q[:, :, h], k[:, :, h].transpose(0, 2, 1))).max() for h in range(H)) / math.sqrt(hd) * 1.4427
+    assert largest > 60.0
+    want = O.attention_received_from_qk(qk[..., :D], qk[..., D:2 * D], H)
+    assert np.all(np.abs(got - want) <= largest * 2.0 ** -22 * want + 1e-36)
+
+
+@pytest.mark.gpu
 def test_attention_scores_of_infinite_logits():
     """Logits of minus infinity for all keys of one wavefront (32 of 64) give probability 0 there and leave
     the rest alone; a NaN in one query reaches every token of its frame and head, and no other frame."""
