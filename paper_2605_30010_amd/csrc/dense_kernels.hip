@@ -341,7 +341,8 @@ __device__ __forceinline__ void gemm_epilogue_lds(f32x4 (&acc)[NS][MS], const Ge
 // of the wavefronts that need them.  Only for launches of one tile per workgroup: further tiles' scales cost more than a launch that computes them
 // (fetched beside the k-loop, 46656 rows: QKV 292 -> 324 us, fc1 445 -> 475).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int MINB, int EPI, bool STATS>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(WAVES_M *WAVES_N * 64, MINB) void gemm_stream_kernel(ET_GEMM_FIRST, GemmArgs g) {
+  ET_GEMM_TAKE_FIRST(g);
   constexpr int BK = 64, STAGES = 2;
   constexpr int NW = WAVES_M * WAVES_N;
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
@@ -614,7 +615,7 @@ int launch_gemm_stream_cfg(const GemmArgs &g, hipStream_t s) {
   {                                                                                              \
     constexpr auto kern = gemm_stream_kernel<BM, BN, WAVES_M, WAVES_N, MINB, E, STATS>;          \
     if (int rc = allow_lds<kern>(lds_bytes)) return rc;                                          \
-    hipLaunchKernelGGL(kern, grid, block, lds_bytes, s, g, tiles_m, tiles_n);                    \
+    hipLaunchKernelGGL(kern, grid, block, lds_bytes, s, ET_GEMM_GIVE_FIRST(g), g);                    \
   }
   switch (g.epilogue) {
     case EPI_BIAS:

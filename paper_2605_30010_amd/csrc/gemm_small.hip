@@ -138,7 +138,8 @@ __device__ __forceinline__ void finish_tile64(const f32x16 (&acc)[2][2], const G
 // 20-40 % slower from two on.
 // ---------------------------------------------------------------------------------------
 template <int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_wave_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(256, 2) void gemm_wave_kernel(ET_GEMM_FIRST, GemmArgs g) {
+  ET_GEMM_TAKE_FIRST(g);
   constexpr int NW = 4;
   extern __shared__ __align__(16) uint16_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -225,7 +226,8 @@ __global__ __launch_bounds__(256, 2) void gemm_wave_kernel(GemmArgs g, int tiles
 // (One wavefront per tile: as slow as the 64 x 128 tile, its SIMD's matrix unit takes 1024 cycles per k-tile.)
 // ---------------------------------------------------------------------------------------
 template <int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_strip_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(256, 2) void gemm_strip_kernel(ET_GEMM_FIRST, GemmArgs g) {
+  ET_GEMM_TAKE_FIRST(g);
   constexpr int ST = 4, SLOT = 8192;                     // slots; elements of one: 64 rows of A, 64 of W, 128 bytes each
   extern __shared__ __align__(16) uint16_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -350,7 +352,8 @@ struct PairShape {
 };
 
 template <int BM, int BN, int EPI>
-__global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(512, 1) void gemm_pair_kernel(ET_GEMM_FIRST, GemmArgs g) {
+  ET_GEMM_TAKE_FIRST(g);
   using S = PairShape<BM, BN>;
   constexpr int WN = BN / 64, WPG = S::WPG, KH = S::KH, ST = S::ST;
   constexpr int A_BLK = BM / 8 / WPG, W_BLK = BN / 8 / WPG, LOADS = A_BLK + W_BLK;     // 1 KiB loads per wavefront and k-tile
@@ -494,7 +497,8 @@ struct DuoShape {
 };
 
 template <int EPI>
-__global__ __launch_bounds__(512, 1) void gemm_duo_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(512, 1) void gemm_duo_kernel(ET_GEMM_FIRST, GemmArgs g) {
+  ET_GEMM_TAKE_FIRST(g);
   using S = DuoShape;
   constexpr int BM = S::BM, BN = S::BN, MS = 4, MH = 2, NS = BN / 32;
   constexpr int WL = BN / 32, AL = 2, LOADS = WL + 2 * AL;       // 1 KiB loads per wavefront: of the weight tile, of either half of the activation tile
@@ -656,7 +660,8 @@ __global__ __launch_bounds__(512, 1) void gemm_duo_kernel(GemmArgs g, int tiles_
 // (207 workgroups): 64 -> 59 us; 13122 rows: 131 -> 124 us; 1456 rows, 3456 x 1152: 20 -> 18.8 us.
 // ---------------------------------------------------------------------------------------
 template <int EPI>
-__global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(512, 1) void gemm_half_kernel(ET_GEMM_FIRST, GemmArgs g) {
+  ET_GEMM_TAKE_FIRST(g);
   constexpr int BM = 256, BN = 128, ST = 3, STAGE = (BM + BN) * 64;
   constexpr int A_BLK = BM / 64, W_BLK = BN / 64, LOADS = A_BLK + W_BLK;      // 1 KiB loads per wavefront and k-tile
   extern __shared__ __align__(16) uint16_t lds[];
@@ -770,11 +775,11 @@ __global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs g, int tiles
 
 }  // namespace
 
-template <void (*KERN)(GemmArgs, int, int)>
+template <void (*KERN)(ET_GEMM_FIRST, GemmArgs)>
 static int launch_small(const GemmArgs &g, hipStream_t s, int bm, int bn, int threads, size_t lds_bytes) {
   if (int rc = allow_lds<KERN>(lds_bytes)) return rc;
   const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.n_store + bn - 1) / bn;
-  hipLaunchKernelGGL(KERN, dim3(tiles_m * tiles_n), dim3(threads), lds_bytes, s, g, tiles_m, tiles_n);
+  hipLaunchKernelGGL(KERN, dim3(tiles_m * tiles_n), dim3(threads), lds_bytes, s, ET_GEMM_GIVE_FIRST(g), g);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }
