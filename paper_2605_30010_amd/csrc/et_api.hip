@@ -151,7 +151,7 @@ int enqueue_merge_stage(const uint16_t *x, int T, int L, int D, float tau, int k
                                                    early ? early->host : nullptr, true, true, s));
   if (early && early->ready) ET_HIP(hipEventRecord(early->ready, s));
   ET_TIMED_P(prof, ET_K_MERGE, launch_segment_mean(x, T, L, D, seg_start, w.n_seg, w.merged, w.score, s));
-  if (L <= 7680) {     // selection and gather in one launch
+  if (L <= kFusedSelectTokens) {     // selection and gather in one launch
     ET_TIMED_P(prof, ET_K_SELECT, launch_topk_gather(w.score, w.merged, T, w.n_seg, L, D, k, kept, cu_tokens, packed, s));
   } else {
     ET_TIMED_P(prof, ET_K_SELECT, launch_topk(w.score, T, w.n_seg, L, k, kept, cu_tokens, s));
@@ -187,21 +187,23 @@ int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy
     po.count = plan->frame_count_dev;
     po.dyn = plan->frame_dynamic_dev;
   }
-  if (step.do_plan) {
-    ET_TIMED_P(prof, ET_K_SIMILARITY, launch_similarity(x, T, L, D, w.cos, w.part, s));
-    ET_TIMED_P(prof, ET_K_SCAN, launch_sim_mean_scan(w.part, similarity_blocks(L), T, L, 0.f, sim, nullptr, nullptr,
-                                                     nullptr, true, false, s));
-  }
-  ET_TIMED_P(prof, ET_K_SCAN, launch_plan(sim, T, L, pa, k_uniform, step, seg_start, w.frame_first, w.frame_count,
+  if (step.do_plan) ET_TIMED_P(prof, ET_K_SIMILARITY, launch_similarity(x, T, L, D, w.cos, w.part, s));
+  ET_TIMED_P(prof, ET_K_SCAN, launch_plan(w.part, similarity_blocks(L), sim, T, L, pa, k_uniform, step, seg_start, w.frame_first, w.frame_count,
                                           w.frame_dyn, w.frame_w, w.orig_first, w.orig_count, cu_tokens, info, po, s));
   ET_TIMED_P(prof, ET_K_MERGE, launch_plan_merge(x, T, L, D, info, w.frame_first, w.frame_count, w.frame_w,
                                                  step.do_plan && pol.merge_mode == ET_MERGE_MEAN, w.merged,
                                                  w.score, s));
   if (step.do_counts) {
     // (score_override: scores computed elsewhere, e.g. the attention received, instead of the L2 norms)
-    ET_TIMED_P(prof, ET_K_SELECT, launch_select_policy(score_override ? score_override : w.score, T, info, w.frame_dyn, cu_tokens, L,
-                                                       pol.select_mode == ET_SELECT_UNIFORM, kept, s));
-    ET_TIMED_P(prof, ET_K_COMPACT, launch_compact_ragged(w.merged, kept, T, info, cu_tokens, L, D, packed, s));
+    const float *score = score_override ? score_override : w.score;
+    const bool uniform = pol.select_mode == ET_SELECT_UNIFORM;
+    if (L <= kFusedSelectTokens) {     // selection and gather in one launch
+      ET_TIMED_P(prof, ET_K_SELECT, launch_select_gather_policy(score, w.merged, T, info, w.frame_dyn, cu_tokens, L, D, uniform,
+                                                                uniform ? k_uniform : L, kept, packed, s));
+    } else {
+      ET_TIMED_P(prof, ET_K_SELECT, launch_select_policy(score, T, info, w.frame_dyn, cu_tokens, L, uniform, kept, s));
+      ET_TIMED_P(prof, ET_K_COMPACT, launch_compact_ragged(w.merged, kept, T, info, cu_tokens, L, D, packed, s));
+    }
   }
   return ET_OK;
 }

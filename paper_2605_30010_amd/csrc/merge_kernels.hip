@@ -91,42 +91,14 @@ __global__ __launch_bounds__(kSimWaves * kWave) void similarity_kernel(
 // ---------------------------------------------------------------------------------------
 // s_t = (sum of the n_src values of row t of `src`) / L: src is either the per-workgroup
 // partial sums the similarity kernel left (n_src = its grid width) or the cosines themselves
-// (n_src = L).  Fixed order: lane-strided partial sums, then a butterfly; one wavefront per
-// pair.  Then the boundary scan of Eq. 1 with alpha = 1: frame t opens a segment iff
+// (n_src = L); see mean_over_positions.  Then the boundary scan of Eq. 1 with alpha = 1: frame t opens a segment iff
 // !(s_t >= tau).  One workgroup; wavefront 0 does the scan with ballots.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void sim_mean_scan_kernel(
     const float *__restrict__ src, int n_src, int T, int L, float tau, float *__restrict__ sim,
     int32_t *__restrict__ seg_start, int32_t *__restrict__ n_seg, int32_t *__restrict__ n_host, int do_mean, int do_scan) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-  if (do_mean) {
-    // a wavefront sums four rows at a time, their loads issued together (the kernel is one round trip
-    // to memory per 64 rows when a row has at most 256 values); each row's sum keeps its fixed order
-    constexpr int U = 4;
-    for (int t0 = wave; t0 < T - 1; t0 += U * n_waves) {
-      float acc[U] = {0.f, 0.f, 0.f, 0.f};
-      for (int i0 = lane; i0 < n_src; i0 += 4 * kWave) {
-        float v[U][4];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int t = t0 + u * n_waves, i = i0 + j * kWave;
-            v[u][j] = (t < T - 1 && i < n_src) ? src[(size_t)t * n_src + i] : 0.f;
-          }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[u] += v[u][j];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float a = wave_sum(acc[u]);
-        const int t = t0 + u * n_waves;
-        if (lane == 0 && t < T - 1) sim[t] = a / (float)L;
-      }
-    }
-  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (do_mean) mean_over_positions(src, n_src, T, L, sim, nullptr, 0);
   if (!do_scan) return;
   __threadfence_block();
   __syncthreads();
@@ -257,7 +229,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_gather_kernel(
   int32_t *sel = reinterpret_cast<int32_t *>(smem + L);
   __shared__ SelectShared sh;
   const int n = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   // the frame's scores are fetched before the frame count is known (row n < gridDim.y lies inside the
   // score buffer whether or not the frame exists), so that the two loads overlap
   const float *row = score + (size_t)n * L;
@@ -272,29 +244,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_gather_kernel(
   __syncthreads();
   if (blockIdx.x == 0)
     for (int j = tid; j < k; j += kSelThreads) kept[(size_t)n * k + j] = sel[j];
-  // gather: a wavefront's rows (two with the launcher's grid) are all in flight at once
-  const int chunks = D / 8;
-  const int stride = 4 * gridDim.x;
-  for (int j = blockIdx.x * 4 + wave; j < k; j += 2 * stride) {
-    const int j2 = j + stride;
-    const int l0 = sel[j], l1 = j2 < k ? sel[j2] : l0;
-    const uint4 *s0 = reinterpret_cast<const uint4 *>(merged + ((size_t)n * L + l0) * D);
-    const uint4 *s1 = reinterpret_cast<const uint4 *>(merged + ((size_t)n * L + l1) * D);
-    uint4 *d0 = reinterpret_cast<uint4 *>(out + ((size_t)n * k + j) * D);
-    uint4 *d1 = reinterpret_cast<uint4 *>(out + ((size_t)n * k + j2) * D);
-    for (int c = lane; c < chunks; c += 4 * kWave) {
-      uint4 v0[4], v1[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c + u * kWave < chunks) { v0[u] = s0[c + u * kWave]; v1[u] = s1[c + u * kWave]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c + u * kWave < chunks) {
-          d0[c + u * kWave] = v0[u];
-          if (j2 < k) d1[c + u * kWave] = v1[u];
-        }
-    }
-  }
+  gather_selected(merged + (size_t)n * L * D, sel, k, D, out + (size_t)n * k * D);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -376,13 +326,11 @@ int launch_topk(const float *score, int n_rows_max, const int32_t *n_rows_dev, i
 
 int launch_topk_gather(const float *score, const uint16_t *merged, int n_rows_max, const int32_t *n_rows_dev, int L,
                        int D, int k, int32_t *kept, int32_t *cu_tokens, uint16_t *out, hipStream_t s) {
-  if (L > 7680) {
-    set_error("tokens per frame %d above the 7680 the fused selection supports", L);
+  if (L > kFusedSelectTokens) {
+    set_error("tokens per frame %d above the %d the fused selection supports", L, kFusedSelectTokens);
     return ET_ERR_UNSUPPORTED;
   }
-  int per_frame = (k + 7) / 8;             // workgroups per frame: two rows per wavefront, at most 32 workgroups
-  per_frame = per_frame > 32 ? 32 : per_frame;
-  hipLaunchKernelGGL(topk_gather_kernel, dim3(per_frame, n_rows_max), dim3(kSelThreads),
+  hipLaunchKernelGGL(topk_gather_kernel, dim3(gather_workgroups(k), n_rows_max), dim3(kSelThreads),
                      (size_t)(L + k) * sizeof(uint32_t), s, score, merged, n_rows_dev, L, D, k, kept, cu_tokens, out);
   ET_LAUNCH_CHECK();
   return ET_OK;

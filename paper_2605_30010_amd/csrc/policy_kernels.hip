@@ -136,15 +136,24 @@ __device__ __forceinline__ void build_plan_64(const float *sim, int T, const Pol
   n_out = __popcll(emits);
 }
 
-// One wavefront.  Up to 64 frames are planned by all lanes, longer clips by lane 0 on LDS copies (T <= kPlanLds) or on
-// global memory, where every step is a round trip; the arrays are written by all lanes.
-constexpr int kPlanLds = 1024;
-__global__ __launch_bounds__(kWave) void plan_kernel(
-    const float *__restrict__ sim, int T, int L, PolicyArgs p, int k_uniform, PlanStep st, int32_t *__restrict__ seg_start,
+// One workgroup.  With st.do_plan all its wavefronts first take the frames' similarities from the sums that the similarity kernel
+// left (by themselves that was a launch of 5 us whose result this kernel fetched back; now 6 us for both).  The rest is one wavefront's: up to
+// 64 frames are planned by all lanes, longer clips by lane 0 on LDS copies (T <= kPlanLds) or on global memory, where
+// every step is a round trip; the arrays are written by all lanes.
+constexpr int kPlanLds = 1024, kPlanThreads = 1024;
+
+// Behind it every lane of the wavefront sees what its lanes wrote, in LDS or in memory.
+__device__ __forceinline__ void wave_meets() {
+  __threadfence_block();
+  __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(kPlanThreads) void plan_kernel(
+    const float *__restrict__ part, int n_part, float *sim, int T, int L, PolicyArgs p, int k_uniform, PlanStep st, int32_t *__restrict__ seg_start,
     int32_t *__restrict__ frame_first, int32_t *__restrict__ frame_count, int32_t *__restrict__ frame_dyn,
     float *__restrict__ frame_w, int32_t *orig_first, int32_t *orig_count, int32_t *__restrict__ cu_tokens, int32_t *__restrict__ info,
     PlanOut out) {
-  // T = current number of frames.  st.do_plan: build segments and output frames from sim (else the
+  // T = current number of frames.  st.do_plan: build segments and output frames from part [T-1, n_part] (else the
   // identity plan over the T current frames, dynamic flags left as they are).  st.do_counts: token
   // counts and offsets of the selection.  orig_first / orig_count: range of ORIGINAL frames behind
   // each current frame (st.init_orig: identity, first stage), updated in place; seg_start is
@@ -152,16 +161,20 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
   __shared__ float l_sim[kPlanLds], l_w[2 * kPlanLds];
   __shared__ int32_t l_seg[kPlanLds + 1], l_first[kPlanLds], l_count[kPlanLds], l_dyn[kPlanLds];
   __shared__ int head[2];
-  const int lane = threadIdx.x;
-  int N = T;
+  const int lane = threadIdx.x;                    // (the plan's own wavefront)
+  int N = T, n_segments = T;
+  int my_first = lane, my_count = 1, my_dyn = 1;   // of output frame `lane`: up to 64 frames nothing is read back
+  if (st.do_plan) {
+    mean_over_positions(part, n_part, T, L, sim, l_sim, kPlanLds);
+    __threadfence_block();
+    __syncthreads();
+  }
+  if (threadIdx.x >= kWave) return;                // (no barrier of the workgroup behind this line)
   if (st.do_plan) {
     const bool in_lds = T <= kPlanLds;             // (uniform)
-    if (in_lds && T > kWave)
-      for (int t = lane; t < T - 1; t += kWave) l_sim[t] = sim[t];
-    __syncthreads();
     if (T <= kWave) {
       int n_seg = 0, n = 0;
-      build_plan_64(sim, T, p, PlanLists{l_seg, l_first, l_count, l_dyn, l_w}, lane, n_seg, n);
+      build_plan_64(l_sim, T, p, PlanLists{l_seg, l_first, l_count, l_dyn, l_w}, lane, n_seg, n);
       if (lane == 0) {
         head[0] = n_seg;
         head[1] = n;
@@ -172,10 +185,9 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
       else build_plan(sim, T, p, PlanLists{seg_start, frame_first, frame_count, frame_dyn, frame_w}, n_seg, n);
       head[0] = n_seg;
       head[1] = n;
-      __threadfence_block();
     }
-    __syncthreads();
-    const int n_seg = head[0];
+    wave_meets();
+    const int n_seg = n_segments = head[0];
     N = head[1];
     // segment starts and frame ranges in original frame indices: 64 entries at a time are read before they are
     // written, and entry n only needs entries >= n
@@ -189,20 +201,22 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
     if (lane == 0) seg_start[n_seg] = st.t_orig;
     for (int n0 = 0; n0 < N; n0 += kWave) {
       const int n = n0 + lane;
-      int of = 0, oe = 0;
+      int of = 0, oe = 0, dyn = 0;
       if (n < N) {
         const int f = in_lds ? l_first[n] : frame_first[n], c = in_lds ? l_count[n] : frame_count[n], l = f + c - 1;
         of = st.init_orig ? f : orig_first[f];
         oe = st.init_orig ? l + 1 : orig_first[l] + orig_count[l];
+        dyn = in_lds ? l_dyn[n] : frame_dyn[n];
         if (in_lds) {
           frame_first[n] = f;
           frame_count[n] = c;
-          frame_dyn[n] = l_dyn[n];
+          frame_dyn[n] = dyn;
           frame_w[2 * n] = l_w[2 * n];
           frame_w[2 * n + 1] = l_w[2 * n + 1];
         }
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (all 64 entries have been read)
+      if (!st.init_orig) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (all 64 entries have been read)
+      if (n0 == 0) my_first = of, my_count = oe - of, my_dyn = dyn;
       if (n < N) {
         orig_first[n] = of;
         orig_count[n] = oe - of;
@@ -224,19 +238,25 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
     if (st.init_orig) {
       for (int i = lane; i <= T; i += kWave) seg_start[i] = i;
       if (lane == 0) info[1] = T;
+    } else {
+      n_segments = info[1];
+      if (lane < N) {
+        my_first = orig_first[lane];
+        my_count = orig_count[lane];
+        my_dyn = frame_dyn[lane];
+      }
     }
   }
   if (lane == 0) info[0] = N;
   if (lane == 0 && out.header) {
     out.header[0] = N;
-    out.header[1] = info[1];
+    out.header[1] = n_segments;
   }
-  __threadfence_block();
-  __syncthreads();
+  if (N > kWave) wave_meets();
   for (int n = lane; n < N; n += kWave) {
-    if (out.first) out.first[n] = orig_first[n];
-    if (out.count) out.count[n] = orig_count[n];
-    if (out.dyn) out.dyn[n] = frame_dyn[n];
+    if (out.first) out.first[n] = N > kWave ? orig_first[n] : my_first;
+    if (out.count) out.count[n] = N > kWave ? orig_count[n] : my_count;
+    if (out.dyn) out.dyn[n] = N > kWave ? frame_dyn[n] : my_dyn;
   }
   if (!st.do_counts) return;
   int n_dyn_tok, n_sta_tok;
@@ -252,7 +272,7 @@ __global__ __launch_bounds__(kWave) void plan_kernel(
   int total = 0;                                   // tokens before the 64 frames at n0
   for (int n0 = 0; n0 < N; n0 += kWave) {
     const int n = n0 + lane, here = N - n0 < kWave ? N - n0 : kWave;
-    const bool dyn = n < N && (p.select_mode == ET_SELECT_UNIFORM || frame_dyn[n]);
+    const bool dyn = n < N && (p.select_mode == ET_SELECT_UNIFORM || (N > kWave ? frame_dyn[n] : my_dyn));
     const unsigned long long m = __ballot(dyn);
     const int before = __popcll(m & ((1ull << lane) - 1ull)), all = __popcll(m);
     if (n < N) cu_tokens[n] = total + before * n_dyn_tok + (lane - before) * n_sta_tok;
@@ -337,26 +357,15 @@ __global__ __launch_bounds__(kRowsPerBlock * kWave) void plan_merge_kernel(
 
 // ---------------------------------------------------------------------------------------
 // Per-frame selection with ragged output.  Dynamic frames (and every frame in uniform mode): the
-// radix select of the simple path (select_common.h) with k = cu[n+1] - cu[n].  Static frames: one thread per local
-// window of w consecutive positions, arg-max of the key, lowest position on ties.
+// radix select of the simple path (select_common.h) with k = cu[n+1] - cu[n].  Static frames (`windows`): one thread per local
+// window of w consecutive positions, arg-max of the key, lowest position on ties.  The keys have been staged in LDS by this
+// workgroup; dst may be LDS or global memory.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelThreads) void select_policy_kernel(
-    const float *__restrict__ score, const int32_t *__restrict__ info, const int32_t *__restrict__ frame_dyn,
-    const int32_t *__restrict__ cu_tokens, int L, int all_topk, int32_t *__restrict__ kept) {
-  extern __shared__ uint32_t keys[];     // [L]
-  __shared__ SelectShared sh;
-
-  const int n = blockIdx.x;
-  if (n >= info[0]) return;
+__device__ __forceinline__ void select_frame(const uint32_t *keys, int L, int k, bool windows, int r_hat, int32_t *dst, SelectShared &sh) {
   const int tid = threadIdx.x;
-  const int out0 = cu_tokens[n], k = cu_tokens[n + 1] - out0;
-  const float *row = score + (size_t)n * L;
-  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
   __syncthreads();
-  int32_t *dst = kept + out0;
-
-  if (!all_topk && !frame_dyn[n]) {                  // static frame: local windows (Eq. 6)
-    const int r_hat = info[3], w = L / r_hat;
+  if (windows) {                                     // static frame: local windows (Eq. 6)
+    const int w = L / r_hat;
     for (int j = tid; j < k; j += kSelThreads) {
       const int lo = j * w, hi = min(lo + w, L);
       int best = lo;
@@ -371,6 +380,45 @@ __global__ __launch_bounds__(kSelThreads) void select_policy_kernel(
   }
 
   radix_select_emit(keys, L, k, dst, sh);
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_policy_kernel(
+    const float *__restrict__ score, const int32_t *__restrict__ info, const int32_t *__restrict__ frame_dyn,
+    const int32_t *__restrict__ cu_tokens, int L, int all_topk, int32_t *__restrict__ kept) {
+  extern __shared__ uint32_t keys[];     // [L]
+  __shared__ SelectShared sh;
+
+  const int n = blockIdx.x;
+  if (n >= info[0]) return;
+  const int out0 = cu_tokens[n], k = cu_tokens[n + 1] - out0;
+  const float *row = score + (size_t)n * L;
+  for (int i = threadIdx.x; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
+  select_frame(keys, L, k, !all_topk && !frame_dyn[n], info[3], kept + out0, sh);
+}
+
+// Selection and gather in one launch, as topk_gather_kernel does it: the workgroups of a frame repeat its selection into LDS
+// and copy their share of the kept rows; the first one also writes the kept positions.  Bound: the chain of the selection's passes.
+__global__ __launch_bounds__(kSelThreads) void select_gather_policy_kernel(
+    const float *__restrict__ score, const uint16_t *__restrict__ merged, const int32_t *__restrict__ info,
+    const int32_t *__restrict__ frame_dyn, const int32_t *__restrict__ cu_tokens, int L, int D, int all_topk,
+    int32_t *__restrict__ kept, uint16_t *__restrict__ out) {
+  extern __shared__ uint32_t smem[];     // keys [L], then the kept positions [up to L]
+  uint32_t *keys = smem;
+  int32_t *sel = reinterpret_cast<int32_t *>(smem + L);
+  __shared__ SelectShared sh;
+  const int n = blockIdx.y, tid = threadIdx.x;
+  // (fetched before the frame count is known: entry n < gridDim.y lies inside every buffer whether or not the frame exists, and
+  // the loads overlap)
+  const int n_frames = info[0], r_hat = info[3], dyn = frame_dyn[n], out0 = cu_tokens[n], out1 = cu_tokens[n + 1];
+  const float *row = score + (size_t)n * L;
+  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
+  if (n >= n_frames) return;
+  const int k = out1 - out0;
+  select_frame(keys, L, k, !all_topk && !dyn, r_hat, sel, sh);
+  __syncthreads();
+  if (blockIdx.x == 0)
+    for (int j = tid; j < k; j += kSelThreads) kept[(size_t)out0 + j] = sel[j];
+  gather_selected(merged + (size_t)n * L * D, sel, k, D, out + (size_t)out0 * D);
 }
 
 // Gather with per-frame counts: out[cu[n] + j, :] = merged[n, kept[cu[n] + j], :].
@@ -393,11 +441,11 @@ __global__ __launch_bounds__(kRowsPerBlock * kWave) void compact_ragged_kernel(
 
 }  // namespace
 
-int launch_plan(const float *sim, int T, int L, const PolicyArgs &p, int k_uniform, const PlanStep &st,
+int launch_plan(const float *part, int n_part, float *sim, int T, int L, const PolicyArgs &p, int k_uniform, const PlanStep &st,
                 int32_t *seg_start, int32_t *frame_first, int32_t *frame_count, int32_t *frame_dyn,
                 float *frame_w, int32_t *orig_first, int32_t *orig_count, int32_t *cu_tokens, int32_t *info,
                 const PlanOut &out, hipStream_t s) {
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kWave), 0, s, sim, T, L, p, k_uniform, st, seg_start, frame_first,
+  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(st.do_plan ? kPlanThreads : kWave), 0, s, part, n_part, sim, T, L, p, k_uniform, st, seg_start, frame_first,
                      frame_count, frame_dyn, frame_w, orig_first, orig_count, cu_tokens, info, out);
   ET_LAUNCH_CHECK();
   return ET_OK;
@@ -421,6 +469,19 @@ int launch_select_policy(const float *score, int T, const int32_t *info, const i
   }
   hipLaunchKernelGGL(select_policy_kernel, dim3(T), dim3(kSelThreads), (size_t)L * sizeof(uint32_t), s, score,
                      info, frame_dyn, cu_tokens, L, all_topk ? 1 : 0, kept);
+  ET_LAUNCH_CHECK();
+  return ET_OK;
+}
+
+int launch_select_gather_policy(const float *score, const uint16_t *merged, int T, const int32_t *info, const int32_t *frame_dyn,
+                                const int32_t *cu_tokens, int L, int D, bool all_topk, int k_most, int32_t *kept, uint16_t *out,
+                                hipStream_t s) {
+  if (L > kFusedSelectTokens) {
+    set_error("tokens per frame %d above the %d the fused selection supports", L, kFusedSelectTokens);
+    return ET_ERR_UNSUPPORTED;
+  }
+  hipLaunchKernelGGL(select_gather_policy_kernel, dim3(gather_workgroups(k_most), T), dim3(kSelThreads), (size_t)2 * L * sizeof(uint32_t),
+                     s, score, merged, info, frame_dyn, cu_tokens, L, D, all_topk ? 1 : 0, kept, out);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

@@ -1,5 +1,5 @@
-// Per-frame top-k by radix select (Eq. 4), shared by the uniform selection (merge_kernels.hip) and
-// the decoupled selection (policy_kernels.hip).  Device code only.
+// What the simple stage (merge_kernels.hip) and the paper-exact one (policy_kernels.hip) share: the mean of the cosines, the
+// per-frame top-k by radix select (Eq. 4) and the gather.
 #pragma once
 #include "et_common.h"
 
@@ -7,6 +7,41 @@ namespace et {
 
 constexpr int kSelThreads = 256;                   // one workgroup of four wavefronts per frame
 constexpr int kSelWaves = kSelThreads / kWave;
+
+// sim[t] = (sum of the n_src values of row t of src) / L for t = 0 .. T-2, by all wavefronts of a workgroup; the first n_copy
+// also to `copy`.  Fixed order: lane-strided partial sums, then a butterfly; one wavefront per pair.
+__device__ __forceinline__ void mean_over_positions(const float *src, int n_src, int T, int L, float *sim, float *copy, int n_copy) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+  // a wavefront sums four rows at a time, their loads issued together (the kernel is one round trip
+  // to memory per 64 rows when a row has at most 256 values); each row's sum keeps its fixed order
+  constexpr int U = 4;
+  for (int t0 = wave; t0 < T - 1; t0 += U * n_waves) {
+    float acc[U] = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = lane; i0 < n_src; i0 += 4 * kWave) {
+      float v[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int t = t0 + u * n_waves, i = i0 + j * kWave;
+          v[u][j] = (t < T - 1 && i < n_src) ? src[(size_t)t * n_src + i] : 0.f;
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[u] += v[u][j];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float a = wave_sum(acc[u]);
+      const int t = t0 + u * n_waves;
+      if (lane == 0 && t < T - 1) {
+        sim[t] = a / (float)L;
+        if (t < n_copy) copy[t] = a / (float)L;
+      }
+    }
+  }
+}
 
 // Scores are non-negative floats (or NaN), so key = bits + 1 (NaN -> 0) orders them as unsigned
 // integers: non-negative finite / infinite floats have bits < 0x7F800001.
@@ -145,6 +180,40 @@ __device__ __forceinline__ void radix_select_emit(const uint32_t *keys, int L, i
     }
     if (gt || (eq && eq_rank < need_eq)) dst[gt_rank + (eq_rank < need_eq ? eq_rank : need_eq)] = i;
   }
+}
+
+// The kept rows of one frame, shared by the gridDim.x workgroups of that frame: row j of `out` is row sel[j] (LDS) of `frame`,
+// rows j = blockIdx.x * 4 + wavefront, + 4 gridDim.x, ...  A wavefront's rows (two with the launchers' grids) are all in flight at once.
+__device__ __forceinline__ void gather_selected(const uint16_t *frame, const int32_t *sel, int k, int D, uint16_t *out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int chunks = D / 8;
+  const int stride = kSelWaves * gridDim.x;
+  for (int j = blockIdx.x * kSelWaves + wave; j < k; j += 2 * stride) {
+    const int j2 = j + stride;
+    const int l0 = sel[j], l1 = j2 < k ? sel[j2] : l0;
+    const uint4 *s0 = reinterpret_cast<const uint4 *>(frame + (size_t)l0 * D);
+    const uint4 *s1 = reinterpret_cast<const uint4 *>(frame + (size_t)l1 * D);
+    uint4 *d0 = reinterpret_cast<uint4 *>(out + (size_t)j * D);
+    uint4 *d1 = reinterpret_cast<uint4 *>(out + (size_t)j2 * D);
+    for (int c = lane; c < chunks; c += 4 * kWave) {
+      uint4 v0[4], v1[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u * kWave < chunks) { v0[u] = s0[c + u * kWave]; v1[u] = s1[c + u * kWave]; }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u * kWave < chunks) {
+          d0[c + u * kWave] = v0[u];
+          if (j2 < k) d1[c + u * kWave] = v1[u];
+        }
+    }
+  }
+}
+
+// Workgroups per frame for that: two rows per wavefront, at most 32 workgroups.
+inline int gather_workgroups(int k) {
+  const int n = (k + 2 * kSelWaves - 1) / (2 * kSelWaves);
+  return n > 32 ? 32 : n;
 }
 
 }  // namespace et

@@ -108,6 +108,28 @@ def test_merge_select_policy_matches_oracle(pi, T, L, D, mean_len):
         assert simple["cu_tokens"].tolist() == r["cu_tokens"].tolist()
 
 
+# One workgroup's share of a frame (8 rows per workgroup, 32 of them at most), the selection's 256 threads, the longest frame that is
+# selected and gathered in one launch, and one token more.
+@pytest.mark.parametrize("T,L,D,ratio", [(1, 1, 8, 0.5), (3, 1, 8, 1.0), (5, 7, 64, 0.3), (4, 255, 64, 0.9), (4, 257, 4096, 0.4),
+                                         (6, 1000, 1152, 0.2), (3, 7680, 8, 0.5), (3, 7680, 8, 1.0), (3, 7681, 8, 0.5)])
+@pytest.mark.parametrize("select", ["uniform", "decoupled"])
+def test_policy_selection_over_the_sizes(T, L, D, ratio, select):
+    """Whole-number tokens, one segment, nothing fused: scores and rows are exact, ties included."""
+    rng = np.random.default_rng(L + D)
+    x = np.zeros((T, L, D))
+    x[:, :, 0] = rng.integers(1, 60, (L,))
+    x[:, :, 1:] = rng.integers(-2, 3, (L, D - 1))
+    pol = _f32_policy(dict(merge_mode="alg1", select_mode=select, alpha=0.9, tau_seg=0.5, tau_merge=2.0, ratio=ratio))
+    ref = O.merge_select_policy(x, pol)
+    r = et.et_merge_select_policy(torch.from_numpy(x).to(device="cuda", dtype=torch.bfloat16), pol)
+    assert r["n_frames_out"] == T and r["n_segments"] == 1
+    assert r["cu_tokens"].tolist() == list(ref["cu_tokens"])
+    kept = np.asarray(ref["kept_idx"])
+    assert np.array_equal(r["kept_idx"].cpu().numpy(), kept)
+    frame = np.repeat(np.arange(T), np.diff(ref["cu_tokens"]))
+    assert np.array_equal(r["tokens"].float().cpu().numpy(), x[frame, kept].astype(np.float32))
+
+
 def _alg1_golden_cases():
     import os
     out = []
