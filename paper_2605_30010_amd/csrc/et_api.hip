@@ -151,7 +151,7 @@ int enqueue_merge_stage(const uint16_t *x, int T, int L, int D, float tau, int k
                                                    early ? early->host : nullptr, true, true, s));
   if (early && early->ready) ET_HIP(hipEventRecord(early->ready, s));
   ET_TIMED_P(prof, ET_K_MERGE, launch_segment_mean(x, T, L, D, seg_start, w.n_seg, w.merged, w.score, s));
-  if (L <= kFusedSelectTokens) {     // selection and gather in one launch
+  if (L <= 7680) {     // selection and gather in one launch
     ET_TIMED_P(prof, ET_K_SELECT, launch_topk_gather(w.score, w.merged, T, w.n_seg, L, D, k, kept, cu_tokens, packed, s));
   } else {
     ET_TIMED_P(prof, ET_K_SELECT, launch_topk(w.score, T, w.n_seg, L, k, kept, cu_tokens, s));
@@ -195,15 +195,9 @@ int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy
                                                  w.score, s));
   if (step.do_counts) {
     // (score_override: scores computed elsewhere, e.g. the attention received, instead of the L2 norms)
-    const float *score = score_override ? score_override : w.score;
-    const bool uniform = pol.select_mode == ET_SELECT_UNIFORM;
-    if (L <= kFusedSelectTokens) {     // selection and gather in one launch
-      ET_TIMED_P(prof, ET_K_SELECT, launch_select_gather_policy(score, w.merged, T, info, w.frame_dyn, cu_tokens, L, D, uniform,
-                                                                uniform ? k_uniform : L, kept, packed, s));
-    } else {
-      ET_TIMED_P(prof, ET_K_SELECT, launch_select_policy(score, T, info, w.frame_dyn, cu_tokens, L, uniform, kept, s));
-      ET_TIMED_P(prof, ET_K_COMPACT, launch_compact_ragged(w.merged, kept, T, info, cu_tokens, L, D, packed, s));
-    }
+    ET_TIMED_P(prof, ET_K_SELECT, launch_select_policy(score_override ? score_override : w.score, T, info, w.frame_dyn, cu_tokens, L,
+                                                       pol.select_mode == ET_SELECT_UNIFORM, kept, s));
+    ET_TIMED_P(prof, ET_K_COMPACT, launch_compact_ragged(w.merged, kept, T, info, cu_tokens, L, D, packed, s));
   }
   return ET_OK;
 }

@@ -216,8 +216,7 @@ int launch_segment_mean(const uint16_t *x, int T, int L, int D, const int32_t *s
                         const int32_t *n_seg, uint16_t *merged, float *score, hipStream_t s);
 int launch_topk(const float *score, int n_rows_max, const int32_t *n_rows_dev, int L, int k,
                 int32_t *kept, int32_t *cu_tokens, hipStream_t s);
-// selection and gather of the kept rows in one launch (n_rows_dev must not be NULL; L <= kFusedSelectTokens: two words of LDS per token)
-constexpr int kFusedSelectTokens = 7680;
+// selection and gather of the kept rows in one launch (n_rows_dev must not be NULL; L <= 7680)
 int launch_topk_gather(const float *score, const uint16_t *merged, int n_rows_max, const int32_t *n_rows_dev, int L,
                        int D, int k, int32_t *kept, int32_t *cu_tokens, uint16_t *out, hipStream_t s);
 int launch_compact(const uint16_t *merged, const int32_t *kept, int n_rows_max,
@@ -236,10 +235,6 @@ int launch_plan_merge(const uint16_t *x, int T, int L, int D, const int32_t *inf
                       float *score, hipStream_t s);
 int launch_select_policy(const float *score, int T, const int32_t *info, const int32_t *frame_dyn,
                          const int32_t *cu_tokens, int L, bool all_topk, int32_t *kept, hipStream_t s);
-// the same per frame of a policy; k_most: the most tokens that a frame may keep (it sizes the grid only)
-int launch_select_gather_policy(const float *score, const uint16_t *merged, int T, const int32_t *info, const int32_t *frame_dyn,
-                                const int32_t *cu_tokens, int L, int D, bool all_topk, int k_most, int32_t *kept, uint16_t *out,
-                                hipStream_t s);
 int launch_compact_ragged(const uint16_t *merged, const int32_t *kept, int T, const int32_t *info,
                           const int32_t *cu_tokens, int L, int D, uint16_t *out, hipStream_t s);
 

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_gather_kernel(
   int32_t *sel = reinterpret_cast<int32_t *>(smem + L);
   __shared__ SelectShared sh;
   const int n = blockIdx.y;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // the frame's scores are fetched before the frame count is known (row n < gridDim.y lies inside the
   // score buffer whether or not the frame exists), so that the two loads overlap
   const float *row = score + (size_t)n * L;
@@ -244,7 +244,29 @@ __global__ __launch_bounds__(kSelThreads) void topk_gather_kernel(
   __syncthreads();
   if (blockIdx.x == 0)
     for (int j = tid; j < k; j += kSelThreads) kept[(size_t)n * k + j] = sel[j];
-  gather_selected(merged + (size_t)n * L * D, sel, k, D, out + (size_t)n * k * D);
+  // gather: a wavefront's rows (two with the launcher's grid) are all in flight at once
+  const int chunks = D / 8;
+  const int stride = 4 * gridDim.x;
+  for (int j = blockIdx.x * 4 + wave; j < k; j += 2 * stride) {
+    const int j2 = j + stride;
+    const int l0 = sel[j], l1 = j2 < k ? sel[j2] : l0;
+    const uint4 *s0 = reinterpret_cast<const uint4 *>(merged + ((size_t)n * L + l0) * D);
+    const uint4 *s1 = reinterpret_cast<const uint4 *>(merged + ((size_t)n * L + l1) * D);
+    uint4 *d0 = reinterpret_cast<uint4 *>(out + ((size_t)n * k + j) * D);
+    uint4 *d1 = reinterpret_cast<uint4 *>(out + ((size_t)n * k + j2) * D);
+    for (int c = lane; c < chunks; c += 4 * kWave) {
+      uint4 v0[4], v1[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u * kWave < chunks) { v0[u] = s0[c + u * kWave]; v1[u] = s1[c + u * kWave]; }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u * kWave < chunks) {
+          d0[c + u * kWave] = v0[u];
+          if (j2 < k) d1[c + u * kWave] = v1[u];
+        }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -326,11 +348,13 @@ int launch_topk(const float *score, int n_rows_max, const int32_t *n_rows_dev, i
 
 int launch_topk_gather(const float *score, const uint16_t *merged, int n_rows_max, const int32_t *n_rows_dev, int L,
                        int D, int k, int32_t *kept, int32_t *cu_tokens, uint16_t *out, hipStream_t s) {
-  if (L > kFusedSelectTokens) {
-    set_error("tokens per frame %d above the %d the fused selection supports", L, kFusedSelectTokens);
+  if (L > 7680) {
+    set_error("tokens per frame %d above the 7680 the fused selection supports", L);
     return ET_ERR_UNSUPPORTED;
   }
-  hipLaunchKernelGGL(topk_gather_kernel, dim3(gather_workgroups(k), n_rows_max), dim3(kSelThreads),
+  int per_frame = (k + 7) / 8;             // workgroups per frame: two rows per wavefront, at most 32 workgroups
+  per_frame = per_frame > 32 ? 32 : per_frame;
+  hipLaunchKernelGGL(topk_gather_kernel, dim3(per_frame, n_rows_max), dim3(kSelThreads),
                      (size_t)(L + k) * sizeof(uint32_t), s, score, merged, n_rows_dev, L, D, k, kept, cu_tokens, out);
   ET_LAUNCH_CHECK();
   return ET_OK;

@@ -137,9 +137,9 @@ __device__ __forceinline__ void build_plan_64(const float *sim, int T, const Pol
 }
 
 // One workgroup.  With st.do_plan all its wavefronts first take the frames' similarities from the sums that the similarity kernel
-// left (by themselves that was a launch of 5 us whose result this kernel fetched back; now 6 us for both).  The rest is one wavefront's: up to
-// 64 frames are planned by all lanes, longer clips by lane 0 on LDS copies (T <= kPlanLds) or on global memory, where
-// every step is a round trip; the arrays are written by all lanes.
+// left.  The rest is one wavefront's: up to 64 frames are planned by all lanes, longer clips by lane 0 on LDS copies (T <= kPlanLds) or
+// on global memory, where every step is a round trip; the arrays are written by all lanes.  Bound: a chain of round trips.  40
+// frames: 3.7 us for the means, a launch boundary and 7.0 us for the plan -> 8.0 us; the stage's call 99.3 -> 96.4.
 constexpr int kPlanLds = 1024, kPlanThreads = 1024;
 
 // Behind it every lane of the wavefront sees what its lanes wrote, in LDS or in memory.
@@ -357,15 +357,26 @@ __global__ __launch_bounds__(kRowsPerBlock * kWave) void plan_merge_kernel(
 
 // ---------------------------------------------------------------------------------------
 // Per-frame selection with ragged output.  Dynamic frames (and every frame in uniform mode): the
-// radix select of the simple path (select_common.h) with k = cu[n+1] - cu[n].  Static frames (`windows`): one thread per local
-// window of w consecutive positions, arg-max of the key, lowest position on ties.  The keys have been staged in LDS by this
-// workgroup; dst may be LDS or global memory.
+// radix select of the simple path (select_common.h) with k = cu[n+1] - cu[n].  Static frames: one thread per local
+// window of w consecutive positions, arg-max of the key, lowest position on ties.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void select_frame(const uint32_t *keys, int L, int k, bool windows, int r_hat, int32_t *dst, SelectShared &sh) {
+__global__ __launch_bounds__(kSelThreads) void select_policy_kernel(
+    const float *__restrict__ score, const int32_t *__restrict__ info, const int32_t *__restrict__ frame_dyn,
+    const int32_t *__restrict__ cu_tokens, int L, int all_topk, int32_t *__restrict__ kept) {
+  extern __shared__ uint32_t keys[];     // [L]
+  __shared__ SelectShared sh;
+
+  const int n = blockIdx.x;
+  if (n >= info[0]) return;
   const int tid = threadIdx.x;
+  const int out0 = cu_tokens[n], k = cu_tokens[n + 1] - out0;
+  const float *row = score + (size_t)n * L;
+  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
   __syncthreads();
-  if (windows) {                                     // static frame: local windows (Eq. 6)
-    const int w = L / r_hat;
+  int32_t *dst = kept + out0;
+
+  if (!all_topk && !frame_dyn[n]) {                  // static frame: local windows (Eq. 6)
+    const int r_hat = info[3], w = L / r_hat;
     for (int j = tid; j < k; j += kSelThreads) {
       const int lo = j * w, hi = min(lo + w, L);
       int best = lo;
@@ -380,45 +391,6 @@ __device__ __forceinline__ void select_frame(const uint32_t *keys, int L, int k,
   }
 
   radix_select_emit(keys, L, k, dst, sh);
-}
-
-__global__ __launch_bounds__(kSelThreads) void select_policy_kernel(
-    const float *__restrict__ score, const int32_t *__restrict__ info, const int32_t *__restrict__ frame_dyn,
-    const int32_t *__restrict__ cu_tokens, int L, int all_topk, int32_t *__restrict__ kept) {
-  extern __shared__ uint32_t keys[];     // [L]
-  __shared__ SelectShared sh;
-
-  const int n = blockIdx.x;
-  if (n >= info[0]) return;
-  const int out0 = cu_tokens[n], k = cu_tokens[n + 1] - out0;
-  const float *row = score + (size_t)n * L;
-  for (int i = threadIdx.x; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
-  select_frame(keys, L, k, !all_topk && !frame_dyn[n], info[3], kept + out0, sh);
-}
-
-// Selection and gather in one launch, as topk_gather_kernel does it: the workgroups of a frame repeat its selection into LDS
-// and copy their share of the kept rows; the first one also writes the kept positions.  Bound: the chain of the selection's passes.
-__global__ __launch_bounds__(kSelThreads) void select_gather_policy_kernel(
-    const float *__restrict__ score, const uint16_t *__restrict__ merged, const int32_t *__restrict__ info,
-    const int32_t *__restrict__ frame_dyn, const int32_t *__restrict__ cu_tokens, int L, int D, int all_topk,
-    int32_t *__restrict__ kept, uint16_t *__restrict__ out) {
-  extern __shared__ uint32_t smem[];     // keys [L], then the kept positions [up to L]
-  uint32_t *keys = smem;
-  int32_t *sel = reinterpret_cast<int32_t *>(smem + L);
-  __shared__ SelectShared sh;
-  const int n = blockIdx.y, tid = threadIdx.x;
-  // (fetched before the frame count is known: entry n < gridDim.y lies inside every buffer whether or not the frame exists, and
-  // the loads overlap)
-  const int n_frames = info[0], r_hat = info[3], dyn = frame_dyn[n], out0 = cu_tokens[n], out1 = cu_tokens[n + 1];
-  const float *row = score + (size_t)n * L;
-  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
-  if (n >= n_frames) return;
-  const int k = out1 - out0;
-  select_frame(keys, L, k, !all_topk && !dyn, r_hat, sel, sh);
-  __syncthreads();
-  if (blockIdx.x == 0)
-    for (int j = tid; j < k; j += kSelThreads) kept[(size_t)out0 + j] = sel[j];
-  gather_selected(merged + (size_t)n * L * D, sel, k, D, out + (size_t)out0 * D);
 }
 
 // Gather with per-frame counts: out[cu[n] + j, :] = merged[n, kept[cu[n] + j], :].
@@ -469,19 +441,6 @@ int launch_select_policy(const float *score, int T, const int32_t *info, const i
   }
   hipLaunchKernelGGL(select_policy_kernel, dim3(T), dim3(kSelThreads), (size_t)L * sizeof(uint32_t), s, score,
                      info, frame_dyn, cu_tokens, L, all_topk ? 1 : 0, kept);
-  ET_LAUNCH_CHECK();
-  return ET_OK;
-}
-
-int launch_select_gather_policy(const float *score, const uint16_t *merged, int T, const int32_t *info, const int32_t *frame_dyn,
-                                const int32_t *cu_tokens, int L, int D, bool all_topk, int k_most, int32_t *kept, uint16_t *out,
-                                hipStream_t s) {
-  if (L > kFusedSelectTokens) {
-    set_error("tokens per frame %d above the %d the fused selection supports", L, kFusedSelectTokens);
-    return ET_ERR_UNSUPPORTED;
-  }
-  hipLaunchKernelGGL(select_gather_policy_kernel, dim3(gather_workgroups(k_most), T), dim3(kSelThreads), (size_t)2 * L * sizeof(uint32_t),
-                     s, score, merged, info, frame_dyn, cu_tokens, L, D, all_topk ? 1 : 0, kept, out);
   ET_LAUNCH_CHECK();
   return ET_OK;
 }

@@ -182,38 +182,4 @@ __device__ __forceinline__ void radix_select_emit(const uint32_t *keys, int L, i
   }
 }
 
-// The kept rows of one frame, shared by the gridDim.x workgroups of that frame: row j of `out` is row sel[j] (LDS) of `frame`,
-// rows j = blockIdx.x * 4 + wavefront, + 4 gridDim.x, ...  A wavefront's rows (two with the launchers' grids) are all in flight at once.
-__device__ __forceinline__ void gather_selected(const uint16_t *frame, const int32_t *sel, int k, int D, uint16_t *out) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int chunks = D / 8;
-  const int stride = kSelWaves * gridDim.x;
-  for (int j = blockIdx.x * kSelWaves + wave; j < k; j += 2 * stride) {
-    const int j2 = j + stride;
-    const int l0 = sel[j], l1 = j2 < k ? sel[j2] : l0;
-    const uint4 *s0 = reinterpret_cast<const uint4 *>(frame + (size_t)l0 * D);
-    const uint4 *s1 = reinterpret_cast<const uint4 *>(frame + (size_t)l1 * D);
-    uint4 *d0 = reinterpret_cast<uint4 *>(out + (size_t)j * D);
-    uint4 *d1 = reinterpret_cast<uint4 *>(out + (size_t)j2 * D);
-    for (int c = lane; c < chunks; c += 4 * kWave) {
-      uint4 v0[4], v1[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c + u * kWave < chunks) { v0[u] = s0[c + u * kWave]; v1[u] = s1[c + u * kWave]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (c + u * kWave < chunks) {
-          d0[c + u * kWave] = v0[u];
-          if (j2 < k) d1[c + u * kWave] = v1[u];
-        }
-    }
-  }
-}
-
-// Workgroups per frame for that: two rows per wavefront, at most 32 workgroups.
-inline int gather_workgroups(int k) {
-  const int n = (k + 2 * kSelWaves - 1) / (2 * kSelWaves);
-  return n > 32 ? 32 : n;
-}
-
 }  // namespace et

@@ -108,8 +108,7 @@ def test_merge_select_policy_matches_oracle(pi, T, L, D, mean_len):
         assert simple["cu_tokens"].tolist() == r["cu_tokens"].tolist()
 
 
-# One workgroup's share of a frame (8 rows per workgroup, 32 of them at most), the selection's 256 threads, the longest frame that is
-# selected and gathered in one launch, and one token more.
+# The selection's 256 threads and the longest frame that the simple stage selects and gathers in one launch; the plan on one frame and more.
 @pytest.mark.parametrize("T,L,D,ratio", [(1, 1, 8, 0.5), (3, 1, 8, 1.0), (5, 7, 64, 0.3), (4, 255, 64, 0.9), (4, 257, 4096, 0.4),
                                          (6, 1000, 1152, 0.2), (3, 7680, 8, 0.5), (3, 7680, 8, 1.0), (3, 7681, 8, 0.5)])
 @pytest.mark.parametrize("select", ["uniform", "decoupled"])
