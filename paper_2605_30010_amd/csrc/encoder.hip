@@ -4,6 +4,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <utility>
 #include <vector>
 
 #include "et_common.h"
@@ -431,7 +432,8 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const et_config &c = e->cfg;
   const int L = e->L, D = e->D;
-  const EncWs w = carve_encoder(e, workspace_dev, T);
+  EncWs w = carve_encoder(e, workspace_dev, T);
+  uint16_t *spare = carve_merge(w.merge, T, L, D).merged;      // the other place of the residual stream (policy stages)
   e->prof.kinds.clear();
   e->prof.phase = 0;
 
@@ -465,22 +467,25 @@ static int encode_impl(et_encoder *e, const float *frames_dev, int32_t T, int32_
     const bool merge_here = merges_at(i), select_here = selects_at(i);
     if (merge_here || select_here) have_pieces = false;
     if (policy && (merge_here || select_here)) {
-      const MergeWs mw = carve_merge(w.merge, T, L, D);
+      MergeWs mw = carve_merge(w.merge, T, L, D);
       int32_t *info = mw.n_seg + 8;
+      mw.merged = spare;
       const PlanStep step{merge_here ? 1 : 0, select_here ? 1 : 0, first_stage ? 1 : 0, T};
       HostCell cell;
       int rc = enqueue_policy_stage(w.x, n_frames, L, D, *policy, step, mw, first_stage ? out->frame_sim_dev : nullptr,
                                     out->seg_start_dev, out->kept_idx_dev, out->cu_tokens_dev, w.x, info, s,
-                                    &e->prof, select_here ? plan : nullptr, cell.ptr, (select_here && by_attention) ? w.att_score : nullptr);
+                                    &e->prof, select_here ? plan : nullptr, cell.ptr, cell.ptr ? e->count_ready : nullptr,
+                                    (select_here && by_attention) ? w.att_score : nullptr);
       if (rc) return rc;
-      if (!select_here)      // frames keep all L tokens: the merged frames become the residual stream
-        ET_HIP(hipMemcpyAsync(w.x, mw.merged, (size_t)n_frames * L * D * 2, hipMemcpyDeviceToDevice, s));
+      if (!select_here) std::swap(w.x, spare);      // frames keep all L tokens: the merged frames are the residual stream
       int32_t hi[5] = {0, 0, 0, 0, 0};
-      if (!cell.ptr) ET_HIP(hipMemcpyAsync(hi, info, sizeof(hi), hipMemcpyDeviceToHost, s));
-      ET_HIP(hipStreamSynchronize(s));
-      if (cell.ptr) {
+      if (cell.ptr) {        // the counts are final after the plan: merge and selection still run while the next blocks are enqueued
+        ET_HIP(hipEventSynchronize(e->count_ready));
         memcpy(hi, cell.ptr, sizeof(hi));
         cell.done = true;
+      } else {
+        ET_HIP(hipMemcpyAsync(hi, info, sizeof(hi), hipMemcpyDeviceToHost, s));
+        ET_HIP(hipStreamSynchronize(s));
       }
       if (hi[0] < 1 || hi[0] > n_frames || hi[1] < 1 || hi[1] > T) {
         set_error("plan read back from the device is inconsistent (N = %d, segments = %d)", hi[0], hi[1]);

@@ -176,7 +176,7 @@ int check_policy(const et_policy *p) {
 int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy &pol, const PlanStep &step,
                          const MergeWs &w, float *sim_out, int32_t *seg_start, int32_t *kept,
                          int32_t *cu_tokens, uint16_t *packed, int32_t *info, hipStream_t s, Profiler *prof,
-                         const et_plan_out *plan, int32_t *header, const float *score_override) {
+                         const et_plan_out *plan, int32_t *header, hipEvent_t ready, const float *score_override) {
   float *sim = sim_out ? sim_out : w.sim;
   const PolicyArgs pa{pol.merge_mode, pol.select_mode, pol.alpha, pol.tau_seg, pol.tau_merge, pol.ratio};
   const int k_uniform = et_keep_count(L, pol.ratio);
@@ -190,6 +190,7 @@ int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy
   if (step.do_plan) ET_TIMED_P(prof, ET_K_SIMILARITY, launch_similarity(x, T, L, D, w.cos, w.part, s));
   ET_TIMED_P(prof, ET_K_SCAN, launch_plan(w.part, similarity_blocks(L), sim, T, L, pa, k_uniform, step, seg_start, w.frame_first, w.frame_count,
                                           w.frame_dyn, w.frame_w, w.orig_first, w.orig_count, cu_tokens, info, po, s));
+  if (ready) ET_HIP(hipEventRecord(ready, s));
   ET_TIMED_P(prof, ET_K_MERGE, launch_plan_merge(x, T, L, D, info, w.frame_first, w.frame_count, w.frame_w,
                                                  step.do_plan && pol.merge_mode == ET_MERGE_MEAN, w.merged,
                                                  w.score, s));

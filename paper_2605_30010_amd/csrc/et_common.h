@@ -190,7 +190,8 @@ int check_policy(const et_policy *p);
 int enqueue_policy_stage(const uint16_t *x, int T, int L, int D, const et_policy &pol, const PlanStep &step,
                          const MergeWs &w, float *sim_out, int32_t *seg_start, int32_t *kept,
                          int32_t *cu_tokens, uint16_t *packed, int32_t *info, hipStream_t s,
-                         struct Profiler *prof, const et_plan_out *plan, int32_t *header, const float *score_override = nullptr);
+                         struct Profiler *prof, const et_plan_out *plan, int32_t *header, hipEvent_t ready = nullptr,
+                         const float *score_override = nullptr);
 MergeWs carve_merge(void *ws, int T, int L, int D);
 // Where the host learns the segment count: the scan kernel writes it to `host` (pinned memory) and, if given,
 // `ready` is recorded right behind it, so the host can wait for that event only and enqueue the following blocks under
