@@ -68,6 +68,12 @@ def stage_bytes(T, L, D, N, k):
     return 2 * T * L * D * 2 + N * L * D * 2 + 2 * N * k * D * 2 + 2 * T * L * 4
 
 
+def select_bytes(L, D, N, k):
+    """Algorithmic bytes of selection and gather: one launch where rows are narrow, else two."""
+    rank, copy = N * L * 4 + N * k * 4, 2 * N * k * D * 2
+    return {"select": rank + copy} if D <= 768 else {"select": rank, "compact": N * k * 4 + copy}
+
+
 def bytes_tables(shape, T, N, k):
     """Algorithmic HBM bytes per launch of the bandwidth-bound kernels."""
     D, L = shape.d_model, shape.tokens_per_frame
@@ -76,7 +82,7 @@ def bytes_tables(shape, T, N, k):
         ("similarity", 0): X + (T - 1) * L * 4,
         ("scan", 0): (T - 1) * ((L + 3) // 4) * 4 + (T - 1) * 4 + (T + 1) * 4,
         ("merge", 0): X + N * L * D * 2 + N * L * 4,
-        ("select", 0): N * L * 4 + N * k * 4 + 2 * N * k * D * 2,      # selection and gather are one launch
+        **{(kind, 0): b for kind, b in select_bytes(L, D, N, k).items()},
         # row statistics of the LayerNorms folded into the QKV / fc1 GEMMs: the rows are read, one float per row
         # is written (phase 1 also holds the one real LayerNorm, the final one: slightly under-counted)
         ("layernorm", 0): T * L * D * 2 + T * L * 4,
@@ -256,7 +262,7 @@ def merge_microbench(et, torch, steps, warmup, variant=0):
     b_alg = stage_bytes(T, L, D, N, k)
     alg = {"similarity": T * L * D * 2 + (T - 1) * L * 4, "scan": (T - 1) * ((L + 3) // 4) * 4 + 2 * T * 4,
            "merge": T * L * D * 2 + N * L * D * 2 + N * L * 4,
-           "select": N * L * 4 + N * k * 4 + 2 * N * k * D * 2}          # selection and gather are one launch
+           **select_bytes(L, D, N, k)}
 
     def timed(cold, level):
         et.et_merge_profile_enable(level)
@@ -284,7 +290,7 @@ def merge_microbench(et, torch, steps, warmup, variant=0):
            "kernels": k_cold,
            "cache_resident": {"avg_us": round(us_warm, 2), "gbs": round(b_alg / us_warm / 1e3, 1),
                               "kernels": {n_: e["avg_us"] for n_, e in k_warm.items()}},
-           "timed": "first launch's start to last launch's end on the launch stream (4 launches, gaps included)",
+           "timed": "first launch's start to last launch's end on the launch stream (gaps included)",
            "decisions_match_oracle": True}
     return res, rec
 
@@ -404,7 +410,7 @@ def main():
         kernels["share_kept_blocks"] = round(kept_share, 4)
         # the compression stage inside the clip, as one bandwidth figure (its tensor is cache-resident here:
         # block m - 1 has just written it; the cold figure is merge_stage_c5)
-        stage_ms = sum(prof[(kk, 0)][0] for kk in ("similarity", "scan", "merge", "select"))
+        stage_ms = sum(prof[(kk, 0)][0] for kk in ("similarity", "scan", "merge", "select", "compact"))
         stage_cnt = max(prof[("similarity", 0)][1], 1)
         D, L = shape.d_model, shape.tokens_per_frame
         sb = stage_bytes(T, L, D, N, k)

@@ -227,8 +227,8 @@ int et_merge_profile_enable(int32_t on);
 int et_merge_profile_read(double *ms, int64_t *launches, double *total_ms, int64_t *calls, int32_t reset);
 
 /* ---- single steps (the device code of the hot path, one step per call; for parity tests and
- *      micro-benchmarks).  All asynchronous on `hip_stream` unless stated.  The hot path itself runs
- *      selection and gather (et_topk_select + et_compact_tokens) as ONE launch on the same select
+ *      micro-benchmarks).  All asynchronous on `hip_stream` unless stated.  On narrow rows the hot path
+ *      runs selection and gather (et_topk_select + et_compact_tokens) as ONE launch on the same select
  *      routine; the two calls below launch them separately. ------------- */
 
 /* Sec. 3.2: cos_dev [T-1, L] float32 per-position cosine similarities of frames t and t-1,

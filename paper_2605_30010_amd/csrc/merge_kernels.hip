@@ -192,33 +192,34 @@ __global__ __launch_bounds__(kMeanWaves * kWave) void segment_mean_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// Per-frame top-k: one 256-thread workgroup per frame, keys staged in LDS (select_common.h).
+// Per-frame top-k: one 256-thread workgroup per frame, keys staged in LDS (select_common.h).  Bound: the chain of the scores'
+// loads and the radix passes.  With the scores' four loads in flight, the frame count beside them and the gather (compact_kernel) as
+// the stage's launches on rows of 1152: 64 frames of 729 merged to 6, a third kept, 85.7 -> 84.8 us per call, nine tenths 91.1 -> 87.9.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kSelThreads) void topk_kernel(
     const float *__restrict__ score, const int32_t *__restrict__ n_rows_dev, int L, int k,
     int32_t *__restrict__ kept, int32_t *__restrict__ cu_tokens) {
   extern __shared__ uint32_t keys[];     // [L]
   __shared__ SelectShared sh;
-  const int n = blockIdx.x;
+  const int n = blockIdx.x, tid = threadIdx.x;
+  // (fetched before the frame count is known: row n < gridDim.x lies inside the score buffer whether or not the frame exists)
+  stage_keys(score + (size_t)n * L, L, keys);
   const int n_rows = n_rows_dev ? *n_rows_dev : (int)gridDim.x;
   if (n >= n_rows) return;
-  const int tid = threadIdx.x;
   if (cu_tokens && tid == 0) {
     cu_tokens[n] = n * k;
     if (n == 0) cu_tokens[n_rows] = n_rows * k;
   }
-  const float *row = score + (size_t)n * L;
-  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
   radix_select_emit(keys, L, k, kept + (size_t)n * k, sh);
 }
 
 // ---------------------------------------------------------------------------------------
-// Selection and gather in one launch (what the stage runs): gridDim.x workgroups per frame each
+// Selection and gather in one launch (what the stage runs on narrow rows): gridDim.x workgroups per frame each
 // repeat the frame's radix select (a few microseconds on L keys, all in LDS) into an LDS list and
 // then copy their share of the kept rows, rows j = blockIdx.x * 4 + wavefront, + 4 gridDim.x, ...:
 //   out[n*k + j, :] = merged[n, sel[j], :]   (Eq. 7).
-// The repeated select costs nothing in time (the workgroups run side by side), and the gather no
-// longer waits for a kernel boundary and a dependent index load.  Workgroup 0 of a frame also
+// The repeated select runs side by side, and the gather waits for no kernel boundary and no
+// dependent index load; what takes the time on wide rows is that few workgroups copy.  Workgroup 0 of a frame also
 // writes the kept positions and the token offsets.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kSelThreads) void topk_gather_kernel(
@@ -232,8 +233,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_gather_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // the frame's scores are fetched before the frame count is known (row n < gridDim.y lies inside the
   // score buffer whether or not the frame exists), so that the two loads overlap
-  const float *row = score + (size_t)n * L;
-  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
+  stage_keys(score + (size_t)n * L, L, keys);
   const int n_rows = *n_rows_dev;
   if (n >= n_rows) return;
   if (blockIdx.x == 0 && tid == 0) {
@@ -276,12 +276,12 @@ __global__ __launch_bounds__(kRowsPerBlock * kWave) void compact_kernel(
     const uint16_t *__restrict__ merged, const int32_t *__restrict__ kept,
     const int32_t *__restrict__ n_rows_dev, int L, int D, int k, uint16_t *__restrict__ out) {
   const int n = blockIdx.y;
-  if (n_rows_dev && n >= *n_rows_dev) return;
   const int lane = threadIdx.x & 63;
   const int j = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
   if (j >= k) return;
   const size_t orow = (size_t)n * k + j;
-  const int l = kept[orow];
+  const int l = kept[orow];              // (n < gridDim.y: inside the array whether or not the frame exists; fetched beside the count)
+  if (n_rows_dev && n >= *n_rows_dev) return;
   if (l < 0 || l >= L) return;           // never follow a corrupt index out of bounds
   const uint4 *src = reinterpret_cast<const uint4 *>(merged + ((size_t)n * L + l) * D);
   uint4 *dst = reinterpret_cast<uint4 *>(out + orow * D);

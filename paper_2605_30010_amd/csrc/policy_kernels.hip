@@ -367,16 +367,18 @@ __global__ __launch_bounds__(kSelThreads) void select_policy_kernel(
   __shared__ SelectShared sh;
 
   const int n = blockIdx.x;
-  if (n >= info[0]) return;
   const int tid = threadIdx.x;
-  const int out0 = cu_tokens[n], k = cu_tokens[n + 1] - out0;
-  const float *row = score + (size_t)n * L;
-  for (int i = tid; i < L; i += kSelThreads) keys[i] = score_key(row[i]);
+  // (fetched before the frame count is known: entry n < gridDim.x lies inside every buffer whether or not the frame exists, and the
+  // loads overlap)
+  const int n_frames = info[0], r_hat = info[3], dyn = frame_dyn[n], out0 = cu_tokens[n], out1 = cu_tokens[n + 1];
+  stage_keys(score + (size_t)n * L, L, keys);
+  if (n >= n_frames) return;
+  const int k = out1 - out0;
   __syncthreads();
   int32_t *dst = kept + out0;
 
-  if (!all_topk && !frame_dyn[n]) {                  // static frame: local windows (Eq. 6)
-    const int r_hat = info[3], w = L / r_hat;
+  if (!all_topk && !dyn) {                  // static frame: local windows (Eq. 6)
+    const int w = L / r_hat;
     for (int j = tid; j < k; j += kSelThreads) {
       const int lo = j * w, hi = min(lo + w, L);
       int best = lo;
@@ -398,11 +400,12 @@ __global__ __launch_bounds__(kRowsPerBlock * kWave) void compact_ragged_kernel(
     const uint16_t *__restrict__ merged, const int32_t *__restrict__ kept, const int32_t *__restrict__ info,
     const int32_t *__restrict__ cu_tokens, int L, int D, uint16_t *__restrict__ out) {
   const int n = blockIdx.y;
-  if (n >= info[0]) return;
+  const int n_frames = info[0], out0 = cu_tokens[n], out1 = cu_tokens[n + 1];      // (n < T: inside the array)
+  asm volatile("" ::"s"(n_frames), "s"(out0), "s"(out1));                          // (the three loads overlap)
+  if (n >= n_frames) return;
   const int lane = threadIdx.x & 63;
   const int j = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  const int out0 = cu_tokens[n];
-  if (j >= cu_tokens[n + 1] - out0) return;
+  if (j >= out1 - out0) return;
   const size_t orow = (size_t)out0 + j;
   const int l = kept[orow];
   if (l < 0 || l >= L) return;

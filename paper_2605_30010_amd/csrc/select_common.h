@@ -50,6 +50,19 @@ __device__ __forceinline__ uint32_t score_key(float z) {
   return (z != z) ? 0u : u + 1u;
 }
 
+// The keys of one frame's scores to LDS, four loads per thread in flight (one by one, each waited for the one before: 729 scores
+// cost three trips to memory).
+__device__ __forceinline__ void stage_keys(const float *row, int L, uint32_t *keys) {
+  for (int i0 = threadIdx.x; i0 < L; i0 += 4 * kSelThreads) {
+    float z[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) z[u] = row[min(i0 + u * kSelThreads, L - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i0 + u * kSelThreads < L) keys[i0 + u * kSelThreads] = score_key(z[u]);
+  }
+}
+
 struct SelectShared {
   int hist[256];
   int wave_tot[kSelWaves];

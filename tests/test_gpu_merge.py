@@ -225,6 +225,24 @@ def test_merge_select_matches_oracle(T, L, D, keep, mean_len):
         assert torch.equal(r[key], r2[key])
 
 
+# Rows of 768 values, the widest whose selection and gather are one launch, and wider ones (two launches); the selection's 256 threads
+# and the four scores that each has in flight; one row, all rows.
+@pytest.mark.parametrize("T,L,D,keep", [(3, 256, 768, 0.5), (3, 256, 776, 0.5), (3, 1, 1152, 1.0), (2, 1023, 1152, 0.3),
+                                        (2, 1025, 1152, 1.0), (9, 257, 4096, 0.01)])
+def test_selection_and_gather_on_narrow_and_wide_rows(T, L, D, keep):
+    """Two still scenes of whole numbers: means, scores and rows are exact, ties included."""
+    rng = np.random.default_rng(L + D)
+    scenes = rng.integers(-3, 4, (2, L, D)).astype(np.float64)
+    scenes[:, :, 0] = rng.integers(1, 40, (2, L))
+    x = scenes[(np.arange(T) >= T // 2).astype(int)]
+    x[:, :, 1] *= np.where(np.arange(T) >= T // 2, 1.0, 0.0)[:, None]
+    ref = O.merge_select(x, 0.999, np.float32(keep))
+    r = et.et_merge_select(torch.from_numpy(x).to(device="cuda", dtype=torch.bfloat16), 0.999, keep)
+    assert r["seg_start"].tolist() == ref["seg_start"].tolist() and r["cu_tokens"].tolist() == ref["cu_tokens"].tolist()
+    assert np.array_equal(r["kept_idx"].cpu().numpy(), ref["kept_idx"].reshape(-1))
+    assert np.array_equal(r["tokens"].float().cpu().numpy(), ref["tokens"].astype(np.float32))
+
+
 def test_merge_select_exact_ties_go_to_the_lower_position():
     T, L, D = 6, 96, 128
     bits = make_hidden_states(T, L, D, [1, 1, 1, 1, 1, 1], 5, sigma=0.1, dup_rows=40)
