@@ -28,7 +28,8 @@ __device__ __forceinline__ float across_groups(float v) {
 // Runs blocks 0 .. n_layers - 1 of `a` on frame blockIdx.x.  Roundings to bf16 as in the launches of wider encoders: q | k | v, the
 // scaled q, the probabilities, the attention's result, the residual stream after either half, the MLP's hidden
 // values; all sums in float32, the MFMA steps k-ascending (q | k | v have the bits of gemm_strip_kernel on the scales of
-// piece_scale_kernel).  Rows past the frame's end are zeros and stay finite.
+// piece_scale_kernel).  The stream's rows past the frame's end hold whatever the blocks make of zeros (with ln_eps = 0 not even
+// finite values); their q | k | v are set to zero, so that no query meets them: a probability of 0 times a NaN would be one.
 // JN: the MLP's width in units of 64.
 template <int HD, int JN>
 __global__ __launch_bounds__(512, 1) void narrow_blocks_kernel(NarrowArgs a) {
@@ -122,6 +123,7 @@ __global__ __launch_bounds__(512, 1) void narrow_blocks_kernel(NarrowArgs a) {
           uint2 o;
           o.x = cvt_pk_bf16(fmaf(rs, acc[j][b][0], bq[j][0]), fmaf(rs, acc[j][b][1], bq[j][1]));
           o.y = cvt_pk_bf16(fmaf(rs, acc[j][b][2], bq[j][2]), fmaf(rs, acc[j][b][3], bq[j][3]));
+          if (m >= n) o = make_uint2(0u, 0u);
           if (li + 1 == a.n_layers && m < n) *reinterpret_cast<uint2 *>(a.qkv + ((size_t)start + m) * 3 * kW + c) = o;
           *reinterpret_cast<uint2 *>(buf + m * kQkvLd + c) = o;
         }

@@ -412,3 +412,28 @@ def test_narrow_encoders_run_by_frames(heads, mlp, side, T, layers):
     ref = O.encode_clip(shape, w, frames, 1, -2.0, 1.0)
     assert rel_l2(dev_to_f64(cut["tokens"]), ref["tokens"]) <= TOL
     enc.close()
+
+
+@pytest.mark.parametrize("heads,mlp,side,keep", [(4, 256, 98, 1.0), (2, 200, 112, 0.5), (1, 64, 14, 1.0), (4, 72, 70, 0.3)])
+def test_narrow_encoders_without_ln_eps(heads, mlp, side, keep):
+    """ln_eps = 0: the scale of a row of zeros, as behind the end of a frame of fewer than 64 tokens, is infinite, and nothing of it may reach
+    the frame's own rows; frames that are shorter from the start, by a selection of equal counts, and by one of two counts.
+    Bound: as for narrow encoders with an ln_eps."""
+    from et_inputs import EncoderShape
+    shape = EncoderShape(n_layers=3, d_model=64, n_heads=heads, d_mlp=mlp, patch=14, image_h=side, image_w=side, ln_eps=0.0)
+    w = make_weights(shape, seed=side, bf16=True)
+    frames = make_clip(shape, [2, 1, 3], 6, base="uniform", sigma=0.02)
+    enc = et.Encoder(shape, w, 6)
+    got = _encode(enc, frames, -1, 0.9, 1.0)
+    ref = O.encode_clip(shape, w, frames, -1, 0.9, 1.0)
+    assert rel_l2(dev_to_f64(got["tokens"]), ref["tokens"]) <= 2.0 ** -9 * np.sqrt(7 * 3)
+    cut = _encode(enc, frames, 1, -2.0, keep)                 # one segment, the mean frame after the first block
+    ref = O.encode_clip(shape, w, frames, 1, -2.0, np.float32(keep), force_kept=[cut["kept_idx"].cpu().numpy()])
+    assert rel_l2(dev_to_f64(cut["tokens"]), ref["tokens"]) <= TOL
+    policy = dict(merge_mode="alg1", select_mode="decoupled", alpha=0.5, tau_seg=-2.0, tau_merge=2.0, ratio=float(np.float32(keep)))
+    ragged = enc.encode_policy(torch.from_numpy(frames).cuda(), 1, policy)      # one scene, nothing fused: the inner frames are static
+    cu, kept = ragged["cu_tokens"].tolist(), ragged["kept_idx"].cpu().numpy()
+    ref = O.encode_clip_policy(shape, w, frames, 1, policy, force_kept=[kept[a:b] for a, b in zip(cu, cu[1:])])
+    assert cu == list(ref["cu_tokens"])
+    assert rel_l2(dev_to_f64(ragged["tokens"]), ref["tokens"]) <= TOL
+    enc.close()
