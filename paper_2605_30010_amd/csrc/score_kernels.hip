@@ -14,8 +14,6 @@
 // heads * L (no atomics anywhere: bit-reproducible).  The two-pass kernels load their fragments
 // straight from global memory (16-byte pieces of q / k rows); the head dimension is padded to a
 // multiple of 16 with zero fragments.
-#include <type_traits>
-
 #include "mfma_common.h"
 
 namespace et {
@@ -35,18 +33,17 @@ __device__ __forceinline__ u32x4 load_piece(const uint16_t *row, int chunk, int 
 // One pass.  A workgroup of 8 wavefronts owns one (frame, head) and a contiguous share of the 32-query
 // blocks; wavefront w owns the NB 32-key blocks w, w + 8, ..., whose K fragments stay in registers.
 // Per query block every wavefront computes S^T = K Q^T for its keys (the query on the accumulator's
-// lane axis), exponentiates, and leaves the sum per query in LDS; after one barrier each knows the factor 1 / l
-// that turns its exponentials into probabilities and adds them to its column sums, which stay in registers to the
-// end: one exponential and one logit per (query, key) instead of two.  The exponentials take the reference 0 as long as
-// every query's l stays within 2^+-60 (logits within some 41 of 0: float32 loses nothing there); a workgroup that finds
-// another l starts again with each wavefront's OWN maximum as its reference, leaves (maximum, sum), and uses the factor
-// exp2(m_w - m) / l.  The query blocks come to LDS as fragments (KSTEPS * 1 KiB) by direct loads, three blocks ahead.
-// Bound by the vector unit: per 16 accumulator values 16 multiplications, exponentials (at half rate), additions and
-// fma, 320 clocks against 160 of the matrix unit, which works on the next block in between; of a workgroup's 95 000 clocks at 729
-// tokens 10 000 are its keys' way from memory (one compute unit takes 40 KB per us), 83 000 the loop.  K and Q are read once per workgroup.
-// Measured against the two passes (all launches of a call): 32 frames x 16 heads x 729 tokens of 72: 373 -> 94 us (with a maximum
-// per block 98, sums over the lanes value by value at the end another 4 more); 16 x 16 x 600 of 80: 139 -> 50; 8 x 16 x 729: 114 -> 41;
-// one frame: 63 -> 33; 32 x 12 x 200 of 64: 38 -> 20.
+// lane axis), exponentiates against its OWN maximum, and leaves (maximum, sum) per query in LDS; after one barrier each
+// knows the factor exp2(m_w - m) / l that turns its exponentials into probabilities and adds them to its column sums, which
+// stay in registers to the end: one exponential and one logit per (query, key) instead of two.  (The reference 0 in place of the
+// maxima, while the sums stay within 2^+-60, saves 4 us of the 94 below and costs precision where logits are large: up to 14 %
+// larger errors for standard normal q and k times 1.5 to 3; and a call of large logits has its blocks computed twice, 97 -> 165 us.)
+// The query blocks come to LDS as fragments (KSTEPS * 1 KiB) by direct loads, three blocks ahead.
+// Bound by the vector unit: per 16 accumulator values 16 maxima, fma, exponentials (at half rate), additions and fma, 350 to 380
+// clocks against 160 of the matrix unit, which works on the next block in between; at 729 tokens a tenth of a workgroup's time is its
+// keys' way from memory (one compute unit takes 40 KB per us), the rest the loop.  K and Q are read once per workgroup.
+// Measured against the two passes (all launches of a call): 32 frames x 16 heads x 729 tokens of 72: 373 -> 94 us; 8 x
+// 16 x 729: 114 -> 41; one frame: 63 -> 34; 32 x 12 x 196 of 64: 38 -> 21.
 // ---------------------------------------------------------------------------------------
 constexpr int kPassWaves = 8;
 constexpr int kMaxSplits = 3;        // shares of a (frame, head)'s queries: their partial sums take the room of the two-pass statistics
@@ -111,130 +108,105 @@ __global__ __launch_bounds__(kPassWaves * 64, NB == 1 ? 4 : 2) void attn_score_k
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), known to the compiler: it has no waits for the keys in the loop
-  float col[NB][16];
   const bool any_key = wave * 32 < L;                    // wave-uniform; a wavefront without keys only keeps the barriers
   f32x16 acc[NB];
-  auto query = [&](int turn, int ks) {
-    u32x4 q = *reinterpret_cast<const u32x4 *>(qs[turn] + ks * 512 + lane * 8);
+  float col[NB][16];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) col[b][i] = 0.f;
+  auto query = [&](int slot, int ks) {
+    u32x4 q = *reinterpret_cast<const u32x4 *>(qs[slot] + ks * 512 + lane * 8);
     if (ks == KSTEPS - 1 && pad_last && grp) q = u32x4{0u, 0u, 0u, 0u};
     return q;
   };
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // One pass over the share's query blocks, whose first fragments have landed.  QUICK: exponentials against the reference 0;
-  // returns whether every query's denominator is of ordinary size (all wavefronts with keys find the same denominators).
-  auto pass = [&](auto quick) {
-    constexpr bool QUICK = decltype(quick)::value;
-    bool sound = true;
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) col[b][i] = 0.f;
-    __syncthreads();
+  // Query block qb, whose logits are in acc; leaves those of the next one there (past the share's end unused).
+  auto block = [&](int qb, int buf) {
+    float p[NB][16];
+    float m = -INFINITY, l = 0.f;
+    const int next = (qb + 1 - qb0) % RING;
+    u32x4 q_now;
+    auto step = [&](int b, int ks) {                     // of the next block's logits of key block b
+      acc[b] = mfma32(kf[b][ks], q_now, ks ? acc[b] : zero16);
+      q_now = query(next, ks + 1 < KSTEPS ? ks + 1 : 0);
+    };
     if (any_key) {
+      q_now = query(next, 0);
 #pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        const u32x4 q = query(0, ks);
+      for (int b = 0; b < NB; ++b) {
+        const int k0 = (wave + b * kPassWaves) * 32;
+        if (k0 + 32 > L) {                               // (wave-uniform) keys past the frame
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] = mfma32(kf[b][ks], q, ks ? acc[b] : zero16);
+          for (int i = 0; i < 16; ++i)
+            if (k0 + (i / 4) * 8 + 4 * grp + (i % 4) >= L) acc[b][i] = -INFINITY;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[b][i]);
       }
-    }
-    for (int qb = qb0, buf = 0; qb < qb1; ++qb, buf ^= 1) {
-      issue(qb + RING - 1);
-      float p[NB][16];
-      float m = -INFINITY, l = 0.f;
-      // One step of the next block's logits of key block b (past the share's end unused).
-      const int next = (qb + 1 - qb0) % RING;
-      u32x4 q_now;
-      auto step = [&](int b, int ks) {
-        acc[b] = mfma32(kf[b][ks], q_now, ks ? acc[b] : zero16);
-        q_now = query(next, ks + 1 < KSTEPS ? ks + 1 : 0);
-      };
-      if (any_key) {
-        q_now = query(next, 0);
+      // The wavefront's reference is a whole number, so the factor between two wavefronts' references is an
+      // exact power of two.
+      const float2 mm = both_halves(m);
+      m = ceilf(fmaxf(mm.x, mm.y) * scale_log2);         // (scale_log2 > 0: the order is kept)
+      const float m_ref = m == -INFINITY ? 0.f : m;      // no finite logit here: exponentials are 0, not NaN
+      // The matrix unit works on the next block under the exponentials: of key block b - 1 as soon as its logits are used.
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const int k0 = (wave + b * kPassWaves) * 32;
-          if (k0 + 32 > L) {                             // (wave-uniform) keys past the frame
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-              if (k0 + (i / 4) * 8 + 4 * grp + (i % 4) >= L) acc[b][i] = -INFINITY;
-          }
-          if (!QUICK) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[b][i]);
-          }
-        }
-        float m_ref = 0.f;
-        if (!QUICK) {
-          // The wavefront's reference is a whole number, so the factor between two wavefronts' references is an
-          // exact power of two.
-          const float2 mm = both_halves(m);
-          m = ceilf(fmaxf(mm.x, mm.y) * scale_log2);     // (scale_log2 > 0: the order is kept)
-          m_ref = m == -INFINITY ? 0.f : m;              // no finite logit here: exponentials are 0, not NaN
-        }
-        // The matrix unit works on the next block under the exponentials: of key block b - 1 as soon as its logits are used.
-        float part[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-          for (int ks = 0; ks < KSTEPS; ++ks) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (b > 0) step(b - 1, ks);
-#pragma unroll
-            for (int i = 16 * ks / KSTEPS; i < 16 * (ks + 1) / KSTEPS; ++i) {
-              p[b][i] = __builtin_amdgcn_exp2f(QUICK ? acc[b][i] * scale_log2 : fmaf(acc[b][i], scale_log2, -m_ref));
-              part[i & 3] += p[b][i];
-            }
-          }
-        __builtin_amdgcn_sched_barrier(0);
-        const float2 ll = both_halves((part[0] + part[1]) + (part[2] + part[3]));
-        l = ll.x + ll.y;
-      }
-      if (grp == 0) ex[buf][wave][r32] = make_float2(m, l);
-      wait_vmcnt<RING - 3>();                            // the fragment of the block after the next has landed
-      __syncthreads();
-      // (ex[buf] is written again two blocks on, behind the next barrier; a query block's room is loaded again behind the
-      // barrier that follows its last read)
-      if (any_key) {
-        float2 o[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) o[w] = ex[buf][grp * 4 + w][r32];    // each lane half combines four wavefronts
-        const bool valid = qb * 32 + r32 < L;            // queries past L add nothing
-        float fac;
-        if (QUICK) {
-          const float2 ll = both_halves((o[0].y + o[1].y) + (o[2].y + o[3].y));
-          const float lt = ll.x + ll.y;
-          sound = sound && (!valid || (lt > 0x1p-60f && lt < 0x1p60f));
-          fac = valid ? 1.0f / lt : 0.f;
-        } else {
-          const float2 mm = both_halves(fmaxf(fmaxf(o[0].x, o[1].x), fmaxf(o[2].x, o[3].x)));
-          const float mt = fmaxf(mm.x, mm.y);
-          float lt = 0.f;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) lt += o[w].y * __builtin_amdgcn_exp2f(o[w].x - mt);
-          const float2 ll = both_halves(lt);
-          fac = valid ? __builtin_amdgcn_exp2f(m - mt) / (ll.x + ll.y) : 0.f;
-        }
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
           __builtin_amdgcn_sched_barrier(0);
-          step(NB - 1, ks);
+          if (b > 0) step(b - 1, ks);
 #pragma unroll
-          for (int i = NB * 16 * ks / KSTEPS; i < NB * 16 * (ks + 1) / KSTEPS; ++i) col[i / 16][i % 16] = fmaf(p[i / 16][i % 16], fac, col[i / 16][i % 16]);
+          for (int i = 16 * ks / KSTEPS; i < 16 * (ks + 1) / KSTEPS; ++i) {
+            p[b][i] = __builtin_amdgcn_exp2f(fmaf(acc[b][i], scale_log2, -m_ref));
+            part[i & 3] += p[b][i];
+          }
         }
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      __builtin_amdgcn_sched_barrier(0);
+      const float2 ll = both_halves((part[0] + part[1]) + (part[2] + part[3]));
+      l = ll.x + ll.y;
     }
-    wait_vmcnt<0>();                                     // (the loads past the end)
-    return sound;
-  };
-  const bool sound = pass(std::true_type());
-  if (__syncthreads_or(any_key && !sound)) {             // (and everyone has left the buffers)
+    if (grp == 0) ex[buf][wave][r32] = make_float2(m, l);
+    wait_vmcnt<RING - 3>();                              // the fragment of the block after the next has landed
+    __syncthreads();
+    // (ex[buf] is written again two blocks on, behind the next barrier; a query block's room is loaded again behind the
+    // barrier that follows its last read)
+    if (any_key) {
+      float2 o[4];
 #pragma unroll
-    for (int i = 0; i < RING - 1; ++i) issue(qb0 + i);
-    wait_vmcnt<0>();
-    pass(std::false_type());
+      for (int w = 0; w < 4; ++w) o[w] = ex[buf][grp * 4 + w][r32];    // each lane half combines four wavefronts
+      const float2 mm = both_halves(fmaxf(fmaxf(o[0].x, o[1].x), fmaxf(o[2].x, o[3].x)));
+      const float mt = fmaxf(mm.x, mm.y);
+      float lt = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) lt += o[w].y * __builtin_amdgcn_exp2f(o[w].x - mt);
+      const float2 ll = both_halves(lt);
+      const float fac = qb * 32 + r32 < L ? __builtin_amdgcn_exp2f(m - mt) / (ll.x + ll.y) : 0.f;      // queries past L add nothing
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        __builtin_amdgcn_sched_barrier(0);
+        step(NB - 1, ks);
+#pragma unroll
+        for (int i = NB * 16 * ks / KSTEPS; i < NB * 16 * (ks + 1) / KSTEPS; ++i) col[i / 16][i % 16] = fmaf(p[i / 16][i % 16], fac, col[i / 16][i % 16]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  __syncthreads();
+  if (any_key) {
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      const u32x4 q = query(0, ks);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[b] = mfma32(kf[b][ks], q, ks ? acc[b] : zero16);
+    }
   }
+  for (int qb = qb0, buf = 0; qb < qb1; ++qb, buf ^= 1) {
+    issue(qb + RING - 1);
+    block(qb, buf);
+  }
+  wait_vmcnt<0>();                                       // (the loads past the end)
   // Sums over the 32 queries of each lane half.  Two values of a key block share a register after the first exchange
   // (accumulator rows i in the even, i + 8 in the odd rows of 16 lanes); lane j of a row then stores the j-th sum.
   float *dst = partial + (((size_t)f * n_heads + h) * splits + sp) * L;
