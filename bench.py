@@ -69,9 +69,9 @@ def stage_bytes(T, L, D, N, k):
 
 
 def select_bytes(L, D, N, k):
-    """Algorithmic bytes of selection and gather: one launch where rows are narrow, else two."""
+    """Algorithmic bytes of selection and gather: one launch where rows are narrow and a frame's scores fit LDS beside its list, else two."""
     rank, copy = N * L * 4 + N * k * 4, 2 * N * k * D * 2
-    return {"select": rank + copy} if D <= 768 else {"select": rank, "compact": N * k * 4 + copy}
+    return {"select": rank + copy} if D <= 768 and L <= 7680 else {"select": rank, "compact": N * k * 4 + copy}
 
 
 def bytes_tables(shape, T, N, k):

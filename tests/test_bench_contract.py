@@ -45,6 +45,14 @@ def test_stage_bytes_of_the_merge_only_workload():
     assert round(b / 1e6, 1) == 244.9
 
 
+def test_select_bytes_are_booked_under_the_launches_that_run():
+    """One launch for rows of up to 768 values and 7680 tokens, two otherwise; the same rows and lists either way, the list read once more."""
+    for L, D, fused in ((7680, 768, True), (7681, 768, False), (7680, 776, False)):
+        b = bench.select_bytes(L, D, 4, 100)
+        assert set(b) == ({"select"} if fused else {"select", "compact"})
+        assert sum(b.values()) == 4 * L * 4 + 4 * 100 * 4 * (1 if fused else 2) + 2 * 4 * 100 * D * 2
+
+
 def test_traffic_is_quoted_only_for_the_kernel_the_summary_names():
     value, source = bench.measured_traffic("gemm_fc1@all")
     assert value and value > 2.6e8 and source.startswith("profiles/")
