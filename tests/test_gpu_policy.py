@@ -113,12 +113,12 @@ def test_merge_select_policy_matches_oracle(pi, T, L, D, mean_len):
                                          (6, 1000, 1152, 0.2), (3, 7680, 8, 0.5), (3, 7680, 8, 1.0), (3, 7681, 8, 0.5)])
 @pytest.mark.parametrize("select", ["uniform", "decoupled"])
 def test_policy_selection_over_the_sizes(T, L, D, ratio, select):
-    """Whole-number tokens, one segment, nothing fused: scores and rows are exact, ties included."""
+    """Whole-number tokens, another set in every frame, one segment, nothing fused: scores and rows are exact, ties included."""
     rng = np.random.default_rng(L + D)
     x = np.zeros((T, L, D))
-    x[:, :, 0] = rng.integers(1, 60, (L,))
-    x[:, :, 1:] = rng.integers(-2, 3, (L, D - 1))
-    pol = _f32_policy(dict(merge_mode="alg1", select_mode=select, alpha=0.9, tau_seg=0.5, tau_merge=2.0, ratio=ratio))
+    x[:, :, 0] = rng.integers(1, 60, (T, L))
+    x[:, :, 1:] = rng.integers(-2, 3, (T, L, D - 1))
+    pol = _f32_policy(dict(merge_mode="alg1", select_mode=select, alpha=0.9, tau_seg=-2.0, tau_merge=2.0, ratio=ratio))
     ref = O.merge_select_policy(x, pol)
     r = et.et_merge_select_policy(torch.from_numpy(x).to(device="cuda", dtype=torch.bfloat16), pol)
     assert r["n_frames_out"] == T and r["n_segments"] == 1
