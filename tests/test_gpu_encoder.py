@@ -394,8 +394,8 @@ def test_row_whose_variance_leaves_float32(size):
                                                      (2, 65, 56, 1, 35)])
 def test_narrow_encoders_run_by_frames(heads, mlp, side, T, layers):
     """The kernel that takes a frame through a run of blocks: every head size, frames of 1 to 64 tokens (a last tile of 16 that is full,
-    nearly empty, or the only one), MLP widths on both sides of a multiple of 64, more blocks than one launch holds; and the same rows
-    through a merge in the middle, whose hidden states et_encoder_block_qkv's projection has to match as well.
+    nearly empty, or the only one), MLP widths on both sides of a multiple of 64, few blocks and many; the projection of its last block,
+    which et_encoder_block_qkv gives bit for bit; and a merge in the middle.
     Bound: seven roundings to bf16 per block, each 2^-9 relative at most and independent, two blocks 0.0073."""
     from et_inputs import EncoderShape
     shape = EncoderShape(n_layers=layers, d_model=64, n_heads=heads, d_mlp=mlp, patch=14, image_h=side, image_w=side)
@@ -407,6 +407,14 @@ def test_narrow_encoders_run_by_frames(heads, mlp, side, T, layers):
     err = rel_l2(dev_to_f64(got["tokens"]), ref["tokens"])
     print("narrow encoder", heads, mlp, side, T, layers, "rel-L2 %.4f" % err)
     assert err <= 2.0 ** -9 * np.sqrt(7 * layers)
+    rows = T * shape.tokens_per_frame                         # q | k | v of the last block lie behind the residual stream
+    start = (rows * 64 * 2 + 255) // 256 * 256
+    inside = enc._ws[start:start + rows * 3 * 64 * 2].view(torch.int16).reshape(rows, 3 * 64).clone()
+    front = _truncated(shape, w, layers - 1, T)
+    x = _encode(front, frames, -1, 0.9, 1.0)["tokens"]
+    front.close()
+    qkv, _ = et.et_encoder_block_qkv(enc.handle, layers - 1, x)
+    assert torch.equal(qkv.view(torch.int16), inside)
     cut = _encode(enc, frames, 1, -2.0, 1.0)                  # one segment, all tokens: the mean frame after the first block
     assert cut["n_frames_out"] == 1
     ref = O.encode_clip(shape, w, frames, 1, -2.0, 1.0)
