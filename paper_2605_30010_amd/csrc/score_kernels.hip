@@ -367,8 +367,9 @@ int launch_attention_scores(const uint16_t *qkv, int n_frames, int L, int n_head
   const int ksteps = (head_dim + 15) / 16;
   const dim3 reduce_grid((n_frames * L + 255) / 256);
   // One pass while a workgroup's registers hold the frame's K fragments, 3 blocks of 32 keys per wavefront
-  // (2 above head_dim 96), and the one-dimensional grid stays far below its limit.
-  if (L <= 32 * kPassWaves * (ksteps <= 6 ? 3 : 2) && n_frames <= 65535 && n_heads <= 65535 && (long)n_frames * n_heads <= (1L << 20)) {
+  // (2 above head_dim 96), and the one-dimensional grid stays far below its limit.  Its direct loads to LDS need rows at multiples
+  // of 16 bytes; a caller's tensor that begins elsewhere goes by ordinary loads, which the hardware takes at any address.
+  if (reinterpret_cast<uintptr_t>(qkv) % 16 == 0 && L <= 32 * kPassWaves * (ksteps <= 6 ? 3 : 2) && n_frames <= 65535 && n_heads <= 65535 && (long)n_frames * n_heads <= (1L << 20)) {
     const int nb = (L + 32 * kPassWaves - 1) / (32 * kPassWaves), n_qb = (L + 31) / 32;
     // Shares per (frame, head): the fewest query blocks on the busiest compute unit, a workgroup's own start
     // (K fragments from memory, reduction of the column sums) counted as two.

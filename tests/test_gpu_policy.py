@@ -550,6 +550,20 @@ def test_attention_scores_over_the_sizes(F, n, H, hd):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("begin", [1, 4, 8])
+def test_attention_scores_of_a_tensor_inside_another(begin):
+    """Contiguous rows that begin 2, 8 or 16 bytes into an allocation.  Bound: as over the sizes."""
+    F, n, H, hd = 3, 100, 4, 72
+    bits = f64_to_bits(np.random.default_rng(begin).standard_normal((F * n, 3 * H * hd)))
+    room = torch.zeros(bits.size + 16, dtype=torch.bfloat16, device="cuda")
+    room[begin:begin + bits.size] = bits_to_dev(bits).reshape(-1)
+    got = et.et_attention_scores(room[begin:begin + bits.size].view(F * n, 3 * H * hd), F, n, H, hd).cpu().numpy().astype(np.float64)
+    qk = bf16_bits_to_f32(bits).astype(np.float64).reshape(F, n, 3 * H * hd)
+    want = O.attention_received_from_qk(qk[..., :H * hd], qk[..., H * hd:2 * H * hd], H)
+    assert np.max(np.abs(got - want) / want) < 2e-5
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n,H,hd,size", [(40, 2, 72, 3.0), (300, 2, 72, 6.0), (729, 1, 80, 6.0), (520, 2, 16, 8.0), (200, 1, 128, 4.0)])
 def test_attention_scores_of_large_logits(n, H, hd, size):
     """Denominators that exponentials against a fixed reference would put on both sides of 2^+-60: frames with ordinary queries, queries
@@ -582,6 +596,20 @@ def test_attention_scores_of_mixed_logits(n, H, hd):
     got = et.et_attention_scores(bits_to_dev(bits), F, n, H, hd).cpu().numpy().astype(np.float64)
     qk = bf16_bits_to_f32(bits).astype(np.float64).reshape(F, n, 3 * D)
     want = O.attention_received_from_qk(qk[..., :D], qk[..., D:2 * D], H)
+    assert np.max(np.abs(got - want) / want) < 2e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("begin", [1, 4, 8])
+def test_attention_scores_of_a_tensor_inside_another(begin):
+    """Contiguous rows that begin 2, 8 or 16 bytes into an allocation.  Bound: as over the sizes."""
+    F, n, H, hd = 3, 100, 4, 72
+    bits = f64_to_bits(np.random.default_rng(begin).standard_normal((F * n, 3 * H * hd)))
+    room = torch.zeros(bits.size + 16, dtype=torch.bfloat16, device="cuda")
+    room[begin:begin + bits.size] = bits_to_dev(bits).reshape(-1)
+    got = et.et_attention_scores(room[begin:begin + bits.size].view(F * n, 3 * H * hd), F, n, H, hd).cpu().numpy().astype(np.float64)
+    qk = bf16_bits_to_f32(bits).astype(np.float64).reshape(F, n, 3 * H * hd)
+    want = O.attention_received_from_qk(qk[..., :H * hd], qk[..., H * hd:2 * H * hd], H)
     assert np.max(np.abs(got - want) / want) < 2e-5
 
 
