@@ -205,7 +205,8 @@ int et_encode_clip_policy(et_encoder *enc, const float *frames_dev, int32_t T, i
 /* ---- per-kernel timing (optional) ----------------------------------------------------
  * With profiling on, et_encode_clip brackets every kernel launch with HIP events on
  * `hip_stream` and accumulates elapsed time and launch counts per kernel kind.  Off by
- * default (events cost a little host time). */
+ * default (events cost a little host time).  An encoder of width 64, at most 64 tokens per frame and an MLP of at most 256
+ * runs all blocks between two stages as one launch, under ET_K_MISC. */
 enum {
   ET_K_IM2COL = 0, ET_K_GEMM_PATCH, ET_K_LAYERNORM, ET_K_GEMM_QKV, ET_K_ATTENTION,
   ET_K_GEMM_OUT, ET_K_GEMM_FC1, ET_K_GEMM_FC2, ET_K_SIMILARITY, ET_K_SCAN, ET_K_MERGE,

@@ -218,7 +218,8 @@ static int run_block(et_encoder *e, int layer, const EncWs &w, int rows, const i
 // Whether every frame of the encoder fits the kernel that takes a frame through a run of blocks (narrow_blocks.hip).  A rule
 // on the encoder, not on the call: the stages of one clip, and et_encoder_block_qkv, see the same arithmetic throughout.
 // An encoder of 4 blocks and 64 tokens per frame, merge after two, us per call by launches / by frames: 1 frame 149 / 79, 8 frames 158 / 84, 64 frames
-// 160 / 88.
+// 160 / 88; nothing merged, 256 frames 190 / 84, 600 335 / 158, 2000 836 / 393 (a grid of many rounds); half the tokens kept in
+// front of the first block, 256 frames 183 / 114, 2000 589 / 549.
 static bool is_narrow(const et_encoder *e) {
   return e->D == kNarrowWidth && e->L <= kNarrowTokens && e->Mhp <= kNarrowMlp && (e->hd == 16 || e->hd == 32 || e->hd == 64);
 }

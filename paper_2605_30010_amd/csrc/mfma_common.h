@@ -142,8 +142,8 @@ struct PieceSum {
 
 // What a GEMM kernel needs for its first loads, as arguments of their own in front of the GemmArgs: the command processor
 // hands the first 14 words of scalar arguments over in registers (-amdgpu-kernarg-preload-count; structures stay in memory),
-// so that no load waits for the argument block, which is in no cache yet.  The other kernels take their scalar arguments
-// the same way.  Measured, us per call: one frame through 27 blocks 1819 -> 1779, eight frames 3595 -> 3511.
+// so that no load waits for the argument block, which is in no cache yet.  Kernels whose arguments are plain scalars have them
+// so by themselves; narrow_blocks_kernel, with a structure alone, loads its own.  Measured, us per call: one frame through 27 blocks 1819 -> 1779, eight frames 3595 -> 3511.
 #define ET_GEMM_FIRST                                                                                                       \
   const uint16_t *first_A, const uint16_t *first_W, int first_lda, int first_K, int first_M, int tiles_m, int tiles_n,      \
       int first_stats_ld, const float2 *first_stats, const float *first_scale

@@ -6,8 +6,10 @@
 // frames), here the chain of its eight phases, each a barrier, LDS reads and a few MFMAs per wavefront: 16 500 clocks or 7 us, of
 // which q | k | v 4300 (under the block's weights: 170 KB through one compute unit's vector memory path), attention 2800, GELU 3500.
 // The weights come straight to registers as MFMA operands, issued a phase or more ahead, and lie in that order: as rows, half a
-// cache line per row and load, the same loads took 10 000 clocks.  Wider encoders fill the chip from their GEMMs' tiles
-// instead, and a single compute unit would walk their weights for longer than the launches take.
+// cache line per row and load, the same loads took 10 000 clocks.  The bounds on width, tokens and MLP are this split's: a wavefront
+// holds its 16 columns' weights of a whole block, 160 registers with an MLP of 64 to 240 of the 256 with one of 256, and its 32 of the 64
+// rows' accumulators beside them.  A larger block needs weights in chunks, which has not been tried; wide encoders fill the chip from
+// their GEMMs' tiles instead, and a single compute unit would walk their weights for longer than the launches take.
 #include "mfma_common.h"
 
 namespace et {

@@ -1,5 +1,5 @@
-// What the simple stage (merge_kernels.hip) and the paper-exact one (policy_kernels.hip) share: the mean of the cosines, the
-// per-frame top-k by radix select (Eq. 4) and the gather.
+// What the simple stage (merge_kernels.hip) and the paper-exact one (policy_kernels.hip) share: the mean of the cosines and
+// the per-frame top-k by radix select (Eq. 4).  Device code only.
 #pragma once
 #include "et_common.h"
 
