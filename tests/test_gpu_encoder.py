@@ -391,11 +391,11 @@ def test_row_whose_variance_leaves_float32(size):
 
 
 @pytest.mark.parametrize("heads,mlp,side,T,layers", [(4, 256, 112, 5, 2), (2, 200, 98, 3, 2), (1, 64, 14, 2, 2), (4, 72, 70, 9, 2), (1, 256, 112, 70, 2),
-                                                     (2, 65, 56, 1, 35)])
+                                                     (2, 65, 56, 1, 35), (2, 64, 28, 600, 2)])
 def test_narrow_encoders_run_by_frames(heads, mlp, side, T, layers):
     """The kernel that takes a frame through a run of blocks: every head size, frames of 1 to 64 tokens (a last tile of 16 that is full,
-    nearly empty, or the only one), MLP widths on both sides of a multiple of 64, few blocks and many; the projection of its last block,
-    which et_encoder_block_qkv gives bit for bit; and a merge in the middle.
+    nearly empty, or the only one), MLP widths on both sides of a multiple of 64, few blocks and many, more frames than
+    compute units; the projection of its last block, which et_encoder_block_qkv gives bit for bit; and a merge in the middle.
     Bound: seven roundings to bf16 per block, each 2^-9 relative at most and independent, two blocks 0.0073."""
     from et_inputs import EncoderShape
     shape = EncoderShape(n_layers=layers, d_model=64, n_heads=heads, d_mlp=mlp, patch=14, image_h=side, image_w=side)
